@@ -14,6 +14,7 @@
 //
 // Paper: Integration with Reinforcement Learning Algorithm (train step with no host inputs),
 // Deep Q-Network Model (update equation), Methods (add, sample).
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 
@@ -26,7 +27,6 @@
 namespace rp {
 namespace {
 
-constexpr unsigned int kThreads = kTrainThreads;   // weight kernel
 constexpr unsigned int kRowThreads = 1024;         // row kernel: 16 wavefronts
 constexpr unsigned int kRows = 4;          // experiences per workgroup of the row kernel ...
 constexpr unsigned int kSmallBatch = 512;  // ... and 2 for batches up to this size (no target network):
@@ -765,7 +765,9 @@ struct WArgs {
     unsigned int closes_step;
 };
 
-constexpr unsigned int kTM = 32, kTN = 32, kTK = 128;
+constexpr unsigned int kTM = 32, kTN = 32;
+constexpr unsigned int kTileWaves = 8, kTileThreads = 64 * kTileWaves;
+constexpr unsigned int kTileLd = kTN + 4;    // LDS pitch of a partial tile: rows 8 apart fall into different banks
 
 // Sum over the 16 lanes of a DPP row (lanes 16 q .. 16 q + 15), returned in each of them.
 __device__ __forceinline__ float row16_sum(float v) {
@@ -777,282 +779,287 @@ __device__ __forceinline__ float row16_sum(float v) {
     return v;
 }
 
-// Element k of a parameter array, addressed as the array's (uniform) base plus a 32-bit byte
-// offset: one address register per access instead of 64-bit arithmetic per lane.  (The arrays
-// are far smaller than 4 GiB.)
-__device__ __forceinline__ float ldw(const float* base, unsigned int k) {
-    return *(const __attribute__((address_space(1))) float*)((gbytes)reinterpret_cast<const char*>(base) + k * 4u);
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// Element k (and k + 1, k even) of a parameter array, addressed as the array's (uniform) base plus
+// a 32-bit byte offset: one address register per access instead of 64-bit arithmetic per lane.
+// (The arrays are far smaller than 4 GiB.)
+template <typename V>
+__device__ __forceinline__ V ldw(const float* base, unsigned int k) {
+    return *(const __attribute__((address_space(1))) V*)((gbytes)reinterpret_cast<const char*>(base) + k * 4u);
 }
-__device__ __forceinline__ void stw(float* base, unsigned int k, float v) {
+template <typename V>
+__device__ __forceinline__ void stw(float* base, unsigned int k, V v) {
     typedef __attribute__((address_space(1))) char* gwbytes;
-    *(__attribute__((address_space(1))) float*)((gwbytes)reinterpret_cast<char*>(base) + k * 4u) = v;
+    *(__attribute__((address_space(1))) V*)((gwbytes)reinterpret_cast<char*>(base) + k * 4u) = v;
 }
 
-// One optimizer update of parameter k with gradient gk, from values loaded earlier.
+// One parameter's (or two adjacent ones') weight and moments, loaded ahead of the update.
+template <typename V>
+struct OptValues {
+    V w, m, v;
+};
+template <typename V>
+__device__ __forceinline__ OptValues<V> load_opt(const WArgs& p, unsigned int k) {
+    return OptValues<V>{ldw<V>(p.w, k), ldw<V>(p.m, k), ldw<V>(p.v, k)};
+}
+template <typename V>
+__device__ __forceinline__ void arrived(const OptValues<V>& o) {
+    asm volatile("" ::"v"(o.w), "v"(o.m), "v"(o.v));
+}
+
+__device__ __forceinline__ float component(float x, int) { return x; }
+__device__ __forceinline__ float component(f32x2 x, int e) { return x[e]; }
+__device__ __forceinline__ void set_component(float& x, int, float y) { x = y; }
+__device__ __forceinline__ void set_component(f32x2& x, int e, float y) { x[e] = y; }
+
+// The optimizer's update of parameter k (V = float) or of k and k + 1 with their gradient.
 // r1 = 1 / (1 - beta1^t), r2 = 1 / (1 - beta2^t); sync: this step also refreshes the target network.
-__device__ __forceinline__ float opt_apply(const WArgs& p, unsigned int k, float gk, float wk,
-                                           float mk, float vk, float r1, float r2, bool grad_only,
-                                           bool sync) {
-    stw(p.g, k, gk);
-    if (grad_only) return wk;
+template <typename V>
+__device__ __forceinline__ V opt_apply(const WArgs& p, unsigned int k, V g, OptValues<V> o, float r1, float r2,
+                                       bool grad_only, bool sync) {
+    constexpr int N = sizeof(V) / sizeof(float);
+    stw(p.g, k, g);
+    if (grad_only) return o.w;
     if (p.opt == RP_SGD) {
-        wk -= p.lr * gk;
+#pragma unroll
+        for (int e = 0; e < N; ++e) set_component(o.w, e, component(o.w, e) - p.lr * component(g, e));
     } else {
-        mk = p.beta1 * mk + (1.f - p.beta1) * gk;
-        vk = p.beta2 * vk + (1.f - p.beta2) * gk * gk;
-        stw(p.m, k, mk);
-        stw(p.v, k, vk);
-        // hardware square root and reciprocal (1 ulp each): the quotient is good to a few parts
-        // in 1e7, far inside what the update's own rounding leaves
-        wk -= p.lr * (mk * r1) * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(vk * r2) + p.eps);
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            const float gk = component(g, e);
+            const float mk = p.beta1 * component(o.m, e) + (1.f - p.beta1) * gk;
+            const float vk = p.beta2 * component(o.v, e) + (1.f - p.beta2) * gk * gk;
+            set_component(o.m, e, mk);
+            set_component(o.v, e, vk);
+            // hardware square root and reciprocal (1 ulp each): the quotient is good to a few parts
+            // in 1e7, far inside what the update's own rounding leaves
+            set_component(o.w, e, component(o.w, e) - p.lr * (mk * r1) *
+                                                          __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(vk * r2) + p.eps));
+        }
+        stw(p.m, k, o.m);
+        stw(p.v, k, o.v);
     }
-    stw(p.w, k, wk);
-    if (sync) stw(p.wt, k, wk);
-    return wk;
+    stw(p.w, k, o.w);
+    if (sync) stw(p.wt, k, o.w);
+    return o.w;
 }
 
-// A workgroup owns a 32 x 32 tile of one layer's weight matrix (every matrix here is a whole
-// number of tiles) and wavefront w its 16 x 16 quarter (w >> 1, w & 1): it reduces the outer
-// products over the batch with 16x16x4 fp32 MFMA, 128 batch rows per pass, adds the bias
-// gradient when it sits on tile row 0 (the column sums of its error operands), and applies
-// the optimizer to what it holds.  The MFMA operands go from global
-// memory straight into the registers the instruction reads them from (lane l: batch row
-// 4t + l/16 of step t, column l%16 of the quarter -- 64-byte runs), all 64 loads of a pass
-// requested before the first use; nothing passes through LDS and no wavefront waits for another.
+// A workgroup of eight wavefronts owns a 32 x 32 tile of one layer's weight matrix (every matrix
+// here is a whole number of tiles).  It reduces the outer products over the batch with 16x16x4
+// fp32 MFMA, adds the bias gradient when it sits on tile row 0 (the column sums of its error
+// operands), and applies the optimizer to the tile.
+//
+// What bounds it is the compute unit's vector-memory path: a load instruction takes some sixteen
+// cycles there whether a lane asks for 4 bytes or 8, and an MFMA of this kind 32 cycles of one of
+// four matrix units.  So every wavefront forms the whole tile, four MFMAs per four batch rows, from
+// one 8-byte load per lane and operand (lane 16 q + c: row q of the four, columns 2 c and 2 c + 1
+// of the tile; MFMA (i, j) takes columns 2 c + i of Act and 2 c + j of Err), where a 16 x 16 quarter
+// per wavefront would take two loads per MFMA; and the wavefronts split the BATCH: wavefront w takes
+// rows 4 (w + 8 s) .. + 3 for s = 0, 1, .., T of those in flight at a time.  Their partial tiles
+// are added through LDS in a fixed order, two adjacent columns per thread, which also makes the
+// update's accesses 8 bytes wide.  Quarters over the whole batch -> this, us per launch: 27-256-256-30
+// at batch 32 4.9 -> 4.4, 128 4.9 -> 4.9, 1000 19.2 -> 10.2; 50-512-512-40 at batch 512 15.5 -> 11.7.
+// Rows past the batch re-read its last row and count as zero.
 // FOLD: the variant that also updates a dueling head (the tiles of job fold_job).
 // block: the workgroup's number among the launch's tiles.
-template <bool FOLD>
-__device__ __forceinline__ void weights_tile(const WArgs& p, unsigned int block) {
-    const unsigned int tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+struct TileLds {
+    float part[kTileWaves][kTM][kTileLd];   // each wavefront's partial tile
+    float bpart[kTileWaves][kTN];           // ... and column sums of Err
+    float lpart[kTileWaves];                // ... and share of the loss
+    float turn[kTM][kTN + 1];               // the new weights, on their way to the transposed copy
+};
+
+template <bool FOLD, int T>
+__device__ __forceinline__ void weights_tile(const WArgs& p, unsigned int block, TileLds& lds) {
+    const unsigned int tid = threadIdx.x, lane = tid & 63u;
+    const unsigned int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned int l16 = lane & 15u, lq = lane >> 4;
-    const unsigned int wr = wave >> 1, wc = wave & 1u;
     unsigned int j = 0;
     if (block >= p.job[1].tile_begin) j = 1;
     if (block >= p.job[2].tile_begin) j = 2;
     const WJob jb = j == 0 ? p.job[0] : j == 1 ? p.job[1] : p.job[2];
     const unsigned int tile = block - jb.tile_begin;
     const unsigned int m0 = (tile / jb.tiles_n) * kTM, n0 = (tile % jb.tiles_n) * kTN;
-    // this lane's outputs: rows mm .. mm+3 of column nn
-    const unsigned int nn = n0 + 16u * wc + l16;
-    const unsigned int mm = m0 + 16u * wr + 4u * lq;
-    const bool bias_wave = m0 == 0 && wr == 0;
-    const bool do_bias = bias_wave && lq == 0;
+    const bool bias_tile = m0 == 0;
 
-    // operands of one pass: a[t] = Act[b0 + 4t + lq][m0 + 16 wr + l16], b[t] = Err[same row][nn].
-    // The address of a step's four rows is a scalar and the lane adds its byte offset within
-    // them.  A step past the batch contributes zeros without touching memory; the one step
-    // that straddles its end (batch not a multiple of 4) reads the last row in the lanes past
-    // it and zeroes them.
-    constexpr int kSteps = kTK / 4;
-    float a[kSteps], b[kSteps];
-    const unsigned int ca = (m0 + 16u * wr + l16) * 4u, cb = nn * 4u;
+    // operands of this wavefront's step s: the address of its four rows is a scalar and the lane
+    // adds its byte offset within them (in the last step of a batch that is no multiple of 4, the
+    // lanes past its end that of the last row)
+    const unsigned int n_steps = (p.B + 3u) / 4u, rounds = (n_steps + kTileWaves - 1u) / kTileWaves;
+    const unsigned int ca = (m0 + 2u * l16) * 4u, cb = (n0 + 2u * l16) * 4u;
     const unsigned int la = lq * jb.lda * 4u + ca, lb = lq * jb.ldb * 4u + cb;
     const unsigned int lqc = min(lq, (p.B - 1u) & 3u);
     const unsigned int la_c = lqc * jb.lda * 4u + ca, lb_c = lqc * jb.ldb * 4u + cb;
-    auto load_pass = [&](unsigned int b0) {
-        const gbytes abase = (gbytes)reinterpret_cast<const char*>(jb.act) + (size_t)b0 * jb.lda * 4u;
-        const gbytes bbase = (gbytes)reinterpret_cast<const char*>(jb.err) + (size_t)b0 * jb.ldb * 4u;
-        if (b0 + kTK <= p.B) {
-            // a full pass: straight-line code, every request out before the first use
-#pragma unroll
-            for (int t = 0; t < kSteps; ++t) {
-                gbytes ra = abase + (size_t)(4 * t) * jb.lda * 4u;
-                gbytes rb = bbase + (size_t)(4 * t) * jb.ldb * 4u;
-                asm volatile("" : "+s"(ra), "+s"(rb));
-                a[t] = *(const __attribute__((address_space(1))) float*)(ra + la);
-                b[t] = *(const __attribute__((address_space(1))) float*)(rb + lb);
-            }
-            return;
-        }
-#pragma unroll
-        for (int t = 0; t < kSteps; ++t) {
-            const unsigned int row = b0 + 4u * t;
-            if (row + 4u <= p.B) {
-                gbytes ra = abase + (size_t)(4 * t) * jb.lda * 4u;
-                gbytes rb = bbase + (size_t)(4 * t) * jb.ldb * 4u;
-                asm volatile("" : "+s"(ra), "+s"(rb));
-                a[t] = *(const __attribute__((address_space(1))) float*)(ra + la);
-                b[t] = *(const __attribute__((address_space(1))) float*)(rb + lb);
-            } else if (row < p.B) {
-                gbytes ra = abase + (size_t)(4 * t) * jb.lda * 4u;
-                gbytes rb = bbase + (size_t)(4 * t) * jb.ldb * 4u;
-                asm volatile("" : "+s"(ra), "+s"(rb));
-                const float av = *(const __attribute__((address_space(1))) float*)(ra + la_c);
-                const float bv = *(const __attribute__((address_space(1))) float*)(rb + lb_c);
-                a[t] = row + lq < p.B ? av : 0.f;
-                b[t] = row + lq < p.B ? bv : 0.f;
-            } else {
-                a[t] = 0.f;
-                b[t] = 0.f;
-            }
-        }
+    f32x2 a[T], b[T];
+    auto load_step = [&](int slot, unsigned int s) {
+        const unsigned int step = min(wave + kTileWaves * s, n_steps - 1u);
+        const bool last = step == n_steps - 1u;
+        gbytes ra = (gbytes)reinterpret_cast<const char*>(jb.act) + (size_t)(4u * step) * jb.lda * 4u;
+        gbytes rb = (gbytes)reinterpret_cast<const char*>(jb.err) + (size_t)(4u * step) * jb.ldb * 4u;
+        asm volatile("" : "+s"(ra), "+s"(rb));
+        a[slot] = *(const __attribute__((address_space(1))) f32x2*)(ra + (last ? la_c : la));
+        b[slot] = *(const __attribute__((address_space(1))) f32x2*)(rb + (last ? lb_c : lb));
     };
-    load_pass(0);
+#pragma unroll
+    for (int s = 0; s < T; ++s) load_step(s, (unsigned int)s);
 
-    // bias corrections and the optimizer state of this lane's outputs
-    const float c1 = p.ctr->c1, c2 = p.ctr->c2;
+    // this thread's outputs after the reduction: row mm, columns nn and nn + 1
+    const unsigned int row = tid >> 4, c2 = (tid & 15u) * 2u;
+    const unsigned int mm = m0 + row, nn = n0 + c2;
+    const bool do_bias = bias_tile && row == 0;
+    // bias corrections and the optimizer state of this thread's outputs
+    const float c1 = p.ctr->c1, c2_adam = p.ctr->c2;
     const bool sync = p.wt && p.sync_every && p.ctr->adam_t % p.sync_every == 0;
-    // (dueling head updated here: the lane of action nn holds the state of that action's
-    // advantage weights instead; the state-value weight of row 4 lq + l16 of the quarter, and
-    // of the bias row in lane 4, belongs to lanes l16 = 0 .. 4 of the left wavefronts)
+    // (dueling head updated here: the thread of actions nn, nn + 1 holds the state of those actions'
+    // advantage weights instead, and the first of a row's threads that of its state-value weight)
     const bool fold = FOLD && j == p.fold_job;
     const unsigned int O = p.head_A + 1u;
-    const bool colv = nn < p.head_A;
-    const bool val_lane = fold && wc == 0 && (l16 < 4 || (l16 == 4 && do_bias));
+    const bool col0 = nn < p.head_A, col1 = nn + 1u < p.head_A;
     // (every load below is unconditional, from an index that is valid in every lane: a branch
     // here would make the wavefront wait for the operand loads in flight)
-    float w_old[4], m_old[4], v_old[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const unsigned int k = fold ? p.head_off + (mm + v) * O + (colv ? 1u + nn : 0u)
-                                    : jb.w_off + (mm + v) * jb.ldw + nn;
-        w_old[v] = ldw(p.w, k);
-        m_old[v] = ldw(p.m, k);
-        v_old[v] = ldw(p.v, k);
+    OptValues<f32x2> old, oldb;
+    OptValues<float> oldv, oldbv;
+    unsigned int kval = 0, kbval = 0;
+    if (fold) {
+        const unsigned int hrow = p.head_off + mm * O, hbias = p.head_off + jb.M * O;
+        const unsigned int o0 = col0 ? 1u + nn : 0u, o1 = col1 ? 2u + nn : 0u;
+        const OptValues<float> x0 = load_opt<float>(p, hrow + o0), x1 = load_opt<float>(p, hrow + o1);
+        const OptValues<float> y0 = load_opt<float>(p, hbias + o0), y1 = load_opt<float>(p, hbias + o1);
+        old = OptValues<f32x2>{{x0.w, x1.w}, {x0.m, x1.m}, {x0.v, x1.v}};
+        oldb = OptValues<f32x2>{{y0.w, y1.w}, {y0.m, y1.m}, {y0.v, y1.v}};
+        kval = hrow;
+        kbval = hbias;
+        oldv = load_opt<float>(p, kval);
+        oldbv = load_opt<float>(p, kbval);
+    } else {
+        old = load_opt<f32x2>(p, jb.w_off + mm * jb.ldw + nn);
+        oldb = load_opt<f32x2>(p, jb.b_off + nn);
     }
-    const unsigned int hbias = p.head_off + jb.M * O;
-    const unsigned int kb = fold ? hbias + (colv ? 1u + nn : 0u) : jb.b_off + nn;
-    const float wb_old = ldw(p.w, kb), mb_old = ldw(p.m, kb), vb_old = ldw(p.v, kb);
-    const unsigned int kval = !val_lane ? kb : l16 < 4 ? p.head_off + (mm + l16) * O : hbias;
-    const float vw_old = ldw(p.w, kval), vm_old = ldw(p.m, kval), vv_old = ldw(p.v, kval);
 
-    // the last workgroup of the launch that closes the step (never on a tile row with a bias)
-    // also reduces the per-sample losses: fetch them now
+    // the last workgroup of the launch that closes the step also reduces the per-sample losses
     const bool loss_block = p.closes_step && block == p.n_tiles - 1;
     float loss_part = 0.f;
-    if (loss_block && tid < 64)
-        for (unsigned int i = tid; i < p.B; i += 64) loss_part += p.lossi[i];
 
-    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.f;   // this lane's share of the column sum of Err (rows = lq mod 4)
-    for (unsigned int b0 = 0; b0 < p.B; b0 += kTK) {
-        if (b0 + kTK <= p.B) {
+    f32x4 acc[2][2];
 #pragma unroll
-            for (int t = 0; t < kSteps; ++t) {
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[t], acc, 0, 0, 0);
-                if (bias_wave) bsum += b[t];
-            }
-        } else {
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int t = 0; t < kSteps; ++t) {
-                if (b0 + 4u * t >= p.B) break;   // steps past the batch hold zeros
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[t], acc, 0, 0, 0);
-                if (bias_wave) bsum += b[t];
-            }
+        for (int k = 0; k < 2; ++k) acc[i][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x2 bsum = {0.f, 0.f};   // this lane's share of the column sums of Err
+    for (unsigned int s0 = 0; s0 < rounds; s0 += T) {
+#pragma unroll
+        for (int s = 0; s < T; ++s) {
+            const bool live = 4u * (wave + kTileWaves * (s0 + s)) + lq < p.B;
+            const f32x2 av = live ? a[s] : f32x2{0.f, 0.f}, bv = live ? b[s] : f32x2{0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    acc[i][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[k], acc[i][k], 0, 0, 0);
+            bsum += bv;
+            if (s0 + T < rounds) load_step(s, s0 + T + s);
         }
-        if (b0 + kTK < p.B) load_pass(b0 + kTK);
     }
-    if (bias_wave) {
-        bsum += __shfl_xor(bsum, 16);
-        bsum += __shfl_xor(bsum, 32);
+    // MFMA (i, k) left this lane rows 4 lq .. + 3 of column l16 of its 16 x 16 product: entries
+    // (2 (4 lq + v) + i, 2 l16 + k) of the tile
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            *reinterpret_cast<f32x2*>(&lds.part[wave][8u * lq + 2 * v + i][2u * l16]) = f32x2{acc[i][0][v], acc[i][1][v]};
+    if (bias_tile) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            bsum[k] += __shfl_xor(bsum[k], 16);
+            bsum[k] += __shfl_xor(bsum[k], 32);
+        }
+        if (lq == 0) *reinterpret_cast<f32x2*>(&lds.bpart[wave][2u * l16]) = bsum;
+    }
+    if (loss_block) {
+        for (unsigned int i = tid; i < p.B; i += kTileThreads) loss_part += p.lossi[i];
+        loss_part = wave_sum(loss_part);
+        if (lane == 0) lds.lpart[wave] = loss_part;
     }
 
     // The optimizer state requested before the products has long arrived.  Naming every value
     // as an operand here makes the compiler wait for them now, before the first store: vmcnt
     // counts stores as well and retires in order, so a wait for one of these loads placed among
     // the stores below would also wait for the stores ahead of it to complete.
-#pragma unroll
-    for (int v = 0; v < 4; ++v) asm volatile("" ::"v"(w_old[v]), "v"(m_old[v]), "v"(v_old[v]));
-    asm volatile("" ::"v"(wb_old), "v"(mb_old), "v"(vb_old), "v"(vw_old), "v"(vm_old), "v"(vv_old));
-    const float r1 = 1.f / c1, r2 = 1.f / c2;
+    arrived(old);
+    arrived(oldb);
     if (fold) {
-        // Dueling head (Q = V + A - mean A).  This lane holds dW[k][nn] of the plain layer for
-        // hidden units k = mm .. mm+3 (entries 0..3) and, on the bias row, for k = H (entry 4).
-        // The head's gradients are dV[k] = sum_a dW[k][a] and dA[k][a] = dW[k][a] - mean_a' dW[k][a'],
-        // kept to the weights the head has (a gradient of zero where it has none: moments and
-        // weight stay as they are); after their optimizer step the plain layer's row is rebuilt
-        // as V[k] + A[k][a] - mean_a' A[k][a'].  A row's 32 columns sit in 16 lanes of each of the
-        // two wavefronts of a tile row, so both sums take a lane reduction and a few words of LDS.
-        __shared__ float hsum[2][2][17][2];   // [gradient / new weights][wr][row][wc]
-        __shared__ float hval[2][17];         // new state-value weights [wr][row]
+        arrived(oldv);
+        arrived(oldbv);
+    }
+    const float r1 = 1.f / c1, r2 = 1.f / c2_adam;
+    lds_barrier();
+    f32x2 g = {0.f, 0.f}, gb = {0.f, 0.f};
+#pragma unroll
+    for (unsigned int w = 0; w < kTileWaves; ++w) g += *reinterpret_cast<const f32x2*>(&lds.part[w][row][c2]);
+    if (do_bias) {
+#pragma unroll
+        for (unsigned int w = 0; w < kTileWaves; ++w) gb += *reinterpret_cast<const f32x2*>(&lds.bpart[w][c2]);
+    }
+    if (fold) {
+        // Dueling head (Q = V + A - mean A).  This thread holds dW[k][nn], dW[k][nn + 1] of the plain
+        // layer for hidden unit k = mm and, on tile row 0, for the bias row k = H.  The head's
+        // gradients are dV[k] = sum_a dW[k][a] and dA[k][a] = dW[k][a] - mean_a' dW[k][a'], kept to
+        // the weights the head has (a gradient of zero where it has none: moments and weight stay
+        // as they are); after their optimizer step the plain layer's row is rebuilt as
+        // V[k] + A[k][a] - mean_a' A[k][a'].  A row's 32 columns sit in one DPP row of 16 lanes.
         const float inv_A = 1.f / (float)p.head_A;
         const unsigned int H = jb.M;
-        const float x[5] = {acc[0], acc[1], acc[2], acc[3], bias_wave ? bsum : 0.f};
-        float red[5];
-#pragma unroll
-        for (int i = 0; i < 5; ++i) red[i] = row16_sum(colv ? x[i] : 0.f);
-        if (l16 == 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) hsum[0][wr][4u * lq + i][wc] = red[i];
-            if (lq == 0) hsum[0][wr][16][wc] = red[4];
-        }
-        lds_barrier();   // (not __syncthreads: that would also wait for global stores in flight)
-        float gsum[5];
-#pragma unroll
-        for (int i = 0; i < 5; ++i) {
-            const unsigned int slot = i < 4 ? 4u * lq + i : 16u;
-            gsum[i] = hsum[0][wr][slot][0] + hsum[0][wr][slot][1];
-        }
-        float a_new[5];   // this lane's new advantage weight (0 where the head has none)
-#pragma unroll
-        for (int i = 0; i < 5; ++i) a_new[i] = 0.f;
-        if (colv) {
-#pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                if (i == 4 && !do_bias) continue;
-                const unsigned int k = i < 4 ? mm + i : H;
-                const bool a_on = head_connected(H, k, 1);
-                const float wn = opt_apply(p, p.head_off + k * O + 1u + nn,
-                                           a_on ? x[i] - gsum[i] * inv_A : 0.f,
-                                           i < 4 ? w_old[i & 3] : wb_old, i < 4 ? m_old[i & 3] : mb_old,
-                                           i < 4 ? v_old[i & 3] : vb_old, r1, r2, false, sync);
-                a_new[i] = a_on ? wn : 0.f;
-            }
-        }
-        if (val_lane) {
-            const unsigned int k = l16 < 4 ? mm + l16 : H;
-            const bool v_on = head_connected(H, k, 0);
-            const unsigned int slot = l16 < 4 ? 4u * lq + l16 : 16u;
-            const float gv = hsum[0][wr][slot][0] + hsum[0][wr][slot][1];
-            const float wn = opt_apply(p, kval, v_on ? gv : 0.f, vw_old, vm_old, vv_old, r1, r2, false, sync);
-            hval[wr][slot] = v_on ? wn : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < 5; ++i) red[i] = row16_sum(a_new[i]);
-        if (l16 == 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) hsum[1][wr][4u * lq + i][wc] = red[i];
-            if (lq == 0) hsum[1][wr][16][wc] = red[4];
-        }
-        lds_barrier();
-        if (colv) {
-#pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                if (i == 4 && !do_bias) continue;
-                const unsigned int slot = i < 4 ? 4u * lq + i : 16u;
-                const unsigned int k = i < 4 ? mm + i : H;
-                const float amean = (hsum[1][wr][slot][0] + hsum[1][wr][slot][1]) * inv_A;
-                const float e = hval[wr][slot] + a_new[i] - amean;
-                const unsigned int eff = (i < 4 ? jb.w_off + k * jb.ldw : jb.b_off) + nn;
-                stw(p.w, eff, e);
-                if (sync) stw(p.wt, eff, e);
-            }
-        }
+        auto head_row = [&](unsigned int k, f32x2 x, const OptValues<f32x2>& o, unsigned int kv,
+                            const OptValues<float>& ov, unsigned int eff) {
+            const float gsum = row16_sum((col0 ? x[0] : 0.f) + (col1 ? x[1] : 0.f));
+            const bool a_on = head_connected(H, k, 1), v_on = head_connected(H, k, 0);
+            const unsigned int ka = p.head_off + k * O + 1u + nn;
+            float a0 = 0.f, a1 = 0.f, val = 0.f;   // new weights (0 where the head has none)
+            if (col0) a0 = opt_apply<float>(p, ka, a_on ? x[0] - gsum * inv_A : 0.f,
+                                            OptValues<float>{o.w[0], o.m[0], o.v[0]}, r1, r2, false, sync);
+            if (col1) a1 = opt_apply<float>(p, ka + 1u, a_on ? x[1] - gsum * inv_A : 0.f,
+                                            OptValues<float>{o.w[1], o.m[1], o.v[1]}, r1, r2, false, sync);
+            if (!a_on) a0 = a1 = 0.f;
+            if (c2 == 0) val = opt_apply<float>(p, kv, v_on ? gsum : 0.f, ov, r1, r2, false, sync);
+            if (!v_on || c2 != 0) val = 0.f;
+            const float amean = row16_sum(a0 + a1) * inv_A;
+            const float vnew = row16_sum(val);
+            const float e0 = vnew + a0 - amean, e1 = vnew + a1 - amean;
+            if (col0) stw(p.w, eff, e0);
+            if (col1) stw(p.w, eff + 1u, e1);
+            if (sync && col0) stw(p.wt, eff, e0);
+            if (sync && col1) stw(p.wt, eff + 1u, e1);
+        };
+        head_row(mm, g, old, kval, oldv, jb.w_off + mm * jb.ldw + nn);
+        if (do_bias) head_row(H, gb, oldb, kbval, oldbv, jb.b_off + nn);
     } else {
         const bool grad_only = j == p.grad_only_job;
-        float w_new[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            w_new[v] = opt_apply(p, jb.w_off + (mm + v) * jb.ldw + nn, acc[v], w_old[v], m_old[v],
-                                 v_old[v], r1, r2, grad_only, sync);
-        if (jb.wT)
-            *reinterpret_cast<float4*>(jb.wT + (size_t)nn * jb.M + mm) =
-                make_float4(w_new[0], w_new[1], w_new[2], w_new[3]);
-        if (do_bias) opt_apply(p, jb.b_off + nn, bsum, wb_old, mb_old, vb_old, r1, r2, grad_only, sync);
-    }
-    if (loss_block && tid < 64) {
-        const float s = wave_sum(loss_part);
-        if (tid == 0) {
-            p.ctr->loss = s / (float)p.B;
-            p.ctr->step += 1;
+        const f32x2 w_new = opt_apply(p, jb.w_off + mm * jb.ldw + nn, g, old, r1, r2, grad_only, sync);
+        if (do_bias) opt_apply(p, jb.b_off + nn, gb, oldb, r1, r2, grad_only, sync);
+        if (jb.wT) {
+            // (through LDS, so that the transposed copy's rows leave as 128-byte runs)
+            lds.turn[row][c2] = w_new[0];
+            lds.turn[row][c2 + 1u] = w_new[1];
+            lds_barrier();
+            *reinterpret_cast<f32x2*>(jb.wT + (size_t)(n0 + row) * jb.M + m0 + c2) =
+                f32x2{lds.turn[c2][row], lds.turn[c2 + 1u][row]};
         }
+    }
+    if (loss_block && tid == 0) {
+        float s = 0.f;
+#pragma unroll
+        for (unsigned int w = 0; w < kTileWaves; ++w) s += lds.lpart[w];
+        p.ctr->loss = s / (float)p.B;
+        p.ctr->step += 1;
     }
 }
 
-template <bool FOLD>
-__global__ __launch_bounds__(kThreads) void fused_weights_kernel(WArgs p) {
+template <bool FOLD, int T>
+__global__ __launch_bounds__(kTileThreads) void fused_weights_kernel(WArgs p) {
+    __shared__ __attribute__((aligned(16))) TileLds lds;
     touch_kernel_args<WArgs>();
-    weights_tile<FOLD>(p, blockIdx.x);
+    weights_tile<FOLD, T>(p, blockIdx.x, lds);
 }
 
 // The launch of tiles of the fp32 step on MFMA, with two more kinds of workgroup in it:
@@ -1066,23 +1073,42 @@ __global__ __launch_bounds__(kThreads) void fused_weights_kernel(WArgs p) {
 //  - after the tiles, next_blocks workgroups append, sample and gather for the NEXT train step
 //    (inside a recorded run of steps): they touch nothing this step reads or writes (the next
 //    step's batch goes to a buffer of its own), so the next step begins with its first layer.
-template <bool FOLD>
-__global__ __launch_bounds__(kThreads) void fused_weights_ahead_kernel(WArgs p, MmArgs dz, unsigned int dz_nx,
-                                                                       unsigned int dz_blocks,
-                                                                       AppendGatherArgs next,
-                                                                       unsigned int next_blocks) {
-    __shared__ float part[3][64][4];
+// Both take fewer threads than a tile; the wavefronts beyond theirs end at once (a barrier waits
+// for the wavefronts that are left).
+template <bool FOLD, int T>
+__global__ __launch_bounds__(kTileThreads) void fused_weights_ahead_kernel(WArgs p, MmArgs dz, unsigned int dz_nx,
+                                                                           unsigned int dz_blocks,
+                                                                           AppendGatherArgs next,
+                                                                           unsigned int next_blocks) {
+    extern __shared__ uint4 smem[];   // a workgroup is one of the three kinds and has all of it
     if (blockIdx.x < dz_blocks) {
+        if (threadIdx.x >= kMmThreads) return;
         const unsigned int by = blockIdx.x / dz_nx;
-        mm_f32_block<true, MM_MASK, true, 8>(dz, blockIdx.x - by * dz_nx, by, 0u, part);
+        mm_f32_block<true, MM_MASK, true, 8>(dz, blockIdx.x - by * dz_nx, by, 0u,
+                                             reinterpret_cast<float(*)[64][4]>(smem));
         return;
     }
     const unsigned int block = blockIdx.x - dz_blocks;
     if (block >= p.n_tiles) {
+        if (threadIdx.x >= kGatherThreads) return;
         append_gather_block<4, kDrawUniform>(next, block - p.n_tiles, next_blocks);
         return;
     }
-    weights_tile<FOLD>(p, block);
+    weights_tile<FOLD, T>(p, block, *reinterpret_cast<TileLds*>(smem));
+}
+
+// The variants of the two kernels above: T steps in flight per wavefront cover a batch of 32 T rows
+// in one go; beyond 256 rows eight are kept in flight (four would leave the loads' latency exposed,
+// sixteen gained nothing).
+typedef void (*WeightsKernel)(WArgs);
+typedef void (*WeightsAheadKernel)(WArgs, MmArgs, unsigned int, unsigned int, AppendGatherArgs, unsigned int);
+WeightsKernel weights_kernel(bool fold, unsigned int B) {
+    if (B <= 128u) return fold ? fused_weights_kernel<true, 4> : fused_weights_kernel<false, 4>;
+    return fold ? fused_weights_kernel<true, 8> : fused_weights_kernel<false, 8>;
+}
+WeightsAheadKernel weights_ahead_kernel(bool fold, unsigned int B) {
+    if (B <= 128u) return fold ? fused_weights_ahead_kernel<true, 4> : fused_weights_ahead_kernel<false, 4>;
+    return fold ? fused_weights_ahead_kernel<true, 8> : fused_weights_ahead_kernel<false, 8>;
 }
 
 size_t row_kernel_lds(unsigned int Dp, unsigned int H, unsigned int Ap) {
@@ -1285,13 +1311,10 @@ hipError_t enqueue_weights_update(trainer* t, hipStream_t st, bool* folded_head,
             next = *t->rec_next;
             append_gather_shape(next, &nb, &lds);
         }
+        lds = std::max(lds, sizeof(TileLds));
         const dim3 grid(rec.dz_blocks + nt + nb);
-        if (fold)
-            hipLaunchKernelGGL(fused_weights_ahead_kernel<true>, grid, dim3(kThreads), lds, st, w, rec.dz,
-                               rec.dz_nx, rec.dz_blocks, next, nb);
-        else
-            hipLaunchKernelGGL(fused_weights_ahead_kernel<false>, grid, dim3(kThreads), lds, st, w, rec.dz,
-                               rec.dz_nx, rec.dz_blocks, next, nb);
+        hipLaunchKernelGGL(weights_ahead_kernel(fold, t->B), grid, dim3(kTileThreads), lds, st, w, rec.dz,
+                           rec.dz_nx, rec.dz_blocks, next, nb);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (dz1) {
@@ -1300,13 +1323,11 @@ hipError_t enqueue_weights_update(trainer* t, hipStream_t st, bool* folded_head,
             w1.grad_only_job = ~0u;
             w1.fold_job = ~0u;
             w1.closes_step = 0;
-            hipLaunchKernelGGL(fused_weights_kernel<false>, dim3(w1.n_tiles), dim3(kThreads), 0, st, w1);
+            hipLaunchKernelGGL(weights_kernel(false, t->B), dim3(w1.n_tiles), dim3(kTileThreads), 0, st, w1);
             if (launches) *launches = 2;
         }
-    } else if (fold) {
-        hipLaunchKernelGGL(fused_weights_kernel<true>, dim3(nt), dim3(kThreads), 0, st, w);
     } else {
-        hipLaunchKernelGGL(fused_weights_kernel<false>, dim3(nt), dim3(kThreads), 0, st, w);
+        hipLaunchKernelGGL(weights_kernel(fold, t->B), dim3(nt), dim3(kTileThreads), 0, st, w);
     }
     if (folded_head) *folded_head = fold;
     return hipGetLastError();
@@ -1314,8 +1335,7 @@ hipError_t enqueue_weights_update(trainer* t, hipStream_t st, bool* folded_head,
 
 void* weights_ahead_func(const trainer* t) {
     const bool fold = t->dueling && t->Ap == kTN;
-    return fold ? reinterpret_cast<void*>(fused_weights_ahead_kernel<true>)
-                : reinterpret_cast<void*>(fused_weights_ahead_kernel<false>);
+    return reinterpret_cast<void*>(weights_ahead_kernel(fold, t->B));
 }
 
 hipError_t patch_weights_ahead_node(trainer* t, hipGraphExec_t exec, hipGraphNode_t node,
