@@ -1084,7 +1084,7 @@ __global__ __launch_bounds__(kTileThreads) void fused_weights_ahead_kernel(WArgs
     if (blockIdx.x < dz_blocks) {
         if (threadIdx.x >= kMmThreads) return;
         const unsigned int by = blockIdx.x / dz_nx;
-        mm_f32_block<true, MM_MASK, true, 8>(dz, blockIdx.x - by * dz_nx, by, 0u,
+        mm_f32_block<true, MM_MASK, 8>(dz, blockIdx.x - by * dz_nx, by, 0u,
                                              reinterpret_cast<float(*)[64][4]>(smem));
         return;
     }

@@ -18,10 +18,10 @@
 namespace rp {
 namespace {
 
-template <bool NT, int EPI, bool KSPLIT, int P>
+template <bool NT, int EPI, int P>
 __global__ __launch_bounds__(kMmThreads) void mm_f32_kernel(MmArgs p) {
     __shared__ float part[3][64][4];
-    mm_f32_block<NT, EPI, KSPLIT, P>(p, blockIdx.x, blockIdx.y, blockIdx.z, part);
+    mm_f32_block<NT, EPI, P>(p, blockIdx.x, blockIdx.y, blockIdx.z, part);
 }
 
 // The same launch with more rows of workgroups after the product's tiles_y, which copy n4
@@ -47,14 +47,31 @@ __device__ __forceinline__ void copy_block(const CopyArgs& c, unsigned int block
     }
 }
 
-template <bool NT, int EPI, bool KSPLIT, int P>
+template <bool NT, int EPI, int P>
 __global__ __launch_bounds__(kMmThreads) void mm_f32_copy_kernel(MmArgs p, unsigned int tiles_y, CopyArgs c) {
     __shared__ float part[3][64][4];
     if (blockIdx.y >= tiles_y) {
         copy_block(c, (blockIdx.y - tiles_y) * gridDim.x + blockIdx.x);
         return;
     }
-    mm_f32_block<NT, EPI, KSPLIT, P>(p, blockIdx.x, blockIdx.y, blockIdx.z, part);
+    mm_f32_block<NT, EPI, P>(p, blockIdx.x, blockIdx.y, blockIdx.z, part);
+}
+
+// The product in tiles of 32 x 32 (mm_f32_tile32), and the copy's workgroups after the tiles'.
+// An XCD takes consecutive tiles: rows of tiles where A is the larger operand, columns of tiles
+// where B is, so that each L2 fetches its share of that operand once and all of the other.
+template <bool NT, int EPI, int W, int P>
+__global__ __launch_bounds__(64 * W) void mm_f32_tiles_kernel(MmArgs p, unsigned int tiles_m, unsigned int tiles_n,
+                                                              CopyArgs c) {
+    __shared__ __attribute__((aligned(16))) float part[W][kMmTile][kMmTileLd];
+    const unsigned int count = tiles_m * tiles_n;
+    if (blockIdx.x >= count) {
+        if (threadIdx.x < kMmThreads) copy_block(c, blockIdx.x - count);
+        return;
+    }
+    const unsigned int tile = block_to_tile(blockIdx.x, count);
+    if (tiles_m >= tiles_n) mm_f32_tile32<NT, EPI, W, P>(p, tile % tiles_n, tile / tiles_n, part);
+    else mm_f32_tile32<NT, EPI, W, P>(p, tile / tiles_m, tile % tiles_m, part);
 }
 
 // The first two layers in one launch, for a narrow first layer (H = 32 TPW <= 128 units over
@@ -191,39 +208,39 @@ hipError_t launch_mm(hipStream_t st, const MmArgs& a, unsigned int M_total, unsi
                      const CopyArgs* copy = nullptr) {
     MmArgs p = a;
     p.K = a.K / kgroups;
-    const bool ks = kgroups > 1 || want_ksplit(M_total, a.N, p.K);
-    const unsigned int TM = ks ? 16u : 32u;
-    p.tiles_per_part = (a.rows_per_part + TM - 1u) / TM;
+    if (kgroups == 1 && !want_ksplit(M_total, a.N, p.K)) {
+        if constexpr (EPI == MM_PARTIAL) {
+            return hipErrorInvalidValue;   // (partial products are for split contractions)
+        } else {
+            p.tiles_per_part = (a.rows_per_part + kMmTile - 1u) / kMmTile;
+            const unsigned int tiles_m = p.tiles_per_part * a.parts, tiles_n = a.N / kMmTile;
+            const CopyArgs c = copy ? *copy : CopyArgs{nullptr, nullptr, 0u};
+            const dim3 grid(tiles_m * tiles_n + (c.n4 + 4u * kMmThreads - 1u) / (4u * kMmThreads));
+            const unsigned int groups = p.K >> 4;
+            if (groups >= 32)
+                hipLaunchKernelGGL((mm_f32_tiles_kernel<NT, EPI, 8, 4>), grid, dim3(512), 0, st, p, tiles_m, tiles_n, c);
+            else if (groups >= 16)
+                hipLaunchKernelGGL((mm_f32_tiles_kernel<NT, EPI, 4, 4>), grid, dim3(256), 0, st, p, tiles_m, tiles_n, c);
+            else
+                hipLaunchKernelGGL((mm_f32_tiles_kernel<NT, EPI, 4, 2>), grid, dim3(256), 0, st, p, tiles_m, tiles_n, c);
+            return hipGetLastError();
+        }
+    }
+    p.tiles_per_part = (a.rows_per_part + 15u) / 16u;
     const unsigned int tiles_y = p.tiles_per_part * a.parts;
     const dim3 block(kMmThreads);
-    const unsigned int ng = (p.K >> 4) >> (ks ? 2 : 0);
+    const unsigned int ng = p.K >> 6;
     if constexpr (!NT && EPI == MM_BIAS_RELU) if (copy) {
-        const unsigned int cb = (copy->n4 + 4u * kMmThreads - 1u) / (4u * kMmThreads), nx = a.N / TM;
+        const unsigned int cb = (copy->n4 + 4u * kMmThreads - 1u) / (4u * kMmThreads), nx = a.N / 16u;
         const dim3 grid(nx, tiles_y + (cb + nx - 1u) / nx, 1);
-#define RP_MM_COPY(KS, P_) \
-    hipLaunchKernelGGL((mm_f32_copy_kernel<NT, EPI, KS, P_>), grid, block, 0, st, p, tiles_y, *copy)
-        if (ks) {
-            if (ng >= 8) RP_MM_COPY(true, 8);
-            else if (ng >= 4) RP_MM_COPY(true, 4);
-            else RP_MM_COPY(true, 2);
-        } else {
-            if (ng >= 8) RP_MM_COPY(false, 8);
-            else if (ng >= 4) RP_MM_COPY(false, 4);
-            else RP_MM_COPY(false, 2);
-        }
-#undef RP_MM_COPY
+        if (ng >= 8) hipLaunchKernelGGL((mm_f32_copy_kernel<NT, EPI, 8>), grid, block, 0, st, p, tiles_y, *copy);
+        else hipLaunchKernelGGL((mm_f32_copy_kernel<NT, EPI, 4>), grid, block, 0, st, p, tiles_y, *copy);
         return hipGetLastError();
     }
-    const dim3 grid(a.N / TM, tiles_y, kgroups);
-    if (ks) {
-        if (ng >= 8) hipLaunchKernelGGL((mm_f32_kernel<NT, EPI, true, 8>), grid, block, 0, st, p);
-        else if (ng >= 4) hipLaunchKernelGGL((mm_f32_kernel<NT, EPI, true, 4>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((mm_f32_kernel<NT, EPI, true, 2>), grid, block, 0, st, p);
-    } else {
-        if (ng >= 8) hipLaunchKernelGGL((mm_f32_kernel<NT, EPI, false, 8>), grid, block, 0, st, p);
-        else if (ng >= 4) hipLaunchKernelGGL((mm_f32_kernel<NT, EPI, false, 4>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((mm_f32_kernel<NT, EPI, false, 2>), grid, block, 0, st, p);
-    }
+    const dim3 grid(a.N / 16u, tiles_y, kgroups);
+    if (ng >= 8) hipLaunchKernelGGL((mm_f32_kernel<NT, EPI, 8>), grid, block, 0, st, p);
+    else if (ng >= 4) hipLaunchKernelGGL((mm_f32_kernel<NT, EPI, 4>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((mm_f32_kernel<NT, EPI, 2>), grid, block, 0, st, p);
     return hipGetLastError();
 }
 

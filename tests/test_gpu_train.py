@@ -1049,3 +1049,23 @@ def test_paper_shaped_free_running_drift(B, capsys):
         assert curve[100] <= 1e-2
     finally:
         oracle.set_threads(1)
+
+
+@pytest.mark.parametrize("D,H,H2,A,batch,target_sync,dueling", [
+    # weight-gradient tiles: the batch's steps of four rows over eight wavefronts, T in flight
+    (27, 64, 0, 8, 1, 0, False), (27, 64, 0, 8, 3, 0, True), (27, 64, 0, 8, 33, 0, False),
+    (27, 64, 0, 30, 127, 0, True), (27, 64, 0, 30, 129, 0, False), (27, 64, 0, 30, 255, 3, True),
+    (27, 64, 0, 30, 257, 0, False), (27, 64, 0, 30, 514, 0, True),
+    # products in 32 x 32 tiles: K of 2, 4, 12, 18 and 36 groups of 16 over four and eight wavefronts,
+    # rows that end inside a tile, two parts, the dZ1 product in tiles of its own
+    (40, 512, 576, 40, 520, 2, False), (27, 192, 1024, 30, 150, 0, True), (33, 256, 320, 5, 401, 3, False),
+])
+def test_fp32_tile_edges(B, D, H, H2, A, batch, target_sync, dueling):
+    """The fp32 steps' tiled kernels where a batch, a contraction or a launch ends inside a tile or a
+    round of loads; tolerances of the other fp32 cases (the sums are fp32, in another order)."""
+    rows = synth.experiences(batch + 120, D, A, 0.05, seed=71)
+    pr = Pair(B, capacity=batch + 60, D=D, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=5, appends=3,
+              target_sync=target_sync, dueling=dueling, lr=1e-3)
+    pr.append_only(synth.take(rows, 0, batch + 90))
+    for k in range(batch + 90, batch + 120, 3):
+        assert pr.step(synth.take(rows, k, k + 3), compare=(k % 2 == 0) or k >= batch + 114) == 0
