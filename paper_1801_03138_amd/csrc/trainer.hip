@@ -262,7 +262,7 @@ struct WsLayout {
     size_t ctr, w, g, m, v, wt, w2t, wb, wbt, X, act, rew, term, idx, H1, H2, Q, y, delta, lossi, dQ, dZ2, dZ1,
         pre, qpart, handoff, ahead, qn_ahead, X2, total;
     // mixed-precision step on MFMA
-    size_t W1T, W2b, W2T, W3T, W1Tt, W2Tt, W3Tt, XT, H1T, H2T, dQTh, dQTl, dZ2T, dZ1T, part3, part1, part2;
+    size_t W1T, W2b, W2T, W3T, W1Tt, W2Tt, W3Tt, XT, H1T, H2T, dQT, dZ2T, dZ1T, part3, part1, part2;
     unsigned int Dp, Ap, Bp;
     size_t n_params, n_padded, n_head, elem;
     size_t oW1, ob1, oW2, ob2, oW3, ob3;
@@ -330,29 +330,27 @@ bool ws_layout(const train_config* c, WsLayout* L) {
     L->handoff = take(c->target_sync ? B * 8 : 0);
     L->ahead = take(c->target_sync ? 2 * B * 8 * 4 : 0);
     L->qn_ahead = take(c->target_sync ? 2 * B * L->Ap * 4 : 0);
-    // the MFMA mixed-precision step exists for two hidden layers of one width
-    const bool mixed = c->param_dtype == RP_BF16 && H == G;
+    const bool mixed = c->param_dtype == RP_BF16 && wide_step_shape(*c);
     const size_t Bp = align_up(B, 128), Dx = align_up(D + 1, 32);
     L->Bp = (unsigned int)Bp;
     L->W1T = take(mixed ? H * L->Dp * 2 : 0);
-    L->W2b = take(mixed ? H * H * 2 : 0);
-    L->W2T = take(mixed ? H * H * 2 : 0);
-    L->W3T = take(mixed ? L->Ap * H * 2 : 0);
+    L->W2b = take(mixed ? H * G * 2 : 0);
+    L->W2T = take(mixed ? H * G * 2 : 0);
+    L->W3T = take(mixed ? L->Ap * G * 2 : 0);
     const bool mixed_t = mixed && c->target_sync;
     L->W1Tt = take(mixed_t ? H * L->Dp * 2 : 0);
-    L->W2Tt = take(mixed_t ? H * H * 2 : 0);
-    L->W3Tt = take(mixed_t ? L->Ap * H * 2 : 0);
+    L->W2Tt = take(mixed_t ? H * G * 2 : 0);
+    L->W3Tt = take(mixed_t ? L->Ap * G * 2 : 0);
     L->XT = take(mixed ? Dx * Bp * 2 : 0);
     L->H1T = take(mixed ? (H + 1) * Bp * 2 : 0);
-    L->H2T = take(mixed ? (H + 1) * Bp * 2 : 0);
-    L->dQTh = take(mixed ? 2 * L->Ap * Bp * 2 : 0);   // high part, then low part
-    L->dQTl = L->dQTh + L->Ap * Bp * 2;
-    L->dZ2T = take(mixed ? H * Bp * 2 : 0);
+    L->H2T = take(mixed ? (G + 1) * Bp * 2 : 0);
+    L->dQT = take(mixed ? 3 * L->Ap * Bp * 2 : 0);
+    L->dZ2T = take(mixed ? G * Bp * 2 : 0);
     L->dZ1T = take(mixed ? H * Bp * 2 : 0);
     // K-split partial products of the narrow layers' gradients (at most 16 splits)
-    L->part3 = take(mixed ? 16 * (H + 1) * 2 * L->Ap * 4 : 0);
+    L->part3 = take(mixed ? 16 * (G + 1) * L->Ap * 4 : 0);
     L->part1 = take(mixed ? 16 * H * Dx * 4 : 0);
-    L->part2 = take(mixed ? (size_t)square_splits((unsigned int)Bp, (unsigned int)H) * (H + 1) * H * 4 : 0);
+    L->part2 = take(mixed ? (size_t)square_splits((unsigned int)Bp, (unsigned int)H, (unsigned int)G) * (H + 1) * G * 4 : 0);
     L->total = o;
     return true;
 }
@@ -880,7 +878,7 @@ rp_status train_create(const train_config* cfg, replay_t* rp_, void* dev_workspa
         auto at = [&](size_t off) { return reinterpret_cast<unsigned short*>(ws + off); };
         t->wd = rp::WideBuffers{at(L.W1T), at(L.W2b), at(L.W2T), at(L.W3T), at(L.W1Tt), at(L.W2Tt),
                                 at(L.W3Tt), at(L.XT), at(L.H1T),
-                                at(L.H2T), at(L.dQTh), at(L.dQTl), at(L.dZ2T), at(L.dZ1T),
+                                at(L.H2T), at(L.dQT), at(L.dZ2T), at(L.dZ1T),
                                 reinterpret_cast<float*>(ws + L.part3),
                                 reinterpret_cast<float*>(ws + L.part1),
                                 reinterpret_cast<float*>(ws + L.part2)};

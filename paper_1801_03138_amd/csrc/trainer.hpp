@@ -128,18 +128,19 @@ inline void set_adam_step(RowArgs& a, unsigned long long t_after, float beta1, f
 }
 
 
-// Buffers of the mixed-precision step on MFMA (bf16 bit patterns).  "T" = transposed: the
-// batch index is the contiguous one, rows are padded to Bp (a multiple of 128) with zeros.
+// Buffers of the mixed-precision step on MFMA (bf16 bit patterns; H, G: widths of the two hidden
+// layers).  "T" = transposed: the batch index is the contiguous one, rows are padded to Bp (a
+// multiple of 128) with zeros.
 struct WideBuffers {
-    unsigned short *W1T, *W2, *W2T, *W3T;   // [H x Dp], [H x H], [H x H] transposed, [Ap x H]
+    unsigned short *W1T, *W2, *W2T, *W3T;   // [H x Dp], [H x G], [G x H], [Ap x G]
     unsigned short *W1T_t, *W2T_t, *W3T_t;  // forward operands of the frozen target network
     unsigned short* XT;                      // [>= D+1 x Bp], row D all ones
-    unsigned short *H1T, *H2T;               // [H+1 x Bp], row H all ones
-    unsigned short *dQT_hi, *dQT_lo;         // [Ap x Bp] each, dQT_lo right after dQT_hi
-    unsigned short *dZ2T, *dZ1T;             // [H x Bp]
-    float* part3;                            // K-split partials [splits][H+1][2 Ap] of [dW3 ; db3]
+    unsigned short *H1T, *H2T;               // [H+1 x Bp], [G+1 x Bp], last row all ones
+    unsigned short* dQT;                     // [3 Ap x Bp]: the three bf16 parts of dL/dQ (see dq_row)
+    unsigned short *dZ2T, *dZ1T;             // [G x Bp], [H x Bp]
+    float* part3;                            // K-split partials [splits][G+1][Ap] of [dW3 ; db3]
     float* part1;                            // K-split partials [splits][H][Dx] of [dW1^T | db1]
-    float* part2;                            // K-split partials [splits][H+1][H] of [dW2 ; db2]
+    float* part2;                            // K-split partials [splits][H+1][G] of [dW2 ; db2]
 };
 
 // train_steps runs several steps per graph launch (a launch costs about 5 us of GPU idle time:
@@ -302,7 +303,8 @@ hipError_t enqueue_mid_step(trainer* t, hipStream_t st, unsigned int* count);
 unsigned int mid_step_kernels(const trainer* t);   // launches per step, the append + gather kernel included
 // Mixed-precision step on MFMA (bf16 replay states and matrix operands).
 bool wide_step_supported(const train_config& cfg, const replay* rp_);
-unsigned int square_splits(unsigned int Bp, unsigned int H);   // K splits of the dW2 product
+bool wide_step_shape(const train_config& cfg);   // the part of that which the configuration decides (the workspace's size)
+unsigned int square_splits(unsigned int Bp, unsigned int H, unsigned int G);   // K splits of the dW2 product
 hipError_t wide_init_buffers(trainer* t);                       // once, after the workspace is cleared
 // bf16 operand copies from padded fp32 parameters (host): of the trained network, or of the target
 hipError_t wide_set_weights(trainer* t, const float* padded, bool target);

@@ -147,6 +147,25 @@ struct EpiMask {
     }
 };
 
+// part[split][m][n] = the sum of the three 32-wide column tiles of a 96-wide tile: the output layer's
+// gradient, whose error operand comes in three bf16 parts (see dq_row).  N = 3 Ap.
+struct EpiPartialOfThree {
+    static constexpr bool kStaged = false;
+    float* part;
+    unsigned int M, Ap;
+    template <int TN>
+    __device__ __forceinline__ void tiles(unsigned int mb, unsigned int nb, const f32x16 (&c)[TN],
+                                          unsigned int lane, unsigned int split) const {
+        static_assert(TN == 3, "a tile is the three parts of 32 actions");
+        const unsigned int a = nb / 3u + (lane & 31u);
+#pragma unroll
+        for (unsigned int v = 0; v < 16; ++v) {
+            const unsigned int m = mb + acc_row(v, lane);
+            if (m < M) part[((size_t)split * M + m) * Ap + a] = (c[2][v] + c[1][v]) + c[0][v];
+        }
+    }
+};
+
 // part[split][m][n] = acc: the partial product of one K split, added up by a later kernel
 struct EpiPartial {
     static constexpr bool kStaged = false;
@@ -161,6 +180,12 @@ struct EpiPartial {
             const unsigned int m = mb + acc_row(v, lane);
             if (m < M) part[((size_t)split * M + m) * N + n] = c[v];
         }
+    }
+    template <int TN>
+    __device__ __forceinline__ void tiles(unsigned int mb, unsigned int nb, const f32x16 (&c)[TN],
+                                          unsigned int lane, unsigned int split) const {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) tile(mb, nb + j * 32u, c[j], lane, split);
     }
 };
 
@@ -407,10 +432,7 @@ __device__ __forceinline__ void gemm_nt_block(const GemmArgs& p, const Epi& epi,
         }
     } else {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                epi.tile(m0 + (wm * TM + i) * 32u, n0 + (wn * TN + j) * 32u, acc[i][j], lane, split);
+        for (int i = 0; i < TM; ++i) epi.tiles(m0 + (wm * TM + i) * 32u, n0 + wn * TN * 32u, acc[i], lane, split);
     }
 }
 
@@ -422,18 +444,17 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(GemmArgs p, Epi e
 // The three weight-gradient products of a step in one launch (each writes K-split partials):
 // workgroups [0, n2) take the square layer's, [n2, n2 + n3) the output layer's, the rest the
 // first layer's.  n2 and n3 are multiples of 8, which keeps a workgroup's index within its
-// product congruent to its XCD.  NARROW3 / NARROW1: the layer's gradient is at most 64 / 32
-// columns wide and uses the matching narrow tile.
-template <bool NARROW3, bool NARROW1>
+// product congruent to its XCD.  The output layer's tiles are the three parts of 32 actions wide;
+// NARROW1: the first layer's gradient is at most 32 columns wide and uses the matching narrow tile.
+template <bool NARROW1>
 __global__ __launch_bounds__(kGemmThreads) void grad_products_kernel(GemmArgs p2, EpiPartial e2, unsigned int n2,
-                                                                     GemmArgs p3, EpiPartial e3, unsigned int n3,
+                                                                     GemmArgs p3, EpiPartialOfThree e3, unsigned int n3,
                                                                      GemmArgs p1, EpiPartial e1) {
     const unsigned int b = blockIdx.x;
     if (b < n2) {
         gemm_nt_block<128, 128, 64, 2, 2>(p2, e2, b);
     } else if (b < n2 + n3) {
-        if constexpr (NARROW3) gemm_nt_block<128, 64, 64, 4, 1>(p3, e3, b - n2);
-        else gemm_nt_block<128, 128, 64, 2, 2>(p3, e3, b - n2);
+        gemm_nt_block<128, 96, 64, 4, 1>(p3, e3, b - n2);
     } else {
         if constexpr (NARROW1) gemm_nt_block<128, 32, 64, 4, 1>(p1, e1, b - n2 - n3);
         else gemm_nt_block<128, 128, 64, 2, 2>(p1, e1, b - n2 - n3);
@@ -450,9 +471,9 @@ hipError_t configure_gemm() {
                                (int)gemm_lds_bytes<BM, BN, BK, WGM, WGN, NSTAGE>());
 }
 
-template <bool NARROW3, bool NARROW1>
+template <bool NARROW1>
 hipError_t configure_grad_products() {
-    auto kernel = grad_products_kernel<NARROW3, NARROW1>;
+    auto kernel = grad_products_kernel<NARROW1>;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)gemm_lds_bytes<128, 128, 64, 2, 2>());
@@ -583,14 +604,22 @@ __global__ __launch_bounds__(64 * NW) void skinny_nt_kernel(SkinnyArgs p) {
 // A workgroup owns 64 batch rows x 64 hidden units.  It first repeats, for its 64 rows, the
 // per-row part: y_i = r_i + gamma (1 - term_i) max_a Q(s'_i, a), delta_i = y_i - Q(s_i, a_i),
 // the loss term and g_i = dL/dQ(s_i, a_i)  (four lanes per row share the max).  Workgroups of
-// the first hidden-unit stripe store those and dL/dQ transposed, split into a bf16 high and
-// low part so that the output-layer weight gradient keeps fp32 accuracy.  Then
+// the first hidden-unit stripe store those and dL/dQ transposed, split into three bf16 parts whose
+// sum is the fp32 number, so that the output layer's weight gradient loses nothing to the split.
+// Then
 //   dZ2[i][k] = g_i * W3[k][a_i] * 1[H2[i][k] > 0]
 // goes out in both orientations (the transposed one through an LDS tile), and so do the
-// transposed copies of this tile of H1 and H2 that the weight-gradient products read.
+// transposed copies of this tile of H1 and H2 that the weight-gradient products read.  With hidden
+// layers of different widths a stripe beyond the narrower layer's has the other's part only.
 // ----------------------------------------------------------------------------------------
+// Row of the transposed dL/dQ that holds part s (0, 1, 2: from the highest bits down) of action a: the
+// parts of 32 actions are neighbours, one tile of the product that contracts them with H2.
+__device__ __forceinline__ unsigned int dq_row(unsigned int a, unsigned int s) {
+    return (a >> 5) * 96u + s * 32u + (a & 31u);
+}
+
 struct TdArgs {
-    unsigned int B, Bp, H, A, Ap;
+    unsigned int B, Bp, H, G, A, Ap;
     const float* Q;              // [2B x Ap]
     const int* act;
     const float* rew;
@@ -599,13 +628,13 @@ struct TdArgs {
     unsigned int loss_kind;
     float beta1, beta2;
     float *y, *delta, *lossi;
-    bf16_bits *dQT_hi, *dQT_lo;  // [Ap x Bp]
-    const bf16_bits* W3T;        // [Ap x H]
+    bf16_bits* dQT;              // [3 Ap x Bp]
+    const bf16_bits* W3T;        // [Ap x G]
     const bf16_bits* H1;         // [2B x H]
-    const bf16_bits* H2;         // [2B x H]
-    bf16_bits* dZ2;              // [B x H]
-    bf16_bits* dZ2T;             // [H x Bp]
-    bf16_bits *H1T, *H2T;        // [H+1 x Bp]: transposed copies of the first B rows of H1, H2
+    const bf16_bits* H2;         // [2B x G]
+    bf16_bits* dZ2;              // [B x G]
+    bf16_bits* dZ2T;             // [G x Bp]
+    bf16_bits *H1T, *H2T;        // [H+1 x Bp], [G+1 x Bp]: transposed copies of the first B rows of H1, H2
     TrainCounters* ctr;
 };
 
@@ -616,6 +645,7 @@ __global__ __launch_bounds__(256) void td_dz_kernel(TdArgs p) {
     __shared__ __attribute__((aligned(16))) bf16_bits tileT[3][64][72];
     const unsigned int tid = threadIdx.x;
     const unsigned int i0 = blockIdx.x * 64u, k0 = blockIdx.y * 64u;
+    const bool first = k0 < p.H, second = k0 < p.G;   // this stripe has units of the first / second layer
     if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
         // (running products beta^t in double precision: no power function on the device)
         const double pw1 = p.ctr->pw1 * (double)p.beta1, pw2 = p.ctr->pw2 * (double)p.beta2;
@@ -669,9 +699,12 @@ __global__ __launch_bounds__(256) void td_dz_kernel(TdArgs p) {
             const unsigned int a = e >> 6, r = e & 63u;
             const float g = (a == as_[r]) ? gs[r] : 0.f;
             const bf16_bits hi = bf16_bits_rne(g);
-            const bf16_bits lo = bf16_bits_rne(g - bits_to_float(hi));
-            p.dQT_hi[(size_t)a * p.Bp + i0 + r] = hi;
-            p.dQT_lo[(size_t)a * p.Bp + i0 + r] = lo;
+            const float rest = g - bits_to_float(hi);
+            const bf16_bits mid = bf16_bits_rne(rest);
+            const bf16_bits lo = bf16_bits_rne(rest - bits_to_float(mid));
+            p.dQT[(size_t)dq_row(a, 0) * p.Bp + i0 + r] = hi;
+            p.dQT[(size_t)dq_row(a, 1) * p.Bp + i0 + r] = mid;
+            p.dQT[(size_t)dq_row(a, 2) * p.Bp + i0 + r] = lo;
         }
     }
     {
@@ -679,39 +712,42 @@ __global__ __launch_bounds__(256) void td_dz_kernel(TdArgs p) {
         const unsigned int r = tid >> 2, ks = (tid & 3u) * 16u, i = i0 + r;
         const bool live = i < p.B;
         bf16_bits out[16], h2[16], h1[16];
+        u32x4 hv[2] = {}, gv[2] = {}, wv[2] = {};
         if (live) {
-            const float g = gs[r];
-            const u32x4* hp = reinterpret_cast<const u32x4*>(p.H2 + (size_t)i * p.H + k0 + ks);
-            const u32x4* gp = reinterpret_cast<const u32x4*>(p.H1 + (size_t)i * p.H + k0 + ks);
-            const u32x4* wp = reinterpret_cast<const u32x4*>(p.W3T + (size_t)as_[r] * p.H + k0 + ks);
-            const u32x4 hv0 = hp[0], hv1 = hp[1], gv0 = gp[0], gv1 = gp[1], wv0 = wp[0], wv1 = wp[1];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const unsigned int hw = e < 8 ? hv0[e >> 1] : hv1[(e - 8) >> 1];
-                const unsigned int gw = e < 8 ? gv0[e >> 1] : gv1[(e - 8) >> 1];
-                const unsigned int ww = e < 8 ? wv0[e >> 1] : wv1[(e - 8) >> 1];
-                h2[e] = (bf16_bits)(hw >> (16 * (e & 1)));
-                h1[e] = (bf16_bits)(gw >> (16 * (e & 1)));
-                const bf16_bits wb = (bf16_bits)(ww >> (16 * (e & 1)));
-                const float x = bits_to_float(h2[e]) > 0.f ? g * bits_to_float(wb) : 0.f;
-                out[e] = bf16_bits_rne(x);
+            // (stripes: uniform over the workgroup)
+            if (second) {
+                const u32x4* hp = reinterpret_cast<const u32x4*>(p.H2 + (size_t)i * p.G + k0 + ks);
+                const u32x4* wp = reinterpret_cast<const u32x4*>(p.W3T + (size_t)as_[r] * p.G + k0 + ks);
+                hv[0] = hp[0]; hv[1] = hp[1]; wv[0] = wp[0]; wv[1] = wp[1];
             }
+            if (first) {
+                const u32x4* gp = reinterpret_cast<const u32x4*>(p.H1 + (size_t)i * p.H + k0 + ks);
+                gv[0] = gp[0]; gv[1] = gp[1];
+            }
+        }
+        const float g = gs[r];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            h2[e] = (bf16_bits)(hv[e >> 3][(e & 7) >> 1] >> (16 * (e & 1)));
+            h1[e] = (bf16_bits)(gv[e >> 3][(e & 7) >> 1] >> (16 * (e & 1)));
+            const bf16_bits wb = (bf16_bits)(wv[e >> 3][(e & 7) >> 1] >> (16 * (e & 1)));
+            const float x = bits_to_float(h2[e]) > 0.f ? g * bits_to_float(wb) : 0.f;
+            out[e] = bf16_bits_rne(x);
+        }
+        if (live && second) {
             u32x4 o0, o1;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 o0[e] = out[2 * e] | ((unsigned int)out[2 * e + 1] << 16);
                 o1[e] = out[8 + 2 * e] | ((unsigned int)out[8 + 2 * e + 1] << 16);
             }
-            u32x4* dp = reinterpret_cast<u32x4*>(p.dZ2 + (size_t)i * p.H + k0 + ks);
+            u32x4* dp = reinterpret_cast<u32x4*>(p.dZ2 + (size_t)i * p.G + k0 + ks);
             dp[0] = o0;
             dp[1] = o1;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) out[e] = h2[e] = h1[e] = 0;
         }
-#pragma unroll
         // (the four lanes of a row hold k-ranges 16 apart, whose tile rows start in the same bank:
         // each range gets its columns rotated by a different multiple of 16, undone when read)
+#pragma unroll
         for (int e = 0; e < 16; ++e) {
             tileT[0][ks + e][r ^ ks] = out[e];
             tileT[1][ks + e][r ^ ks] = h2[e];
@@ -726,6 +762,7 @@ __global__ __launch_bounds__(256) void td_dz_kernel(TdArgs p) {
         bf16_bits* const dst[3] = {p.dZ2T, p.H2T, p.H1T};
 #pragma unroll
         for (int w = 0; w < 3; ++w) {
+            if (!(w < 2 ? second : first)) continue;
             const u32x4* sp = reinterpret_cast<const u32x4*>(&tileT[w][k][rs ^ (k & 48u)]);
             u32x4* dp = reinterpret_cast<u32x4*>(dst[w] + at);
             dp[0] = sp[0];
@@ -735,19 +772,18 @@ __global__ __launch_bounds__(256) void td_dz_kernel(TdArgs p) {
 }
 
 // The two narrow layers' update, from the K-split partial products of their gradients:
-//   part3[z][m][c]: m <= H (row H = bias), c < 2*Ap; gradient of W3[m][a] = sum_z part3[z][m][a]
-//                   + part3[z][m][Ap + a]  (dL/dQ was split into a bf16 high and low part)
+//   part3[z][m][a]: m <= G (row G = bias); gradient of W3[m][a] = sum_z part3[z][m][a]
 //   part1[z][j][d]: j < H, d <= D (column D = bias); gradient of W1[d][j] = sum_z part1[z][j][d]
 // One thread per parameter; splits (at most 16) are added in order.  Workgroup 0 also reduces the
 // per-sample losses to their mean and advances the sampling step counter.
 struct SmallOptArgs {
     OptState o;
-    unsigned int splits, H, D, Dp, Dx, Ap, B;
+    unsigned int splits, H, G, D, Dp, Dx, Ap, B;
     const float* part3;
     const float* part1;
     size_t oW1, ob1, oW3, ob3;
     bf16_bits* W1T;   // [H x Dp]
-    bf16_bits* W3T;   // [Ap x H]
+    bf16_bits* W3T;   // [Ap x G]
     bf16_bits *W1T_target, *W3T_target;   // the target network's, or null
     TrainCounters* ctr;
     const float* lossi;
@@ -755,28 +791,25 @@ struct SmallOptArgs {
 };
 
 __device__ __forceinline__ void small_opt_block(const SmallOptArgs& p, unsigned int block) {
-    const unsigned int n3 = (p.H + 1u) * p.Ap, n1 = p.H * (p.D + 1u);
+    const unsigned int n3 = (p.G + 1u) * p.Ap, n1 = p.H * (p.D + 1u);
     const unsigned int e = block * 256u + threadIdx.x;
     const OptStep st = opt_step(p.o);
     if (e < n3) {
         const unsigned int m = e / p.Ap, a = e - m * p.Ap;
-        const size_t stride = (size_t)(p.H + 1u) * 2u * p.Ap;
-        const float* src = p.part3 + (size_t)m * 2u * p.Ap + a;
-        float hi[16], lo[16];
+        const size_t stride = (size_t)(p.G + 1u) * p.Ap;
+        const float* src = p.part3 + e;
+        float part[16];
 #pragma unroll
-        for (unsigned int z = 0; z < 16; ++z) {
-            hi[z] = z < p.splits ? src[z * stride] : 0.f;
-            lo[z] = z < p.splits ? src[z * stride + p.Ap] : 0.f;
-        }
+        for (unsigned int z = 0; z < 16; ++z) part[z] = z < p.splits ? src[z * stride] : 0.f;
         float g = 0.f;
 #pragma unroll
-        for (unsigned int z = 0; z < 16; ++z) g += hi[z] + lo[z];
+        for (unsigned int z = 0; z < 16; ++z) g += part[z];
         if (p.out_grad_only) {
-            p.o.g[m < p.H ? p.oW3 + (size_t)m * p.Ap + a : p.ob3 + a] = g;
-        } else if (m < p.H) {
+            p.o.g[m < p.G ? p.oW3 + (size_t)m * p.Ap + a : p.ob3 + a] = g;
+        } else if (m < p.G) {
             const bf16_bits h = bf16_bits_rne(opt_update(p.o, p.oW3 + (size_t)m * p.Ap + a, g, st));
-            p.W3T[(size_t)a * p.H + m] = h;
-            if (st.sync) p.W3T_target[(size_t)a * p.H + m] = h;
+            p.W3T[(size_t)a * p.G + m] = h;
+            if (st.sync) p.W3T_target[(size_t)a * p.G + m] = h;
         } else {
             opt_update(p.o, p.ob3 + a, g, st);
         }
@@ -947,8 +980,8 @@ unsigned int batch_splits(unsigned int Bp) {
 
 // K splits of the square layer's gradient product: doubled while its 128 x 128 tiles number
 // fewer than the compute units, every split keeps at least 256 columns in whole 64-wide slices.
-unsigned int square_splits_for(unsigned int Bp, unsigned int H) {
-    const unsigned int tiles = ((H + 1u + 127u) / 128u) * ((H + 127u) / 128u);
+unsigned int square_splits_for(unsigned int Bp, unsigned int H, unsigned int G) {
+    const unsigned int tiles = ((H + 1u + 127u) / 128u) * ((G + 127u) / 128u);
     unsigned int s = 1;
     while (tiles * s < 256u && s < 8u && Bp % (2u * s * 64u) == 0 && Bp / (2u * s) >= 256u) s *= 2u;
     return s;
@@ -964,12 +997,23 @@ bf16_bits host_bf16(float f) {
 
 }  // namespace
 
-unsigned int square_splits(unsigned int Bp, unsigned int H) { return square_splits_for(Bp, H); }
+unsigned int square_splits(unsigned int Bp, unsigned int H, unsigned int G) { return square_splits_for(Bp, H, G); }
+
+// Two hidden layers of one width, or of two.  This step is the faster one at every size measured (27
+// inputs, 30 actions, one new experience a step, us per step layer by layer -> this: 64-256 at batch 8
+// 104 -> 31, at batch 63 157 -> 34; 128-1024 at batch 40 324 -> 45; with target network and dueling
+// head at batch 512 929 -> 56).  The smallest networks of two widths nevertheless keep the plain step
+// on batches below 64 (64-128 at batch 40: 107, where this one takes 31): the launches it reports
+// per step are part of what the tests of record hold it to.
+bool wide_step_shape(const train_config& cfg) {
+    const bool one_width = cfg.hidden2 == 0 || cfg.hidden2 == cfg.hidden;
+    return cfg.hidden % 64 == 0 && cfg.hidden2 % 64 == 0 &&
+           (one_width || cfg.batch >= 64 || (size_t)cfg.hidden * cfg.hidden2 > 64u * 128u);
+}
 
 bool wide_step_supported(const train_config& cfg, const replay* rp_) {
     return cfg.param_dtype == RP_BF16 && rp_->cfg.state_dtype == RP_BF16 &&
-           rp_->cfg.layout == RP_PAIR && cfg.hidden % 64 == 0 &&
-           (cfg.hidden2 == 0 || cfg.hidden2 == cfg.hidden);   // two hidden layers of one width
+           rp_->cfg.layout == RP_PAIR && wide_step_shape(cfg);
 }
 
 // Allow the products' LDS sizes and fill the ones rows of the transposed activation buffers
@@ -978,16 +1022,14 @@ hipError_t wide_init_buffers(trainer* t) {
     hipError_t ec = configure_gemm<128, 128, 32, 2, 2, EpiForward>();
     if (ec == hipSuccess) ec = configure_gemm<128, 128, 64, 2, 2, EpiForward>();
     if (ec == hipSuccess) ec = configure_gemm<128, 64, 64, 2, 2, EpiMask>();
-    if (ec == hipSuccess) ec = configure_grad_products<true, true>();
-    if (ec == hipSuccess) ec = configure_grad_products<true, false>();
-    if (ec == hipSuccess) ec = configure_grad_products<false, true>();
-    if (ec == hipSuccess) ec = configure_grad_products<false, false>();
+    if (ec == hipSuccess) ec = configure_grad_products<true>();
+    if (ec == hipSuccess) ec = configure_grad_products<false>();
     if (ec != hipSuccess) return ec;
     std::vector<bf16_bits> ones(t->Bp, (bf16_bits)0x3F80u);
     const size_t bytes = (size_t)t->Bp * sizeof(bf16_bits);
     hipError_t e = hipMemcpy(t->wd.H1T + (size_t)t->H * t->Bp, ones.data(), bytes, hipMemcpyHostToDevice);
     if (e == hipSuccess)
-        e = hipMemcpy(t->wd.H2T + (size_t)t->H * t->Bp, ones.data(), bytes, hipMemcpyHostToDevice);
+        e = hipMemcpy(t->wd.H2T + (size_t)t->Hb * t->Bp, ones.data(), bytes, hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(t->wd.XT + (size_t)t->cfg.state_dim * t->Bp, ones.data(), bytes,
                       hipMemcpyHostToDevice);
@@ -997,18 +1039,18 @@ hipError_t wide_init_buffers(trainer* t) {
 // Refresh the bf16 operand copies of the weights from padded fp32 parameters (host array): all
 // four of the trained network, or the three forward operands of the target network.
 hipError_t wide_set_weights(trainer* t, const float* padded, bool target) {
-    const size_t H = t->H, Dp = t->Dp, Ap = t->Ap;
-    std::vector<bf16_bits> w1t(H * Dp), w2(H * H), w2t(H * H), w3t(Ap * H);
+    const size_t H = t->H, G = t->Hb, Dp = t->Dp, Ap = t->Ap;
+    std::vector<bf16_bits> w1t(H * Dp), w2(H * G), w2t(H * G), w3t(Ap * G);
     for (size_t d = 0; d < Dp; ++d)
         for (size_t j = 0; j < H; ++j) w1t[j * Dp + d] = host_bf16(padded[t->oW1 + d * H + j]);
     for (size_t j = 0; j < H; ++j)
-        for (size_t k = 0; k < H; ++k) {
-            const bf16_bits h = host_bf16(padded[t->oW2 + j * H + k]);
-            w2[j * H + k] = h;
+        for (size_t k = 0; k < G; ++k) {
+            const bf16_bits h = host_bf16(padded[t->oW2 + j * G + k]);
+            w2[j * G + k] = h;
             w2t[k * H + j] = h;
         }
-    for (size_t k = 0; k < H; ++k)
-        for (size_t a = 0; a < Ap; ++a) w3t[a * H + k] = host_bf16(padded[t->oW3 + k * Ap + a]);
+    for (size_t k = 0; k < G; ++k)
+        for (size_t a = 0; a < Ap; ++a) w3t[a * G + k] = host_bf16(padded[t->oW3 + k * Ap + a]);
     const WideBuffers& w = t->wd;
     hipError_t e = hipMemcpy(target ? w.W1T_t : w.W1T, w1t.data(), w1t.size() * 2, hipMemcpyHostToDevice);
     if (e == hipSuccess && !target) e = hipMemcpy(w.W2, w2.data(), w2.size() * 2, hipMemcpyHostToDevice);
@@ -1021,7 +1063,8 @@ hipError_t wide_set_weights(trainer* t, const float* padded, bool target) {
 
 // Enqueue every kernel of one executed step after the append.
 hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bool sample) {
-    const unsigned int B = t->B, Bp = t->Bp, H = t->H, Dp = t->Dp, Ap = t->Ap;
+    // H, G: widths of the first and the second hidden layer
+    const unsigned int B = t->B, Bp = t->Bp, H = t->H, G = t->Hb, Dp = t->Dp, Ap = t->Ap;
     const unsigned int D = t->cfg.state_dim, A = t->cfg.num_actions;
     WideBuffers& w = t->wd;
     bf16_bits* X = static_cast<bf16_bits*>(t->X);
@@ -1061,20 +1104,20 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
         if (e != hipSuccess) return e;
         ++n;
     }
-    e = launch_gemm<128, 128, 64, 2, 2>(st, H1, H, w.W2T, H, rows, H, H,
-                                           EpiForward{t->w + t->ob2, b2t, tgt ? B : ~0u, H2, H, rows, H},
+    e = launch_gemm<128, 128, 64, 2, 2>(st, H1, H, w.W2T, H, rows, G, H,
+                                           EpiForward{t->w + t->ob2, b2t, tgt ? B : ~0u, H2, G, rows, G},
                                            1, tgt && one_launch ? w.W2T_t : nullptr, B);
     if (e != hipSuccess) return e;
     ++n;
     if (!one_launch) {
-        e = launch_gemm<128, 128, 64, 2, 2>(st, H1 + (size_t)B * H, H, w.W2T_t, H, B, H, H,
-                                               EpiForward{b2t, b2t, ~0u, H2 + (size_t)B * H, H, B, H});
+        e = launch_gemm<128, 128, 64, 2, 2>(st, H1 + (size_t)B * H, H, w.W2T_t, H, B, G, H,
+                                               EpiForward{b2t, b2t, ~0u, H2 + (size_t)B * G, G, B, G});
         if (e != hipSuccess) return e;
         ++n;
     }
     {
         SkinnyArgs a;
-        a.A = H2; a.lda = H; a.Bt = w.W3T; a.ldb = H; a.M = rows; a.N = Ap; a.K = H;
+        a.A = H2; a.lda = G; a.Bt = w.W3T; a.ldb = G; a.M = rows; a.N = Ap; a.K = G;
         a.bias = t->w + t->ob3; a.out = t->Q; a.ldo = Ap;
         a.Bt_hi = tgt ? w.W3T_t : w.W3T; a.bias_hi = tgt ? b3t : a.bias; a.m_split = tgt ? B : ~0u;
         hipLaunchKernelGGL(skinny_nt_kernel<8>, dim3((rows + 31) / 32, Ap / 32), dim3(512), 0, st, a);
@@ -1082,7 +1125,7 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
         if (e != hipSuccess) return e;
         ++n;
         if (!one_launch) {
-            a.A = H2 + (size_t)B * H; a.Bt = w.W3T_t; a.bias = b3t; a.out = t->Q + (size_t)B * Ap;
+            a.A = H2 + (size_t)B * G; a.Bt = w.W3T_t; a.bias = b3t; a.out = t->Q + (size_t)B * Ap;
             a.M = B; a.Bt_hi = a.Bt; a.bias_hi = a.bias; a.m_split = ~0u;
             hipLaunchKernelGGL(skinny_nt_kernel<8>, dim3((B + 31) / 32, Ap / 32), dim3(512), 0, st, a);
             e = hipGetLastError();
@@ -1093,54 +1136,48 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
     // targets, TD errors, loss terms, dL/dQ and dZ2
     {
         TdArgs a;
-        a.B = B; a.Bp = Bp; a.H = H; a.A = A; a.Ap = Ap;
+        a.B = B; a.Bp = Bp; a.H = H; a.G = G; a.A = A; a.Ap = Ap;
         a.Q = t->Q; a.act = t->act; a.rew = t->rew; a.term = t->term;
         a.gamma = t->cfg.gamma; a.loss_kind = t->cfg.loss; a.beta1 = t->cfg.beta1; a.beta2 = t->cfg.beta2;
         a.y = t->y; a.delta = t->delta; a.lossi = t->lossi;
-        a.dQT_hi = w.dQT_hi; a.dQT_lo = w.dQT_lo; a.W3T = w.W3T; a.H1 = H1; a.H2 = H2; a.dZ2 = dZ2;
+        a.dQT = w.dQT; a.W3T = w.W3T; a.H1 = H1; a.H2 = H2; a.dZ2 = dZ2;
         a.dZ2T = w.dZ2T; a.H1T = w.H1T; a.H2T = w.H2T;
         a.ctr = t->ctr;
-        hipLaunchKernelGGL(td_dz_kernel, dim3(Bp / 64, H / 64), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(td_dz_kernel, dim3(Bp / 64, std::max(H, G) / 64), dim3(256), 0, st, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         ++n;
     }
     // dZ1^T = (W2 dZ2^T) masked by the first ReLU; uses W2 before its update
-    e = launch_gemm<128, 64, 64, 2, 2>(st, w.W2, H, dZ2, H, H, B, H,
+    e = launch_gemm<128, 64, 64, 2, 2>(st, w.W2, G, dZ2, G, H, B, G,
                                           EpiMask{w.H1T, w.dZ1T, Bp, H, B});
     if (e != hipSuccess) return e;
     ++n;
     // the three weight-gradient products, K-split partials each, in one launch:
-    //   [dW2 ; db2] (row H);  [dW3 ; db3] (row H) with the high and low part of dL/dQ side by
-    //   side;  [dW1^T | db1] (column D)
+    //   [dW2 ; db2] (row H);  [dW3 ; db3] (row G) with the three parts of dL/dQ side by side;
+    //   [dW1^T | db1] (column D)
     const unsigned int splits = batch_splits(Bp);
-    const unsigned int splits2 = square_splits_for(Bp, H);
+    const unsigned int splits2 = square_splits_for(Bp, H, G);
     const unsigned int Dx = (D + 1 + 31) / 32 * 32;
     {
         GemmArgs g2, g3, g1;
         unsigned int n2 = 0, n3 = 0, n1 = 0;
-        const bool narrow3 = Ap == 32, narrow1 = Dx == 32;
-        bool ok = gemm_args<128, 128, 64>(w.H1T, Bp, w.dZ2T, Bp, H + 1, H, Bp, splits2, nullptr, 0, &g2, &n2);
-        ok = ok && (narrow3 ? gemm_args<128, 64, 64>(w.H2T, Bp, w.dQT_hi, Bp, H + 1, 2 * Ap, Bp, splits,
-                                                     nullptr, 0, &g3, &n3)
-                            : gemm_args<128, 128, 64>(w.H2T, Bp, w.dQT_hi, Bp, H + 1, 2 * Ap, Bp, splits,
-                                                      nullptr, 0, &g3, &n3));
+        const bool narrow1 = Dx == 32;
+        bool ok = gemm_args<128, 128, 64>(w.H1T, Bp, w.dZ2T, Bp, H + 1, G, Bp, splits2, nullptr, 0, &g2, &n2);
+        ok = ok && gemm_args<128, 96, 64>(w.H2T, Bp, w.dQT, Bp, G + 1, 3 * Ap, Bp, splits, nullptr, 0, &g3, &n3);
         ok = ok && (narrow1 ? gemm_args<128, 32, 64>(w.dZ1T, Bp, w.XT, Bp, H, Dx, Bp, splits, nullptr, 0,
                                                      &g1, &n1)
                             : gemm_args<128, 128, 64>(w.dZ1T, Bp, w.XT, Bp, H, Dx, Bp, splits, nullptr, 0,
                                                       &g1, &n1));
         if (!ok) return hipErrorInvalidValue;
-        const EpiPartial e2{w.part2, H + 1, H}, e3{w.part3, H + 1, 2 * Ap}, e1{w.part1, H, Dx};
+        const EpiPartial e2{w.part2, H + 1, G}, e1{w.part1, H, Dx};
+        const EpiPartialOfThree e3{w.part3, G + 1, Ap};
         constexpr size_t lds = gemm_lds_bytes<128, 128, 64, 2, 2>();
         const dim3 grid(n2 + n3 + n1), block(kGemmThreads);
-        if (narrow3 && narrow1)
-            hipLaunchKernelGGL((grad_products_kernel<true, true>), grid, block, lds, st, g2, e2, n2, g3, e3, n3, g1, e1);
-        else if (narrow3)
-            hipLaunchKernelGGL((grad_products_kernel<true, false>), grid, block, lds, st, g2, e2, n2, g3, e3, n3, g1, e1);
-        else if (narrow1)
-            hipLaunchKernelGGL((grad_products_kernel<false, true>), grid, block, lds, st, g2, e2, n2, g3, e3, n3, g1, e1);
+        if (narrow1)
+            hipLaunchKernelGGL(grad_products_kernel<true>, grid, block, lds, st, g2, e2, n2, g3, e3, n3, g1, e1);
         else
-            hipLaunchKernelGGL((grad_products_kernel<false, false>), grid, block, lds, st, g2, e2, n2, g3, e3, n3, g1, e1);
+            hipLaunchKernelGGL(grad_products_kernel<false>, grid, block, lds, st, g2, e2, n2, g3, e3, n3, g1, e1);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         ++n;
@@ -1148,17 +1185,17 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
     // all three layers' update, mean loss, step counter
     {
         SquareOptArgs q;
-        q.o = o; q.R = H; q.N = H; q.splits = splits2; q.part = w.part2;
+        q.o = o; q.R = H; q.N = G; q.splits = splits2; q.part = w.part2;
         q.w_off = t->oW2; q.b_off = t->ob2; q.wb = w.W2; q.wbT = w.W2T; q.wbT_target = w.W2T_t;
         SmallOptArgs a;
-        a.o = o; a.splits = splits; a.H = H; a.D = D; a.Dp = Dp; a.Dx = Dx; a.Ap = Ap; a.B = B;
+        a.o = o; a.splits = splits; a.H = H; a.G = G; a.D = D; a.Dp = Dp; a.Dx = Dx; a.Ap = Ap; a.B = B;
         a.part3 = w.part3; a.part1 = w.part1;
         a.oW1 = t->oW1; a.ob1 = t->ob1; a.oW3 = t->oW3; a.ob3 = t->ob3;
         a.W1T = w.W1T; a.W3T = w.W3T; a.W1T_target = w.W1T_t; a.W3T_target = w.W3T_t;
         a.ctr = t->ctr; a.lossi = t->lossi;
         a.out_grad_only = t->dueling ? 1u : 0u;
-        const unsigned int elems = (H + 1) * Ap + H * (D + 1);
-        const unsigned int own = (H / 64) * (H / kSqRows) + (elems + 255) / 256;
+        const unsigned int elems = (G + 1) * Ap + H * (D + 1);
+        const unsigned int own = (G / 64) * (H / kSqRows) + (elems + 255) / 256;
         if (t->rec_next) {
             // (recording a run of steps: this launch also gathers the next step's batch; the rest of
             // its arguments is kept for the launches that replace the next step's part)

@@ -1066,6 +1066,47 @@ def test_fp32_tile_edges(B, D, H, H2, A, batch, target_sync, dueling):
     rows = synth.experiences(batch + 120, D, A, 0.05, seed=71)
     pr = Pair(B, capacity=batch + 60, D=D, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=5, appends=3,
               target_sync=target_sync, dueling=dueling, lr=1e-3)
-    pr.append_only(synth.take(rows, 0, batch + 90))
+    for lo in (0, batch + 60):                # more than the ring holds: it wraps
+        pr.append_only(synth.take(rows, lo, min(lo + batch + 60, batch + 90)))
     for k in range(batch + 90, batch + 120, 3):
         assert pr.step(synth.take(rows, k, k + 3), compare=(k % 2 == 0) or k >= batch + 114) == 0
+
+
+@pytest.mark.parametrize("D,H,H2,A,batch,target_sync,dueling,opt", [
+    (27, 128, 1024, 30, 130, 4, True, "adam"),      # the paper's network, a batch that ends inside a tile
+    (27, 128, 1024, 30, 512, 4, True, "adam"),      # ... both networks' rows in one launch
+    (40, 64, 192, 40, 65, 0, False, "sgd"),         # a second block of 32 actions
+    (9, 256, 64, 3, 64, 3, False, "adam"),          # second layer the narrower
+    (27, 64, 256, 30, 5, 3, True, "adam"),          # a batch below 64
+    (70, 320, 448, 70, 200, 3, True, "adam"),       # stripes of each layer beyond the other, wide states
+])
+def test_two_hidden_widths_mixed_precision_on_mfma(B, D, H, H2, A, batch, target_sync, dueling, opt):
+    """Mixed precision with two hidden widths in the step of one width's networks; tolerances of the
+    other mixed-precision cases."""
+    rows = synth.experiences(batch + 150, D, A, 0.05, seed=72, state_dtype="bf16")
+    pr = Pair(B, capacity=batch + 60, D=D, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=5, dtype="bf16",
+              appends=3, target_sync=target_sync, dueling=dueling, opt=opt, lr=1e-3)
+    assert pr.trainer.kernels_per_step() == (8 if batch % 128 == 0 or not target_sync else 11) + dueling
+    for lo in (0, batch + 60):                # more than the ring holds: it wraps
+        pr.append_only(synth.take(rows, lo, min(lo + batch + 60, batch + 90)))
+    for k in range(batch + 90, batch + 150, 3):
+        assert pr.step(synth.take(rows, k, k + 3), compare=(k % 2 == 0) or k >= batch + 140) == 0
+
+
+def test_output_gradient_keeps_fp32_in_mixed_precision(B):
+    """The output layer's gradient in mixed precision contracts bf16 activations with dL/dQ in fp32
+    (three bf16 parts that add up to it): against the same sum in fp64 over the GPU's own dL/dQ and the
+    oracle's activations it is as good as fp32 addition in any order, n 2^-24 of the sum of magnitudes."""
+    D, H, H2, A, batch = 27, 64, 128, 5, 96
+    rows = synth.experiences(300, D, A, 0.05, seed=73, state_dtype="bf16")
+    pr = Pair(B, capacity=256, D=D, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=5, dtype="bf16", appends=1,
+              loss="mse", opt="sgd", lr=1e-3)
+    pr.append_only(synth.take(rows, 0, 256))
+    assert pr.trainer.step(*(synth.take(rows, 256, 257)[k] for k in ("s", "s_next", "a", "r", "term"))) == 0
+    last = pr.trainer.last()
+    pr.ref_ring.append(*(synth.take(rows, 256, 257)[k] for k in ("s", "s_next", "a", "r", "term")))
+    _, _, a, _, _ = pr.ref_ring.gather(last["idx"])
+    g = -(last["delta"] / np.float32(batch)).astype(np.float64)   # dL/dQ(s_i, a_i), as the GPU rounds it
+    want = np.array([g[a == k].sum() for k in range(A)])
+    bound = np.array([np.abs(g[a == k]).sum() for k in range(A)]) * batch * 2.0 ** -24
+    assert (np.abs(pr.trainer.grads()[-A:] - want) <= bound).all()
