@@ -57,7 +57,8 @@ enum { RP_F32 = 0, RP_BF16 = 1, RP_U8 = 2 };
 enum { RP_PAIR = 0, RP_CHAIN = 1 };
 enum { RP_HUBER = 0, RP_MSE = 1 };
 enum { RP_SGD = 0, RP_ADAM = 1 };
-/* train_config.flags: GRAPH = an executed step is replayed as one HIP graph launch;
+/* train_config.flags: GRAPH = train_steps replays runs of 2 to 32 steps as one HIP graph launch
+ * each (a single step is launched kernel by kernel);
  * LAYERED = always use the one-kernel-per-layer step, also where the two-kernel step for
  * small fp32 networks would apply (both give the same results to rounding). */
 enum { RP_TRAIN_GRAPH = 1, RP_TRAIN_LAYERED = 2 };

@@ -114,16 +114,20 @@ def _check(status):
 
 
 def _stream_ptr(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    # (the pointer alone: building torch's stream object takes longer than a small call's checks)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
+# Addresses go to the library as plain integers, which ctypes takes for its pointer arguments; the
+# caller keeps the array alive until the call returns.
 def _dev(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _host(arr):
-    return None if arr is None else arr.ctypes.data_as(C.c_void_p)
+    return None if arr is None else arr.__array_interface__["data"][0]
 
 
 # torch dtypes a device array of each state type may have (bf16 bits also travel as 16-bit ints)
@@ -138,6 +142,9 @@ def check_device_array(t, dtypes, numel, device, what):
     kernels would read or write out of bounds.  Raises ValueError otherwise; returns t."""
     if not isinstance(t, torch.Tensor):
         raise ValueError(f"{what}: expected a torch tensor on {device}, got {type(t).__name__}")
+    # the tensor that fits, as nearly all do, passes in one expression; the reasons come after
+    if t.device == device and t.dtype in dtypes and t.numel() == numel and t.is_contiguous():
+        return t
     dev = torch.device(device)
     if t.device.type != dev.type or (dev.index is not None and t.device.index != dev.index):
         raise ValueError(f"{what}: tensor is on {t.device}, the replay is on {dev}")

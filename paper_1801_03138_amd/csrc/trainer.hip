@@ -914,8 +914,6 @@ rp_status train_create(const train_config* cfg, replay_t* rp_, void* dev_workspa
     t->launch_seq = 0;
     t->handoff_ticks = rp::kHandoffTicks;
     t->handoff_break = false;
-    t->graph = nullptr;
-    t->graph_exec = nullptr;
     t->capture_stream = nullptr;
     t->host_step = 0;
     t->host_adam_t = 0;
@@ -982,31 +980,19 @@ rp_status train_create(const train_config* cfg, replay_t* rp_, void* dev_workspa
                       : (t->wide || t->mid) ? rp::append_gather_func(rp_->geom)
                                             : rp::append_pair_func(rp_->geom);
     t->payload_kargs[0] = t->fused ? static_cast<void*>(&t->row_args) : static_cast<void*>(&t->append_args);
-    t->payload_node[0] = nullptr;
     for (auto& run : t->runs) {
         run.graph = nullptr;
         run.exec = nullptr;
     }
 
     if (cfg->flags & RP_TRAIN_GRAPH) {
-        // recorded once with the replay's staging area as a stand-in payload; the payload
-        // kernel's argument is replaced before every launch
+        // runs of several steps, each recorded once with the replay's staging area as a stand-in
+        // payload; the payload kernels' arguments are replaced before every launch
         const rp::Payload stand_in{rp_->stage_s, rp_->stage_s_next, rp_->stage_a, rp_->stage_r,
                                    rp_->stage_term};
         e = hipStreamCreateWithFlags(&t->capture_stream, hipStreamNonBlocking);
         t->gather_ahead = (t->mid || t->wide) && cfg->appends_per_step && rp_->cfg.sampling == RP_WITH_REPLACEMENT;
         if (t->wide) t->X_buf[1] = t->X_buf[0];   // (its optimizer kernel does not read the batch)
-        if (e == hipSuccess) e = hipStreamBeginCapture(t->capture_stream, hipStreamCaptureModeThreadLocal);
-        if (e == hipSuccess) {
-            hipError_t ek = rp::enqueue_append_and_step(t, stand_in, t->capture_stream,
-                                                        &t->kernels_per_step);
-            e = hipStreamEndCapture(t->capture_stream, &t->graph);
-            if (ek != hipSuccess) e = ek;
-        }
-        if (e == hipSuccess && rp::has_payload_node(t))
-            e = rp::find_payload_nodes(t, t->graph, 1, t->payload_node, t->payload_np);
-        if (e == hipSuccess) e = hipGraphInstantiate(&t->graph_exec, t->graph, nullptr, nullptr, 0);
-        // the same for runs of several steps
         for (unsigned int g = 0; g < rp::kRuns && e == hipSuccess; ++g) {
             trainer::StepRun& run = t->runs[g];
             e = hipStreamBeginCapture(t->capture_stream, hipStreamCaptureModeThreadLocal);
@@ -1031,7 +1017,7 @@ rp_status train_create(const train_config* cfg, replay_t* rp_, void* dev_workspa
                         t->rec_next = &next_gather;
                     }
                 }
-                ek = rp::enqueue_append_and_step(t, stand_in, t->capture_stream, nullptr);
+                ek = rp::enqueue_append_and_step(t, stand_in, t->capture_stream, k == 0 ? &t->kernels_per_step : nullptr);
                 t->rec_next = nullptr;
             }
             t->rec_skip_gather = false;
@@ -1074,8 +1060,6 @@ rp_status train_create(const train_config* cfg, replay_t* rp_, void* dev_workspa
 
 rp_status train_destroy(trainer_t* t) {
     if (!t) return RP_OK;
-    if (t->graph_exec) (void)hipGraphExecDestroy(t->graph_exec);
-    if (t->graph) (void)hipGraphDestroy(t->graph);
     for (auto& run : t->runs) {
         if (run.exec) (void)hipGraphExecDestroy(run.exec);
         if (run.graph) (void)hipGraphDestroy(run.graph);
@@ -1113,14 +1097,11 @@ rp_status train_step(trainer_t* t, const void* s, const void* s_next, const int3
         if (n)
             RP_CHECK_HIP(rp::launch_append(rpl->geom, rp::RingPos{rpl->head, rpl->size, rpl->total}, n,
                                            src.s, src.s_next, src.a, src.r, src.term, st));
-    } else if (t->graph_exec) {
-        if (t->payload_node[0]) {
-            rp::set_payload_args(t, src, 0);
-            RP_CHECK_HIP(hipGraphExecKernelNodeSetParams(t->graph_exec, t->payload_node[0],
-                                                         &t->payload_np[0]));
-        }
-        RP_CHECK_HIP(hipGraphLaunch(t->graph_exec, st));
     } else {
+        // One step on its own is launched kernel by kernel, with recorded runs or without: the host
+        // takes longer to replace an argument block in a graph of so few nodes and to launch it
+        // than to launch its kernels (us per call at batch 32, graph -> kernels: two-kernel step
+        // 22.8 -> 16.6, six-kernel step of the paper's network 36.3 -> 32.9).
         RP_CHECK_HIP(rp::enqueue_append_and_step(t, src, st, nullptr));
     }
     if (host_src) RP_CHECK_HIP(rp::commit_host_slots(t, 1, st));
@@ -1141,24 +1122,7 @@ rp_status train_step_batch(trainer_t* t, const void* s, const void* s_next, cons
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const rp::Payload batch{static_cast<const unsigned char*>(s),
                             static_cast<const unsigned char*>(s_next), a, r, term};
-    if (t->fused && t->graph_exec && t->payload_node[0]) {
-        // the recorded step with its row kernel pointed at the batch: nothing appended or drawn
-        t->row_args.src = rp::Payload{nullptr, nullptr, nullptr, nullptr, nullptr};
-        t->row_args.n_append = 0;
-        t->row_args.batch = batch;
-        t->row_args.from_batch = 1;
-        t->row_args.head = rpl->head;
-        t->row_args.step = t->host_step;
-        t->row_args.size_after = (unsigned int)rpl->size;
-        t->row_args.total_after = rpl->total;
-        rp::set_adam_step(t->row_args, t->host_adam_t + 1, t->cfg.beta1, t->cfg.beta2);
-        rp::stamp_launch(t, t->row_args);
-        RP_CHECK_HIP(hipGraphExecKernelNodeSetParams(t->graph_exec, t->payload_node[0],
-                                                     &t->payload_np[0]));
-        RP_CHECK_HIP(hipGraphLaunch(t->graph_exec, st));
-    } else {
-        RP_CHECK_HIP(rp::enqueue_batch_step(t, batch, st));
-    }
+    RP_CHECK_HIP(rp::enqueue_batch_step(t, batch, st));
     t->host_step += 1;
     t->host_adam_t += 1;
     return RP_OK;

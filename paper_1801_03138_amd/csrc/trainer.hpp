@@ -200,21 +200,17 @@ struct trainer {
     bool wide;                       // mixed-precision step on MFMA
     bool mid;                        // fp32 step on MFMA, one product per kernel
     rp::WideBuffers wd;
-    hipGraph_t graph;
-    hipGraphExec_t graph_exec;
     hipStream_t capture_stream;
     unsigned int kernels_per_step;
     uint64_t host_step;              // mirror of ctr->step
     uint64_t host_adam_t;            // mirror of ctr->adam_t
     // The kernel that consumes the step's new experiences (fused row kernel, or the append
-    // kernel of the layered step): host copy of its argument block, and its node in the graph,
-    // whose argument is replaced before every launch.
+    // kernel of the layered step): host copy of its argument block, which
+    // replaces that of its node in a recorded run before every launch.
     rp::RowArgs row_args;
     rp::AppendGatherArgs append_args;   // the append kernel reads its leading AppendArgs part
     void* payload_func;
     void* payload_kargs[1];          // -> row_args / append_args
-    hipGraphNode_t payload_node[1];
-    hipKernelNodeParams payload_np[1];
     // Runs of consecutive steps recorded as one graph each, for train_steps: one launch (and one
     // launch gap on the GPU) per run; each step's payload kernel has its own node.
     struct StepRun {
