@@ -106,8 +106,6 @@ struct GatherOut {
     float* out_r;
     unsigned char* out_term;
     unsigned int* out_idx;
-    void* out_s_t;
-    unsigned int out_t_ld;
 };
 
 // Argument block of the kernel that appends and then samples and gathers in one launch.  It

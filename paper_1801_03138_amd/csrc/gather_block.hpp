@@ -197,12 +197,10 @@ __device__ __forceinline__ void gather_pair_rows(const RingGeom& g, unsigned lon
                 const unsigned int* w = reinterpret_cast<const unsigned int*>(base);
                 if (o.out_s) static_cast<unsigned int*>(o.out_s)[at + col] = w[col];
                 if (o.out_s_next) static_cast<unsigned int*>(o.out_s_next)[at + col] = w[D + col];
-                if (o.out_s_t) static_cast<unsigned int*>(o.out_s_t)[(size_t)col * o.out_t_ld + i0 + row] = w[col];
             } else if (ELEM == 2) {
                 const unsigned short* h = reinterpret_cast<const unsigned short*>(base);
                 if (o.out_s) static_cast<unsigned short*>(o.out_s)[at + col] = h[col];
                 if (o.out_s_next) static_cast<unsigned short*>(o.out_s_next)[at + col] = h[D + col];
-                if (o.out_s_t) static_cast<unsigned short*>(o.out_s_t)[(size_t)col * o.out_t_ld + i0 + row] = h[col];
             } else {
                 if (o.out_s) static_cast<float*>(o.out_s)[at + col] = unit_from_u8(base[col]);
                 if (o.out_s_next) static_cast<float*>(o.out_s_next)[at + col] = unit_from_u8(base[D + col]);

@@ -554,11 +554,9 @@ hipError_t launch_sample_gather(const RingGeom& g, unsigned long long seed,
                                 const unsigned long long* step_ptr, unsigned int batch,
                                 void* out_s, void* out_s_next, unsigned int out_ld, int* out_a,
                                 float* out_r, unsigned char* out_term, unsigned int* out_idx,
-                                hipStream_t stream, void* out_s_t, unsigned int out_t_ld,
-                                unsigned int size_value, unsigned long long head_value,
+                                hipStream_t stream, unsigned int size_value, unsigned long long head_value,
                                 unsigned int* draw_scratch, unsigned int* launched, bool draw_in_gather) {
     if (launched) *launched = 0;
-    if (out_s_t && (g.layout != RP_PAIR || g.elem_bytes == 1)) return hipErrorInvalidValue;
     // A batch without duplicates is drawn by a kernel of its own when the caller has scratch for
     // it, unless the caller allows the draw inside the gather's launch and the batch is one that
     // leaves lanes idle (2^G lanes per draw): beyond that the draws alone keep every SIMD of the
@@ -584,7 +582,7 @@ hipError_t launch_sample_gather(const RingGeom& g, unsigned long long seed,
         // (a block's 4 or 16 rows are gathered in groups of one row per 2^lane_shift threads)
         const size_t lds = (size_t)rows_per_pass * g.row_bytes;
         const unsigned int blocks = (batch + R - 1) / R;
-        const GatherOut out{out_s, out_s_next, out_ld, out_a, out_r, out_term, out_idx, out_s_t, out_t_ld};
+        const GatherOut out{out_s, out_s_next, out_ld, out_a, out_r, out_term, out_idx};
 #define RP_LAUNCH_DISTINCT(E, GG)                                                                      \
     hipLaunchKernelGGL((sample_gather_pair_distinct_kernel<E, GG, 1>), dim3(blocks), dim3(kThreads),   \
                        lds, stream, g, seed, step_value, step_ptr, size_value, batch, lane_shift, out)
@@ -613,7 +611,7 @@ hipError_t launch_sample_gather(const RingGeom& g, unsigned long long seed,
         const unsigned int blocks = (batch + R - 1) / R;
         const int mode = drawn ? kDrawGiven : distinct ? kDrawDistinct : kDrawUniform;
         const size_t lds = (mode == kDrawDistinct ? 4 * (size_t)U * kThreads : 0) + (size_t)R * g.row_bytes;
-        const GatherOut out{out_s, out_s_next, out_ld, out_a, out_r, out_term, out_idx, out_s_t, out_t_ld};
+        const GatherOut out{out_s, out_s_next, out_ld, out_a, out_r, out_term, out_idx};
 #define RP_LAUNCH_PAIR(E, UU, MM)                                                                  \
     hipLaunchKernelGGL((sample_gather_pair_kernel<E, UU, MM>), dim3(blocks), dim3(kThreads), lds,   \
                        stream, g, seed, step_value, step_ptr, size_value, batch, lane_shift, out, drawn)
@@ -847,7 +845,7 @@ static rp_status sample_gather_with(replay_t* rp_, uint64_t step, uint32_t batch
     if (choices == 0 || (rp_->cfg.sampling == RP_DISTINCT && choices < batch)) return RP_SKIPPED_BURN_IN;
     RP_CHECK_HIP(rp::launch_sample_gather(rp_->geom, rp_->cfg.seed, step, nullptr, batch, out_s,
                                           out_s_next, rp_->cfg.state_dim, out_a, out_r, out_term,
-                                          out_idx, static_cast<hipStream_t>(hip_stream), nullptr, 0,
+                                          out_idx, static_cast<hipStream_t>(hip_stream),
                                           (unsigned int)rp_->size, rp_->head, draw_scratch, nullptr,
                                           draw_in_gather));
     return RP_OK;

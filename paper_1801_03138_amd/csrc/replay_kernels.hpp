@@ -30,8 +30,6 @@ void append_gather_shape(const AppendGatherArgs& a, unsigned int* blocks, size_t
 // Sample `batch` slots and unpack them.  The sampling step is *step_ptr when
 // step_ptr is non-null (device), else step_value.  out_ld is the row pitch of
 // out_s / out_s_next in elements (>= D); columns D..out_ld-1 are not written.
-// out_s_t (PAIR rings with 2- or 4-byte elements; may be null) receives the old states
-// transposed: element (column, i) at out_s_t[column * out_t_ld + i].
 // size_value, head_value: the number of experiences held and the write position, when the
 // caller mirrors them; size_value = 0 = read both from the device-resident ring state.
 // draw_scratch (device, `batch` words; may be null): with it, a batch without duplicates is drawn
@@ -43,8 +41,7 @@ hipError_t launch_sample_gather(const RingGeom& g, unsigned long long seed,
                                 const unsigned long long* step_ptr, unsigned int batch,
                                 void* out_s, void* out_s_next, unsigned int out_ld, int* out_a,
                                 float* out_r, unsigned char* out_term, unsigned int* out_idx,
-                                hipStream_t stream, void* out_s_t = nullptr,
-                                unsigned int out_t_ld = 0, unsigned int size_value = 0,
+                                hipStream_t stream, unsigned int size_value = 0,
                                 unsigned long long head_value = 0, unsigned int* draw_scratch = nullptr,
                                 unsigned int* launched = nullptr, bool draw_in_gather = false);
 

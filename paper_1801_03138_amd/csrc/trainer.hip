@@ -217,14 +217,12 @@ __global__ __launch_bounds__(kThreads) void optimizer_kernel(
 }
 
 // A caller-provided batch (structure of arrays, B rows) into the step's input buffers:
-// X = [S ; S'] with row pitch Dp, the per-row fields, the batch position as "slot", and, for the
-// MFMA step, the transposed copy of S.  E = element type of a state (4 or 2 bytes).
+// X = [S ; S'] with row pitch Dp, the per-row fields, the batch position as "slot".  E = element type of a state (4 or 2 bytes).
 template <typename E>
 __global__ __launch_bounds__(kThreads) void load_batch_kernel(
     unsigned int B, unsigned int D, unsigned int Dp, const E* __restrict__ s,
     const E* __restrict__ s_next, const int* __restrict__ a, const float* __restrict__ r,
-    const unsigned char* __restrict__ term, E* __restrict__ X, E* __restrict__ XT,
-    unsigned int ldt, int* __restrict__ act, float* __restrict__ rew,
+    const unsigned char* __restrict__ term, E* __restrict__ X, int* __restrict__ act, float* __restrict__ rew,
     unsigned char* __restrict__ trm, unsigned int* __restrict__ idx) {
     const size_t e = (size_t)blockIdx.x * kThreads + threadIdx.x;
     if (e < (size_t)B * D) {
@@ -232,7 +230,6 @@ __global__ __launch_bounds__(kThreads) void load_batch_kernel(
         const E v = s[e];
         X[(size_t)i * Dp + c] = v;
         X[(size_t)(B + i) * Dp + c] = s_next[e];
-        if (XT) XT[(size_t)c * ldt + i] = v;
     }
     if (e < B) {
         act[e] = a[e];
@@ -262,7 +259,7 @@ struct WsLayout {
     size_t ctr, w, g, m, v, wt, w2t, wb, wbt, X, act, rew, term, idx, H1, H2, Q, y, delta, lossi, dQ, dZ2, dZ1,
         pre, qpart, handoff, ahead, qn_ahead, X2, total;
     // mixed-precision step on MFMA
-    size_t W1T, W2b, W2T, W3T, W1Tt, W2Tt, W3Tt, XT, H1T, H2T, dQT, dZ2T, dZ1T, part3, part1, part2;
+    size_t W1T, W2b, W2T, W3T, W1Tt, W2Tt, W3Tt, dQ3, part3, part1, part2;
     unsigned int Dp, Ap, Bp;
     size_t n_params, n_padded, n_head, elem;
     size_t oW1, ob1, oW2, ob2, oW3, ob3;
@@ -341,12 +338,7 @@ bool ws_layout(const train_config* c, WsLayout* L) {
     L->W1Tt = take(mixed_t ? H * L->Dp * 2 : 0);
     L->W2Tt = take(mixed_t ? H * G * 2 : 0);
     L->W3Tt = take(mixed_t ? L->Ap * G * 2 : 0);
-    L->XT = take(mixed ? Dx * Bp * 2 : 0);
-    L->H1T = take(mixed ? (H + 1) * Bp * 2 : 0);
-    L->H2T = take(mixed ? (G + 1) * Bp * 2 : 0);
-    L->dQT = take(mixed ? 3 * L->Ap * Bp * 2 : 0);
-    L->dZ2T = take(mixed ? G * Bp * 2 : 0);
-    L->dZ1T = take(mixed ? H * Bp * 2 : 0);
+    L->dQ3 = take(mixed ? B * 3 * L->Ap * 2 : 0);
     // K-split partial products of the narrow layers' gradients (at most 16 splits)
     L->part3 = take(mixed ? 16 * (G + 1) * L->Ap * 4 : 0);
     L->part1 = take(mixed ? 16 * H * Dx * 4 : 0);
@@ -508,7 +500,7 @@ hipError_t enqueue_step(trainer* t, hipStream_t st, unsigned int* count, bool sa
     if (sample) {
         e = launch_sample_gather(t->rp_->geom, t->rp_->cfg.seed, 0, &t->ctr->step, t->B, t->X,
                                  static_cast<unsigned char*>(t->X) + (size_t)B * Dp * eb, t->Dp,
-                                 t->act, t->rew, t->term, t->idx, st, nullptr, 0, 0, 0,
+                                 t->act, t->rew, t->term, t->idx, st, 0, 0,
                                  t->rp_->draw_scratch, &launched);
         if (e != hipSuccess) return e;
         n += launched;
@@ -595,8 +587,7 @@ hipError_t enqueue_append_and_step(trainer* t, const Payload& src, hipStream_t s
         t->append_args = make_append_gather_args(
             r->geom, RingPos{r->head, r->size, r->total}, t->cfg.appends_per_step, src, r->cfg.seed,
             nullptr, t->B,
-            GatherOut{X, X + (size_t)t->B * Dp * t->elem, Dp, t->act, t->rew, t->term, t->idx,
-                      t->wide ? t->wd.XT : nullptr, t->Bp});
+            GatherOut{X, X + (size_t)t->B * Dp * t->elem, Dp, t->act, t->rew, t->term, t->idx});
         t->append_args.step_value = t->host_step;   // (the host mirrors the device's counter exactly)
         unsigned int blocks;
         size_t lds;
@@ -625,7 +616,7 @@ hipError_t enqueue_append_and_step(trainer* t, const Payload& src, hipStream_t s
         unsigned int launched = 0;
         hipError_t e = launch_sample_gather(r->geom, r->cfg.seed, 0, &t->ctr->step, t->B, t->X,
                                             static_cast<unsigned char*>(t->X) + (size_t)t->B * t->Dp * 4, t->Dp,
-                                            t->act, t->rew, t->term, t->idx, st, nullptr, 0, 0, 0,
+                                            t->act, t->rew, t->term, t->idx, st, 0, 0,
                                             r->draw_scratch, &launched);
         if (e != hipSuccess) return e;
         e = enqueue_mid_step(t, st, &k);
@@ -649,14 +640,12 @@ hipError_t enqueue_batch_step(trainer* t, const Payload& batch, hipStream_t st) 
         typedef unsigned short E;
         hipLaunchKernelGGL(load_batch_kernel<E>, dim3(blocks), dim3(kThreads), 0, st, B, D, t->Dp,
                            reinterpret_cast<const E*>(batch.s), reinterpret_cast<const E*>(batch.s_next),
-                           batch.a, batch.r, batch.term, static_cast<E*>(t->X),
-                           t->wide ? t->wd.XT : nullptr, t->Bp, t->act, t->rew, t->term, t->idx);
+                           batch.a, batch.r, batch.term, static_cast<E*>(t->X), t->act, t->rew, t->term, t->idx);
     } else {
         hipLaunchKernelGGL(load_batch_kernel<float>, dim3(blocks), dim3(kThreads), 0, st, B, D, t->Dp,
                            reinterpret_cast<const float*>(batch.s),
                            reinterpret_cast<const float*>(batch.s_next), batch.a, batch.r, batch.term,
-                           static_cast<float*>(t->X), static_cast<float*>(nullptr), 0u, t->act,
-                           t->rew, t->term, t->idx);
+                           static_cast<float*>(t->X), t->act, t->rew, t->term, t->idx);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -877,8 +866,7 @@ rp_status train_create(const train_config* cfg, replay_t* rp_, void* dev_workspa
     {
         auto at = [&](size_t off) { return reinterpret_cast<unsigned short*>(ws + off); };
         t->wd = rp::WideBuffers{at(L.W1T), at(L.W2b), at(L.W2T), at(L.W3T), at(L.W1Tt), at(L.W2Tt),
-                                at(L.W3Tt), at(L.XT), at(L.H1T),
-                                at(L.H2T), at(L.dQT), at(L.dZ2T), at(L.dZ1T),
+                                at(L.W3Tt), at(L.dQ3),
                                 reinterpret_cast<float*>(ws + L.part3),
                                 reinterpret_cast<float*>(ws + L.part1),
                                 reinterpret_cast<float*>(ws + L.part2)};
@@ -936,9 +924,9 @@ rp_status train_create(const train_config* cfg, replay_t* rp_, void* dev_workspa
         }
     }
     if (t->wide) {
-        e = rp::wide_init_buffers(t);
+        e = rp::wide_configure();
         if (e != hipSuccess) {
-            rp::set_error("train_create: preparing the transposed buffers failed: %s", hipGetErrorString(e));
+            rp::set_error("train_create: setting up the step kernels failed: %s", hipGetErrorString(e));
             return fail(RP_EHIP);
         }
     }
@@ -1013,7 +1001,7 @@ rp_status train_create(const train_config* cfg, replay_t* rp_, void* dev_workspa
                             rp_->geom, rp::RingPos{rp_->head, rp_->size, rp_->total}, cfg->appends_per_step,
                             stand_in, rp_->cfg.seed, nullptr, t->B,
                             rp::GatherOut{Xn, Xn + (size_t)t->B * t->Dp * t->elem, t->Dp, t->act, t->rew,
-                                          t->term, t->idx, t->wide ? t->wd.XT : nullptr, t->Bp});
+                                          t->term, t->idx});
                         t->rec_next = &next_gather;
                     }
                 }

@@ -129,15 +129,11 @@ inline void set_adam_step(RowArgs& a, unsigned long long t_after, float beta1, f
 
 
 // Buffers of the mixed-precision step on MFMA (bf16 bit patterns; H, G: widths of the two hidden
-// layers).  "T" = transposed: the batch index is the contiguous one, rows are padded to Bp (a
-// multiple of 128) with zeros.
+// layers; "T" = transposed).
 struct WideBuffers {
     unsigned short *W1T, *W2, *W2T, *W3T;   // [H x Dp], [H x G], [G x H], [Ap x G]
     unsigned short *W1T_t, *W2T_t, *W3T_t;  // forward operands of the frozen target network
-    unsigned short* XT;                      // [>= D+1 x Bp], row D all ones
-    unsigned short *H1T, *H2T;               // [H+1 x Bp], [G+1 x Bp], last row all ones
-    unsigned short* dQT;                     // [3 Ap x Bp]: the three bf16 parts of dL/dQ (see dq_row)
-    unsigned short *dZ2T, *dZ1T;             // [G x Bp], [H x Bp]
+    unsigned short* dQ;                      // [B x 3 Ap]: the three bf16 parts of dL/dQ (see dq_col)
     float* part3;                            // K-split partials [splits][G+1][Ap] of [dW3 ; db3]
     float* part1;                            // K-split partials [splits][H][Dx] of [dW1^T | db1]
     float* part2;                            // K-split partials [splits][H+1][G] of [dW2 ; db2]
@@ -301,10 +297,10 @@ unsigned int mid_step_kernels(const trainer* t);   // launches per step, the app
 bool wide_step_supported(const train_config& cfg, const replay* rp_);
 bool wide_step_shape(const train_config& cfg);   // the part of that which the configuration decides (the workspace's size)
 unsigned int square_splits(unsigned int Bp, unsigned int H, unsigned int G);   // K splits of the dW2 product
-hipError_t wide_init_buffers(trainer* t);                       // once, after the workspace is cleared
+hipError_t wide_configure();                                    // once, at creation
 // bf16 operand copies from padded fp32 parameters (host): of the trained network, or of the target
 hipError_t wide_set_weights(trainer* t, const float* padded, bool target);
 // Enqueue the step's kernels after the append; `sample` = draw and gather the batch first
-// (otherwise X, XT and the per-row fields have been filled by the caller).
+// (otherwise X and the per-row fields have been filled by the caller).
 hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bool sample);
 }  // namespace rp

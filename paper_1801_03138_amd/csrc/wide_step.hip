@@ -1,16 +1,16 @@
 // Mixed-precision train step for wide networks, where the step is bound by the dense products:
 // bf16 operands, fp32 accumulation on 32x32x16 MFMA, fp32 master weights and Adam moments.
 //
-// Every product is brought to one form, C[m][n] = sum_k A[m][k] * Bt[n][k] with both operands
-// stored K-contiguous, which is the form the MFMA lane layout reads with 16-byte loads.  The
-// forward layers therefore read transposed bf16 copies of the weights, and the weight
-// gradients, which contract over the batch, read transposed copies of the activations and of
-// the pre-activation gradients; the kernels that produce those tensors write both orientations.
-// A bias gradient is the product of the error with a vector of ones: the transposed activation
-// buffers carry one extra row of ones, so the bias gradient falls out of the weight-gradient
-// product as one more output row.  The weight-gradient products contract over the batch, which
-// is long while their outputs are small: they are split along the batch over several workgroups
-// per tile, and the optimizer kernels add the fp32 partial products up.
+// The forward products and the error of the first layer have the form C[m][n] = sum_k A[m][k] *
+// Bt[n][k] with both operands stored K-contiguous, which is the form the MFMA lane layout reads
+// with 16-byte loads; the forward layers therefore read transposed bf16 copies of the weights.  The
+// weight gradients contract over the batch, C[m][n] = sum_i A[i][m] * B[i][n], and read activations
+// and errors as the other kernels leave them, one row per experience: the transposing LDS
+// read turns a slice of batch rows into MFMA operands.  A bias gradient is the product of the error
+// with a vector of ones, which the workgroups of one tile row (column) form beside their tile, with
+// a constant register as operand.  These products have a long contraction and small outputs:
+// they are split along the batch over several workgroups per tile, and the optimizer kernels add
+// the fp32 partial products up.
 //
 // Paper: Integration with Reinforcement Learning Algorithm (train step with no host inputs),
 // Deep Q-Network Model (update equation).
@@ -95,16 +95,14 @@ __device__ __forceinline__ float opt_update(const OptState& o, size_t k, float g
 
 // ----------------------------------------------------------------------------------------
 // Epilogues of the tiled product.
-// "Staged" epilogues (bf16 output in the product's own orientation; pre() also gets the first
-// row of the workgroup's tile): the product is formed with
-// the MFMA operands exchanged, so a lane holds four consecutive columns of one output row; it
-// passes each value through pre(), rounds to bf16 and parks the wavefront's tile in LDS, from
-// where it leaves in 16-byte pieces -- eight lanes write one 128-byte run of a row -- through
-// store().  Other epilogues get the raw 32x32 accumulator tiles.
+// bf16 output (gemm_nt_block; pre() also gets the first row of the workgroup's tile): the product
+// is formed with the MFMA operands exchanged, so a lane holds four consecutive columns of one
+// output row; it passes each value through pre(), rounds to bf16 and parks the wavefront's tile in
+// LDS, from where it leaves in 16-byte pieces -- eight lanes write one 128-byte run of a row --
+// through store().  The gradients' epilogues (gemm_tn_block) get the raw 32x32 accumulator tiles.
 // ----------------------------------------------------------------------------------------
 // out[m][n] = bf16(relu(acc + bias[n]))
 struct EpiForward {
-    static constexpr bool kStaged = true;
     const float* bias;
     const float* bias_hi;     // bias for rows from m_split on (the target network's)
     unsigned int m_split;
@@ -124,7 +122,6 @@ struct EpiForward {
 // out[m][n] = bf16(acc) where mask[m][n] > 0, else 0  (the ReLU derivative; both [M x ld]).
 // Columns from N up to the next multiple of 8 are written as zeros.
 struct EpiMask {
-    static constexpr bool kStaged = true;
     const bf16_bits* mask;
     bf16_bits* out;
     unsigned int ld;
@@ -147,45 +144,72 @@ struct EpiMask {
     }
 };
 
-// part[split][m][n] = the sum of the three 32-wide column tiles of a 96-wide tile: the output layer's
-// gradient, whose error operand comes in three bf16 parts (see dq_row).  N = 3 Ap.
-struct EpiPartialOfThree {
-    static constexpr bool kStaged = false;
+// Partial gradients of one K split, added up by the optimizer kernel.  M: rows of the weight
+// matrix (of its transpose in EpiFirst); sums() gets the 32 column (row) sums of an error tile.
+// part[split][m][n] = acc, row M the bias
+struct EpiSquare {
+    float* part;
+    unsigned int M, N;
+    template <int TN>
+    __device__ __forceinline__ void tiles(unsigned int mb, unsigned int nb, const f32x16 (&c)[TN],
+                                          unsigned int lane, unsigned int split) const {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            if (mb >= M || nb + j * 32u >= N) continue;   // (M and N are whole numbers of 32)
+            float* at = part + ((size_t)split * (M + 1u) + mb + acc_row(0, lane)) * N + nb + j * 32u + (lane & 31u);
+#pragma unroll
+            for (unsigned int v = 0; v < 16; ++v) at[acc_row(v, 0) * N] = c[j][v];
+        }
+    }
+    // every row of the accumulator holds the 32 sums
+    __device__ __forceinline__ void sums(unsigned int nb, const f32x16 (&c)[1], unsigned int lane, unsigned int split) const {
+        const unsigned int n = nb + lane;
+        if (lane < 32u && n < N) part[((size_t)split * (M + 1u) + M) * N + n] = c[0][0];
+    }
+};
+
+// The output layer's, whose error operand comes in three bf16 parts (see dq_col): the three 32-wide
+// column tiles of a 96-wide tile are added.
+struct EpiOutput {
     float* part;
     unsigned int M, Ap;
     template <int TN>
     __device__ __forceinline__ void tiles(unsigned int mb, unsigned int nb, const f32x16 (&c)[TN],
                                           unsigned int lane, unsigned int split) const {
         static_assert(TN == 3, "a tile is the three parts of 32 actions");
-        const unsigned int a = nb / 3u + (lane & 31u);
+        if (mb >= M) return;                              // (a whole number of 32)
+        float* at = part + ((size_t)split * (M + 1u) + mb + acc_row(0, lane)) * Ap + nb / 3u + (lane & 31u);
 #pragma unroll
-        for (unsigned int v = 0; v < 16; ++v) {
-            const unsigned int m = mb + acc_row(v, lane);
-            if (m < M) part[((size_t)split * M + m) * Ap + a] = (c[2][v] + c[1][v]) + c[0][v];
-        }
+        for (unsigned int v = 0; v < 16; ++v) at[acc_row(v, 0) * Ap] = (c[2][v] + c[1][v]) + c[0][v];
+    }
+    __device__ __forceinline__ void sums(unsigned int nb, const f32x16 (&c)[3], unsigned int lane, unsigned int split) const {
+        if (lane < 32u)
+            part[((size_t)split * (M + 1u) + M) * Ap + nb / 3u + lane] = (c[2][0] + c[1][0]) + c[0][0];
     }
 };
 
-// part[split][m][n] = acc: the partial product of one K split, added up by a later kernel
-struct EpiPartial {
-    static constexpr bool kStaged = false;
+// The first layer's, transposed: part[split][j][d], d < D, column D the bias.
+struct EpiFirst {
     float* part;
-    unsigned int M, N;
-    __device__ __forceinline__ void tile(unsigned int mb, unsigned int nb, const f32x16& c,
-                                         unsigned int lane, unsigned int split) const {
-        const unsigned int n = nb + (lane & 31u);
-        if (n >= N) return;
-#pragma unroll
-        for (unsigned int v = 0; v < 16; ++v) {
-            const unsigned int m = mb + acc_row(v, lane);
-            if (m < M) part[((size_t)split * M + m) * N + n] = c[v];
-        }
-    }
+    unsigned int M, D, Dx;
     template <int TN>
     __device__ __forceinline__ void tiles(unsigned int mb, unsigned int nb, const f32x16 (&c)[TN],
                                           unsigned int lane, unsigned int split) const {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) tile(mb, nb + j * 32u, c[j], lane, split);
+        for (int j = 0; j < TN; ++j) {
+            const unsigned int d = nb + j * 32u + (lane & 31u);
+            if (mb >= M || d >= D) continue;              // (M is a whole number of 32)
+            float* at = part + ((size_t)split * M + mb + acc_row(0, lane)) * Dx + d;
+#pragma unroll
+            for (unsigned int v = 0; v < 16; ++v) at[acc_row(v, 0) * Dx] = c[j][v];
+        }
+    }
+    // every column of the accumulator holds the 32 sums
+    __device__ __forceinline__ void sums(unsigned int mb, const f32x16 (&c)[1], unsigned int lane, unsigned int split) const {
+        if (mb >= M || (lane & 31u) != 0u) return;
+        float* at = part + ((size_t)split * M + mb + acc_row(0, lane)) * Dx + D;
+#pragma unroll
+        for (unsigned int v = 0; v < 16; ++v) at[acc_row(v, 0) * Dx] = c[0][v];
     }
 };
 
@@ -198,9 +222,7 @@ struct EpiPartial {
 // so LDS rows cannot be padded; instead the 16-byte piece at position c of row r holds piece
 // c ^ swz(r) of that row's slice (the lanes fetch their global pieces in that order), which
 // spreads the MFMA operand reads of 16 consecutive rows over all banks.
-// The contraction may also be split over `splits` workgroups per tile, each taking K / splits
-// consecutive columns and handing its split number to the epilogue.
-// K / splits must be a multiple of BK.  Loads of rows beyond M / N are redirected to the last valid row:
+// K must be a multiple of BK.  Loads of rows beyond M / N are redirected to the last valid row:
 // such rows only feed accumulator rows / columns that the epilogue never stores.
 // ----------------------------------------------------------------------------------------
 struct GemmArgs {
@@ -210,7 +232,8 @@ struct GemmArgs {
     const bf16_bits* Bt_hi;        // B operand of the tiles whose first row is m_split or beyond
     unsigned int m_split;
     unsigned int ldb;
-    unsigned int M, N, K;          // K: columns one workgroup contracts over
+    unsigned int M, N, K;          // K: length one workgroup contracts over
+    unsigned int batch;            // products over the batch: rows of the operands
     unsigned int tiles_m, tiles_n, splits;
     unsigned int band;             // tiles are numbered band by band: `band` tile columns at a time, rows fastest after that
 };
@@ -218,18 +241,55 @@ struct GemmArgs {
 template <int BM, int BN, int BK, int WGM, int WGN, int NSTAGE = 2>
 constexpr size_t gemm_lds_bytes() {
     const size_t slices = NSTAGE * (size_t)(BM + BN) * BK * 2;
-    // staged epilogues park every wavefront's bf16 tile, rows padded by 16 bytes
+    // the epilogue parks every wavefront's bf16 tile, rows padded by 16 bytes
     const size_t parked = 4 * (size_t)(BM / WGM) * ((BN / WGN) * 2 + 16);
     return slices > parked ? slices : parked;
 }
 
 #define RP_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
-#define RP_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
+
+
+// Workgroups are dealt to the eight XCDs round-robin; each XCD gets a contiguous range of
+// tile numbers, and tiles are numbered so that such a range is a compact block of the output
+// (bands of `band` tile columns, within a band row by row): the workgroups that share an L2
+// then share as few operand panels as possible, and each panel is fetched by few XCDs.  False: the
+// workgroup has no tile.
+template <int BM, int BN>
+__device__ __forceinline__ bool tile_of(const GemmArgs& p, unsigned int block, unsigned int* m0, unsigned int* n0,
+                                        unsigned int* split) {
+    const unsigned int per_split = p.tiles_m * p.tiles_n, n_tiles = per_split * p.splits;
+    const unsigned int per_xcd = (n_tiles + 7u) / 8u;
+    const unsigned int tile_s = (block & 7u) * per_xcd + (block >> 3);
+    if (tile_s >= n_tiles) return false;
+    const unsigned int tile = tile_s % per_split;
+    const unsigned int band_tiles = p.tiles_m * p.band, band_id = tile / band_tiles, in_band = tile % band_tiles;
+    const unsigned int width = min(p.band, p.tiles_n - band_id * p.band);
+    *m0 = (in_band / width) * BM;
+    *n0 = (band_id * p.band + in_band % width) * BN;
+    *split = tile_s / per_split;
+    return true;
+}
+
+// s_waitcnt vmcnt(N), nothing else
+template <unsigned int N>
+__device__ __forceinline__ void wait_loads() {
+    __builtin_amdgcn_s_waitcnt((N & 0xFu) | ((N >> 4) << 14) | 0x0F70u);
+}
+// waits until at most `slices` (< NSTAGE - 1) slices of L loads each are in flight
+template <int L, int NSTAGE, int K = 0>
+__device__ __forceinline__ void wait_slices(unsigned int slices) {
+    if constexpr (K + 2 >= NSTAGE) {
+        wait_loads<K * L>();
+    } else {
+        if (slices == K) wait_loads<K * L>();
+        else wait_slices<L, NSTAGE, K + 1>(slices);
+    }
+}
 
 template <int BM, int BN, int BK, int WGM, int WGN, int NSTAGE = 2, class Epi>
 __device__ __forceinline__ void gemm_nt_block(const GemmArgs& p, const Epi& epi, unsigned int block) {
     static_assert(WGM * WGN == 4, "four wavefronts");
-    static_assert(NSTAGE >= 2 && NSTAGE <= 4, "slices in flight");
+    static_assert(NSTAGE >= 2, "slices in flight");
     static_assert(BK == 32 || BK == 64, "slice width");
     constexpr int RB = BK * 2;                             // bytes per LDS row
     constexpr int CPR = RB / 16;                           // 16-byte pieces per row
@@ -243,19 +303,8 @@ __device__ __forceinline__ void gemm_nt_block(const GemmArgs& p, const Epi& epi,
     extern __shared__ uint4 gemm_smem[];
     unsigned char* smem = reinterpret_cast<unsigned char*>(gemm_smem);
 
-    // Workgroups are dealt to the eight XCDs round-robin; each XCD gets a contiguous range of
-    // tile numbers, and tiles are numbered so that such a range is a compact block of the output
-    // (bands of `band` tile columns, within a band row by row): the workgroups that share an L2
-    // then share as few operand panels as possible, and each panel is fetched by few XCDs.
-    const unsigned int per_split = p.tiles_m * p.tiles_n, n_tiles = per_split * p.splits;
-    const unsigned int per_xcd = (n_tiles + 7u) / 8u;
-    const unsigned int tile_s = (block & 7u) * per_xcd + (block >> 3);
-    if (tile_s >= n_tiles) return;
-    const unsigned int split = tile_s / per_split, tile = tile_s % per_split;
-    const unsigned int band_tiles = p.tiles_m * p.band, band_id = tile / band_tiles, in_band = tile % band_tiles;
-    const unsigned int width = min(p.band, p.tiles_n - band_id * p.band);
-    const unsigned int m0 = (in_band / width) * BM, n0 = (band_id * p.band + in_band % width) * BN;
-    const unsigned int k_base = split * p.K;
+    unsigned int m0, n0, split;
+    if (!tile_of<BM, BN>(p, block, &m0, &n0, &split)) return;
 
     const unsigned int tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const unsigned int wn = wave % WGN, wm = wave / WGN;
@@ -289,20 +338,15 @@ __device__ __forceinline__ void gemm_nt_block(const GemmArgs& p, const Epi& epi,
         b_off[u] = (gn * p.ldb + (lc ^ swz(r)) * 8u) * 2u;
     }
     typedef const __attribute__((address_space(1))) char* gchar;
-    const gchar a_base = (gchar)reinterpret_cast<const char*>(p.A + k_base);
-    const gchar b_base = (gchar)reinterpret_cast<const char*>((m0 >= p.m_split ? p.Bt_hi : p.Bt) + k_base);
+    const gchar a_base = (gchar)reinterpret_cast<const char*>(p.A);
+    const gchar b_base = (gchar)reinterpret_cast<const char*>(m0 >= p.m_split ? p.Bt_hi : p.Bt);
     // request u (0 .. GA + GB - 1) of a slice: one wavefront-wide 16-byte-per-lane load into LDS
     constexpr int L = GA + GB;                              // loads per wavefront and slice
     auto fetch_one = [&](int u, unsigned int buf, unsigned int k0) {
-        if (u < GA) {
-            unsigned char* sa = smem + buf * STAGE + (wave_u * GA) * 1024u;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(a_base + (size_t)k0 * 2u + a_off[u < GA ? u : 0]),
-                                             RP_LDS_PTR(sa + u * 1024), 16, 0, 0);
-        } else {
-            unsigned char* sb = smem + buf * STAGE + A_BYTES + (wave_u * GB) * 1024u;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(b_base + (size_t)k0 * 2u + b_off[u >= GA ? u - GA : 0]),
-                                             RP_LDS_PTR(sb + (u - GA) * 1024), 16, 0, 0);
-        }
+        gchar row = (u < GA ? a_base : b_base) + (size_t)k0 * 2u;
+        const unsigned int off = u < GA ? a_off[u < GA ? u : 0] : b_off[u >= GA ? u - GA : 0];
+        unsigned char* dst = smem + buf * STAGE + (u < GA ? (wave_u * GA + u) * 1024u : A_BYTES + (wave_u * GB + u - GA) * 1024u);
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(row + off), RP_LDS_PTR(dst), 16, 0, 0);
     };
     auto fetch = [&](unsigned int buf, unsigned int k0) {
 #pragma unroll
@@ -349,9 +393,7 @@ __device__ __forceinline__ void gemm_nt_block(const GemmArgs& p, const Epi& epi,
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    acc[i][j] = Epi::kStaged
-                                    ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(b[s & 1][j]), as_bf16x8(a[s & 1][i]), acc[i][j], 0, 0, 0)
-                                    : __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a[s & 1][i]), as_bf16x8(b[s & 1][j]), acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(b[s & 1][j]), as_bf16x8(a[s & 1][i]), acc[i][j], 0, 0, 0);
                     if (FETCH) {
                         const int m = (s * TM + i) * TN + j;          // this MFMA's number within the slice
 #pragma unroll
@@ -369,10 +411,6 @@ __device__ __forceinline__ void gemm_nt_block(const GemmArgs& p, const Epi& epi,
     // With two workgroups on a compute unit two slices are enough (the other workgroup computes
     // while this one waits); a workgroup that has a compute unit to itself needs its requests
     // further ahead than one slice's multiply time.
-    auto wait_vm = [](auto n) {                             // s_waitcnt vmcnt(n), nothing else
-        constexpr unsigned int N = decltype(n)::value;
-        __builtin_amdgcn_s_waitcnt((N & 0xFu) | ((N >> 4) << 14) | 0x0F70u);
-    };
     const unsigned int nk = p.K / BK;
 #pragma unroll
     for (unsigned int s0 = 0; s0 + 1 < (unsigned int)NSTAGE; ++s0)
@@ -382,57 +420,318 @@ __device__ __forceinline__ void gemm_nt_block(const GemmArgs& p, const Epi& epi,
     // the compiler moved all accumulators between register files on every iteration)
     unsigned int kt = 0;
     for (; kt + NSTAGE - 1 < nk; ++kt) {
-        wait_vm(std::integral_constant<unsigned int, (NSTAGE - 2) * L>{});
+        wait_loads<(NSTAGE - 2) * L>();
         __syncthreads();
         multiply(kt % NSTAGE, std::true_type{}, (kt + NSTAGE - 1) % NSTAGE, (kt + NSTAGE - 1) * BK);
     }
     // the last NSTAGE - 1 slices: nothing left to request
     for (; kt < nk; ++kt) {
-        const unsigned int later = nk - 1u - kt;
-        if (NSTAGE >= 4 && later == 2u) wait_vm(std::integral_constant<unsigned int, 2 * L>{});
-        else if (NSTAGE >= 3 && later == 1u) wait_vm(std::integral_constant<unsigned int, L>{});
-        else wait_vm(std::integral_constant<unsigned int, 0>{});
+        wait_slices<L, NSTAGE>(nk - 1u - kt);
         __syncthreads();
         multiply(kt % NSTAGE, std::false_type{}, 0u, 0u);
     }
 
-    if constexpr (Epi::kStaged) {
-        // The accumulator of tile (i, j) is transposed: element v of a lane is output row
-        // lane % 32, column acc_row(v, lane).  Park the wavefront's (TM*32) x (TN*32) tile as
-        // bf16 in its own LDS region (the operand slices are no longer needed).
-        constexpr int TSTRIDE = TN * 64 + 16;                // bytes per parked row
-        constexpr int CR = TN * 4;                           // 16-byte pieces per row
-        constexpr int RP = 64 / CR;                          // rows per pass of the wavefront
-        static_assert(4 * TM * 32 * TSTRIDE <= (int)gemm_lds_bytes<BM, BN, BK, WGM, WGN, NSTAGE>(), "parked tiles fit");
-        __syncthreads();
-        unsigned char* park = smem + wave * (TM * 32 * TSTRIDE);
-        const unsigned int wm0 = m0 + wm * TM * 32u, wn0 = n0 + wn * TN * 32u;
+    // The accumulator of tile (i, j) is transposed: element v of a lane is output row
+    // lane % 32, column acc_row(v, lane).  Park the wavefront's (TM*32) x (TN*32) tile as
+    // bf16 in its own LDS region (the operand slices are no longer needed).
+    constexpr int TSTRIDE = TN * 64 + 16;                // bytes per parked row
+    constexpr int CR = TN * 4;                           // 16-byte pieces per row
+    constexpr int RP = 64 / CR;                          // rows per pass of the wavefront
+    static_assert(4 * TM * 32 * TSTRIDE <= (int)gemm_lds_bytes<BM, BN, BK, WGM, WGN, NSTAGE>(), "parked tiles fit");
+    __syncthreads();
+    unsigned char* park = smem + wave * (TM * 32 * TSTRIDE);
+    const unsigned int wm0 = m0 + wm * TM * 32u, wn0 = n0 + wn * TN * 32u;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (unsigned int grp = 0; grp < 4; ++grp) {
+                const unsigned int nl = j * 32u + 8u * grp + 4u * (lane >> 5);
+                bf16_bits h[4];
+#pragma unroll
+                for (unsigned int e = 0; e < 4; ++e)
+                    h[e] = bf16_bits_rne(epi.pre(m0, wn0 + nl + e, acc[i][j][4 * grp + e]));
+                uint2 pk;
+                pk.x = (unsigned int)h[0] | ((unsigned int)h[1] << 16);
+                pk.y = (unsigned int)h[2] | ((unsigned int)h[3] << 16);
+                *reinterpret_cast<uint2*>(park + (i * 32u + (lane & 31u)) * TSTRIDE + nl * 2u) = pk;
+            }
+    // same wavefront reads what it wrote: LDS operations of a wavefront complete in order
+#pragma unroll
+    for (int pass = 0; pass < TM * 32 / RP; ++pass) {
+        const unsigned int row = pass * RP + lane / CR, piece = lane % CR;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(park + row * TSTRIDE + piece * 16u);
+        epi.store(wm0 + row, wn0 + piece * 8u, v);
+    }
+}
+
+// ----------------------------------------------------------------------------------------
+// Tiled product over the batch, C[m][n] = sum_i A[i][m] * B[i][n]: both operands as the other kernels
+// leave them, one row per experience, no transposed copies in memory.  A slice is 64 batch rows of
+// the workgroup's BM and BN columns; it goes straight into LDS as in gemm_nt_block, and the
+// transposing LDS read (ds_read_b64_tr_b16) hands a lane four consecutive batch rows of its column:
+// within 16 lanes, lane r points at 8 bytes of row r / 4, columns 4 (r mod 4).. of a 4 x 16 block and
+// receives column r of its four rows.  A 32-lane pass of that read covers 64 bytes of four rows: a row
+// of 64 bytes, or of 192, puts those on different banks by itself, in rows of 256 bytes the
+// 64-byte groups are rotated by XOR with the row number (the lanes fetch their global pieces in
+// that order).  The contraction ends at row `batch`: of a slice that it ends in, the rows beyond are
+// overwritten with zeros in LDS, and slices beyond are left out.
+//
+// A workgroup is eight wavefronts, two groups of four: both groups cover the whole tile, each for half
+// of a slice's steps, and add their accumulators through LDS at the end.  The square layer's tiles
+// have a compute unit to themselves, and with one wavefront per SIMD the transposing reads (twice
+// the instructions of the 16-byte ones), the MFMAs and the requests hardly overlapped: 23.9 us per
+// launch at batch 4096 and 1024 units with one group, 21.8 with two.  Deeper pipelines (four slices of
+// 64 or 32 rows: 23.8, 24.4) and two workgroups per compute unit (128 registers, spills: 23.2) were slower.
+//
+// Transposed copies of H1, H2 and both errors (24 MB written and 16 MB read a step by the kernel
+// before) with a row of ones for the biases (one more tile row of 128) made this launch 18.9 us but
+// the kernel before 12.8 us, now 6.4: 97.7 -> 92.9 us per step; at batch 512, 512 units 49.1 -> 45.1.
+//
+// The bias gradients are sums over one operand's columns: the workgroups of the first tile row
+// (SUM_ROWS: of the first tile column) multiply the fragments of B (of A) that they hold anyway
+// with a register of ones, one more MFMA a wavefront and 16 rows (three for the three-part tile).
+// ----------------------------------------------------------------------------------------
+constexpr int kTnSlice = 64, kTnStages = 2;   // batch rows of a slice, slices in LDS
+
+template <int BM, int BN>
+constexpr size_t gemm_tn_lds_bytes() {
+    // the slices, or the second group's accumulators and its sums
+    return std::max(kTnStages * (size_t)kTnSlice * (BM + BN) * 2, (size_t)BM * BN * 4 + 4 * 4096);
+}
+constexpr unsigned int kTnThreads = 512;
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+template <int BM, int BN, int WGM, int WGN, bool SUM_ROWS, class Epi>
+__device__ __forceinline__ void gemm_tn_block(const GemmArgs& p, const Epi& epi, unsigned int block) {
+    unsigned int m0, n0, split;
+    if (!tile_of<BM, BN>(p, block, &m0, &n0, &split)) return;
+    const bool with_sums = (SUM_ROWS ? n0 : m0) == 0u;
+    static_assert(WGM * WGN == 4, "four wavefronts a group");
+    constexpr int ROWA = BM * 2, ROWB = BN * 2;            // bytes per LDS row
+    constexpr int CPA = BM / 8, CPB = BN / 8;              // 16-byte pieces per row
+    constexpr unsigned int A_BYTES = kTnSlice * ROWA, STAGE = kTnSlice * (ROWA + ROWB);
+    // loads per slice, and per wavefront (where they do not divide evenly, some are made twice: every
+    // wavefront then counts the same number in flight)
+    constexpr int NA = kTnSlice * CPA / 64, NB = kTnSlice * CPB / 64;
+    constexpr int GA = (NA + 7) / 8, GB = (NB + 7) / 8, L = GA + GB;
+    constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32;  // 32x32 tiles per wavefront
+    static_assert(TM >= 1 && TN >= 1, "wavefront shape");
+    // sums a wavefront forms: all three parts of a three-part tile, else one tile's, each wavefront another
+    constexpr int NS = TN == 3 ? 3 : 1;
+    static_assert(SUM_ROWS ? WGN >= TM && NS == 1 : (NS == 3 || WGM >= TN), "every tile's sums have a wavefront");
+
+    extern __shared__ uint4 gemm_smem[];
+    unsigned char* smem = reinterpret_cast<unsigned char*>(gemm_smem);
+    const unsigned int tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const unsigned int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const unsigned int group = wave_u >> 2, wn = (wave_u & 3u) % WGN, wm = (wave_u & 3u) / WGN;
+    const unsigned int k_base = split * p.K;
+
+    // loader: the slice's pieces in LDS order, 64 a request.  Columns past the operand are redirected
+    // to its first: such columns only feed accumulator elements that the epilogue never stores.
+    auto a_load = [&](int u) { return min(wave_u * GA + u, (unsigned int)NA - 1u); };
+    auto b_load = [&](int u) { return min(wave_u * GB + u, (unsigned int)NB - 1u); };
+    unsigned int a_off[GA], b_off[GB];
+#pragma unroll
+    for (int u = 0; u < GA; ++u) {
+        const unsigned int at = a_load(u) * 64u + lane, r = at / CPA;
+        const unsigned int col = m0 + 8u * ((at % CPA) ^ (CPA == 16 ? 4u * (r & 3u) : 0u));
+        a_off[u] = (r * p.lda + (col < p.M ? col : 0u)) * 2u;
+    }
+#pragma unroll
+    for (int u = 0; u < GB; ++u) {
+        const unsigned int at = b_load(u) * 64u + lane, r = at / CPB;
+        const unsigned int col = n0 + 8u * ((at % CPB) ^ (CPB == 16 ? 4u * (r & 3u) : 0u));
+        b_off[u] = (r * p.ldb + (col < p.N ? col : 0u)) * 2u;
+    }
+    // request u of the slice at row k: the slice's first row is kept in scalar registers (the empty asm
+    // pins it there), the lane adds its 32-bit offset
+    typedef const __attribute__((address_space(1))) char* gchar;
+    auto request_at = [&](int u, unsigned int buf, gchar row, unsigned int off) {
+        unsigned char* dst = smem + buf * STAGE + (u < GA ? a_load(u) * 1024u : A_BYTES + b_load(u - GA) * 1024u);
+        asm volatile("" : "+s"(row));
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(row + off), RP_LDS_PTR(dst), 16, 0, 0);
+    };
+    auto fetch_one = [&](int u, unsigned int buf, unsigned int k) {
+        if (u < GA) request_at(u, buf, (gchar)reinterpret_cast<const char*>(p.A + (size_t)k * p.lda), a_off[u < GA ? u : 0]);
+        else request_at(u, buf, (gchar)reinterpret_cast<const char*>(p.Bt + (size_t)k * p.ldb), b_off[u >= GA ? u - GA : 0]);
+    };
+
+    f32x16 acc[TM][TN], sum[NS];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < TN; ++j) acc[i][j][v] = 0.f;
 #pragma unroll
-                for (unsigned int grp = 0; grp < 4; ++grp) {
-                    const unsigned int nl = j * 32u + 8u * grp + 4u * (lane >> 5);
-                    bf16_bits h[4];
+        for (int j = 0; j < NS; ++j) sum[j][v] = 0.f;
+    }
+    const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+
+    // where a lane reads in a slice: its row of the 4 x 16 blocks (batch rows 8 (lane / 32) + 0..3 of a
+    // 16-deep step, 4..7 with the second read) and its 8 bytes of a 32-wide tile
+    constexpr int STEPS = kTnSlice / 32;                   // 16-deep steps a group takes of a slice
+    const unsigned int rr = (lane >> 2) & 3u, lrow = group * STEPS * 16u + 8u * (lane >> 5) + rr;
+    const unsigned int lcol = 32u * ((lane >> 4) & 1u) + 8u * (lane & 3u);
+    unsigned int a_at[TM], b_at[TN];
 #pragma unroll
-                    for (unsigned int e = 0; e < 4; ++e)
-                        h[e] = bf16_bits_rne(epi.pre(m0, wn0 + nl + e, acc[i][j][4 * grp + e]));
-                    uint2 pk;
-                    pk.x = (unsigned int)h[0] | ((unsigned int)h[1] << 16);
-                    pk.y = (unsigned int)h[2] | ((unsigned int)h[3] << 16);
-                    *reinterpret_cast<uint2*>(park + (i * 32u + (lane & 31u)) * TSTRIDE + nl * 2u) = pk;
+    for (int i = 0; i < TM; ++i) {
+        const unsigned int t = wm * TM + i;
+        a_at[i] = lrow * ROWA + 64u * (CPA == 16 ? t ^ rr : t) + lcol;
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const unsigned int t = wn * TN + j;
+        b_at[j] = A_BYTES + lrow * ROWB + 64u * (CPB == 16 ? t ^ rr : t) + lcol;
+    }
+    typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+    auto fragment = [&](unsigned int at, unsigned int row_bytes) {   // batch rows 0..3 and 4..7 of the lane's eight
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)RP_LDS_PTR(smem + at));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)RP_LDS_PTR(smem + at + 4u * row_bytes));
+        return __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    // one slice's multiply, with the next one's requests between the MFMAs (as in gemm_nt_block)
+    auto multiply = [&](unsigned int buf, auto fetch_flag, unsigned int fbuf, unsigned int fk0) {
+        constexpr bool FETCH = decltype(fetch_flag)::value;
+        constexpr int NM = STEPS * TM * TN;
+        u32x4 a[2][TM], b[2][TN];
+        auto request = [&](int s, int set) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) a[set][i] = fragment(buf * STAGE + a_at[i] + 16u * s * ROWA, ROWA);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) b[set][j] = fragment(buf * STAGE + b_at[j] + 16u * s * ROWB, ROWB);
+        };
+        request(0, 0);
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            if (s + 1 < STEPS) request(s + 1, (s + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (with_sums) {
+#pragma unroll
+                for (int j = 0; j < NS; ++j) {
+                    if constexpr (SUM_ROWS) {
+                        const u32x4 x = TM > 1 && wn ? a[s & 1][TM - 1] : a[s & 1][0];
+                        sum[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(x), as_bf16x8(ones), sum[j], 0, 0, 0);
+                    } else {
+                        const u32x4 x = NS == 3 ? b[s & 1][j] : TN > 1 && wm ? b[s & 1][TN - 1] : b[s & 1][0];
+                        sum[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ones), as_bf16x8(x), sum[j], 0, 0, 0);
+                    }
                 }
-        // same wavefront reads what it wrote: LDS operations of a wavefront complete in order
+            }
 #pragma unroll
-        for (int pass = 0; pass < TM * 32 / RP; ++pass) {
-            const unsigned int row = pass * RP + lane / CR, piece = lane % CR;
-            const u32x4 v = *reinterpret_cast<const u32x4*>(park + row * TSTRIDE + piece * 16u);
-            epi.store(wm0 + row, wn0 + piece * 8u, v);
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a[s & 1][i]), as_bf16x8(b[s & 1][j]), acc[i][j], 0, 0, 0);
+                    if (FETCH) {
+                        const int m = (s * TM + i) * TN + j;
+#pragma unroll
+                        for (int u = m * L / NM; u < (m + 1) * L / NM; ++u) fetch_one(u, fbuf, fk0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            __builtin_amdgcn_sched_barrier(0);
         }
-    } else {
+    };
+
+    // (the pipeline of gemm_nt_block)  The last slice may end with the operands' rows: its requests
+    // beyond them fetch the last row, and what they brought is overwritten with zeros.
+    const unsigned int rows = p.batch > k_base ? min(p.K, p.batch - k_base) : 0u;
+    const unsigned int nk = (rows + kTnSlice - 1u) / kTnSlice, left = rows % kTnSlice;
+    auto last_offsets = [&]() {                              // before that slice's requests
 #pragma unroll
-        for (int i = 0; i < TM; ++i) epi.tiles(m0 + (wm * TM + i) * 32u, n0 + wn * TN * 32u, acc[i], lane, split);
+        for (int u = 0; u < GA; ++u) {
+            const unsigned int r = (a_load(u) * 64u + lane) / CPA;
+            a_off[u] -= r < left ? 0u : (r - (left - 1u)) * p.lda * 2u;
+        }
+#pragma unroll
+        for (int u = 0; u < GB; ++u) {
+            const unsigned int r = (b_load(u) * 64u + lane) / CPB;
+            b_off[u] -= r < left ? 0u : (r - (left - 1u)) * p.ldb * 2u;
+        }
+    };
+#pragma unroll
+    for (unsigned int s0 = 0; s0 + 1 < (unsigned int)kTnStages; ++s0)
+        if (s0 < nk) {
+            if (left && s0 + 1u == nk) last_offsets();
+#pragma unroll
+            for (int u = 0; u < L; ++u) fetch_one(u, s0, k_base + s0 * kTnSlice);
+        }
+    unsigned int kt = 0;
+    for (; kt + kTnStages - 1 < nk; ++kt) {
+        if (left && kt + kTnStages == nk) last_offsets();
+        wait_loads<(kTnStages - 2) * L>();
+        __syncthreads();
+        multiply(kt % kTnStages, std::true_type{}, (kt + kTnStages - 1) % kTnStages, k_base + (kt + kTnStages - 1) * kTnSlice);
+    }
+    for (; kt < nk; ++kt) {
+        wait_slices<L, kTnStages>(nk - 1u - kt);
+        __syncthreads();
+        if (left && kt + 1u == nk) {
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            u32x4* sa = reinterpret_cast<u32x4*>(smem + (kt % kTnStages) * STAGE);
+            u32x4* sb = reinterpret_cast<u32x4*>(smem + (kt % kTnStages) * STAGE + A_BYTES);
+            for (unsigned int e = left * CPA + tid; e < (unsigned int)kTnSlice * CPA; e += kTnThreads) sa[e] = zero;
+            for (unsigned int e = left * CPB + tid; e < (unsigned int)kTnSlice * CPB; e += kTnThreads) sb[e] = zero;
+            __syncthreads();
+        }
+        multiply(kt % kTnStages, std::false_type{}, 0u, 0u);
+    }
+
+    // the second group hands its accumulators and sums to the first
+    __syncthreads();
+    f32x4* const give = reinterpret_cast<f32x4*>(smem) + (wave_u & 3u) * (TM * TN * 256u) + lane;
+    f32x4* const give_sums = reinterpret_cast<f32x4*>(smem + (size_t)BM * BN * 4) + (wave_u & 3u) * 256u + lane;
+    if (group) {
+#pragma unroll
+        for (int q = 0; q < TM * TN * 4; ++q) {
+            const f32x16& c = acc[q / 4 / TN][q / 4 % TN];
+            give[q * 64] = f32x4{c[q % 4 * 4], c[q % 4 * 4 + 1], c[q % 4 * 4 + 2], c[q % 4 * 4 + 3]};
+        }
+        if (with_sums) {
+            // (a column sum is in every row: one element is enough)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                give_sums[q * 64] = SUM_ROWS ? f32x4{sum[0][q * 4], sum[0][q * 4 + 1], sum[0][q * 4 + 2], sum[0][q * 4 + 3]}
+                                             : f32x4{sum[0][0], sum[NS > 1 ? 1 : 0][0], sum[NS > 2 ? 2 : 0][0], 0.f};
+        }
+    }
+    __syncthreads();
+    if (group) return;
+#pragma unroll
+    for (int q = 0; q < TM * TN * 4; ++q) {
+        const f32x4 x = give[q * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[q / 4 / TN][q / 4 % TN][q % 4 * 4 + e] += x[e];
+    }
+    if (with_sums) {
+#pragma unroll
+        for (int q = 0; q < (SUM_ROWS ? 4 : 1); ++q) {
+            const f32x4 x = give_sums[q * 64];
+            if constexpr (SUM_ROWS) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[0][q * 4 + e] += x[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < NS; ++e) sum[e][0] += x[e];
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) epi.tiles(m0 + (wm * TM + i) * 32u, n0 + wn * TN * 32u, acc[i], lane, split);
+    if (with_sums) {
+        // (of the wavefronts that formed the same sums one stores them)
+        if constexpr (SUM_ROWS) {
+            if (wn < TM) epi.sums(m0 + (wm * TM + wn) * 32u, sum, lane, split);
+        } else if constexpr (NS == 3) {
+            if (wm == 0) epi.sums(n0, sum, lane, split);
+        } else {
+            if (wm < TN) epi.sums(n0 + (wn * TN + wm) * 32u, sum, lane, split);
+        }
     }
 }
 
@@ -445,19 +744,19 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(GemmArgs p, Epi e
 // workgroups [0, n2) take the square layer's, [n2, n2 + n3) the output layer's, the rest the
 // first layer's.  n2 and n3 are multiples of 8, which keeps a workgroup's index within its
 // product congruent to its XCD.  The output layer's tiles are the three parts of 32 actions wide;
-// NARROW1: the first layer's gradient is at most 32 columns wide and uses the matching narrow tile.
+// NARROW1: the states are at most 32 wide and the first layer's gradient uses the matching tile.
 template <bool NARROW1>
-__global__ __launch_bounds__(kGemmThreads) void grad_products_kernel(GemmArgs p2, EpiPartial e2, unsigned int n2,
-                                                                     GemmArgs p3, EpiPartialOfThree e3, unsigned int n3,
-                                                                     GemmArgs p1, EpiPartial e1) {
+__global__ __launch_bounds__(kTnThreads) void grad_products_kernel(GemmArgs p2, EpiSquare e2, unsigned int n2,
+                                                                     GemmArgs p3, EpiOutput e3, unsigned int n3,
+                                                                     GemmArgs p1, EpiFirst e1) {
     const unsigned int b = blockIdx.x;
     if (b < n2) {
-        gemm_nt_block<128, 128, 64, 2, 2>(p2, e2, b);
+        gemm_tn_block<128, 128, 2, 2, false>(p2, e2, b);
     } else if (b < n2 + n3) {
-        gemm_nt_block<128, 96, 64, 4, 1>(p3, e3, b - n2);
+        gemm_tn_block<128, 96, 4, 1, false>(p3, e3, b - n2);
     } else {
-        if constexpr (NARROW1) gemm_nt_block<128, 32, 64, 4, 1>(p1, e1, b - n2 - n3);
-        else gemm_nt_block<128, 128, 64, 2, 2>(p1, e1, b - n2 - n3);
+        if constexpr (NARROW1) gemm_tn_block<128, 32, 4, 1, true>(p1, e1, b - n2 - n3);
+        else gemm_tn_block<128, 128, 2, 2, true>(p1, e1, b - n2 - n3);
     }
 }
 
@@ -476,7 +775,7 @@ hipError_t configure_grad_products() {
     auto kernel = grad_products_kernel<NARROW1>;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)gemm_lds_bytes<128, 128, 64, 2, 2>());
+                               (int)gemm_tn_lds_bytes<128, 128>());
 }
 
 // Arguments and workgroup count (a multiple of 8) of one product with BM x BN tiles and BK-wide
@@ -494,6 +793,7 @@ bool gemm_args(const bf16_bits* A, unsigned int lda, const bf16_bits* Bt, unsign
     a->tiles_m = (M + BM - 1) / BM;
     a->tiles_n = (N + BN - 1) / BN;
     a->splits = splits;
+    a->batch = 0;
     const unsigned int n_tiles = a->tiles_m * a->tiles_n * splits;
     *blocks = 8u * ((n_tiles + 7u) / 8u);
     // band width: the one for which an XCD's share of the tiles (a block of about per_xcd / band
@@ -538,7 +838,8 @@ hipError_t launch_gemm(hipStream_t st, const bf16_bits* A, unsigned int lda, con
 }
 
 // ----------------------------------------------------------------------------------------
-// Skinny product for the output layer, Q = H2 W3 + b3 (a few 32-wide column tiles, many rows):
+// Product with few output tiles: the output layer, Q = H2 W3 + b3 (a few 32-wide column tiles, many
+// rows), and others on small batches (few_tiles):
 // one 32x32 output tile per workgroup; the wavefronts split K, each loading its MFMA operands
 // straight from global memory (eight 16-deep steps requested before the first multiply), and
 // add their accumulators through LDS.  K is a multiple of 16.  Rows beyond M / N read row 0
@@ -550,17 +851,25 @@ struct SkinnyArgs {
     const bf16_bits* Bt;
     unsigned int ldb;
     unsigned int M, N, K;
-    const float* bias;   // [N]
-    float* out;          // [M x ldo], fp32
-    unsigned int ldo;
     // tiles whose first row is m_split (a multiple of 32) or beyond use these (the target network's)
     const bf16_bits* Bt_hi;
-    const float* bias_hi;
     unsigned int m_split;
 };
 
-template <int NW>
-__global__ __launch_bounds__(64 * NW) void skinny_nt_kernel(SkinnyArgs p) {
+// out[m][n] = acc + bias[n], fp32
+struct SkinnyBias {
+    const float* bias;   // [N]
+    const float* bias_hi;
+    unsigned int m_split;
+    float* out;          // [M x ldo]
+    unsigned int ldo;
+    __device__ __forceinline__ void store(unsigned int m, unsigned int n, float x) const {
+        out[(size_t)m * ldo + n] = x + (m >= m_split ? bias_hi : bias)[n];
+    }
+};
+
+template <int NW, class Epi>
+__global__ __launch_bounds__(64 * NW) void skinny_nt_kernel(SkinnyArgs p, Epi epi) {
     __shared__ float red[NW * 16 * 64];
     const unsigned int tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const unsigned int m0 = blockIdx.x * 32u, n0 = blockIdx.y * 32u;
@@ -568,7 +877,6 @@ __global__ __launch_bounds__(64 * NW) void skinny_nt_kernel(SkinnyArgs p) {
     const bf16_bits* ap = p.A + (size_t)(am < p.M ? am : 0u) * p.lda + 8u * (lane >> 5);
     const bool hi = m0 >= p.m_split;
     const bf16_bits* bp = (hi ? p.Bt_hi : p.Bt) + (size_t)(bn < p.N ? bn : 0u) * p.ldb + 8u * (lane >> 5);
-    const float* bias = hi ? p.bias_hi : p.bias;
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
     f32x16 acc;
 #pragma unroll
@@ -595,31 +903,28 @@ __global__ __launch_bounds__(64 * NW) void skinny_nt_kernel(SkinnyArgs p) {
 #pragma unroll
         for (unsigned int w = 0; w < (unsigned int)NW; ++w) s += red[(w * 16u + v) * 64u + l];
         const unsigned int m = m0 + acc_row(v, l), n = n0 + (l & 31u);
-        if (m < p.M && n < p.N) p.out[(size_t)m * p.ldo + n] = s + bias[n];
+        if (m < p.M && n < p.N) epi.store(m, n, s);
     }
 }
 
 // ----------------------------------------------------------------------------------------
 // TD target, loss and the gradient at the second hidden layer's pre-activation.
-// A workgroup owns 64 batch rows x 64 hidden units.  It first repeats, for its 64 rows, the
-// per-row part: y_i = r_i + gamma (1 - term_i) max_a Q(s'_i, a), delta_i = y_i - Q(s_i, a_i),
-// the loss term and g_i = dL/dQ(s_i, a_i)  (four lanes per row share the max).  Workgroups of
-// the first hidden-unit stripe store those and dL/dQ transposed, split into three bf16 parts whose
-// sum is the fp32 number, so that the output layer's weight gradient loses nothing to the split.
-// Then
-//   dZ2[i][k] = g_i * W3[k][a_i] * 1[H2[i][k] > 0]
-// goes out in both orientations (the transposed one through an LDS tile), and so do the
-// transposed copies of this tile of H1 and H2 that the weight-gradient products read.  With hidden
-// layers of different widths a stripe beyond the narrower layer's has the other's part only.
+// A workgroup owns 16 batch rows x 256 hidden units, sixteen lanes to a row.  The lanes of a row
+// work out y_i = r_i + gamma (1 - term_i) max_a Q(s'_i, a), delta_i = y_i - Q(s_i, a_i), the loss
+// term and g_i = dL/dQ(s_i, a_i) among themselves, without LDS or a barrier, while their share of H2
+// is on its way.  Workgroups of the first stripe of units store those and dL/dQ, split into three
+// bf16 parts whose sum is the fp32 number, so that the output layer's weight gradient loses nothing
+// to the split.  Then dZ2[i][k] = g_i * W3[k][a_i] * 1[H2[i][k] > 0] goes out, 16 bytes a lane.
+// Bound by memory: H2 in, dZ2 out (8 MB each at batch 4096 and 1024 units).
 // ----------------------------------------------------------------------------------------
-// Row of the transposed dL/dQ that holds part s (0, 1, 2: from the highest bits down) of action a: the
+// Column of dL/dQ that holds part s (0, 1, 2: from the highest bits down) of action a: the
 // parts of 32 actions are neighbours, one tile of the product that contracts them with H2.
-__device__ __forceinline__ unsigned int dq_row(unsigned int a, unsigned int s) {
+__device__ __forceinline__ unsigned int dq_col(unsigned int a, unsigned int s) {
     return (a >> 5) * 96u + s * 32u + (a & 31u);
 }
 
 struct TdArgs {
-    unsigned int B, Bp, H, G, A, Ap;
+    unsigned int B, G, A, Ap;
     const float* Q;              // [2B x Ap]
     const int* act;
     const float* rew;
@@ -628,24 +933,18 @@ struct TdArgs {
     unsigned int loss_kind;
     float beta1, beta2;
     float *y, *delta, *lossi;
-    bf16_bits* dQT;              // [3 Ap x Bp]
+    bf16_bits* dQ;               // [B x 3 Ap]
     const bf16_bits* W3T;        // [Ap x G]
-    const bf16_bits* H1;         // [2B x H]
     const bf16_bits* H2;         // [2B x G]
     bf16_bits* dZ2;              // [B x G]
-    bf16_bits* dZ2T;             // [G x Bp]
-    bf16_bits *H1T, *H2T;        // [H+1 x Bp], [G+1 x Bp]: transposed copies of the first B rows of H1, H2
     TrainCounters* ctr;
 };
 
+constexpr unsigned int kTdRows = 16, kTdCols = 256;
+
 __global__ __launch_bounds__(256) void td_dz_kernel(TdArgs p) {
-    __shared__ float gs[64];
-    __shared__ unsigned int as_[64];
-    // [k][row] tiles, padded: dZ2, H2 and H1 on their way to the transposed buffers
-    __shared__ __attribute__((aligned(16))) bf16_bits tileT[3][64][72];
-    const unsigned int tid = threadIdx.x;
-    const unsigned int i0 = blockIdx.x * 64u, k0 = blockIdx.y * 64u;
-    const bool first = k0 < p.H, second = k0 < p.G;   // this stripe has units of the first / second layer
+    const unsigned int tid = threadIdx.x, part = tid & 15u;
+    const unsigned int i = blockIdx.x * kTdRows + (tid >> 4), k0 = blockIdx.y * kTdCols + part * 8u;
     if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
         // (running products beta^t in double precision: no power function on the device)
         const double pw1 = p.ctr->pw1 * (double)p.beta1, pw2 = p.ctr->pw2 * (double)p.beta2;
@@ -655,119 +954,64 @@ __global__ __launch_bounds__(256) void td_dz_kernel(TdArgs p) {
         p.ctr->c1 = (float)(1.0 - pw1);
         p.ctr->c2 = (float)(1.0 - pw2);
     }
-    {
-        const unsigned int r = tid >> 2, part = tid & 3u, i = i0 + r;
-        const bool live = i < p.B;
-        float best = -INFINITY;
-        if (live) {
-            const float* qn = p.Q + (size_t)(p.B + i) * p.Ap;
-            for (unsigned int a = part; a < p.A; a += 4) best = fmaxf(best, qn[a]);
+    if (i >= p.B) return;                           // (the same for all lanes of a row)
+    unsigned int ai = (unsigned int)p.act[i];
+    if (ai >= p.A) ai = p.A - 1;                    // an out-of-range action must not turn into a wild address
+    u32x4 hv[2] = {}, wv[2] = {};
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+        if (k0 + 128u * e < p.G) {
+            hv[e] = *reinterpret_cast<const u32x4*>(p.H2 + (size_t)i * p.G + k0 + 128u * e);
+            wv[e] = *reinterpret_cast<const u32x4*>(p.W3T + (size_t)ai * p.G + k0 + 128u * e);
         }
-        best = fmaxf(best, __shfl_xor(best, 1, 64));
-        best = fmaxf(best, __shfl_xor(best, 2, 64));
-        if (part == 0) {
-            float g = 0.f;
-            unsigned int ai = 0;
-            if (live) {
-                ai = (unsigned int)p.act[i];
-                if (ai >= p.A) ai = p.A - 1;  // an out-of-range action must not turn into a wild address
-                const float q = p.Q[(size_t)i * p.Ap + ai];
-                const float y = p.rew[i] + (p.term[i] ? 0.f : p.gamma * best);
-                const float d = y - q;
-                float li, slope;
-                if (p.loss_kind == RP_MSE || fabsf(d) <= 1.f) {
-                    li = 0.5f * d * d;
-                    slope = d;
-                } else {
-                    li = fabsf(d) - 0.5f;
-                    slope = d > 0.f ? 1.f : -1.f;
-                }
-                g = -slope / (float)p.B;
-                if (blockIdx.y == 0) {
-                    p.y[i] = y;
-                    p.delta[i] = d;
-                    p.lossi[i] = li;
-                }
-            }
-            gs[r] = g;
-            as_[r] = ai;
-        }
+    float best = -INFINITY;
+    const float* qn = p.Q + (size_t)(p.B + i) * p.Ap;
+    for (unsigned int a = part; a < p.A; a += 16u) best = fmaxf(best, qn[a]);
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) best = fmaxf(best, __shfl_xor(best, m, 64));
+    const float q = p.Q[(size_t)i * p.Ap + ai];
+    const float y = p.rew[i] + (p.term[i] ? 0.f : p.gamma * best);
+    const float d = y - q;
+    float li, slope;
+    if (p.loss_kind == RP_MSE || fabsf(d) <= 1.f) {
+        li = 0.5f * d * d;
+        slope = d;
+    } else {
+        li = fabsf(d) - 0.5f;
+        slope = d > 0.f ? 1.f : -1.f;
     }
-    __syncthreads();
+    const float g = -slope / (float)p.B;
     if (blockIdx.y == 0) {
-        for (unsigned int e = tid; e < p.Ap * 64u; e += 256u) {
-            const unsigned int a = e >> 6, r = e & 63u;
-            const float g = (a == as_[r]) ? gs[r] : 0.f;
-            const bf16_bits hi = bf16_bits_rne(g);
-            const float rest = g - bits_to_float(hi);
-            const bf16_bits mid = bf16_bits_rne(rest);
-            const bf16_bits lo = bf16_bits_rne(rest - bits_to_float(mid));
-            p.dQT[(size_t)dq_row(a, 0) * p.Bp + i0 + r] = hi;
-            p.dQT[(size_t)dq_row(a, 1) * p.Bp + i0 + r] = mid;
-            p.dQT[(size_t)dq_row(a, 2) * p.Bp + i0 + r] = lo;
+        if (part == 0) {
+            p.y[i] = y;
+            p.delta[i] = d;
+            p.lossi[i] = li;
+        }
+        const bf16_bits hi = bf16_bits_rne(g);
+        const float rest = g - bits_to_float(hi);
+        const bf16_bits mid = bf16_bits_rne(rest);
+        const bf16_bits lo = bf16_bits_rne(rest - bits_to_float(mid));
+        bf16_bits* dq = p.dQ + (size_t)i * 3u * p.Ap;
+        // two actions a lane: a row's 32-wide parts leave as 64-byte runs
+        for (unsigned int a = 2u * part; a < p.Ap; a += 32u) {
+            const unsigned int shift = a == ai ? 0u : 16u;
+            const bool mine = (a ^ ai) < 2u;        // (a is even)
+            *reinterpret_cast<unsigned int*>(dq + dq_col(a, 0)) = mine ? (unsigned int)hi << shift : 0u;
+            *reinterpret_cast<unsigned int*>(dq + dq_col(a, 1)) = mine ? (unsigned int)mid << shift : 0u;
+            *reinterpret_cast<unsigned int*>(dq + dq_col(a, 2)) = mine ? (unsigned int)lo << shift : 0u;
         }
     }
-    {
-        // 16 consecutive hidden units of one row per thread
-        const unsigned int r = tid >> 2, ks = (tid & 3u) * 16u, i = i0 + r;
-        const bool live = i < p.B;
-        bf16_bits out[16], h2[16], h1[16];
-        u32x4 hv[2] = {}, gv[2] = {}, wv[2] = {};
-        if (live) {
-            // (stripes: uniform over the workgroup)
-            if (second) {
-                const u32x4* hp = reinterpret_cast<const u32x4*>(p.H2 + (size_t)i * p.G + k0 + ks);
-                const u32x4* wp = reinterpret_cast<const u32x4*>(p.W3T + (size_t)as_[r] * p.G + k0 + ks);
-                hv[0] = hp[0]; hv[1] = hp[1]; wv[0] = wp[0]; wv[1] = wp[1];
-            }
-            if (first) {
-                const u32x4* gp = reinterpret_cast<const u32x4*>(p.H1 + (size_t)i * p.H + k0 + ks);
-                gv[0] = gp[0]; gv[1] = gp[1];
-            }
-        }
-        const float g = gs[r];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            h2[e] = (bf16_bits)(hv[e >> 3][(e & 7) >> 1] >> (16 * (e & 1)));
-            h1[e] = (bf16_bits)(gv[e >> 3][(e & 7) >> 1] >> (16 * (e & 1)));
-            const bf16_bits wb = (bf16_bits)(wv[e >> 3][(e & 7) >> 1] >> (16 * (e & 1)));
-            const float x = bits_to_float(h2[e]) > 0.f ? g * bits_to_float(wb) : 0.f;
-            out[e] = bf16_bits_rne(x);
-        }
-        if (live && second) {
-            u32x4 o0, o1;
+    for (int e = 0; e < 2; ++e) {
+        u32x4 out;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                o0[e] = out[2 * e] | ((unsigned int)out[2 * e + 1] << 16);
-                o1[e] = out[8 + 2 * e] | ((unsigned int)out[8 + 2 * e + 1] << 16);
-            }
-            u32x4* dp = reinterpret_cast<u32x4*>(p.dZ2 + (size_t)i * p.G + k0 + ks);
-            dp[0] = o0;
-            dp[1] = o1;
+        for (int x = 0; x < 4; ++x) {
+            const float h_lo = __uint_as_float(hv[e][x] << 16), h_hi = __uint_as_float(hv[e][x] & 0xFFFF0000u);
+            const float w_lo = __uint_as_float(wv[e][x] << 16), w_hi = __uint_as_float(wv[e][x] & 0xFFFF0000u);
+            out[x] = (unsigned int)bf16_bits_rne(h_lo > 0.f ? g * w_lo : 0.f) |
+                     ((unsigned int)bf16_bits_rne(h_hi > 0.f ? g * w_hi : 0.f) << 16);
         }
-        // (the four lanes of a row hold k-ranges 16 apart, whose tile rows start in the same bank:
-        // each range gets its columns rotated by a different multiple of 16, undone when read)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            tileT[0][ks + e][r ^ ks] = out[e];
-            tileT[1][ks + e][r ^ ks] = h2[e];
-            tileT[2][ks + e][r ^ ks] = h1[e];
-        }
-    }
-    __syncthreads();
-    {
-        // 16 consecutive batch rows of one hidden unit per thread
-        const unsigned int k = tid >> 2, rs = (tid & 3u) * 16u;
-        const size_t at = (size_t)(k0 + k) * p.Bp + i0 + rs;
-        bf16_bits* const dst[3] = {p.dZ2T, p.H2T, p.H1T};
-#pragma unroll
-        for (int w = 0; w < 3; ++w) {
-            if (!(w < 2 ? second : first)) continue;
-            const u32x4* sp = reinterpret_cast<const u32x4*>(&tileT[w][k][rs ^ (k & 48u)]);
-            u32x4* dp = reinterpret_cast<u32x4*>(dst[w] + at);
-            dp[0] = sp[0];
-            dp[1] = sp[1];
-        }
+        if (k0 + 128u * e < p.G) *reinterpret_cast<u32x4*>(p.dZ2 + (size_t)i * p.G + k0 + 128u * e) = out;
     }
 }
 
@@ -981,10 +1225,19 @@ unsigned int batch_splits(unsigned int Bp) {
 // K splits of the square layer's gradient product: doubled while its 128 x 128 tiles number
 // fewer than the compute units, every split keeps at least 256 columns in whole 64-wide slices.
 unsigned int square_splits_for(unsigned int Bp, unsigned int H, unsigned int G) {
-    const unsigned int tiles = ((H + 1u + 127u) / 128u) * ((G + 127u) / 128u);
+    const unsigned int tiles = ((H + 127u) / 128u) * ((G + 127u) / 128u);
     unsigned int s = 1;
     while (tiles * s < 256u && s < 8u && Bp % (2u * s * 64u) == 0 && Bp / (2u * s) >= 256u) s *= 2u;
     return s;
+}
+
+// H2 = relu(H1 W2 + b2) for `rows` rows; with hi, rows from m_split on take those weights and biases.
+hipError_t second_layer(hipStream_t st, const bf16_bits* H1, unsigned int rows, unsigned int H, unsigned int G,
+                        const bf16_bits* W2T, const float* b2, bf16_bits* H2, const bf16_bits* hi, const float* b2_hi,
+                        unsigned int m_split) {
+    if (!hi) m_split = ~0u;
+    return launch_gemm<128, 128, 64, 2, 2>(st, H1, H, W2T, H, rows, G, H, EpiForward{b2, b2_hi, m_split, H2, G, rows, G},
+                                           1, hi, m_split);
 }
 
 bf16_bits host_bf16(float f) {
@@ -1016,24 +1269,14 @@ bool wide_step_supported(const train_config& cfg, const replay* rp_) {
            rp_->cfg.layout == RP_PAIR && wide_step_shape(cfg);
 }
 
-// Allow the products' LDS sizes and fill the ones rows of the transposed activation buffers
-// (once, at creation).
-hipError_t wide_init_buffers(trainer* t) {
+// Allow the products' LDS sizes (once, at creation).
+hipError_t wide_configure() {
     hipError_t ec = configure_gemm<128, 128, 32, 2, 2, EpiForward>();
     if (ec == hipSuccess) ec = configure_gemm<128, 128, 64, 2, 2, EpiForward>();
     if (ec == hipSuccess) ec = configure_gemm<128, 64, 64, 2, 2, EpiMask>();
     if (ec == hipSuccess) ec = configure_grad_products<true>();
     if (ec == hipSuccess) ec = configure_grad_products<false>();
-    if (ec != hipSuccess) return ec;
-    std::vector<bf16_bits> ones(t->Bp, (bf16_bits)0x3F80u);
-    const size_t bytes = (size_t)t->Bp * sizeof(bf16_bits);
-    hipError_t e = hipMemcpy(t->wd.H1T + (size_t)t->H * t->Bp, ones.data(), bytes, hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(t->wd.H2T + (size_t)t->Hb * t->Bp, ones.data(), bytes, hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(t->wd.XT + (size_t)t->cfg.state_dim * t->Bp, ones.data(), bytes,
-                      hipMemcpyHostToDevice);
-    return e;
+    return ec;
 }
 
 // Refresh the bf16 operand copies of the weights from padded fp32 parameters (host array): all
@@ -1071,6 +1314,7 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
     bf16_bits* H1 = static_cast<bf16_bits*>(t->H1);
     bf16_bits* H2 = static_cast<bf16_bits*>(t->H2);
     bf16_bits* dZ2 = static_cast<bf16_bits*>(t->dZ2);
+    bf16_bits* dZ1 = static_cast<bf16_bits*>(t->dZ1);
     unsigned int n = 0;
     OptState o{t->w, t->g, t->m, t->v, t->cfg.opt, t->cfg.lr, t->cfg.beta1, t->cfg.beta2, t->cfg.eps,
                t->ctr, t->wt, t->cfg.target_sync};
@@ -1082,13 +1326,12 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
     const bool one_launch = !tgt || B % 128 == 0;
     const unsigned int rows = one_launch ? 2 * B : B;   // rows of the first forward launch
 
-    // sample B slots and unpack into X = [S ; S'] and the transposed copy of S
+    // sample B slots and unpack into X = [S ; S']
     hipError_t e = hipSuccess;
     unsigned int launched = 0;
     if (sample) {
         e = launch_sample_gather(t->rp_->geom, t->rp_->cfg.seed, 0, &t->ctr->step, B, X,
-                                 X + (size_t)B * Dp, Dp, t->act, t->rew, t->term, t->idx, st, w.XT, Bp,
-                                 0, 0, t->rp_->draw_scratch, &launched);
+                                 X + (size_t)B * Dp, Dp, t->act, t->rew, t->term, t->idx, st, 0, 0, t->rp_->draw_scratch, &launched);
         if (e != hipSuccess) return e;
         n += launched;
     }
@@ -1104,30 +1347,29 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
         if (e != hipSuccess) return e;
         ++n;
     }
-    e = launch_gemm<128, 128, 64, 2, 2>(st, H1, H, w.W2T, H, rows, G, H,
-                                           EpiForward{t->w + t->ob2, b2t, tgt ? B : ~0u, H2, G, rows, G},
-                                           1, tgt && one_launch ? w.W2T_t : nullptr, B);
+    const float* b2 = t->w + t->ob2;
+    e = second_layer(st, H1, rows, H, G, w.W2T, b2, H2, tgt && one_launch ? w.W2T_t : nullptr, b2t, B);
     if (e != hipSuccess) return e;
     ++n;
     if (!one_launch) {
-        e = launch_gemm<128, 128, 64, 2, 2>(st, H1 + (size_t)B * H, H, w.W2T_t, H, B, G, H,
-                                               EpiForward{b2t, b2t, ~0u, H2 + (size_t)B * G, G, B, G});
+        e = second_layer(st, H1 + (size_t)B * H, B, H, G, w.W2T_t, b2t, H2 + (size_t)B * G, nullptr, nullptr, 0);
         if (e != hipSuccess) return e;
         ++n;
     }
     {
         SkinnyArgs a;
         a.A = H2; a.lda = G; a.Bt = w.W3T; a.ldb = G; a.M = rows; a.N = Ap; a.K = G;
-        a.bias = t->w + t->ob3; a.out = t->Q; a.ldo = Ap;
-        a.Bt_hi = tgt ? w.W3T_t : w.W3T; a.bias_hi = tgt ? b3t : a.bias; a.m_split = tgt ? B : ~0u;
-        hipLaunchKernelGGL(skinny_nt_kernel<8>, dim3((rows + 31) / 32, Ap / 32), dim3(512), 0, st, a);
+        a.Bt_hi = tgt ? w.W3T_t : w.W3T; a.m_split = tgt ? B : ~0u;
+        const float* b3 = t->w + t->ob3;
+        hipLaunchKernelGGL((skinny_nt_kernel<8, SkinnyBias>), dim3((rows + 31) / 32, Ap / 32), dim3(512), 0, st, a,
+                           SkinnyBias{b3, tgt ? b3t : b3, a.m_split, t->Q, Ap});
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         ++n;
         if (!one_launch) {
-            a.A = H2 + (size_t)B * G; a.Bt = w.W3T_t; a.bias = b3t; a.out = t->Q + (size_t)B * Ap;
-            a.M = B; a.Bt_hi = a.Bt; a.bias_hi = a.bias; a.m_split = ~0u;
-            hipLaunchKernelGGL(skinny_nt_kernel<8>, dim3((B + 31) / 32, Ap / 32), dim3(512), 0, st, a);
+            a.A = H2 + (size_t)B * G; a.M = B; a.Bt = a.Bt_hi = w.W3T_t; a.m_split = ~0u;
+            hipLaunchKernelGGL((skinny_nt_kernel<8, SkinnyBias>), dim3((B + 31) / 32, Ap / 32), dim3(512), 0, st, a,
+                               SkinnyBias{b3t, b3t, ~0u, t->Q + (size_t)B * Ap, Ap});
             e = hipGetLastError();
         }
     }
@@ -1136,21 +1378,20 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
     // targets, TD errors, loss terms, dL/dQ and dZ2
     {
         TdArgs a;
-        a.B = B; a.Bp = Bp; a.H = H; a.G = G; a.A = A; a.Ap = Ap;
+        a.B = B; a.G = G; a.A = A; a.Ap = Ap;
         a.Q = t->Q; a.act = t->act; a.rew = t->rew; a.term = t->term;
         a.gamma = t->cfg.gamma; a.loss_kind = t->cfg.loss; a.beta1 = t->cfg.beta1; a.beta2 = t->cfg.beta2;
         a.y = t->y; a.delta = t->delta; a.lossi = t->lossi;
-        a.dQT = w.dQT; a.W3T = w.W3T; a.H1 = H1; a.H2 = H2; a.dZ2 = dZ2;
-        a.dZ2T = w.dZ2T; a.H1T = w.H1T; a.H2T = w.H2T;
+        a.dQ = w.dQ; a.W3T = w.W3T; a.H2 = H2; a.dZ2 = dZ2;
         a.ctr = t->ctr;
-        hipLaunchKernelGGL(td_dz_kernel, dim3(Bp / 64, std::max(H, G) / 64), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(td_dz_kernel, dim3((B + kTdRows - 1) / kTdRows, (G + kTdCols - 1) / kTdCols), dim3(256),
+                           0, st, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         ++n;
     }
-    // dZ1^T = (W2 dZ2^T) masked by the first ReLU; uses W2 before its update
-    e = launch_gemm<128, 64, 64, 2, 2>(st, w.W2, G, dZ2, G, H, B, G,
-                                          EpiMask{w.H1T, w.dZ1T, Bp, H, B});
+    // dZ1 = (dZ2 W2^T) masked by the first ReLU; uses W2 before its update
+    e = launch_gemm<128, 64, 64, 2, 2>(st, dZ2, G, w.W2, G, B, H, G, EpiMask{H1, dZ1, H, B, H});
     if (e != hipSuccess) return e;
     ++n;
     // the three weight-gradient products, K-split partials each, in one launch:
@@ -1162,18 +1403,18 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
     {
         GemmArgs g2, g3, g1;
         unsigned int n2 = 0, n3 = 0, n1 = 0;
-        const bool narrow1 = Dx == 32;
-        bool ok = gemm_args<128, 128, 64>(w.H1T, Bp, w.dZ2T, Bp, H + 1, G, Bp, splits2, nullptr, 0, &g2, &n2);
-        ok = ok && gemm_args<128, 96, 64>(w.H2T, Bp, w.dQT, Bp, G + 1, 3 * Ap, Bp, splits, nullptr, 0, &g3, &n3);
-        ok = ok && (narrow1 ? gemm_args<128, 32, 64>(w.dZ1T, Bp, w.XT, Bp, H, Dx, Bp, splits, nullptr, 0,
-                                                     &g1, &n1)
-                            : gemm_args<128, 128, 64>(w.dZ1T, Bp, w.XT, Bp, H, Dx, Bp, splits, nullptr, 0,
-                                                      &g1, &n1));
+        const bool narrow1 = Dp == 32;
+        bool ok = gemm_args<128, 128, 64>(H1, H, dZ2, G, H, G, Bp, splits2, nullptr, 0, &g2, &n2);
+        ok = ok && gemm_args<128, 96, 64>(H2, G, w.dQ, 3 * Ap, G, 3 * Ap, Bp, splits, nullptr, 0, &g3, &n3);
+        ok = ok && (narrow1 ? gemm_args<128, 32, 64>(dZ1, H, X, Dp, H, Dp, Bp, splits, nullptr, 0, &g1, &n1)
+                            : gemm_args<128, 128, 64>(dZ1, H, X, Dp, H, Dp, Bp, splits, nullptr, 0, &g1, &n1));
         if (!ok) return hipErrorInvalidValue;
-        const EpiPartial e2{w.part2, H + 1, G}, e1{w.part1, H, Dx};
-        const EpiPartialOfThree e3{w.part3, G + 1, Ap};
-        constexpr size_t lds = gemm_lds_bytes<128, 128, 64, 2, 2>();
-        const dim3 grid(n2 + n3 + n1), block(kGemmThreads);
+        g2.batch = g3.batch = g1.batch = B;
+        const EpiSquare e2{w.part2, H, G};
+        const EpiOutput e3{w.part3, G, Ap};
+        const EpiFirst e1{w.part1, H, D, Dx};
+        constexpr size_t lds = gemm_tn_lds_bytes<128, 128>();
+        const dim3 grid(n2 + n3 + n1), block(kTnThreads);
         if (narrow1)
             hipLaunchKernelGGL(grad_products_kernel<true>, grid, block, lds, st, g2, e2, n2, g3, e3, n3, g1, e1);
         else

@@ -1110,3 +1110,43 @@ def test_output_gradient_keeps_fp32_in_mixed_precision(B):
     want = np.array([g[a == k].sum() for k in range(A)])
     bound = np.array([np.abs(g[a == k]).sum() for k in range(A)]) * batch * 2.0 ** -24
     assert (np.abs(pr.trainer.grads()[-A:] - want) <= bound).all()
+
+
+@pytest.mark.parametrize("D,H,H2,A,batch", [
+    (27, 64, 64, 5, 1),           # one row of the first slice
+    (31, 64, 64, 33, 63),         # last column of the first layer's tile the bias; a second block of actions
+    (32, 192, 192, 3, 65),        # the bias behind the padded states; one row of the second slice
+    (33, 64, 128, 32, 129),       # states beyond one tile; a row beyond the padding of 128
+    (27, 128, 192, 30, 257),
+    (64, 320, 320, 64, 191),      # widths that end inside a tile of 128
+    (27, 128, 128, 30, 1000),     # several splits, the last one ends inside a slice
+])
+def test_mixed_precision_gradients_over_ragged_batches(B, D, H, H2, A, batch):
+    """The weight gradients contract over the batch in slices of 64 rows of the batch-major activations
+    and errors; tolerances of the other mixed-precision cases."""
+    rows = synth.experiences(batch + 60, D, A, 0.05, seed=74, state_dtype="bf16")
+    pr = Pair(B, capacity=batch + 30, D=D, H=H, H2=H2 if H2 != H else 0, A=A, batch=batch, burn_in=1, seed=5,
+              dtype="bf16", appends=1, opt="sgd", lr=1e-3)
+    pr.append_only(synth.take(rows, 0, batch + 30))
+    for k in range(batch + 30, batch + 36):
+        assert pr.step(synth.take(rows, k, k + 1), compare=True) == 0
+
+
+@pytest.mark.parametrize("batch", [1, 65, 130])
+def test_mixed_precision_gradients_ignore_the_next_states_of_terminals(B, batch):
+    """The rows of S' lie behind those of S in the activations: where every experience is terminal, what
+    they hold, infinities included, changes no bit of the gradients."""
+    D, H, A = 27, 128, 6
+    rows = synth.experiences(batch + 1, D, A, 0.05, seed=75, state_dtype="bf16")
+    rows["term"][:] = 1
+    grads = []
+    for bits in (0x0000, 0x7F80):
+        rows["s_next"][:] = bits
+        ring = B.Replay(batch + 1, D, B.RP_BF16, burn_in=1, seed=3)
+        tr = B.Trainer(ring, H, A, batch, param_dtype=B.RP_BF16, opt=B.RP_SGD, appends_per_step=1, lr=1e-3,
+                       init_params=synth.init_params(D, H, A, 3))
+        args = [rows[k] for k in ("s", "s_next", "a", "r", "term")]
+        ring.append(*(x[:batch] for x in args))
+        assert tr.step(*(x[batch:] for x in args)) == 0
+        grads.append(tr.grads())
+    assert np.isfinite(grads[0]).all() and np.array_equal(grads[0], grads[1])
