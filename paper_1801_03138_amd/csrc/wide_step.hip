@@ -868,6 +868,30 @@ struct SkinnyBias {
     }
 };
 
+// out[m][n] = bf16(relu(acc + bias[n]))
+struct SkinnyRelu {
+    const float* bias;   // [N]
+    const float* bias_hi;
+    unsigned int m_split;
+    bf16_bits* out;      // [M x ldo]
+    unsigned int ldo;
+    __device__ __forceinline__ void store(unsigned int m, unsigned int n, float x) const {
+        x += (m >= m_split ? bias_hi : bias)[n];
+        out[(size_t)m * ldo + n] = bf16_bits_rne(x > 0.f ? x : 0.f);
+    }
+};
+
+// out[m][n] = bf16(acc) where mask[m][n] > 0, else 0  (both [M x ld])
+struct SkinnyMask {
+    const bf16_bits* mask;
+    bf16_bits* out;
+    unsigned int ld;
+    __device__ __forceinline__ void store(unsigned int m, unsigned int n, float x) const {
+        const size_t at = (size_t)m * ld + n;
+        out[at] = bits_to_float(mask[at]) > 0.f ? bf16_bits_rne(x) : (bf16_bits)0;
+    }
+};
+
 template <int NW, class Epi>
 __global__ __launch_bounds__(64 * NW) void skinny_nt_kernel(SkinnyArgs p, Epi epi) {
     __shared__ float red[NW * 16 * 64];
@@ -1231,11 +1255,26 @@ unsigned int square_splits_for(unsigned int Bp, unsigned int H, unsigned int G) 
     return s;
 }
 
+// A product with M x N outputs that has few tiles of 128 x 64: those leave most of the chip idle, each
+// a serial chain over the whole contraction, and the product in 32 x 32 tiles, K split over eight
+// wavefronts, is the faster one although it fetches its operands more often.  us per step, tiled
+// -> this (27 inputs, 30 actions), for the first layer's error: 8 tiles (batch 512, 128-1024) 48.2 ->
+// 41.7, 64 tiles (batch 512, 1024-1024) 61.3 -> 59.2, 128 tiles (batch 1024) 68.1 -> 73.3; for the second
+// layer: 64 tiles (batch 256, 1024-1024) 54.8 -> 51.3, 16 (batch 40, 1024-1024) 51.7 -> 44.9, K = 64
+// (batch 100, 64-64) 27.1 -> 25.9, 128 tiles (batch 512, 1024-1024) 59.4 -> 63.1.
+bool few_tiles(unsigned int M, unsigned int N) { return (size_t)((M + 127u) / 128u) * ((N + 63u) / 64u) <= 64u; }
+
 // H2 = relu(H1 W2 + b2) for `rows` rows; with hi, rows from m_split on take those weights and biases.
 hipError_t second_layer(hipStream_t st, const bf16_bits* H1, unsigned int rows, unsigned int H, unsigned int G,
                         const bf16_bits* W2T, const float* b2, bf16_bits* H2, const bf16_bits* hi, const float* b2_hi,
                         unsigned int m_split) {
     if (!hi) m_split = ~0u;
+    if (few_tiles(rows, G)) {
+        const SkinnyArgs a{H1, H, W2T, H, rows, G, H, hi ? hi : W2T, m_split};
+        hipLaunchKernelGGL((skinny_nt_kernel<8, SkinnyRelu>), dim3((rows + 31) / 32, G / 32), dim3(512), 0, st, a,
+                           SkinnyRelu{b2, b2_hi, m_split, H2, G});
+        return hipGetLastError();
+    }
     return launch_gemm<128, 128, 64, 2, 2>(st, H1, H, W2T, H, rows, G, H, EpiForward{b2, b2_hi, m_split, H2, G, rows, G},
                                            1, hi, m_split);
 }
@@ -1391,7 +1430,14 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
         ++n;
     }
     // dZ1 = (dZ2 W2^T) masked by the first ReLU; uses W2 before its update
-    e = launch_gemm<128, 64, 64, 2, 2>(st, dZ2, G, w.W2, G, B, H, G, EpiMask{H1, dZ1, H, B, H});
+    if (few_tiles(B, H)) {
+        const SkinnyArgs a{dZ2, G, w.W2, G, B, H, G, w.W2, ~0u};
+        hipLaunchKernelGGL((skinny_nt_kernel<8, SkinnyMask>), dim3((B + 31) / 32, H / 32), dim3(512), 0, st, a,
+                           SkinnyMask{H1, dZ1, H});
+        e = hipGetLastError();
+    } else {
+        e = launch_gemm<128, 64, 64, 2, 2>(st, dZ2, G, w.W2, G, B, H, G, EpiMask{H1, dZ1, H, B, H});
+    }
     if (e != hipSuccess) return e;
     ++n;
     // the three weight-gradient products, K-split partials each, in one launch:

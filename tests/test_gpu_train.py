@@ -1150,3 +1150,21 @@ def test_mixed_precision_gradients_ignore_the_next_states_of_terminals(B, batch)
         assert tr.step(*(x[batch:] for x in args)) == 0
         grads.append(tr.grads())
     assert np.isfinite(grads[0]).all() and np.array_equal(grads[0], grads[1])
+
+
+@pytest.mark.parametrize("H,H2,batch,target_sync", [
+    (512, 0, 512, 3),        # second layer 64 tiles of 128 x 64, the most that go in 32 x 32 tiles
+    (512, 0, 576, 0),        # 72 of them; the first layer's error 40
+    (512, 0, 1040, 0),       # the first layer's error 72
+    (64, 192, 37, 3),        # both networks in launches of their own, rows that end inside a tile
+])
+def test_mixed_precision_products_with_few_tiles(B, H, H2, batch, target_sync):
+    """Both sides of the rule that sends the second layer and the first layer's error to 32 x 32 tiles
+    with a split contraction; tolerances of the other mixed-precision cases."""
+    D, A = 27, 30
+    rows = synth.experiences(batch + 60, D, A, 0.05, seed=76, state_dtype="bf16")
+    pr = Pair(B, capacity=batch + 30, D=D, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=5, dtype="bf16",
+              appends=1, target_sync=target_sync, lr=1e-3)
+    pr.append_only(synth.take(rows, 0, batch + 30))
+    for k in range(batch + 30, batch + 34):
+        assert pr.step(synth.take(rows, k, k + 1), compare=True) == 0
