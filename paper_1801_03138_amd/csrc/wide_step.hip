@@ -315,31 +315,27 @@ __device__ __forceinline__ void gemm_nt_block(const GemmArgs& p, const Epi& epi,
 
     // loader: wavefront w moves row groups w*GA.. of A and w*GB.. of B; a lane's piece lands at
     // LDS position `lane` of the group, so the lane fetches the piece that belongs there
-    // A request's address is a wavefront-uniform base (the operand, advanced by the slice's
-    // column: scalar registers) plus a per-lane byte offset that never changes (one 32-bit
-    // register per request, at most a tile's rows away from row 0 of the operand, which must
-    // therefore stay below 4 GiB), and its LDS destination is uniform as well: issuing a request
-    // then costs two scalar instructions and the load itself, no vector arithmetic.
+    // A request's address is a wavefront-uniform base (the tile's first row of the operand, advanced
+    // by the slice's column: 64-bit, in scalar registers) plus a per-lane byte offset that never
+    // changes (one 32-bit register per request, at most a tile's rows long, however large the
+    // operand is), and its LDS destination is uniform as well: issuing a request then costs two
+    // scalar instructions and the load itself, no vector arithmetic.
     const unsigned int lr = lane / CPR, lc = lane % CPR;
     const unsigned int wave_u = __builtin_amdgcn_readfirstlane(wave);
     unsigned int a_off[GA], b_off[GB];
 #pragma unroll
     for (int u = 0; u < GA; ++u) {
         const unsigned int r = (wave * GA + u) * RPI + lr;
-        unsigned int gm = m0 + r;
-        gm = gm < p.M ? gm : p.M - 1;
-        a_off[u] = (gm * p.lda + (lc ^ swz(r)) * 8u) * 2u;
+        a_off[u] = (min(r, p.M - 1u - m0) * p.lda + (lc ^ swz(r)) * 8u) * 2u;
     }
 #pragma unroll
     for (int u = 0; u < GB; ++u) {
         const unsigned int r = (wave * GB + u) * RPI + lr;
-        unsigned int gn = n0 + r;
-        gn = gn < p.N ? gn : p.N - 1;
-        b_off[u] = (gn * p.ldb + (lc ^ swz(r)) * 8u) * 2u;
+        b_off[u] = (min(r, p.N - 1u - n0) * p.ldb + (lc ^ swz(r)) * 8u) * 2u;
     }
     typedef const __attribute__((address_space(1))) char* gchar;
-    const gchar a_base = (gchar)reinterpret_cast<const char*>(p.A);
-    const gchar b_base = (gchar)reinterpret_cast<const char*>(m0 >= p.m_split ? p.Bt_hi : p.Bt);
+    const gchar a_base = (gchar)reinterpret_cast<const char*>(p.A + (size_t)m0 * p.lda);
+    const gchar b_base = (gchar)reinterpret_cast<const char*>((m0 >= p.m_split ? p.Bt_hi : p.Bt) + (size_t)n0 * p.ldb);
     // request u (0 .. GA + GB - 1) of a slice: one wavefront-wide 16-byte-per-lane load into LDS
     constexpr int L = GA + GB;                              // loads per wavefront and slice
     auto fetch_one = [&](int u, unsigned int buf, unsigned int k0) {
