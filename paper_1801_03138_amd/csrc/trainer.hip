@@ -327,7 +327,7 @@ bool ws_layout(const train_config* c, WsLayout* L) {
     L->handoff = take(c->target_sync ? B * 8 : 0);
     L->ahead = take(c->target_sync ? 2 * B * 8 * 4 : 0);
     L->qn_ahead = take(c->target_sync ? 2 * B * L->Ap * 4 : 0);
-    const bool mixed = c->param_dtype == RP_BF16 && wide_step_shape(*c);
+    const bool mixed = c->param_dtype == RP_BF16;
     const size_t Bp = align_up(B, 128), Dx = align_up(D + 1, 32);
     L->Bp = (unsigned int)Bp;
     L->W1T = take(mixed ? H * L->Dp * 2 : 0);

@@ -295,7 +295,6 @@ hipError_t enqueue_mid_step(trainer* t, hipStream_t st, unsigned int* count);
 unsigned int mid_step_kernels(const trainer* t);   // launches per step, the append + gather kernel included
 // Mixed-precision step on MFMA (bf16 replay states and matrix operands).
 bool wide_step_supported(const train_config& cfg, const replay* rp_);
-bool wide_step_shape(const train_config& cfg);   // the part of that which the configuration decides (the workspace's size)
 unsigned int square_splits(unsigned int Bp, unsigned int H, unsigned int G);   // K splits of the dW2 product
 hipError_t wide_configure();                                    // once, at creation
 // bf16 operand copies from padded fp32 parameters (host): of the trained network, or of the target

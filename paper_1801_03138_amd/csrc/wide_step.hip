@@ -1289,19 +1289,12 @@ unsigned int square_splits(unsigned int Bp, unsigned int H, unsigned int G) { re
 
 // Two hidden layers of one width, or of two.  This step is the faster one at every size measured (27
 // inputs, 30 actions, one new experience a step, us per step layer by layer -> this: 64-256 at batch 8
-// 104 -> 31, at batch 63 157 -> 34; 128-1024 at batch 40 324 -> 45; with target network and dueling
-// head at batch 512 929 -> 56).  The smallest networks of two widths nevertheless keep the plain step
-// on batches below 64 (64-128 at batch 40: 107, where this one takes 31): the launches it reports
-// per step are part of what the tests of record hold it to.
-bool wide_step_shape(const train_config& cfg) {
-    const bool one_width = cfg.hidden2 == 0 || cfg.hidden2 == cfg.hidden;
-    return cfg.hidden % 64 == 0 && cfg.hidden2 % 64 == 0 &&
-           (one_width || cfg.batch >= 64 || (size_t)cfg.hidden * cfg.hidden2 > 64u * 128u);
-}
-
+// 104 -> 31, at batch 63 157 -> 34; 64-128 at batch 1 67 -> 24, at batch 40 107 -> 26; 128-1024 at batch
+// 40 324 -> 45; with target network and dueling head at batch 512 929 -> 56), so that the layer-by-layer
+// step is left to those who ask for it.
 bool wide_step_supported(const train_config& cfg, const replay* rp_) {
-    return cfg.param_dtype == RP_BF16 && rp_->cfg.state_dtype == RP_BF16 &&
-           rp_->cfg.layout == RP_PAIR && wide_step_shape(cfg);
+    return cfg.param_dtype == RP_BF16 && rp_->cfg.state_dtype == RP_BF16 && rp_->cfg.layout == RP_PAIR &&
+           cfg.hidden % 64 == 0 && cfg.hidden2 % 64 == 0;
 }
 
 // Allow the products' LDS sizes (once, at creation).

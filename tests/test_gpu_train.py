@@ -880,11 +880,10 @@ def test_two_hidden_widths_on_mfma(B, D, H, H2, A, batch, target_sync, dueling, 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_two_hidden_widths_layer_by_layer(B, dtype):
-    """The plain one-kernel-per-layer step takes two widths as well (fp32 behind RP_TRAIN_LAYERED;
-    in mixed precision it is the step for two different widths)."""
+    """The plain one-kernel-per-layer step, behind RP_TRAIN_LAYERED, takes two widths as well."""
     rows = synth.experiences(300, 27, 30, 0.05, seed=62, state_dtype=dtype)
     pr = Pair(B, capacity=256, D=27, H=64, H2=128, A=30, batch=40, burn_in=100, seed=3, dtype=dtype,
-              appends=2, layered=dtype == "f32", target_sync=5, dueling=True, lr=1e-3)
+              appends=2, layered=True, target_sync=5, dueling=True, lr=1e-3)
     assert pr.trainer.kernels_per_step() == 19
     for k in range(0, 300, 2):
         pr.step(synth.take(rows, k, k + 2), compare=(k % 30 == 0) or k >= 290)
@@ -1077,7 +1076,9 @@ def test_fp32_tile_edges(B, D, H, H2, A, batch, target_sync, dueling):
     (27, 128, 1024, 30, 512, 4, True, "adam"),      # ... both networks' rows in one launch
     (40, 64, 192, 40, 65, 0, False, "sgd"),         # a second block of 32 actions
     (9, 256, 64, 3, 64, 3, False, "adam"),          # second layer the narrower
-    (27, 64, 256, 30, 5, 3, True, "adam"),          # a batch below 64
+    (27, 64, 256, 30, 5, 3, True, "adam"),          # batches below 64
+    (27, 64, 128, 30, 40, 5, True, "adam"),
+    (27, 128, 64, 30, 63, 0, False, "adam"),
     (70, 320, 448, 70, 200, 3, True, "adam"),       # stripes of each layer beyond the other, wide states
 ])
 def test_two_hidden_widths_mixed_precision_on_mfma(B, D, H, H2, A, batch, target_sync, dueling, opt):
