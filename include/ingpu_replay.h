@@ -292,7 +292,7 @@ rp_status train_set_handoff_wait(trainer_t* tr, uint64_t ticks, int break_pairin
  * max_a Q_target(s', a) of its experience 0 from the table that the step before it filled
  * (*from_table = 1) or had it computed inside its own launch (0).  Synchronises. */
 rp_status train_get_target_source(trainer_t* tr, uint32_t* from_table);
-/* Number of GPU kernels one executed train step launches (graph nodes). */
+/* Number of GPU kernels one executed train step launches (in a recorded run of steps: the run's first). */
 rp_status train_kernels_per_step(trainer_t* tr, uint32_t* n);
 
 /*

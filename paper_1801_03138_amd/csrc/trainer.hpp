@@ -302,4 +302,5 @@ hipError_t wide_set_weights(trainer* t, const float* padded, bool target);
 // Enqueue the step's kernels after the append; `sample` = draw and gather the batch first
 // (otherwise X and the per-row fields have been filled by the caller).
 hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bool sample);
+unsigned int wide_step_kernels(const trainer* t);   // launches per step, the (append +) gather kernel included
 }  // namespace rp

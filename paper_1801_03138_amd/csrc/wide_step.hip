@@ -1332,6 +1332,13 @@ hipError_t wide_set_weights(trainer* t, const float* padded, bool target) {
     return e;
 }
 
+// Whether the rows of S' share the forward launches of those of S.
+static bool rows_in_one_launch(const trainer* t) { return !t->wt || t->B % 128 == 0; }
+
+// (gather, three forward products, TD errors, the first layer's error, the gradients, the update; what
+// train_create adds itself: the dueling head's update, a draw in a launch of its own)
+unsigned int wide_step_kernels(const trainer* t) { return rows_in_one_launch(t) ? 8u : 11u; }
+
 // Enqueue every kernel of one executed step after the append.
 hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bool sample) {
     // H, G: widths of the first and the second hidden layer
@@ -1349,9 +1356,9 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
     // With a frozen target network the rows of S' (B .. 2B-1) are multiplied by its weights: in
     // the same launch when tiles do not straddle row B, else in a launch of their own.
     const bool tgt = t->wt != nullptr;
+    const bool one_launch = rows_in_one_launch(t);
     const float *b1t = tgt ? t->wt + t->ob1 : nullptr, *b2t = tgt ? t->wt + t->ob2 : nullptr;
     const float* b3t = tgt ? t->wt + t->ob3 : nullptr;
-    const bool one_launch = !tgt || B % 128 == 0;
     const unsigned int rows = one_launch ? 2 * B : B;   // rows of the first forward launch
 
     // sample B slots and unpack into X = [S ; S']

@@ -1209,3 +1209,19 @@ def test_mixed_precision_operands_beyond_4_gib(B, H, H2, batch):
         assert (rows == rows[0]).all(), name
     for lo, hi in ((0, D * H + H), (D * H + H, D * H + H + H * H2 + H2), (D * H + H + H * H2 + H2, len(g))):
         assert_close(g[lo:hi], want[lo:hi], 2 * BF16_RTOL, "gradients of one layer")
+
+
+@pytest.mark.parametrize("appends,distinct", [(2, False), (2, True), (0, False), (0, True)])
+@pytest.mark.parametrize("dtype,H,H2,batch,layered,target_sync,dueling,A", [
+    ("bf16", 128, 0, 64, False, 0, False, 30), ("bf16", 128, 0, 130, False, 3, True, 30),
+    ("bf16", 64, 192, 128, False, 3, True, 40), ("bf16", 64, 128, 40, True, 3, True, 30),
+    ("f32", 64, 0, 32, False, 3, True, 40), ("f32", 128, 1024, 64, False, 3, True, 30),
+    ("f32", 320, 0, 64, False, 0, False, 30), ("f32", 64, 0, 32, True, 0, True, 30)])
+def test_launch_count_with_and_without_recorded_runs(B, dtype, H, H2, batch, layered, target_sync, dueling, A,
+                                                     appends, distinct):
+    """A trainer that records runs of steps counts the launches of a step as it records them; one that
+    does not gives the same number."""
+    counts = [Pair(B, capacity=300, D=27, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=1, dtype=dtype, appends=appends,
+                   layered=layered, target_sync=target_sync, dueling=dueling, distinct=distinct,
+                   use_graph=use_graph).trainer.kernels_per_step() for use_graph in (True, False)]
+    assert counts[0] == counts[1]
