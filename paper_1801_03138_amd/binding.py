@@ -113,11 +113,18 @@ def _check(status):
     return status
 
 
+# torch's own way to the current stream's pointer alone (building its stream object takes longer than
+# a small call's checks): not part of its public interface, so a version may lack it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_ptr(stream=None):
     if stream is not None:
         return stream.cuda_stream
-    # (the pointer alone: building torch's stream object takes longer than a small call's checks)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _raw_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_raw_device())
 
 
 # Addresses go to the library as plain integers, which ctypes takes for its pointer arguments; the

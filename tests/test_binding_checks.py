@@ -1,6 +1,9 @@
 """The Python binding refuses device arrays that do not fit what the kernels will read or write
 (the C interface carries no lengths), before anything is launched.  Runs without a GPU: the checks
 are plain functions over tensor metadata."""
+import importlib.util
+import types
+
 import numpy as np
 import pytest
 import torch
@@ -96,3 +99,15 @@ def test_host_arrays_are_checked_for_length():
         with pytest.raises(ValueError):
             B.check_host_experiences(_cfg(), n, *bad, "t")
     B.check_host_experiences(_cfg(layout=B.RP_CHAIN), n, ok[0], None, ok[2], ok[3], ok[4], "t")
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_torchs_private_calls(monkeypatch, missing):
+    """A torch that lacks the private calls for the current stream's pointer: the public one serves."""
+    monkeypatch.delattr(torch._C, missing, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    spec = importlib.util.spec_from_file_location("binding_of_another_torch", B.__file__)
+    other = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(other)
+    assert other._stream_ptr() == 1234
+    assert other._stream_ptr(types.SimpleNamespace(cuda_stream=5)) == 5
