@@ -298,10 +298,11 @@ __global__ __launch_bounds__(kThreads) void append_sample_gather_pair_kernel(App
 // one state of one sampled experience; s comes from the sampled slot, s' from the slot after
 // it.  MODE 0: uint8 -> float with every access coalesced: a wavefront reads 256 contiguous
 // bytes as one dword per lane and writes 1 KB as one float4 per lane, four times.  Bound by memory,
-// four fifths of it the writes; nothing is touched twice, and loads and stores marked so (non-temporal)
-// are the faster ones: 84x84x4 bytes, batch 256, 72 MB: 17.0 -> 16.2 us (stores alone 16.6; a plain
-// copy's rate would take 13.9).  Pieces of 2 KB take 19.5 us, of 7 KB 17.7.
-// Raw copies of 14,112 floats, batch 256: 16.3 -> 13.9 us, of 14,112 bf16 9.9 -> 8.9; batches of 64 the same.
+// four fifths of it the writes (84x84x4 bytes, batch 256, 72 MB: 16.9 us, a plain copy's rate would
+// take 13.9).  Loads and stores stay ordinary ones: marked non-temporal they gain where the gather runs
+// alone over a ring far larger than the caches (16.9 -> 16.2 us), but lose over rings of 100 MB (13.0 ->
+// 16.2), in small batches (64: 6.2 -> 7.1), and wherever a kernel reads the batch next (gather and
+// a pass over the batch 37.0 -> 38.3; 14,112 floats 26.9 -> 27.8; bf16, batch 32 9.2 -> 10.3).
 // MODE 1: raw 16-byte copies (float / bf16 states).  MODE 2: element-wise fallback for
 // shapes whose rows are not 16-byte multiples.
 // ---------------------------------------------------------------------------------------
@@ -345,7 +346,6 @@ __global__ __launch_bounds__(kThreads) void sample_gather_chain_kernel(
     const unsigned char* src = g.rows + q * g.row_bytes;
 
     if (MODE == 0) {
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
         // state_bytes is a multiple of 4 and output rows are 16-byte aligned
         const unsigned int wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
         const unsigned int base = chunk * 4096u + wave * 1024u + lane * 4u;
@@ -354,15 +354,15 @@ __global__ __launch_bounds__(kThreads) void sample_gather_chain_kernel(
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const unsigned int b0 = base + 256u * j;
-            w[j] = b0 < g.state_bytes ? __builtin_nontemporal_load(reinterpret_cast<const unsigned int*>(src + b0)) : 0u;
+            w[j] = b0 < g.state_bytes ? *reinterpret_cast<const unsigned int*>(src + b0) : 0u;
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const unsigned int b0 = base + 256u * j;
             if (b0 < g.state_bytes) {
-                const f32x4 f = {unit_from_u8(w[j] & 0xFFu), unit_from_u8((w[j] >> 8) & 0xFFu),
-                                 unit_from_u8((w[j] >> 16) & 0xFFu), unit_from_u8(w[j] >> 24)};
-                __builtin_nontemporal_store(f, reinterpret_cast<f32x4*>(dst + b0));
+                const float4 f = make_float4(unit_from_u8(w[j] & 0xFFu), unit_from_u8((w[j] >> 8) & 0xFFu),
+                                             unit_from_u8((w[j] >> 16) & 0xFFu), unit_from_u8(w[j] >> 24));
+                *reinterpret_cast<float4*>(dst + b0) = f;
             }
         }
         return;
@@ -372,8 +372,8 @@ __global__ __launch_bounds__(kThreads) void sample_gather_chain_kernel(
     const unsigned int byte0 = v * 16u;
     if (byte0 >= g.state_bytes) return;
     // the slot is padded to a multiple of 16 bytes, so this load stays inside it
-    const u32x4 val = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src) + v);
-    const unsigned int words[4] = {val[0], val[1], val[2], val[3]};
+    const uint4 val = reinterpret_cast<const uint4*>(src)[v];
+    const unsigned int words[4] = {val.x, val.y, val.z, val.w};
     const unsigned int valid_bytes = min(16u, g.state_bytes - byte0);
     constexpr unsigned int EPV = 16 / ELEM;  // elements per 16-byte vector
     const unsigned int e0 = byte0 / ELEM;
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(kThreads) void sample_gather_chain_kernel(
     } else if (ELEM == 2) {
         unsigned short* dst = static_cast<unsigned short*>(out) + o;
         if (MODE == 1 && valid_bytes == 16) {
-            __builtin_nontemporal_store(val, reinterpret_cast<u32x4*>(dst));
+            *reinterpret_cast<uint4*>(dst) = val;
         } else {
 #pragma unroll
             for (unsigned int j = 0; j < EPV; ++j)
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(kThreads) void sample_gather_chain_kernel(
     } else {
         unsigned int* dst = static_cast<unsigned int*>(out) + o;
         if (MODE == 1 && valid_bytes == 16) {
-            __builtin_nontemporal_store(val, reinterpret_cast<u32x4*>(dst));
+            *reinterpret_cast<uint4*>(dst) = val;
         } else {
 #pragma unroll
             for (unsigned int j = 0; j < EPV; ++j)
