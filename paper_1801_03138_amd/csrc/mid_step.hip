@@ -221,8 +221,10 @@ hipError_t launch_mm(hipStream_t st, const MmArgs& a, unsigned int M_total, unsi
                 hipLaunchKernelGGL((mm_f32_tiles_kernel<NT, EPI, 8, 4>), grid, dim3(512), 0, st, p, tiles_m, tiles_n, c);
             else if (groups >= 16)
                 hipLaunchKernelGGL((mm_f32_tiles_kernel<NT, EPI, 4, 4>), grid, dim3(256), 0, st, p, tiles_m, tiles_n, c);
-            else
+            else if (groups > 4)
                 hipLaunchKernelGGL((mm_f32_tiles_kernel<NT, EPI, 4, 2>), grid, dim3(256), 0, st, p, tiles_m, tiles_n, c);
+            else
+                hipLaunchKernelGGL((mm_f32_tiles_kernel<NT, EPI, 4, 1>), grid, dim3(256), 0, st, p, tiles_m, tiles_n, c);
             return hipGetLastError();
         }
     }

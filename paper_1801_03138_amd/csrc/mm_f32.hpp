@@ -142,9 +142,12 @@ __device__ __forceinline__ unsigned int block_to_tile(unsigned int block, unsign
 // instruction about every sixteen cycles (a 16-byte one takes as long as it needs for 1 KB), so
 // what counts is MFMAs per load: here 16 MFMAs on six loads (two of A; four of B, two columns wide)
 // or four (NT: 16 bytes along K for both), where a 16 x 16 quarter per wavefront takes 4 on five.
-// P groups are in flight at a time; groups past the end re-read the last one and count as zero.
+// P groups are in flight at a time; groups past the end re-read the last one and count as zero, so P is no
+// more than a wavefront has (a contraction of up to 64: one each; with two, half of the loads were
+// repeats, and the steps below took 23.8, 27.2 and 43.6 us).
 // Quarters -> this, us per launch: 1024 x 512 x 512 14.3 -> 11.0 (of which 3.4 are the MFMAs at peak),
-// NT 512 x 512 x 512 10.9 -> 8.5; a contraction of 64, all latency, 5.5 -> 5.7.
+// NT 512 x 512 x 512 10.9 -> 8.5; us per step where the contractions are 32 and 64: 27-256-64-30 at batch
+// 128 22.7 -> 22.0, 27-1024-64-30 at batch 128 26.1 -> 25.4, at batch 600 46.9 -> 39.6.
 constexpr unsigned int kMmTile = 32, kMmTileLd = kMmTile + 4;
 template <bool NT, int EPI, int W, int P>
 __device__ __forceinline__ void mm_f32_tile32(const MmArgs& p, unsigned int bx, unsigned int by,

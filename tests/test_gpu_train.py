@@ -1058,6 +1058,8 @@ def test_paper_shaped_free_running_drift(B, capsys):
     # products in 32 x 32 tiles: K of 2, 4, 12, 18 and 36 groups of 16 over four and eight wavefronts,
     # rows that end inside a tile, two parts, the dZ1 product in tiles of its own
     (40, 512, 576, 40, 520, 2, False), (27, 192, 1024, 30, 150, 0, True), (33, 256, 320, 5, 401, 3, False),
+    # ... of 2 groups, of 4 and of 6, in all three products
+    (27, 1024, 64, 30, 70, 0, False), (60, 256, 64, 8, 33, 3, True), (90, 512, 64, 5, 45, 0, False),
 ])
 def test_fp32_tile_edges(B, D, H, H2, A, batch, target_sync, dueling):
     """The fp32 steps' tiled kernels where a batch, a contraction or a launch ends inside a tile or a
