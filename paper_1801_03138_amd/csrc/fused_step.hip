@@ -1098,15 +1098,19 @@ __global__ __launch_bounds__(kTileThreads) void fused_weights_ahead_kernel(WArgs
 }
 
 // The variants of the two kernels above: T steps in flight per wavefront cover a batch of 32 T rows
-// in one go; beyond 256 rows eight are kept in flight (four would leave the loads' latency exposed,
-// sixteen gained nothing).
+// in one go, and steps past the batch are loads for nothing (27-1024-1024-30, us per step with four steps
+// in flight and with two: batch 8 38.0, 34.8, batch 32 39.2, 36.1, batch 64 44.7, 42.8; 27-256-256-30 at
+// batch 32 17.4, 16.9; one step up to batch 32 is no faster than two).  Beyond 256 rows eight are kept in
+// flight (four would leave the loads' latency exposed, sixteen gained nothing).
 typedef void (*WeightsKernel)(WArgs);
 typedef void (*WeightsAheadKernel)(WArgs, MmArgs, unsigned int, unsigned int, AppendGatherArgs, unsigned int);
 WeightsKernel weights_kernel(bool fold, unsigned int B) {
+    if (B <= 64u) return fold ? fused_weights_kernel<true, 2> : fused_weights_kernel<false, 2>;
     if (B <= 128u) return fold ? fused_weights_kernel<true, 4> : fused_weights_kernel<false, 4>;
     return fold ? fused_weights_kernel<true, 8> : fused_weights_kernel<false, 8>;
 }
 WeightsAheadKernel weights_ahead_kernel(bool fold, unsigned int B) {
+    if (B <= 64u) return fold ? fused_weights_ahead_kernel<true, 2> : fused_weights_ahead_kernel<false, 2>;
     if (B <= 128u) return fold ? fused_weights_ahead_kernel<true, 4> : fused_weights_ahead_kernel<false, 4>;
     return fold ? fused_weights_ahead_kernel<true, 8> : fused_weights_ahead_kernel<false, 8>;
 }

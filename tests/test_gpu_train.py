@@ -1053,6 +1053,7 @@ def test_paper_shaped_free_running_drift(B, capsys):
 @pytest.mark.parametrize("D,H,H2,A,batch,target_sync,dueling", [
     # weight-gradient tiles: the batch's steps of four rows over eight wavefronts, T in flight
     (27, 64, 0, 8, 1, 0, False), (27, 64, 0, 8, 3, 0, True), (27, 64, 0, 8, 33, 0, False),
+    (27, 64, 0, 8, 64, 0, True), (27, 64, 0, 30, 65, 0, False),
     (27, 64, 0, 30, 127, 0, True), (27, 64, 0, 30, 129, 0, False), (27, 64, 0, 30, 255, 3, True),
     (27, 64, 0, 30, 257, 0, False), (27, 64, 0, 30, 514, 0, True),
     # products in 32 x 32 tiles: K of 2, 4, 12, 18 and 36 groups of 16 over four and eight wavefronts,
