@@ -1098,22 +1098,45 @@ def test_two_hidden_widths_mixed_precision_on_mfma(B, D, H, H2, A, batch, target
 
 
 def test_output_gradient_keeps_fp32_in_mixed_precision(B):
-    """The output layer's gradient in mixed precision contracts bf16 activations with dL/dQ in fp32
-    (three bf16 parts that add up to it): against the same sum in fp64 over the GPU's own dL/dQ and the
-    oracle's activations it is as good as fp32 addition in any order, n 2^-24 of the sum of magnitudes."""
-    D, H, H2, A, batch = 27, 64, 128, 5, 96
-    rows = synth.experiences(300, D, A, 0.05, seed=73, state_dtype="bf16")
-    pr = Pair(B, capacity=256, D=D, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=5, dtype="bf16", appends=1,
-              loss="mse", opt="sgd", lr=1e-3)
-    pr.append_only(synth.take(rows, 0, 256))
-    assert pr.trainer.step(*(synth.take(rows, 256, 257)[k] for k in ("s", "s_next", "a", "r", "term"))) == 0
-    last = pr.trainer.last()
-    pr.ref_ring.append(*(synth.take(rows, 256, 257)[k] for k in ("s", "s_next", "a", "r", "term")))
-    _, _, a, _, _ = pr.ref_ring.gather(last["idx"])
-    g = -(last["delta"] / np.float32(batch)).astype(np.float64)   # dL/dQ(s_i, a_i), as the GPU rounds it
-    want = np.array([g[a == k].sum() for k in range(A)])
-    bound = np.array([np.abs(g[a == k]).sum() for k in range(A)]) * batch * 2.0 ** -24
-    assert (np.abs(pr.trainer.grads()[-A:] - want) <= bound).all()
+    """The output layer's gradient in mixed precision contracts bf16 activations with dL/dQ in fp32: three
+    bf16 parts that add up to it exactly.  Weights and states are small whole numbers here, so that the
+    activations are exact in bf16, and every experience of the batch has an action of its own, so
+    that an entry of dW3 (and of db3) is one product: the sum of three exact ones, two roundings at
+    most.  Two parts, without the last one, miss that bound by far in either array."""
+    D, H, H2, A = 27, 64, 128, 64
+    batch, rng = A, np.random.default_rng(73)
+    W1 = rng.integers(-1, 2, (D, H)).astype(np.float32)
+    W2 = np.zeros((H, H2), np.float32)
+    for k in range(H2):
+        W2[rng.choice(H, 3, replace=False), k] = rng.choice([-1, 1], 3)
+    W3 = rng.standard_normal((H2, A)).astype(np.float32)
+    p0 = np.concatenate([W1.ravel(), np.zeros(H), W2.ravel(), np.zeros(H2), W3.ravel(), np.zeros(A)]).astype(np.float32)
+    s = rng.integers(0, 4, (batch, D)).astype(np.float32)
+    h1 = np.maximum(s @ W1, 0)
+    h2 = np.maximum(h1 @ W2, 0).astype(np.float64)
+    assert h1.max() <= 256 and h2.max() <= 256          # whole numbers that bf16 holds
+    rows = synth.experiences(batch, D, A, 0.05, seed=73, state_dtype="bf16")
+    rows["s"], rows["a"] = synth.f32_to_bf16_bits(s), rng.permutation(A).astype(np.int32)
+    ring = B.Replay(64, D, B.RP_BF16, seed=5)
+    tr = B.Trainer(ring, H, A, batch, param_dtype=B.RP_BF16, loss=B.RP_MSE, opt=B.RP_SGD, appends_per_step=0, lr=1e-3,
+                   init_params=p0, hidden2=H2)
+    d = {k: torch.from_numpy(v.view(np.int16) if v.dtype == np.uint16 else v).cuda() for k, v in rows.items()}
+    assert tr.step_batch(d["s"], d["s_next"], d["a"], d["r"], d["term"]) == 0
+    g = -tr.last()["delta"] / np.float32(batch)         # dL/dQ(s_i, a_i); the batch is a power of two: exact
+    hi = synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(g))
+    two_parts = hi + synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(g - hi))
+
+    def gradients(x):
+        dW3, db3 = np.zeros((H2, A)), np.zeros(A)
+        dW3[:, rows["a"]] = h2.T * x.astype(np.float64)
+        db3[rows["a"]] = x
+        return dW3.ravel(), db3
+
+    got = tr.grads()[-(H2 * A + A):]
+    for x, want, without in zip((got[:H2 * A], got[H2 * A:]), gradients(g), gradients(two_parts)):
+        bound = 2.0 ** -23 * np.abs(want)
+        assert (np.abs(x - want) <= bound).all()
+        assert (np.abs(without - want) > 8 * bound).any()
 
 
 @pytest.mark.parametrize("D,H,H2,A,batch", [
