@@ -267,13 +267,17 @@ def test_small_net_every_loss_and_optimizer(B, loss, opt, layered):
 
 @pytest.mark.parametrize("layered", [False, True])
 def test_graph_and_direct_launch_agree_bitwise(B, layered):
+    """200 steps in one call, which a trainer that records runs makes in those and one that does not
+    kernel by kernel."""
     rows = synth.experiences(200, 27, 30, 0.05, seed=2)
     outs = []
     for use_graph in (True, False):
         pr = Pair(B, capacity=150, D=27, H=64, A=30, batch=64, burn_in=10, seed=3,
                   use_graph=use_graph, layered=layered)
-        for k in range(200):
-            pr.step(synth.take(rows, k, k + 1), compare=False)
+        assert pr.trainer.steps(200, *(rows[k] for k in synth.FIELDS)) == 191
+        for lo in (0, 100):
+            part = synth.take(rows, lo, lo + 100)
+            pr.ref_ring.append(*(part[k] for k in synth.FIELDS))
         outs.append((pr.trainer.params(), pr.trainer.last()["loss"], pr.trainer.opt_state()))
         assert pr.gpu_ring.state() == pr.ref_ring.state()
     assert np.array_equal(outs[0][0], outs[1][0]) and outs[0][1] == outs[1][1]
@@ -351,17 +355,19 @@ def test_many_steps_in_flight(B, dtype, layered, device_src):
 @pytest.mark.parametrize("dtype,H,H2,layered,device_src", [
     ("f32", 64, 0, False, True), ("f32", 64, 0, False, False), ("bf16", 128, 0, False, True),
     ("f32", 64, 0, True, True), ("f32", 320, 0, False, True), ("f32", 320, 0, False, False),
-    ("f32", 128, 1024, False, True), ("f32", 128, 1024, False, False)])
+    ("f32", 128, 1024, False, True), ("f32", 128, 1024, False, False),
+    ("bf16", 128, 1024, False, True), ("bf16", 192, 64, False, False)])
 def test_steps_in_flight_equal_steps_synchronised_one_by_one(B, dtype, H, H2, layered, device_src):
     """The argument block of the kernel that consumes a step's new experiences is rewritten in
     the recorded graph before every launch, while earlier launches of the same graph may still be
     running.  2,000 steps queued without any synchronisation (32 or 8 steps per graph launch) must
     leave exactly the state that the same 2,000 steps leave when the device is synchronised after
-    every single step (one step per graph launch): ring, weights, moments, counters and the last
+    every single step (launched kernel by kernel): ring, weights, moments, counters and the last
     step's sampled slots, bit for bit.  Two-kernel step (device and host arrays), MFMA step,
     layered step, fp32 MFMA step (whose recorded runs gather a step's batch in the launch of
-    the step before it; device and host arrays), and the paper's network with a dueling head on
-    that step (where the same launch also holds the product dZ1)."""
+    the step before it; device and host arrays), the paper's network with a dueling head on
+    that step (where the same launch also holds the product dZ1), and two hidden widths with a
+    dueling head in mixed precision."""
     # (the queued side makes the 2,000 steps in calls of these lengths, so that recorded runs of
     # every length, single steps and the hand-over from one run to the next all occur)
     n_steps, per = 2000, 2
@@ -919,7 +925,7 @@ def test_paper_network_step_on_a_given_batch_and_without_appends(B):
         assert_close(tr.grads(), ref.grads, 10 * pr.rtol, "gradients")
 
 
-def _random_configs(n, seed):
+def _random_configs(n, seed, two_widths_bf16=False):
     """Seeded draw of step configurations: every kind of step (two-kernel fp32, MFMA mixed
     precision, layered), shapes on and off the tile sizes, both losses and optimizers, with and
     without the frozen target network, the dueling head and batches without duplicates."""
@@ -930,7 +936,11 @@ def _random_configs(n, seed):
         H = int(rng.choice([64, 128, 192, 256, 320]))
         if dtype == "bf16":
             H = int(rng.choice([64, 128, 192]))
+        if two_widths_bf16:
+            dtype, H = "bf16", int(rng.choice([64, 128, 192]))
         H2 = int(rng.choice([0, 0, 64, 128, 320])) if dtype == "f32" else 0
+        if two_widths_bf16:
+            H2 = int(rng.choice([w for w in (64, 128, 320) if w != H]))
         D = int(rng.integers(1, 70))
         A = int(rng.integers(1, 70))
         batch = int(rng.choice([1, 2, 5, 31, 64, 100, 128, 129, 257]))
@@ -945,25 +955,35 @@ def _random_configs(n, seed):
     return out
 
 
-@pytest.mark.parametrize("c", _random_configs(64, 20261127), ids=lambda c: "-".join(
+@pytest.mark.parametrize("c", _random_configs(64, 20261127) + _random_configs(16, 20261204, True), ids=lambda c: "-".join(
     "%s" % c[k] for k in ("dtype", "D", "H", "H2", "A", "batch", "appends", "opt", "loss")))
 def test_random_configurations(B, c):
     """Twelve teacher-forced steps of a randomly drawn configuration, after a prefill that wraps
-    the ring when the capacity is small."""
-    n_pre = c["capacity"] + 57
-    rows = synth.experiences(n_pre + 12 * max(1, c["appends"]), c["D"], c["A"], 0.05, seed=c["seed"],
-                             state_dtype=c["dtype"])
-    pr = Pair(B, capacity=c["capacity"], D=c["D"], H=c["H"], H2=c["H2"], A=c["A"], batch=c["batch"], burn_in=40,
-              seed=c["seed"], dtype=c["dtype"], loss=c["loss"], opt=c["opt"], lr=1e-3,
-              appends=c["appends"], layered=c["layered"], target_sync=c["target_sync"],
-              distinct=c["distinct"], dueling=c["dueling"])
-    for lo in range(0, n_pre, 200):
-        pr.append_only(synth.take(rows, lo, min(lo + 200, n_pre)))
-    at = n_pre
-    for k in range(12):
-        part = synth.take(rows, at, at + c["appends"])
-        at += c["appends"]
-        assert pr.step(part, compare=True) == 0
+    the ring when the capacity is small; and the same twelve made by one call on a second trainer, in
+    recorded runs, which must leave the same bits behind."""
+    n_pre, steps, per = c["capacity"] + 57, 12, c["appends"]
+    rows = synth.experiences(n_pre + steps * max(1, per), c["D"], c["A"], 0.05, seed=c["seed"], state_dtype=c["dtype"])
+    ends = []
+    for one_call in (False, True):
+        pr = Pair(B, capacity=c["capacity"], D=c["D"], H=c["H"], H2=c["H2"], A=c["A"], batch=c["batch"], burn_in=40,
+                  seed=c["seed"], dtype=c["dtype"], loss=c["loss"], opt=c["opt"], lr=1e-3,
+                  appends=per, layered=c["layered"], target_sync=c["target_sync"],
+                  distinct=c["distinct"], dueling=c["dueling"])
+        for lo in range(0, n_pre, 200):
+            pr.append_only(synth.take(rows, lo, min(lo + 200, n_pre)))
+        if one_call:
+            new = synth.take(rows, n_pre, n_pre + steps * per)
+            assert pr.trainer.steps(steps, *(new[k] for k in synth.FIELDS)) == steps
+        else:
+            for at in range(n_pre, n_pre + steps * per, per) if per else [n_pre] * steps:
+                assert pr.step(synth.take(rows, at, at + per), compare=True) == 0
+        tr = pr.trainer
+        last, (m, v, t, step) = tr.last(), tr.opt_state()
+        ends.append([tr.params(), tr.grads(), tr.target(), m, v, last["Q"], last["Qn"], last["y"], last["idx"],
+                     np.array([t, step]), np.array([last["loss"]]), np.array(pr.gpu_ring.state()),
+                     *pr.gpu_ring.read_rows(0, c["capacity"])])
+    for k, (a, b) in enumerate(zip(*ends)):
+        assert np.array_equal(a, b), k
 
 
 def test_paper_network_free_running_through_recorded_runs(B, capsys):
