@@ -1,5 +1,6 @@
 // The Q-learning train step on a device-resident replay: sample + gather, MLP forward on
-// s and s', TD target / selection / loss, backward, optimizer, replayed as one HIP graph.
+// s and s', TD target / selection / loss, backward, optimizer; calls of several steps replay
+// recorded HIP graphs of up to 32 steps each.
 //
 // Paper: Integration with Reinforcement Learning Algorithm (the step takes no inputs from
 // the host; Q(s,a) is entry i*A + a_i of the flattened network output) and Deep Q-Network
@@ -217,7 +218,8 @@ __global__ __launch_bounds__(kThreads) void optimizer_kernel(
 }
 
 // A caller-provided batch (structure of arrays, B rows) into the step's input buffers:
-// X = [S ; S'] with row pitch Dp, the per-row fields, the batch position as "slot".  E = element type of a state (4 or 2 bytes).
+// X = [S ; S'] with row pitch Dp, the per-row fields, the batch position as "slot".
+// E = element type of a state (4 or 2 bytes).
 template <typename E>
 __global__ __launch_bounds__(kThreads) void load_batch_kernel(
     unsigned int B, unsigned int D, unsigned int Dp, const E* __restrict__ s,
@@ -1086,10 +1088,14 @@ rp_status train_step(trainer_t* t, const void* s, const void* s_next, const int3
             RP_CHECK_HIP(rp::launch_append(rpl->geom, rp::RingPos{rpl->head, rpl->size, rpl->total}, n,
                                            src.s, src.s_next, src.a, src.r, src.term, st));
     } else {
-        // One step on its own is launched kernel by kernel, with recorded runs or without: the host
-        // takes longer to replace an argument block in a graph of so few nodes and to launch it
-        // than to launch its kernels (us per call at batch 32, graph -> kernels: two-kernel step
-        // 22.8 -> 16.6, six-kernel step of the paper's network 36.3 -> 32.9).
+        // One step on its own is launched kernel by kernel, with recorded runs or without, for every
+        // kind of step: the host takes longer to replace an argument block in a graph of one step and
+        // to launch it than to launch its kernels (us per call among others, graph -> kernels, batch
+        // 32: two-kernel step of 256 units 30.2 -> 16.7, seven-kernel step of 320 33.7 -> 29.3, mixed
+        // precision 27-128-128-30 40.3 -> 30.7, the same of 64 units with target network, dueling head
+        // and a draw without duplicates, twelve kernels, 56.5 -> 48.5, layer by layer, fifteen, 88.5 ->
+        // 82.7, with target network and head, nineteen, 114 -> 110; waited for after each call 46.4 ->
+        // 30.0, 54.4 -> 42.9, 60.6 -> 51.9, 80.2 -> 63.2, 110 -> 101, 134 -> 128).
         RP_CHECK_HIP(rp::enqueue_append_and_step(t, src, st, nullptr));
     }
     if (host_src) RP_CHECK_HIP(rp::commit_host_slots(t, 1, st));

@@ -120,13 +120,13 @@ struct EpiForward {
 };
 
 // out[m][n] = bf16(acc) where mask[m][n] > 0, else 0  (the ReLU derivative; both [M x ld]).
-// Columns from N up to the next multiple of 8 are written as zeros.
 struct EpiMask {
     const bf16_bits* mask;
     bf16_bits* out;
     unsigned int ld;
     unsigned int M, N;
     __device__ __forceinline__ float pre(unsigned int, unsigned int, float x) const { return x; }
+    // eight consecutive columns n..n+7 of row m (N is a multiple of 8)
     __device__ __forceinline__ void store(unsigned int m, unsigned int n, const u32x4& v) const {
         if (m >= M || n >= N) return;
         const size_t at = (size_t)m * ld + n;
@@ -136,8 +136,8 @@ struct EpiMask {
         for (int e = 0; e < 4; ++e) {
             // a bf16 is positive when it is non-zero with the sign bit clear (NaN counts as not)
             const unsigned int lo = k[e] & 0xFFFFu, hi = k[e] >> 16;
-            const bool lo_on = lo != 0u && lo <= 0x7F80u && n + 2u * e < N;
-            const bool hi_on = hi != 0u && hi <= 0x7F80u && n + 2u * e + 1u < N;
+            const bool lo_on = lo != 0u && lo <= 0x7F80u;
+            const bool hi_on = hi != 0u && hi <= 0x7F80u;
             o[e] = (lo_on ? v[e] & 0xFFFFu : 0u) | (hi_on ? v[e] & 0xFFFF0000u : 0u);
         }
         *reinterpret_cast<u32x4*>(out + at) = o;
@@ -756,7 +756,7 @@ __global__ __launch_bounds__(kTnThreads) void grad_products_kernel(GemmArgs p2, 
     }
 }
 
-// The dynamic LDS size of each kernel (up to 64 KB) is announced per kernel before the first
+// The dynamic LDS size of each kernel (up to 80 KB, the gradients' launch) is announced per kernel before the first
 // launch (done at trainer creation, outside any stream capture).
 template <int BM, int BN, int BK, int WGM, int WGN, class Epi, int NSTAGE = 2>
 hipError_t configure_gemm() {
