@@ -35,7 +35,8 @@ GATHER_BATCHES = [32, 128, 512, 2048, 8192, 65536]
 # HBM bytes per launch of sample_gather_pair_kernel<4, 2, 0> at batch 65,536 from rocprofv3 PMC runs
 # (FETCH_SIZE 8,186.3 KiB x 2.000 + WRITE_SIZE 14,656.5 KiB x 1.000, the factors being what the
 # same counters read for the 256 MiB plain copy of the copy_calibration leg); the runs and the
-# table are in profiles/gather_kernels_hbm_traffic_pmc.txt.  Set to None when that kernel changes.
+# table are in profiles/gather_kernels_hbm_traffic_pmc.txt.  These constants are set to None, or taken
+# anew, when a kernel that they were counted on changes.
 GATHER_65536_HBM_BYTES = (8186.3 * 2.000 + 14656.5 * 1.000) * 1024
 GATHER_8M_65536_HBM_BYTES = (8215.9 * 2.000 + 14657.0 * 1.000) * 1024
 GATHER_KERNEL = "sample_gather_pair_kernel<4, 2, 0>"
@@ -44,7 +45,7 @@ LARGE_256_HBM_BYTES = (7154.9 * 2.000 + 56461.1 * 1.000) * 1024
 # and for append_pair_bulk_kernel<unsigned int> at 65,536 rows (profiles/append_bulk_kernel_hbm_traffic_pmc.txt)
 APPEND_65536_HBM_BYTES = (7314.5 * 2.000 + 16384.0 * 1.000) * 1024
 # and summed over the seven kernels of one wide step of a recorded run (profiles/wide_step_kernels_hbm_traffic_pmc.txt)
-WIDE_STEP_HBM_BYTES = (90886.2 * 2.000 + 120684.0 * 1.000) * 1024
+WIDE_STEP_HBM_BYTES = (85891.6 * 2.000 + 94051.8 * 1.000) * 1024
 
 
 def log(*a):
@@ -615,7 +616,7 @@ def main():
         "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": "paper-shaped: capacity 1,000,000, state 27 fp32, 30 actions, "
                                "burn-in 50,000, 1 append/step from HBM, batch 128, MLP 27-256-256-30, "
-                               "Huber, Adam 1e-4, one HIP graph per step",
+                               "Huber, Adam 1e-4, calls of many steps in recorded HIP graphs of up to 32",
                    "kernels_per_step": p["kernels_per_step"]},
         "roofline": roofline, "rooflines": rooflines, "cpu_baseline": cpu,
         # context only: another machine, another framework, the paper's own dueling network
