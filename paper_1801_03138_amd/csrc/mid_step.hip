@@ -11,6 +11,8 @@
 //
 // Paper: Deep Q-Network Model (the network and the update equation), Integration with
 // Reinforcement Learning Algorithm (train step with no host inputs).
+#include <algorithm>
+
 #include "mm_f32.hpp"
 #include "replay_kernels.hpp"
 #include "trainer.hpp"
@@ -31,6 +33,11 @@ struct CopyArgs {
     f32x4* dst;
     unsigned int n4;
 };
+
+// Workgroups that copy all of it.
+__host__ __device__ __forceinline__ unsigned int copy_blocks(const CopyArgs& c) {
+    return (c.n4 + 4u * kMmThreads - 1u) / (4u * kMmThreads);
+}
 
 __device__ __forceinline__ void copy_block(const CopyArgs& c, unsigned int block) {
     const unsigned int i0 = block * 4u * kMmThreads + threadIdx.x;
@@ -64,12 +71,13 @@ template <bool NT, int EPI, int W, int P>
 __global__ __launch_bounds__(64 * W) void mm_f32_tiles_kernel(MmArgs p, unsigned int tiles_m, unsigned int tiles_n,
                                                               CopyArgs c) {
     __shared__ __attribute__((aligned(16))) float part[W][kMmTile][kMmTileLd];
-    const unsigned int count = tiles_m * tiles_n;
-    if (blockIdx.x >= count) {
-        if (threadIdx.x < kMmThreads) copy_block(c, blockIdx.x - count);
+    // (the launch is one row of workgroups, or several where one would have 2^32 threads or more)
+    const unsigned int count = tiles_m * tiles_n, block = blockIdx.y * gridDim.x + blockIdx.x;
+    if (block >= count) {
+        if (block - count < copy_blocks(c) && threadIdx.x < kMmThreads) copy_block(c, block - count);
         return;
     }
-    const unsigned int tile = block_to_tile(blockIdx.x, count);
+    const unsigned int tile = block_to_tile(block, count);
     if (tiles_m >= tiles_n) mm_f32_tile32<NT, EPI, W, P>(p, tile % tiles_n, tile / tiles_n, part);
     else mm_f32_tile32<NT, EPI, W, P>(p, tile / tiles_m, tile % tiles_m, part);
 }
@@ -177,7 +185,7 @@ hipError_t launch_two_layers(hipStream_t st, const MmArgs& l1, const MmArgs& l2,
     unsigned int cb = 0;
     if (copy) {
         c = *copy;
-        cb = (c.n4 + 4u * kMmThreads - 1u) / (4u * kMmThreads);
+        cb = copy_blocks(c);
     }
     const dim3 grid(nx, tiles_y + (cb + nx - 1u) / nx, 1), block(kMmThreads);
     const unsigned int H = l1.N, Dp = l1.K;
@@ -201,6 +209,9 @@ unsigned int want_kgroups(unsigned int M, unsigned int N, unsigned int K) {
     return z;
 }
 
+// Workgroups in a row of a launch of tiles: a multiple of the eight XCDs, and 2^31 threads at most.
+constexpr unsigned int kMmRowBlocks = 1u << 22;
+
 // kgroups > 1 (MM_PARTIAL only): a.K is the whole contraction, split over that many workgroups per tile.
 // copy (kgroups 1 only): the launch also copies copy->n4 16-byte pieces, in workgroups of its own.
 template <bool NT, int EPI>
@@ -215,7 +226,8 @@ hipError_t launch_mm(hipStream_t st, const MmArgs& a, unsigned int M_total, unsi
             p.tiles_per_part = (a.rows_per_part + kMmTile - 1u) / kMmTile;
             const unsigned int tiles_m = p.tiles_per_part * a.parts, tiles_n = a.N / kMmTile;
             const CopyArgs c = copy ? *copy : CopyArgs{nullptr, nullptr, 0u};
-            const dim3 grid(tiles_m * tiles_n + (c.n4 + 4u * kMmThreads - 1u) / (4u * kMmThreads));
+            const unsigned int blocks = tiles_m * tiles_n + copy_blocks(c);
+            const dim3 grid(std::min(blocks, kMmRowBlocks), (blocks + kMmRowBlocks - 1u) / kMmRowBlocks);
             const unsigned int groups = p.K >> 4;
             if (groups >= 32)
                 hipLaunchKernelGGL((mm_f32_tiles_kernel<NT, EPI, 8, 4>), grid, dim3(512), 0, st, p, tiles_m, tiles_n, c);
@@ -233,7 +245,7 @@ hipError_t launch_mm(hipStream_t st, const MmArgs& a, unsigned int M_total, unsi
     const dim3 block(kMmThreads);
     const unsigned int ng = p.K >> 6;
     if constexpr (!NT && EPI == MM_BIAS_RELU) if (copy) {
-        const unsigned int cb = (copy->n4 + 4u * kMmThreads - 1u) / (4u * kMmThreads), nx = a.N / 16u;
+        const unsigned int cb = copy_blocks(*copy), nx = a.N / 16u;
         const dim3 grid(nx, tiles_y + (cb + nx - 1u) / nx, 1);
         if (ng >= 8) hipLaunchKernelGGL((mm_f32_copy_kernel<NT, EPI, 8>), grid, block, 0, st, p, tiles_y, *copy);
         else hipLaunchKernelGGL((mm_f32_copy_kernel<NT, EPI, 4>), grid, block, 0, st, p, tiles_y, *copy);

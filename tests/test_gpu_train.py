@@ -30,6 +30,8 @@ mixed-precision path; "close" means |x - y| <= rtol * max(|x|, |y|) + rtol * max
     moments and weights of those entries.  Such steps are counted in Pair.kink_steps, and every
     test ends with the check that they stayed rare (at most 1 + compared steps / 100).
 """
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 import torch
@@ -1217,44 +1219,56 @@ def test_mixed_precision_products_with_few_tiles(B, H, H2, batch, target_sync):
         assert pr.step(synth.take(rows, k, k + 1), compare=True) == 0
 
 
-@pytest.mark.parametrize("H,H2,batch", [
-    (8192, 64, 131_200),     # H1, which the second layer reads, is 4.3 GB
-    (64, 8192, 262_200),     # so is dZ2, which the first layer's error is formed from
+@pytest.mark.parametrize("dtype,H,H2,batch,n", [
+    ("bf16", 8192, 64, 131_200, 100),    # H1, which the second layer reads, is 4.3 GB
+    ("bf16", 64, 8192, 262_200, 100),    # so is dZ2, which the first layer's error is formed from
+    ("f32", 512, 8192, 524_300, 20),     # H2 is 34 GB, in 8.4 million tiles: more than one row of workgroups
 ])
-def test_mixed_precision_operands_beyond_4_gib(B, H, H2, batch):
-    """Products whose operand is larger than 32-bit byte offsets reach.  The batch is a block of 100
+def test_very_large_operands(B, dtype, H, H2, batch, n):
+    """Products whose operand is larger than 32-bit byte offsets reach, or whose launch has more threads
+    than a row of workgroups may have.  The batch is a block of n
     experiences over and over and, last, another block, whose rewards are so large that it makes up
     most of the gradients; 4 GiB is not a whole number of blocks of rows, so that a row that is taken
     from an offset that wrapped around is another experience's.  Every repetition of the block must
     give the same Q-values, the two blocks' Q-values and the gradients (a weighted sum of the two
-    blocks') are the oracle's, at the tolerances of the other mixed-precision cases."""
-    D, A, n = 27, 30, 100
-    copies = batch // n - 1
+    blocks'; in fp32 what no unit on a ReLU kink can reach) are the oracle's, at the tolerances of the
+    other cases of the type."""
+    D, A = 27, 30
+    bf16, copies = dtype == "bf16", batch // n - 1
+    rtol, g_rtol = (BF16_RTOL, 2 * BF16_RTOL) if bf16 else (F32_RTOL, 10 * F32_RTOL)
     p0 = synth.init_params(D, H, A, 7, hidden2=H2)
-    ring = B.Replay(64, D, B.RP_BF16, seed=1)
-    tr = B.Trainer(ring, H, A, batch, param_dtype=B.RP_BF16, loss=B.RP_MSE, opt=B.RP_SGD, lr=1e-3, appends_per_step=0,
-                   init_params=p0, hidden2=H2)
-    blocks = [synth.experiences(n, D, A, 0.1, seed=k, state_dtype="bf16") for k in (77, 78)]
+    st = B.RP_BF16 if bf16 else B.RP_F32
+    ring = B.Replay(64, D, st, seed=1)
+    tr = B.Trainer(ring, H, A, batch, param_dtype=st, loss=B.RP_MSE, opt=B.RP_SGD, lr=1e-3, appends_per_step=0,
+                   use_graph=False, init_params=p0, hidden2=H2)
+    blocks = [synth.experiences(n, D, A, 0.1, seed=k, state_dtype=dtype) for k in (77, 78)]
     blocks[1]["r"] *= np.float32(1e5)
     dev = [{k: torch.from_numpy(v.view(np.int16) if v.dtype == np.uint16 else v).cuda() for k, v in b.items()}
            for b in blocks]
     given = {k: torch.cat([dev[0][k].repeat((copies,) + (1,) * (dev[0][k].dim() - 1)), dev[1][k]]) for k in dev[0]}
     assert tr.step_batch(given["s"], given["s_next"], given["a"], given["r"], given["term"]) == 0
     last, g = tr.last(), tr.grads()
-    cfg = oracle.make_cfg(D, H, A, n, loss=oracle.MSE, opt=oracle.SGD, lr=1e-3, gamma=float(np.float32(0.99)), bf16=1,
-                          hidden2=H2)
-    want = 0.0
+    cfg = oracle.make_cfg(D, H, A, n, loss=oracle.MSE, opt=oracle.SGD, lr=1e-3, gamma=float(np.float32(0.99)),
+                          bf16=int(bf16), hidden2=H2)
+    want, keep = 0.0, np.ones(len(g), bool)
+    oracle.set_threads(16)
     for b, at, weight in ((blocks[0], slice(0, n), copies * n / batch), (blocks[1], slice(batch - n, batch), n / batch)):
-        s, sn = (synth.bf16_bits_to_f32(b[k]).astype(np.float64) for k in ("s", "s_next"))
+        s, sn = ((synth.bf16_bits_to_f32(b[k]) if bf16 else b[k]).astype(np.float64) for k in ("s", "s_next"))
         ref = oracle.train_step(cfg, p0, None, None, 0, s, sn, b["a"], b["r"], b["term"])
-        assert_close(last["Q"][at], ref.Q, BF16_RTOL, "Q(s,.)")
-        assert_close(last["Qn"][at], ref.Qn, BF16_RTOL, "Q(s',.)")
+        assert_close(last["Q"][at], ref.Q, rtol, "Q(s,.)")
+        assert_close(last["Qn"][at], ref.Qn, rtol, "Q(s',.)")
         want = want + weight * ref.grads
+        reach = None if bf16 else Pair.kink_reach(SimpleNamespace(D=D, H=H, H2=H2, A=A, dueling=False), p0, s)
+        if reach is not None:
+            keep &= ~reach
+    oracle.set_threads(1)
+    assert keep.mean() > 0.9
     for name in ("Q", "Qn"):
         rows = last[name][:copies * n].reshape(copies, n, A)
         assert (rows == rows[0]).all(), name
     for lo, hi in ((0, D * H + H), (D * H + H, D * H + H + H * H2 + H2), (D * H + H + H * H2 + H2, len(g))):
-        assert_close(g[lo:hi], want[lo:hi], 2 * BF16_RTOL, "gradients of one layer")
+        if keep[lo:hi].any():
+            assert_close(g[lo:hi][keep[lo:hi]], want[lo:hi][keep[lo:hi]], g_rtol, "gradients of one layer")
 
 
 @pytest.mark.parametrize("appends,distinct", [(2, False), (2, True), (0, False), (0, True)])
