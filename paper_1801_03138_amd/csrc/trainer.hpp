@@ -18,13 +18,9 @@ __device__ __forceinline__ float to_float(float x) { return x; }
 __device__ __forceinline__ float to_float(bf16_t x) {
     return __uint_as_float((unsigned int)x.bits << 16);
 }
-// round to nearest even; NaN stays NaN
-__device__ __forceinline__ unsigned short bf16_bits_rne(float f) {
-    unsigned int u = __float_as_uint(f);
-    if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x007FFFFFu)) return (unsigned short)((u >> 16) | 0x40u);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
-}
+// Round to nearest even; NaN stays NaN.  One instruction on gfx950 for two values; compared over all 2^32
+// floats, it gives the bits of (u + 0x7FFF + (u >> 16 & 1)) >> 16 and of a quieted NaN's upper half.
+__device__ __forceinline__ unsigned short bf16_bits_rne(float f) { return __builtin_bit_cast(unsigned short, (__bf16)f); }
 template <typename T>
 __device__ __forceinline__ T from_float(float x);
 template <>
