@@ -261,7 +261,8 @@ struct WsLayout {
     size_t ctr, w, g, m, v, wt, w2t, wb, wbt, X, act, rew, term, idx, H1, H2, Q, y, delta, lossi, dQ, dZ2, dZ1,
         pre, qpart, handoff, ahead, qn_ahead, X2, total;
     // mixed-precision step on MFMA
-    size_t W1T, W2b, W2T, W3T, W1Tt, W2Tt, W3Tt, dQ3, part3, part1, part2;
+    size_t W1T, W2b, W2T, W3T, W1Tt, W2Tt, W3Tt, dQ3, part3, part1, part2, part2b;
+    WidePlan plan;
     unsigned int Dp, Ap, Bp;
     size_t n_params, n_padded, n_head, elem;
     size_t oW1, ob1, oW2, ob2, oW3, ob3;
@@ -341,10 +342,13 @@ bool ws_layout(const train_config* c, WsLayout* L) {
     L->W2Tt = take(mixed_t ? H * G * 2 : 0);
     L->W3Tt = take(mixed_t ? L->Ap * G * 2 : 0);
     L->dQ3 = take(mixed ? B * 3 * L->Ap * 2 : 0);
-    // K-split partial products of the narrow layers' gradients (at most 16 splits)
-    L->part3 = take(mixed ? 16 * (G + 1) * L->Ap * 4 : 0);
-    L->part1 = take(mixed ? 16 * H * Dx * 4 : 0);
-    L->part2 = take(mixed ? (size_t)square_splits((unsigned int)Bp, (unsigned int)H, (unsigned int)G) * (H + 1) * G * 4 : 0);
+    // K-split partial products of the gradients
+    WidePlan& plan = L->plan;
+    plan = mixed ? wide_plan((unsigned int)B, (unsigned int)H, (unsigned int)G) : WidePlan{};
+    L->part3 = take(mixed ? plan.splits3 * (G + 1) * L->Ap * 4 : 0);
+    L->part1 = take(mixed ? plan.splits1 * H * Dx * 4 : 0);
+    L->part2 = take(mixed ? plan.splits2 * (H + 1) * G * 4 : 0);
+    L->part2b = take(mixed && plan.merged ? plan.splits3 * (L->Ap / 32) * G * 4 : 0);
     L->total = o;
     return true;
 }
@@ -863,6 +867,7 @@ rp_status train_create(const train_config* cfg, replay_t* rp_, void* dev_workspa
                                                               : nullptr;
     t->w2t = cfg->param_dtype == RP_F32 ? reinterpret_cast<float*>(ws + L.w2t) : nullptr;
     t->fused = !(cfg->flags & RP_TRAIN_LAYERED) && rp::fused_step_supported(*cfg, rp_);
+    t->plan = L.plan;
     t->wide = !(cfg->flags & RP_TRAIN_LAYERED) && rp::wide_step_supported(*cfg, rp_);
     t->mid = !(cfg->flags & RP_TRAIN_LAYERED) && !t->fused && rp::mid_step_supported(*cfg, rp_);
     {
@@ -871,7 +876,8 @@ rp_status train_create(const train_config* cfg, replay_t* rp_, void* dev_workspa
                                 at(L.W3Tt), at(L.dQ3),
                                 reinterpret_cast<float*>(ws + L.part3),
                                 reinterpret_cast<float*>(ws + L.part1),
-                                reinterpret_cast<float*>(ws + L.part2)};
+                                reinterpret_cast<float*>(ws + L.part2),
+                                reinterpret_cast<float*>(ws + L.part2b)};
     }
     t->wb = cfg->param_dtype == RP_BF16 ? reinterpret_cast<bf16_t*>(ws + L.wb) : nullptr;
     t->X = ws + L.X;

@@ -20,6 +20,11 @@ __device__ __forceinline__ float to_float(bf16_t x) {
 }
 // Round to nearest even; NaN stays NaN.  One instruction on gfx950 for two values; compared over all 2^32
 // floats, it gives the bits of (u + 0x7FFF + (u >> 16 & 1)) >> 16 and of a quieted NaN's upper half.
+__device__ __forceinline__ unsigned int bf16_pair(float lo, float hi) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned int, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
+}
 __device__ __forceinline__ unsigned short bf16_bits_rne(float f) { return __builtin_bit_cast(unsigned short, (__bf16)f); }
 template <typename T>
 __device__ __forceinline__ T from_float(float x);
@@ -124,6 +129,13 @@ inline void set_adam_step(RowArgs& a, unsigned long long t_after, float beta1, f
 }
 
 
+// Mixed-precision step: how its backward half is launched, and its partial products: in the two launches of large steps, and
+// there in large tiles; splits of the gradients of the output, first and second layer; rows per split of the last.
+struct WidePlan {
+    bool merged, large;
+    unsigned int splits3, splits1, splits2, k2;
+};
+
 // Buffers of the mixed-precision step on MFMA (bf16 bit patterns; H, G: widths of the two hidden
 // layers; "T" = transposed).
 struct WideBuffers {
@@ -133,6 +145,7 @@ struct WideBuffers {
     float* part3;                            // K-split partials [splits][G+1][Ap] of [dW3 ; db3]
     float* part1;                            // K-split partials [splits][H][Dx] of [dW1^T | db1]
     float* part2;                            // K-split partials [splits][H+1][G] of [dW2 ; db2]
+    float* part2b;                           // large steps: partials [splits x blocks of 32 actions][G] of db2
 };
 
 // train_steps runs several steps per graph launch (a launch costs about 5 us of GPU idle time:
@@ -192,6 +205,7 @@ struct trainer {
     bool wide;                       // mixed-precision step on MFMA
     bool mid;                        // fp32 step on MFMA, one product per kernel
     rp::WideBuffers wd;
+    rp::WidePlan plan;
     hipStream_t capture_stream;
     unsigned int kernels_per_step;
     uint64_t host_step;              // mirror of ctr->step
@@ -291,7 +305,7 @@ hipError_t enqueue_mid_step(trainer* t, hipStream_t st, unsigned int* count);
 unsigned int mid_step_kernels(const trainer* t);   // launches per step, the append + gather kernel included
 // Mixed-precision step on MFMA (bf16 replay states and matrix operands).
 bool wide_step_supported(const train_config& cfg, const replay* rp_);
-unsigned int square_splits(unsigned int Bp, unsigned int H, unsigned int G);   // K splits of the dW2 product
+WidePlan wide_plan(unsigned int B, unsigned int H, unsigned int G);
 hipError_t wide_configure();                                    // once, at creation
 // bf16 operand copies from padded fp32 parameters (host): of the trained network, or of the target
 hipError_t wide_set_weights(trainer* t, const float* padded, bool target);

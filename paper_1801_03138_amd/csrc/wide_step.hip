@@ -6,48 +6,37 @@
 // with 16-byte loads; the forward layers therefore read transposed bf16 copies of the weights.  The
 // weight gradients contract over the batch, C[m][n] = sum_i A[i][m] * B[i][n], and read activations
 // and errors as the other kernels leave them, one row per experience: the transposing LDS
-// read turns a slice of batch rows into MFMA operands.  A bias gradient is the product of the error
-// with a vector of ones, which the workgroups of one tile row (column) form beside their tile, with
-// a constant register as operand.  These products have a long contraction and small outputs:
-// they are split along the batch over several workgroups per tile, and the optimizer kernels add
+// read turns a slice of batch rows into MFMA operands.  These products have a long contraction and small
+// outputs: they are split along the batch over several workgroups per tile, and the optimizer kernel adds
 // the fp32 partial products up.
+//
+// The backward half of a step has two forms (WidePlan).  Large steps form the gradients of the output
+// layer and of the second bias beside the TD errors, and that of the first layer beside its error, in two
+// launches (td_grad_kernel, grad_back_kernel); small ones have a launch for each of the TD errors, the first layer's error
+// and all gradients.
 //
 // Paper: Integration with Reinforcement Learning Algorithm (train step with no host inputs),
 // Deep Q-Network Model (update equation).
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
+#include <queue>
 #include <type_traits>
 #include <vector>
 
 #include "gather_block.hpp"
+#include "mm_bf16.hpp"
 #include "replay_kernels.hpp"
 #include "trainer.hpp"
 
 namespace rp {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned short bf16_bits;
-// 16 bytes in flight between a load and its use.  A native vector type: arrays of HIP's uint4
-// struct are not promoted to registers by the compiler and end up in scratch memory.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
 constexpr unsigned int kGemmThreads = 256;
 
 __device__ __forceinline__ float bits_to_float(bf16_bits b) {
     return __uint_as_float((unsigned int)b << 16);
-}
-
-__device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& v) {
-    return __builtin_bit_cast(bf16x8, v);
-}
-
-// Row (0..31 within the 32x32 tile) of accumulator element v held by `lane`; its column is lane % 32.
-__device__ __forceinline__ unsigned int acc_row(unsigned int v, unsigned int lane) {
-    return 8u * (v >> 2) + 4u * (lane >> 5) + (v & 3u);
 }
 
 // ----------------------------------------------------------------------------------------
@@ -119,30 +108,13 @@ struct EpiForward {
     }
 };
 
-// out[m][n] = bf16(acc) where mask[m][n] > 0, else 0  (the ReLU derivative; both [M x ld]).
-struct EpiMask {
-    const bf16_bits* mask;
-    bf16_bits* out;
-    unsigned int ld;
-    unsigned int M, N;
-    __device__ __forceinline__ float pre(unsigned int, unsigned int, float x) const { return x; }
-    // eight consecutive columns n..n+7 of row m (N is a multiple of 8)
-    __device__ __forceinline__ void store(unsigned int m, unsigned int n, const u32x4& v) const {
-        if (m >= M || n >= N) return;
-        const size_t at = (size_t)m * ld + n;
-        const u32x4 k = *reinterpret_cast<const u32x4*>(mask + at);
-        u32x4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            // a bf16 is positive when it is non-zero with the sign bit clear (NaN counts as not)
-            const unsigned int lo = k[e] & 0xFFFFu, hi = k[e] >> 16;
-            const bool lo_on = lo != 0u && lo <= 0x7F80u;
-            const bool hi_on = hi != 0u && hi <= 0x7F80u;
-            o[e] = (lo_on ? v[e] & 0xFFFFu : 0u) | (hi_on ? v[e] & 0xFFFF0000u : 0u);
-        }
-        *reinterpret_cast<u32x4*>(out + at) = o;
-    }
-};
+// Two bf16 values, each kept where the bf16 beside it in k is positive: non-zero with the sign bit clear (NaN
+// counts as not).
+__device__ __forceinline__ unsigned int relu_mask(unsigned int v, unsigned int k) {
+    const unsigned int lo = k & 0xFFFFu, hi = k >> 16;
+    const bool lo_on = lo != 0u && lo <= 0x7F80u, hi_on = hi != 0u && hi <= 0x7F80u;
+    return (lo_on ? v & 0xFFFFu : 0u) | (hi_on ? v & 0xFFFF0000u : 0u);
+}
 
 // Partial gradients of one K split, added up by the optimizer kernel.  M: rows of the weight
 // matrix (of its transpose in EpiFirst); sums() gets the 32 column (row) sums of an error tile.
@@ -225,65 +197,12 @@ struct EpiFirst {
 // K must be a multiple of BK.  Loads of rows beyond M / N are redirected to the last valid row:
 // such rows only feed accumulator rows / columns that the epilogue never stores.
 // ----------------------------------------------------------------------------------------
-struct GemmArgs {
-    const bf16_bits* A;
-    unsigned int lda;
-    const bf16_bits* Bt;
-    const bf16_bits* Bt_hi;        // B operand of the tiles whose first row is m_split or beyond
-    unsigned int m_split;
-    unsigned int ldb;
-    unsigned int M, N, K;          // K: length one workgroup contracts over
-    unsigned int batch;            // products over the batch: rows of the operands
-    unsigned int tiles_m, tiles_n, splits;
-    unsigned int band;             // tiles are numbered band by band: `band` tile columns at a time, rows fastest after that
-};
-
 template <int BM, int BN, int BK, int WGM, int WGN, int NSTAGE = 2>
 constexpr size_t gemm_lds_bytes() {
     const size_t slices = NSTAGE * (size_t)(BM + BN) * BK * 2;
     // the epilogue parks every wavefront's bf16 tile, rows padded by 16 bytes
     const size_t parked = 4 * (size_t)(BM / WGM) * ((BN / WGN) * 2 + 16);
     return slices > parked ? slices : parked;
-}
-
-#define RP_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
-
-
-// Workgroups are dealt to the eight XCDs round-robin; each XCD gets a contiguous range of
-// tile numbers, and tiles are numbered so that such a range is a compact block of the output
-// (bands of `band` tile columns, within a band row by row): the workgroups that share an L2
-// then share as few operand panels as possible, and each panel is fetched by few XCDs.  False: the
-// workgroup has no tile.
-template <int BM, int BN>
-__device__ __forceinline__ bool tile_of(const GemmArgs& p, unsigned int block, unsigned int* m0, unsigned int* n0,
-                                        unsigned int* split) {
-    const unsigned int per_split = p.tiles_m * p.tiles_n, n_tiles = per_split * p.splits;
-    const unsigned int per_xcd = (n_tiles + 7u) / 8u;
-    const unsigned int tile_s = (block & 7u) * per_xcd + (block >> 3);
-    if (tile_s >= n_tiles) return false;
-    const unsigned int tile = tile_s % per_split;
-    const unsigned int band_tiles = p.tiles_m * p.band, band_id = tile / band_tiles, in_band = tile % band_tiles;
-    const unsigned int width = min(p.band, p.tiles_n - band_id * p.band);
-    *m0 = (in_band / width) * BM;
-    *n0 = (band_id * p.band + in_band % width) * BN;
-    *split = tile_s / per_split;
-    return true;
-}
-
-// s_waitcnt vmcnt(N), nothing else
-template <unsigned int N>
-__device__ __forceinline__ void wait_loads() {
-    __builtin_amdgcn_s_waitcnt((N & 0xFu) | ((N >> 4) << 14) | 0x0F70u);
-}
-// waits until at most `slices` (< NSTAGE - 1) slices of L loads each are in flight
-template <int L, int NSTAGE, int K = 0>
-__device__ __forceinline__ void wait_slices(unsigned int slices) {
-    if constexpr (K + 2 >= NSTAGE) {
-        wait_loads<K * L>();
-    } else {
-        if (slices == K) wait_loads<K * L>();
-        else wait_slices<L, NSTAGE, K + 1>(slices);
-    }
 }
 
 template <int BM, int BN, int BK, int WGM, int WGN, int NSTAGE = 2, class Epi>
@@ -422,7 +341,7 @@ __device__ __forceinline__ void gemm_nt_block(const GemmArgs& p, const Epi& epi,
     }
     // the last NSTAGE - 1 slices: nothing left to request
     for (; kt < nk; ++kt) {
-        wait_slices<L, NSTAGE>(nk - 1u - kt);
+        wait_slices<L, NSTAGE - 2>(nk - 1u - kt);
         __syncthreads();
         multiply(kt % NSTAGE, std::false_type{}, 0u, 0u);
     }
@@ -444,13 +363,12 @@ __device__ __forceinline__ void gemm_nt_block(const GemmArgs& p, const Epi& epi,
 #pragma unroll
             for (unsigned int grp = 0; grp < 4; ++grp) {
                 const unsigned int nl = j * 32u + 8u * grp + 4u * (lane >> 5);
-                bf16_bits h[4];
+                float x[4];
 #pragma unroll
-                for (unsigned int e = 0; e < 4; ++e)
-                    h[e] = bf16_bits_rne(epi.pre(m0, wn0 + nl + e, acc[i][j][4 * grp + e]));
+                for (unsigned int e = 0; e < 4; ++e) x[e] = epi.pre(m0, wn0 + nl + e, acc[i][j][4 * grp + e]);
                 uint2 pk;
-                pk.x = (unsigned int)h[0] | ((unsigned int)h[1] << 16);
-                pk.y = (unsigned int)h[2] | ((unsigned int)h[3] << 16);
+                pk.x = bf16_pair(x[0], x[1]);
+                pk.y = bf16_pair(x[2], x[3]);
                 *reinterpret_cast<uint2*>(park + (i * 32u + (lane & 31u)) * TSTRIDE + nl * 2u) = pk;
             }
     // same wavefront reads what it wrote: LDS operations of a wavefront complete in order
@@ -497,8 +415,6 @@ constexpr size_t gemm_tn_lds_bytes() {
     return std::max(kTnStages * (size_t)kTnSlice * (BM + BN) * 2, (size_t)BM * BN * 4 + 4 * 4096);
 }
 constexpr unsigned int kTnThreads = 512;
-
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 template <int BM, int BN, int WGM, int WGN, bool SUM_ROWS, class Epi>
 __device__ __forceinline__ void gemm_tn_block(const GemmArgs& p, const Epi& epi, unsigned int block) {
@@ -665,7 +581,7 @@ __device__ __forceinline__ void gemm_tn_block(const GemmArgs& p, const Epi& epi,
         multiply(kt % kTnStages, std::true_type{}, (kt + kTnStages - 1) % kTnStages, k_base + (kt + kTnStages - 1) * kTnSlice);
     }
     for (; kt < nk; ++kt) {
-        wait_slices<L, kTnStages>(nk - 1u - kt);
+        wait_slices<L, kTnStages - 2>(nk - 1u - kt);
         __syncthreads();
         if (left && kt + 1u == nk) {
             const u32x4 zero = {0u, 0u, 0u, 0u};
@@ -1028,24 +944,466 @@ __global__ __launch_bounds__(256) void td_dz_kernel(TdArgs p) {
         for (int x = 0; x < 4; ++x) {
             const float h_lo = __uint_as_float(hv[e][x] << 16), h_hi = __uint_as_float(hv[e][x] & 0xFFFF0000u);
             const float w_lo = __uint_as_float(wv[e][x] << 16), w_hi = __uint_as_float(wv[e][x] & 0xFFFF0000u);
-            out[x] = (unsigned int)bf16_bits_rne(h_lo > 0.f ? g * w_lo : 0.f) |
-                     ((unsigned int)bf16_bits_rne(h_hi > 0.f ? g * w_hi : 0.f) << 16);
+            out[x] = bf16_pair(h_lo > 0.f ? g * w_lo : 0.f, h_hi > 0.f ? g * w_hi : 0.f);
         }
         if (k0 + 128u * e < p.G) *reinterpret_cast<u32x4*>(p.dZ2 + (size_t)i * p.G + k0 + 128u * e) = out;
     }
 }
 
-// The two narrow layers' update, from the K-split partial products of their gradients:
+// ----------------------------------------------------------------------------------------
+// The backward half of large steps (grad_back_kernel's shapes), in two launches.
+//
+// td_grad_kernel: targets, TD errors, loss terms, dZ2, and what can be formed from dZ2 and H2 while they
+// are in registers: db2 (column sums of dZ2) and [dW3 ; db3].  A workgroup owns 128 columns and every
+// gridDim.x-th chunk of 128 batch rows, sixteen lanes to a row.  The lanes of a row work out
+//   y_i = r_i + gamma (1 - term_i) max_a Q(s'_i, a), delta_i = y_i - Q(s_i, a_i), the loss term and
+//   g_i = dL/dQ(s_i, a_i) among themselves while their share of H2 is on its way; then
+//   dZ2[i][k] = g_i W3[k][a_i] 1[H2[i][k] > 0] goes out, 16 bytes a lane.
+// The chunk's H2 and its dL/dQ (32 actions of it: gridDim.z) go to LDS, the latter in three bf16 parts whose
+// sum is the fp32 number, and dW3 = H2^T dL/dQ is contracted from there.  dL/dQ never goes to memory and
+// H2 is read once (a product of its own read it again, 8 MB at batch 4096 and 1024 units).  A row's dZ2 is the
+// business of the workgroups of its action's block, which hold that block's columns of W3 in LDS: no load
+// waits for an action.
+// ----------------------------------------------------------------------------------------
+constexpr unsigned int kTgRows = 128, kTgCols = 128, kTgThreads = 512, kTgMaxSplits = 32;
+
+struct TdGradArgs {
+    unsigned int B, G, A, Ap;
+    // kz = 0: Q is complete, [2B x Ap].  Otherwise it comes as kz partial products, part_stride elements apart and
+    // without the bias (b3 for the rows of s, b3_hi for those of s'); this kernel adds them up and writes Q.
+    unsigned int kz;
+    size_t part_stride;
+    const float* parts;
+    const float *b3, *b3_hi;
+    float* Q;
+    const int* act;
+    const float* rew;
+    const unsigned char* term;
+    float gamma;
+    unsigned int loss_kind;
+    float beta1, beta2;
+    float *y, *delta, *lossi;
+    const bf16_bits* W3T;        // [Ap x G]
+    const bf16_bits* H2;         // [2B x G]
+    bf16_bits* dZ2;              // [B x G]
+    float* part3;                // [splits][G + 1][Ap], row G: db3
+    float* part2b;               // [splits x blocks of 32 actions][G]: db2
+    TrainCounters* ctr;
+};
+
+// v of the lane N places round the row of 16 lanes
+template <int N>
+__device__ __forceinline__ float row16_ror(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xf, 0xf, false));
+}
+
+template <bool PARTS>
+__global__ __launch_bounds__(kTgThreads) void td_grad_kernel(TdGradArgs p) {
+    constexpr unsigned int PASSES = kTgRows / 32u, DQ = kTgRows * 256u;   // dL/dQ's place behind H2's
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kTgRows * (256u + 192u)];
+    __shared__ __attribute__((aligned(16))) unsigned char w3s[32u * 256u];   // W3's columns of this workgroup
+    __shared__ float colsum[8][kTgCols];
+    const unsigned int tid = threadIdx.x, lane = tid & 63u, part = tid & 15u, row16 = tid >> 4;
+    const unsigned int wave = __builtin_amdgcn_readfirstlane(tid >> 6), t = wave & 3u, h = wave >> 2;
+    const unsigned int c0 = blockIdx.y * kTgCols, k0 = c0 + part * 8u, kc = k0 < p.G ? k0 : 0u;
+    const unsigned int a0 = blockIdx.z * 32u;                // this workgroup's block of actions
+    const bool stripe0 = blockIdx.z == 0 && blockIdx.y == 0;
+    if (stripe0 && blockIdx.x == 0 && tid == 0) {
+        // (running products beta^t in double precision: no power function on the device)
+        const double pw1 = p.ctr->pw1 * (double)p.beta1, pw2 = p.ctr->pw2 * (double)p.beta2;
+        p.ctr->adam_t = p.ctr->adam_t + 1;
+        p.ctr->pw1 = pw1;
+        p.ctr->pw2 = pw2;
+        p.ctr->c1 = (float)(1.0 - pw1);
+        p.ctr->c2 = (float)(1.0 - pw2);
+    }
+    const TnLane l(lane);
+    f32x16 acc[3], sum[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[s][v] = sum[s][v] = 0.f;
+    float cs[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) cs[e] = 0.f;
+    const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    const bool with_sums = blockIdx.y == 0 && t == 0;
+    // a row's Q-values: four neighbouring actions a lane, and every second partial product
+    const unsigned int quad = part & 7u, zsel = part >> 3, nz = PARTS ? p.kz : 1u;
+    const float* const q_in = PARTS ? p.parts : p.Q;
+    const u32x4 w3 = *reinterpret_cast<const u32x4*>(p.W3T + (size_t)(a0 + row16) * p.G + kc);
+
+    const unsigned int chunks = (p.B + kTgRows - 1u) / kTgRows;
+    for (unsigned int c = blockIdx.x; c < chunks; c += gridDim.x) {
+        // (all loads of a chunk are requested before the first use)
+        unsigned int row[PASSES], ai[PASSES];
+        u32x4 hv[PASSES];
+        float best[PASSES], qa[PASSES], rew[PASSES];
+        bool term[PASSES];
+#pragma unroll
+        for (unsigned int q = 0; q < PASSES; ++q) {
+            row[q] = c * kTgRows + q * 32u + row16;
+            const unsigned int i = min(row[q], p.B - 1u);
+            ai[q] = min((unsigned int)p.act[i], p.A - 1u);   // an out-of-range action must not turn into a wild address
+            rew[q] = p.rew[i];
+            term[q] = p.term[i] != 0;
+            hv[q] = *reinterpret_cast<const u32x4*>(p.H2 + (size_t)i * p.G + kc);
+            best[q] = -INFINITY;
+            qa[q] = 0.f;
+        }
+        for (unsigned int ab = 0; ab < p.Ap; ab += 32u) {
+            f32x4 qs[PASSES], qn[PASSES];
+#pragma unroll
+            for (unsigned int q = 0; q < PASSES; ++q) qs[q] = qn[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+            constexpr unsigned int ZU = PARTS ? 2u : 1u;     // partial products requested at a time, per lane
+            for (unsigned int z0 = 0; z0 < nz; z0 += 2u * ZU) {
+                f32x4 xs[ZU][PASSES], xn[ZU][PASSES];
+#pragma unroll
+                for (unsigned int u = 0; u < ZU; ++u) {
+                    const unsigned int z = z0 + 2u * u + zsel;
+                    const float* at = q_in + (size_t)(z < nz ? z : 0u) * p.part_stride + ab + 4u * quad;
+#pragma unroll
+                    for (unsigned int q = 0; q < PASSES; ++q) {
+                        const size_t i = min(row[q], p.B - 1u);
+                        xs[u][q] = *reinterpret_cast<const f32x4*>(at + i * p.Ap);
+                        xn[u][q] = *reinterpret_cast<const f32x4*>(at + (p.B + i) * p.Ap);
+                    }
+                }
+#pragma unroll
+                for (unsigned int u = 0; u < ZU; ++u)
+#pragma unroll
+                    for (unsigned int q = 0; q < PASSES; ++q) {
+                        if (PARTS && z0 + 2u * u + zsel >= nz) continue;
+                        qs[q] += xs[u][q];
+                        qn[q] += xn[u][q];
+                    }
+            }
+            f32x4 bs = {0.f, 0.f, 0.f, 0.f}, bn = bs;
+            if constexpr (PARTS) {
+                bs = *reinterpret_cast<const f32x4*>(p.b3 + ab + 4u * quad);
+                bn = *reinterpret_cast<const f32x4*>(p.b3_hi + ab + 4u * quad);
+            }
+#pragma unroll
+            for (unsigned int q = 0; q < PASSES; ++q) {
+                if constexpr (PARTS) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        qs[q][e] = (qs[q][e] + row16_ror<8>(qs[q][e])) + bs[e];
+                        qn[q][e] = (qn[q][e] + row16_ror<8>(qn[q][e])) + bn[e];
+                    }
+                    if (stripe0 && row[q] < p.B) {
+                        const size_t i = zsel ? (size_t)p.B + row[q] : row[q];
+                        *reinterpret_cast<f32x4*>(p.Q + i * p.Ap + ab + 4u * quad) = zsel ? qn[q] : qs[q];
+                    }
+                }
+                const unsigned int mine = ai[q] - (ab + 4u * quad);
+#pragma unroll
+                for (unsigned int e = 0; e < 4; ++e) {
+                    if (ab + 4u * quad + e < p.A) best[q] = fmaxf(best[q], qn[q][e]);
+                    if (mine == e) qa[q] = qs[q][e];
+                }
+            }
+        }
+        if (c != blockIdx.x) {
+            __syncthreads();                                 // (the last chunk's operands have been read)
+        } else {
+            *reinterpret_cast<u32x4*>(w3s + row16 * 256u + part * 16u) = w3;
+            __syncthreads();
+        }
+#pragma unroll
+        for (unsigned int q = 0; q < PASSES; ++q) {
+            const unsigned int i = min(row[q], p.B - 1u), r = q * 32u + row16;
+            const bool in = row[q] < p.B, owner = ai[q] >> 5 == blockIdx.z;
+            // (lanes 8 apart hold the same)
+            best[q] = fmaxf(best[q], row16_ror<4>(best[q]));
+            best[q] = fmaxf(best[q], row16_ror<2>(best[q]));
+            best[q] = fmaxf(best[q], row16_ror<1>(best[q]));
+            qa[q] += row16_ror<4>(qa[q]);
+            qa[q] += row16_ror<2>(qa[q]);
+            qa[q] += row16_ror<1>(qa[q]);
+            const u32x4 wv = *reinterpret_cast<const u32x4*>(w3s + (ai[q] & 31u) * 256u + part * 16u);
+            const float y = rew[q] + (term[q] ? 0.f : p.gamma * best[q]);
+            const float d = y - qa[q];
+            float li, slope;
+            if (p.loss_kind == RP_MSE || fabsf(d) <= 1.f) {
+                li = 0.5f * d * d;
+                slope = d;
+            } else {
+                li = fabsf(d) - 0.5f;
+                slope = d > 0.f ? 1.f : -1.f;
+            }
+            const float g = -slope / (float)p.B;
+            if (stripe0 && part == 0 && in) {
+                p.y[i] = y;
+                p.delta[i] = d;
+                p.lossi[i] = li;
+            }
+            // dL/dQ's row: two actions a lane and part
+            {
+                const bf16_bits hi = bf16_bits_rne(g);
+                const float rest = g - bits_to_float(hi);
+                const bf16_bits mid = bf16_bits_rne(rest);
+                const bf16_bits lo = bf16_bits_rne(rest - bits_to_float(mid));
+                const unsigned int a = a0 + 2u * part, shift = a == ai[q] ? 0u : 16u;
+                const bool mine = in && (a ^ ai[q]) < 2u;    // (a is even)
+                unsigned int* dq = reinterpret_cast<unsigned int*>(lds + DQ + r * 192u) + part;
+                dq[0] = mine ? (unsigned int)hi << shift : 0u;
+                dq[16] = mine ? (unsigned int)mid << shift : 0u;
+                dq[32] = mine ? (unsigned int)lo << shift : 0u;
+            }
+            // (rows beyond the batch: whatever lies there must not meet a factor of zero)
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            *reinterpret_cast<u32x4*>(lds + r * 256u + 16u * (part ^ (4u * (r & 3u)))) = in && k0 < p.G ? hv[q] : zero;
+            u32x4 out;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const float h_lo = __uint_as_float(hv[q][x] << 16), h_hi = __uint_as_float(hv[q][x] & 0xFFFF0000u);
+                const float w_lo = __uint_as_float(wv[x] << 16), w_hi = __uint_as_float(wv[x] & 0xFFFF0000u);
+                out[x] = bf16_pair(h_lo > 0.f ? g * w_lo : 0.f, h_hi > 0.f ? g * w_hi : 0.f);
+                cs[2 * x] += in && owner ? __uint_as_float(out[x] << 16) : 0.f;
+                cs[2 * x + 1] += in && owner ? __uint_as_float(out[x] & 0xFFFF0000u) : 0.f;
+            }
+            if (in && owner && k0 < p.G) *reinterpret_cast<u32x4*>(p.dZ2 + (size_t)i * p.G + k0) = out;
+        }
+        __syncthreads();
+        // wavefront (t, h): tile t of 32 columns, half h of the rows
+#pragma unroll
+        for (unsigned int s = 0; s < kTgRows / 32u; ++s) {
+            const unsigned int r = h * (kTgRows / 2u) + 16u * s + l.row;
+            const u32x4 a = tn_fragment(lds, r * 256u + tn_tile_at<true>(t, l.rr) + l.col, 256u);
+            u32x4 b[3];
+#pragma unroll
+            for (int x = 0; x < 3; ++x) b[x] = tn_fragment(lds, DQ + r * 192u + 64u * x + l.col, 192u);
+#pragma unroll
+            for (int x = 0; x < 3; ++x)
+                acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b[x]), acc[x], 0, 0, 0);
+            if (with_sums) {
+#pragma unroll
+                for (int x = 0; x < 3; ++x)
+                    sum[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ones), as_bf16x8(b[x]), sum[x], 0, 0, 0);
+            }
+        }
+    }
+
+    // the two halves of the rows are added through LDS, as are the eight wavefronts' column sums
+    __syncthreads();
+    float* const give = reinterpret_cast<float*>(lds) + t * (17u * 64u) + lane;
+    const float sums = (sum[2][0] + sum[1][0]) + sum[0][0];   // (the same in every row)
+    if (h) {
+#pragma unroll
+        for (unsigned int v = 0; v < 16; ++v) give[v * 64u] = (acc[2][v] + acc[1][v]) + acc[0][v];
+        give[16u * 64u] = sums;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        cs[e] += __shfl_xor(cs[e], 16, 64);
+        cs[e] += __shfl_xor(cs[e], 32, 64);
+    }
+    if (lane < 16u) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) colsum[wave][part * 8u + e] = cs[e];
+    }
+    __syncthreads();
+    const size_t split = blockIdx.x;
+    if (tid < kTgCols && c0 + tid < p.G) {
+        float x = 0.f;
+#pragma unroll
+        for (unsigned int w = 0; w < 8; ++w) x += colsum[w][tid];
+        p.part2b[(split * gridDim.z + blockIdx.z) * p.G + c0 + tid] = x;
+    }
+    if (h) return;
+    float* const at = p.part3 + split * (p.G + 1u) * p.Ap + a0 + (lane & 31u);
+    if (c0 + t * 32u < p.G) {                                 // (G is a whole number of 32)
+#pragma unroll
+        for (unsigned int v = 0; v < 16; ++v)
+            at[(size_t)(c0 + t * 32u + acc_row(v, lane)) * p.Ap] = ((acc[2][v] + acc[1][v]) + acc[0][v]) + give[v * 64u];
+    }
+    if (with_sums && lane < 32u) at[(size_t)p.G * p.Ap] = sums + give[16u * 64u];
+}
+
+// grad_back_kernel: the step's two large backward products in one launch, side by side because neither
+// needs the other, and the first layer's gradient with the first of them.
+//  - workgroups [0, n_dz): dZ1 = (dZ2 W2^T) 1[H1 > 0], a tile of BM rows x 128 units.  dZ1 is needed for
+//    [dW1^T | db1] = dZ1^T [X | 1] alone, so the tile stays in LDS as bf16, is contracted there with
+//    its rows of X and never goes to memory: part1[split][j][d] (column D: db1), a split per row of tiles, or
+//    per kGbMaxSplits-th one where there are more.
+//  - the rest: dW2 = H1^T dZ2, K-split partials part2[split][j][k].
+// As launches of their own (dZ1 stored, then all gradients) 16.3 + 21.8 us at batch 4096 and 1024 units.
+constexpr unsigned int kGbMaxSplits = 32;
+typedef MmTile<256, 128, 2, 2, 2, 3> GbLarge;
+typedef MmTile<128, 128, 2, 2, 2, 4> GbSmall;
+
+struct GradBackArgs {
+    GemmArgs dz;                 // A = dZ2, Bt = W2; tiles_m: rows of workgroups
+    GemmArgs dw;                 // A = H1, Bt = dZ2
+    unsigned int n_dz;           // workgroups of the first kind, a multiple of 8
+    const bf16_bits* X;          // [B x Dp]
+    const bf16_bits* H1;
+    unsigned int D, Dp, Dx;
+    float *part1, *part2;
+};
+
+// Byte of element (r, col) of the dZ1 tile in LDS: rows of 256 bytes whose 64-byte groups are rotated by XOR
+// with r mod 4 (for the transposing reads) and the 16-byte pieces of a group with r / 4 mod 4 (for the
+// accumulators' stores, 32 rows of a column at a time).  col: of the first of some columns of one piece.
+__device__ __forceinline__ unsigned int dz_at(unsigned int r, unsigned int col) {
+    return r * 256u + 64u * ((col >> 5) ^ (r & 3u)) + 16u * (((col >> 3) & 3u) ^ ((r >> 2) & 3u)) + (col & 7u) * 2u;
+}
+
+template <class S>
+__device__ __forceinline__ void dz1_block(const GradBackArgs& p, unsigned int block, unsigned char* smem) {
+    static_assert(S::BN == 128 && S::KG == 2, "four tiles of 32 units, and the rows' halves");
+    unsigned int m_first, n0, split;
+    if (!tile_of<S::BM, S::BN>(p.dz, block, &m_first, &n0, &split)) return;
+    const unsigned int tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned int row_split = m_first / S::BM, H = p.dz.N;
+    constexpr unsigned int XT = S::BM * 256u, RED = XT + S::BM * 64u;   // places in LDS of X's rows and the halves' sums
+    static_assert(RED + 4u * 8192u <= S::kLds, "the epilogue fits");
+    unsigned int wm, wn;
+    mm_wave_at<S>(wave, &wm, &wn);
+    const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    for (unsigned int m0 = m_first; m0 < p.dz.M; m0 += p.dz.tiles_m * S::BM) {
+        constexpr unsigned int CR = S::TN * 4u, RP = 64u / CR, PASSES = S::TK * 32u / RP, XN = S::BM * 4u / S::kThreads;
+        u32x4 mk[PASSES], xv[XN];
+        auto load_x = [&](unsigned int d0) {
+#pragma unroll
+            for (unsigned int u = 0; u < XN; ++u) {
+                const unsigned int e = tid + u * S::kThreads, i = min(m0 + (e >> 2), p.dz.M - 1u);
+                xv[u] = *reinterpret_cast<const u32x4*>(p.X + (size_t)i * p.Dp + d0 + (e & 3u) * 8u);
+            }
+        };
+        auto load_mask = [&](unsigned int from, unsigned int to) {
+#pragma unroll
+            for (unsigned int q = 0; q < PASSES; ++q) {
+                if (q < from || q >= to) continue;
+                const unsigned int i = min(m0 + wm + q * RP + lane / CR, p.dz.M - 1u), n = n0 + wn + lane % CR * 8u;
+                mk[q] = *reinterpret_cast<const u32x4*>(p.H1 + (size_t)i * H + (n < H ? n : 0u));
+            }
+        };
+        f32x16 acc[S::TM][S::TN];
+        if (m0 != m_first) __syncthreads();                   // (the last tile's epilogue still read LDS)
+        mm_nt<S>(p.dz, m0, n0, smem, acc, [&]() {
+            // half of the ReLU's mask and X's rows while the last slice is multiplied (no registers for more)
+            load_mask(0, PASSES / 2);
+            load_x(0u);
+        });
+        mm_swap_groups<S>(acc, smem, wave, lane);
+        load_mask(PASSES / 2, PASSES);
+        // (opaque from here on, so that the addresses below are not worked out ahead of the product, where
+        // its registers are needed)
+        unsigned int lane = threadIdx.x & 63u;
+        asm volatile("" : "+v"(lane));
+        const unsigned int tid = wave * 64u + lane;
+        const TnLane l(lane);
+#pragma unroll
+        for (int i = 0; i < S::TK; ++i)
+#pragma unroll
+            for (int j = 0; j < S::TN; ++j)
+#pragma unroll
+                for (unsigned int g = 0; g < 4; ++g) {
+                    uint2 pk;
+                    pk.x = bf16_pair(acc[i][j][4 * g], acc[i][j][4 * g + 1]);
+                    pk.y = bf16_pair(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+                    *reinterpret_cast<uint2*>(smem + dz_at(wm + i * 32u + (lane & 31u), wn + j * 32u + 8u * g + 4u * (lane >> 5))) = pk;
+                }
+        // (the same wavefront reads what it wrote: LDS operations of a wavefront complete in order)
+#pragma unroll
+        for (unsigned int q = 0; q < PASSES; ++q) {
+            const unsigned int r = wm + q * RP + lane / CR;
+            u32x4* at = reinterpret_cast<u32x4*>(smem + dz_at(r, wn + lane % CR * 8u));
+            u32x4 v = *at;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = m0 + r < p.dz.M ? relu_mask(v[e], mk[q][e]) : 0u;
+            *at = v;
+        }
+        // [dW1^T | db1], 32 states at a time: wavefront (t, h) has units 32 t .. and half h of the rows
+        const unsigned int t = wave & 3u, h = wave >> 2;
+        for (unsigned int d0 = 0; d0 < p.Dp; d0 += 32u) {
+#pragma unroll
+            for (unsigned int u = 0; u < XN; ++u)
+                *reinterpret_cast<u32x4*>(smem + XT + (tid + u * S::kThreads) * 16u) = xv[u];
+            if (d0 + 32u < p.Dp) load_x(d0 + 32u);
+            __syncthreads();
+            f32x16 c, sum;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) c[v] = sum[v] = 0.f;
+#pragma unroll
+            for (unsigned int s = 0; s < S::BM / 32u; ++s) {
+                const unsigned int r = h * (S::BM / 2u) + 16u * s + l.row;
+                typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+                const unsigned int col = t * 32u + (l.col >> 1);   // (the lane's first column of its 4 x 16 block)
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)RP_LDS_PTR(smem + dz_at(r, col)));
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)RP_LDS_PTR(smem + dz_at(r + 4u, col)));
+                const u32x4 a = __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                const u32x4 b = tn_fragment(smem, XT + r * 64u + l.col, 64u);
+                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
+                if (d0 == 0) sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(ones), sum, 0, 0, 0);
+            }
+            float* const give = reinterpret_cast<float*>(smem + RED) + t * 2048u + lane;
+            if (h) {
+#pragma unroll
+                for (unsigned int v = 0; v < 16; ++v) {
+                    give[v * 64u] = c[v];
+                    if (d0 == 0) give[1024u + v * 64u] = sum[v];
+                }
+            }
+            __syncthreads();
+            if (!h && n0 + t * 32u < H) {                     // (H is a whole number of 32)
+                const unsigned int d = d0 + (lane & 31u);
+                float* const at = p.part1 + ((size_t)row_split * H + n0 + t * 32u + acc_row(0, lane)) * p.Dx;
+#pragma unroll
+                for (unsigned int v = 0; v < 16; ++v) {
+                    // (a later tile of this workgroup adds to what the first one stored: the same thread did)
+                    if (d < p.D) {
+                        float* const to = at + acc_row(v, 0) * p.Dx + d;
+                        const float x = c[v] + give[v * 64u];
+                        *to = m0 == m_first ? x : *to + x;
+                    }
+                    if (d0 == 0 && (lane & 31u) == 0u) {      // (every column holds the sums)
+                        float* const to = at + acc_row(v, 0) * p.Dx + p.D;
+                        const float x = sum[v] + give[1024u + v * 64u];
+                        *to = m0 == m_first ? x : *to + x;
+                    }
+                }
+            }
+        }
+    }
+}
+
+template <class S>
+__global__ __launch_bounds__(S::kThreads) void grad_back_kernel(GradBackArgs p) {
+    extern __shared__ uint4 gemm_smem[];
+    unsigned char* smem = reinterpret_cast<unsigned char*>(gemm_smem);
+    if (blockIdx.x < p.n_dz) {
+        dz1_block<S>(p, blockIdx.x, smem);
+        return;
+    }
+    unsigned int m0, n0, split;
+    if (!tile_of<S::BM, S::BN>(p.dw, blockIdx.x - p.n_dz, &m0, &n0, &split)) return;
+    const unsigned int lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    f32x16 acc[S::TM][S::TN];
+    mm_tn<S>(p.dw, m0, n0, split * p.dw.K, smem, acc);
+    mm_swap_groups<S>(acc, smem, wave, lane);
+    unsigned int wm, wn;
+    mm_wave_at<S>(wave, &wm, &wn);
+    const EpiSquare epi{p.part2, p.dw.M, p.dw.N};
+#pragma unroll
+    for (int i = 0; i < S::TK; ++i) epi.tiles(m0 + wm + i * 32u, n0 + wn, acc[i], lane, split);
+}
+
+// The update of the two narrow layers and of the second layer's bias, from partial products of their gradients:
 //   part3[z][m][a]: m <= G (row G = bias); gradient of W3[m][a] = sum_z part3[z][m][a]
 //   part1[z][j][d]: j < H, d <= D (column D = bias); gradient of W1[d][j] = sum_z part1[z][j][d]
-// One thread per parameter; splits (at most 16) are added in order.  Workgroup 0 also reduces the
+// One thread per parameter; splits are added in order, sixteen requested at a time.  Workgroup 0 also reduces the
 // per-sample losses to their mean and advances the sampling step counter.
 struct SmallOptArgs {
     OptState o;
-    unsigned int splits, H, G, D, Dp, Dx, Ap, B;
+    unsigned int splits3, splits1, splits_b2, H, G, D, Dp, Dx, Ap, B;
     const float* part3;
     const float* part1;
-    size_t oW1, ob1, oW3, ob3;
+    const float* part_b2;       // [splits_b2] rows of G, b2_stride apart
+    size_t b2_stride;
+    size_t oW1, ob1, ob2, oW3, ob3;
     bf16_bits* W1T;   // [H x Dp]
     bf16_bits* W3T;   // [Ap x G]
     bf16_bits *W1T_target, *W3T_target;   // the target network's, or null
@@ -1053,6 +1411,18 @@ struct SmallOptArgs {
     const float* lossi;
     unsigned int out_grad_only;   // dueling head: only store the output layer's gradient
 };
+
+__device__ __forceinline__ float sum_splits(const float* src, size_t stride, unsigned int splits) {
+    float g = 0.f;
+    for (unsigned int z0 = 0; z0 < splits; z0 += 16u) {
+        float part[16];
+#pragma unroll
+        for (unsigned int z = 0; z < 16; ++z) part[z] = z0 + z < splits ? src[(z0 + z) * stride] : 0.f;
+#pragma unroll
+        for (unsigned int z = 0; z < 16; ++z) g += part[z];
+    }
+    return g;
+}
 
 __device__ __forceinline__ void small_opt_block(const SmallOptArgs& p, unsigned int block) {
     const unsigned int n3 = (p.G + 1u) * p.Ap, n1 = p.H * (p.D + 1u);
@@ -1062,12 +1432,7 @@ __device__ __forceinline__ void small_opt_block(const SmallOptArgs& p, unsigned 
         const unsigned int m = e / p.Ap, a = e - m * p.Ap;
         const size_t stride = (size_t)(p.G + 1u) * p.Ap;
         const float* src = p.part3 + e;
-        float part[16];
-#pragma unroll
-        for (unsigned int z = 0; z < 16; ++z) part[z] = z < p.splits ? src[z * stride] : 0.f;
-        float g = 0.f;
-#pragma unroll
-        for (unsigned int z = 0; z < 16; ++z) g += part[z];
+        const float g = sum_splits(src, stride, p.splits3);
         if (p.out_grad_only) {
             p.o.g[m < p.G ? p.oW3 + (size_t)m * p.Ap + a : p.ob3 + a] = g;
         } else if (m < p.G) {
@@ -1081,12 +1446,7 @@ __device__ __forceinline__ void small_opt_block(const SmallOptArgs& p, unsigned 
         const unsigned int f = e - n3, j = f / (p.D + 1u), d = f - j * (p.D + 1u);
         const size_t stride = (size_t)p.H * p.Dx;
         const float* src = p.part1 + (size_t)j * p.Dx + d;
-        float part[16];
-#pragma unroll
-        for (unsigned int z = 0; z < 16; ++z) part[z] = z < p.splits ? src[z * stride] : 0.f;
-        float g = 0.f;
-#pragma unroll
-        for (unsigned int z = 0; z < 16; ++z) g += part[z];
+        const float g = sum_splits(src, stride, p.splits1);
         if (d < p.D) {
             const bf16_bits h = bf16_bits_rne(opt_update(p.o, p.oW1 + (size_t)d * p.H + j, g, st));
             p.W1T[(size_t)j * p.Dp + d] = h;
@@ -1094,6 +1454,9 @@ __device__ __forceinline__ void small_opt_block(const SmallOptArgs& p, unsigned 
         } else {
             opt_update(p.o, p.ob1 + j, g, st);
         }
+    } else if (e < n3 + n1 + p.G) {
+        const unsigned int k = e - n3 - n1;
+        opt_update(p.o, p.ob2 + k, sum_splits(p.part_b2 + k, p.b2_stride, p.splits_b2), st);
     }
     if (block == 0) {
         __shared__ float wsum[4];
@@ -1109,8 +1472,9 @@ __device__ __forceinline__ void small_opt_block(const SmallOptArgs& p, unsigned 
     }
 }
 
-// The square layer's update from the K-split partial products of [dW ; db] (row R = bias):
-//   part[z][m][n], m <= R, n < N; the gradient is the sum over z, splits added in order.
+// The square layer's update from the K-split partial products of [dW ; db]:
+//   part[z][m][n], m <= R (row R, the bias, is not this kernel's part), n < N; the gradient is the sum
+//   over z, splits added in order.
 // A workgroup owns a kSqRows x 64 tile of W: a thread takes four consecutive columns of a row
 // (16-byte accesses to the partials and to the fp32 weight, gradient and moments), writes the
 // new weights' bf16 copy in the same orientation and parks it in LDS, from where the
@@ -1120,7 +1484,7 @@ struct SquareOptArgs {
     OptState o;
     unsigned int R, N, splits;
     const float* part;
-    size_t w_off, b_off;
+    size_t w_off;
     bf16_bits* wb;              // [R x N]
     bf16_bits* wbT;             // [N x R]
     bf16_bits* wbT_target;      // [N x R] of the target network, or null
@@ -1171,20 +1535,11 @@ __device__ __forceinline__ void square_opt_block(const SquareOptArgs& p, unsigne
         const unsigned int r = q * 16u + r0;
         const size_t at = (size_t)(m0 + r) * p.N + n0 + c4;
         const f32x4 w = opt_update4(p.o, p.w_off + at, g[q], st);
-        bf16_bits h[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) h[e] = bf16_bits_rne(w[e]);
         uint2 pk;
-        pk.x = (unsigned int)h[0] | ((unsigned int)h[1] << 16);
-        pk.y = (unsigned int)h[2] | ((unsigned int)h[3] << 16);
+        pk.x = bf16_pair(w[0], w[1]);
+        pk.y = bf16_pair(w[2], w[3]);
         *reinterpret_cast<uint2*>(p.wb + at) = pk;
         *reinterpret_cast<uint2*>(tile + r * TS + c4) = pk;
-    }
-    if (block_y == 0 && tid < 16) {                        // the bias: row R of the partials
-        const float* src = p.part + (size_t)p.R * p.N + n0 + c4;
-        f32x4 gb = *reinterpret_cast<const f32x4*>(src);
-        for (unsigned int z = 1; z < p.splits; ++z) gb += *reinterpret_cast<const f32x4*>(src + z * zs);
-        opt_update4(p.o, p.b_off + n0 + c4, gb, st);
     }
     __syncthreads();
     // transposed copy: kSqRows / 2 lanes write one column of the tile as pairs of rows
@@ -1275,6 +1630,61 @@ hipError_t second_layer(hipStream_t st, const bf16_bits* H1, unsigned int rows, 
                                            1, hi, m_split);
 }
 
+template <class S>
+hipError_t configure_grad_back() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(grad_back_kernel<S>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::kLds);
+}
+
+// How the backward half of a step is launched.
+WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G) {
+    WidePlan p;
+    const unsigned int Bp = (B + 127u) / 128u * 128u;
+    p.merged = !few_tiles(B, H);
+    p.large = false;
+    p.k2 = Bp;
+    if (!p.merged) {
+        p.splits3 = p.splits1 = batch_splits(Bp);
+        p.splits2 = square_splits_for(Bp, H, G);
+        return p;
+    }
+    // The tiles' height and the splits of dW2's contraction: those whose launch ends first.  A compute unit holds one
+    // workgroup; one takes about 5 us (dZ1's, with the first layer's gradient) or 3 us and, per slice of 64 of its
+    // contraction, 0.75 us in 256 x 128 tiles and 0.4 us in 128 x 128; a split's partials are written and read at 4.5 TB/s.
+    // us per step in large, small tiles (27 inputs, 30 actions): 1024-1024 at batch 4096 83.7, 123.4, 3000 77.5, 91.4,
+    // 2048 71.7, 63.2; 768-768 at 3000 63.9, 67.1; 512-512 at 4096 60.7, 52.0; 192-1024 at 3000 79.0, 73.0.
+    double best = 0.;
+    for (int large = 0; large < 2; ++large) {
+        const unsigned int bm = large ? 256u : 128u;
+        const double slice = large ? 0.75 : 0.4;
+        auto tiles = [bm](unsigned int m, unsigned int n) { return ((m + bm - 1u) / bm) * ((n + 127u) / 128u); };
+        const unsigned int rows = std::min((B + bm - 1u) / bm, kGbMaxSplits), rounds = ((B + bm - 1u) / bm + rows - 1u) / rows;
+        for (unsigned int s = 1; s <= 16u && (s == 1 || B / s >= 256u); s *= 2u) {
+            const unsigned int k = ((B + s - 1u) / s + 63u) / 64u * 64u, splits = (B + k - 1u) / k;
+            const double t_dz = rounds * (5. + G / 64u * slice), t_dw = 3. + k / 64u * slice;
+            std::priority_queue<double, std::vector<double>, std::greater<double>> free_at(std::greater<double>(), std::vector<double>(256, 0.));
+            double end = 0.;
+            const unsigned int n_dz = rows * ((H + 127u) / 128u), n = n_dz + tiles(H, G) * splits;
+            for (unsigned int i = 0; i < n; ++i) {
+                const double t = free_at.top() + (i < n_dz ? t_dz : t_dw);
+                free_at.pop();
+                free_at.push(t);
+                end = std::max(end, t);
+            }
+            end += 8e-6 * splits * H * G / 4.5;
+            if (best != 0. && end >= best) continue;
+            best = end;
+            p.large = large != 0;
+            p.splits2 = splits;
+            p.k2 = k;
+        }
+    }
+    const unsigned int bm = p.large ? 256u : 128u;
+    p.splits1 = std::min((B + bm - 1u) / bm, kGbMaxSplits);
+    p.splits3 = std::min((B + kTgRows - 1u) / kTgRows, kTgMaxSplits);
+    return p;
+}
+
 bf16_bits host_bf16(float f) {
     unsigned int u;
     memcpy(&u, &f, 4);
@@ -1285,7 +1695,7 @@ bf16_bits host_bf16(float f) {
 
 }  // namespace
 
-unsigned int square_splits(unsigned int Bp, unsigned int H, unsigned int G) { return square_splits_for(Bp, H, G); }
+WidePlan wide_plan(unsigned int B, unsigned int H, unsigned int G) { return plan_for(B, H, G); }
 
 // Two hidden layers of one width, or of two.  This step is the faster one at every size measured (27
 // inputs, 30 actions, one new experience a step, us per step layer by layer -> this: 64-256 at batch 8
@@ -1301,9 +1711,10 @@ bool wide_step_supported(const train_config& cfg, const replay* rp_) {
 hipError_t wide_configure() {
     hipError_t ec = configure_gemm<128, 128, 32, 2, 2, EpiForward>();
     if (ec == hipSuccess) ec = configure_gemm<128, 128, 64, 2, 2, EpiForward>();
-    if (ec == hipSuccess) ec = configure_gemm<128, 64, 64, 2, 2, EpiMask>();
     if (ec == hipSuccess) ec = configure_grad_products<true>();
     if (ec == hipSuccess) ec = configure_grad_products<false>();
+    if (ec == hipSuccess) ec = configure_grad_back<GbLarge>();
+    if (ec == hipSuccess) ec = configure_grad_back<GbSmall>();
     return ec;
 }
 
@@ -1337,7 +1748,27 @@ static bool rows_in_one_launch(const trainer* t) { return !t->wt || t->B % 128 =
 
 // (gather, three forward products, TD errors, the first layer's error, the gradients, the update; what
 // train_create adds itself: the dueling head's update, a draw in a launch of its own)
-unsigned int wide_step_kernels(const trainer* t) { return rows_in_one_launch(t) ? 8u : 11u; }
+unsigned int wide_step_kernels(const trainer* t) {
+    return (rows_in_one_launch(t) ? 8u : 11u) - (t->plan.merged ? 1u : 0u);
+}
+
+template <class S>
+static hipError_t launch_grad_back(trainer* t, hipStream_t st, const WidePlan& plan, const bf16_bits* X, const bf16_bits* H1,
+                                   const bf16_bits* dZ2) {
+    const unsigned int B = t->B, H = t->H, G = t->Hb, D = t->cfg.state_dim;
+    GradBackArgs a;
+    unsigned int n_dw = 0;
+    // (rows of workgroups: at most plan.splits1, each with every so many'th tile)
+    bool ok = gemm_args<S::BM, S::BN, 64>(dZ2, G, t->wd.W2, G, std::min(B, plan.splits1 * S::BM), H, G, 1, nullptr, 0, &a.dz, &a.n_dz);
+    ok = ok && gemm_args<S::BM, S::BN, 64>(H1, H, dZ2, G, H, G, plan.splits2 * plan.k2, plan.splits2, nullptr, 0, &a.dw, &n_dw);
+    if (!ok) return hipErrorInvalidValue;
+    a.dz.M = B;
+    a.dw.batch = B;
+    a.X = X; a.H1 = H1; a.D = D; a.Dp = t->Dp; a.Dx = (D + 1 + 31) / 32 * 32;
+    a.part1 = t->wd.part1; a.part2 = t->wd.part2;
+    hipLaunchKernelGGL(grad_back_kernel<S>, dim3(a.n_dz + n_dw), dim3(S::kThreads), S::kLds, st, a);
+    return hipGetLastError();
+}
 
 // Enqueue every kernel of one executed step after the append.
 hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bool sample) {
@@ -1410,74 +1841,93 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
     }
     if (e != hipSuccess) return e;
     if (!one_launch) ++n;
-    // targets, TD errors, loss terms, dL/dQ and dZ2
-    {
-        TdArgs a;
+    const WidePlan& plan = t->plan;
+    const unsigned int Dx = (D + 1 + 31) / 32 * 32;
+    if (plan.merged) {
+        TdGradArgs a;
         a.B = B; a.G = G; a.A = A; a.Ap = Ap;
+        a.kz = 0; a.part_stride = 0; a.parts = nullptr; a.b3 = a.b3_hi = nullptr;
         a.Q = t->Q; a.act = t->act; a.rew = t->rew; a.term = t->term;
         a.gamma = t->cfg.gamma; a.loss_kind = t->cfg.loss; a.beta1 = t->cfg.beta1; a.beta2 = t->cfg.beta2;
         a.y = t->y; a.delta = t->delta; a.lossi = t->lossi;
-        a.dQ = w.dQ; a.W3T = w.W3T; a.H2 = H2; a.dZ2 = dZ2;
+        a.W3T = w.W3T; a.H2 = H2; a.dZ2 = dZ2; a.part3 = w.part3; a.part2b = w.part2b;
         a.ctr = t->ctr;
-        hipLaunchKernelGGL(td_dz_kernel, dim3((B + kTdRows - 1) / kTdRows, (G + kTdCols - 1) / kTdCols), dim3(256),
-                           0, st, a);
+        hipLaunchKernelGGL(td_grad_kernel<false>, dim3(plan.splits3, (G + kTgCols - 1) / kTgCols, Ap / 32), dim3(kTgThreads), 0, st, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         ++n;
-    }
-    // dZ1 = (dZ2 W2^T) masked by the first ReLU; uses W2 before its update
-    if (few_tiles(B, H)) {
-        const SkinnyArgs a{dZ2, G, w.W2, G, B, H, G, w.W2, ~0u};
-        hipLaunchKernelGGL((skinny_nt_kernel<8, SkinnyMask>), dim3((B + 31) / 32, H / 32), dim3(512), 0, st, a,
+        e = plan.large ? launch_grad_back<GbLarge>(t, st, plan, X, H1, dZ2) : launch_grad_back<GbSmall>(t, st, plan, X, H1, dZ2);
+        if (e != hipSuccess) return e;
+        ++n;
+    } else {
+        // targets, TD errors, loss terms, dL/dQ and dZ2
+        {
+            TdArgs a;
+            a.B = B; a.G = G; a.A = A; a.Ap = Ap;
+            a.Q = t->Q; a.act = t->act; a.rew = t->rew; a.term = t->term;
+            a.gamma = t->cfg.gamma; a.loss_kind = t->cfg.loss; a.beta1 = t->cfg.beta1; a.beta2 = t->cfg.beta2;
+            a.y = t->y; a.delta = t->delta; a.lossi = t->lossi;
+            a.dQ = w.dQ; a.W3T = w.W3T; a.H2 = H2; a.dZ2 = dZ2;
+            a.ctr = t->ctr;
+            hipLaunchKernelGGL(td_dz_kernel, dim3((B + kTdRows - 1) / kTdRows, (G + kTdCols - 1) / kTdCols), dim3(256),
+                               0, st, a);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            ++n;
+        }
+        // dZ1 = (dZ2 W2^T) masked by the first ReLU; uses W2 before its update
+        const SkinnyArgs za{dZ2, G, w.W2, G, B, H, G, w.W2, ~0u};
+        hipLaunchKernelGGL((skinny_nt_kernel<8, SkinnyMask>), dim3((B + 31) / 32, H / 32), dim3(512), 0, st, za,
                            SkinnyMask{H1, dZ1, H});
         e = hipGetLastError();
-    } else {
-        e = launch_gemm<128, 64, 64, 2, 2>(st, dZ2, G, w.W2, G, B, H, G, EpiMask{H1, dZ1, H, B, H});
-    }
-    if (e != hipSuccess) return e;
-    ++n;
-    // the three weight-gradient products, K-split partials each, in one launch:
-    //   [dW2 ; db2] (row H);  [dW3 ; db3] (row G) with the three parts of dL/dQ side by side;
-    //   [dW1^T | db1] (column D)
-    const unsigned int splits = batch_splits(Bp);
-    const unsigned int splits2 = square_splits_for(Bp, H, G);
-    const unsigned int Dx = (D + 1 + 31) / 32 * 32;
-    {
-        GemmArgs g2, g3, g1;
-        unsigned int n2 = 0, n3 = 0, n1 = 0;
-        const bool narrow1 = Dp == 32;
-        bool ok = gemm_args<128, 128, 64>(H1, H, dZ2, G, H, G, Bp, splits2, nullptr, 0, &g2, &n2);
-        ok = ok && gemm_args<128, 96, 64>(H2, G, w.dQ, 3 * Ap, G, 3 * Ap, Bp, splits, nullptr, 0, &g3, &n3);
-        ok = ok && (narrow1 ? gemm_args<128, 32, 64>(dZ1, H, X, Dp, H, Dp, Bp, splits, nullptr, 0, &g1, &n1)
-                            : gemm_args<128, 128, 64>(dZ1, H, X, Dp, H, Dp, Bp, splits, nullptr, 0, &g1, &n1));
-        if (!ok) return hipErrorInvalidValue;
-        g2.batch = g3.batch = g1.batch = B;
-        const EpiSquare e2{w.part2, H, G};
-        const EpiOutput e3{w.part3, G, Ap};
-        const EpiFirst e1{w.part1, H, D, Dx};
-        constexpr size_t lds = gemm_tn_lds_bytes<128, 128>();
-        const dim3 grid(n2 + n3 + n1), block(kTnThreads);
-        if (narrow1)
-            hipLaunchKernelGGL(grad_products_kernel<true>, grid, block, lds, st, g2, e2, n2, g3, e3, n3, g1, e1);
-        else
-            hipLaunchKernelGGL(grad_products_kernel<false>, grid, block, lds, st, g2, e2, n2, g3, e3, n3, g1, e1);
-        e = hipGetLastError();
         if (e != hipSuccess) return e;
         ++n;
+        // the three weight-gradient products, K-split partials each, in one launch:
+        //   [dW2 ; db2] (row H);  [dW3 ; db3] (row G) with the three parts of dL/dQ side by side;
+        //   [dW1^T | db1] (column D)
+        const unsigned int splits = plan.splits1, splits2 = plan.splits2;
+        {
+            GemmArgs g2, g3, g1;
+            unsigned int n2 = 0, n3 = 0, n1 = 0;
+            const bool narrow1 = Dp == 32;
+            bool ok = gemm_args<128, 128, 64>(H1, H, dZ2, G, H, G, Bp, splits2, nullptr, 0, &g2, &n2);
+            ok = ok && gemm_args<128, 96, 64>(H2, G, w.dQ, 3 * Ap, G, 3 * Ap, Bp, splits, nullptr, 0, &g3, &n3);
+            ok = ok && (narrow1 ? gemm_args<128, 32, 64>(dZ1, H, X, Dp, H, Dp, Bp, splits, nullptr, 0, &g1, &n1)
+                                : gemm_args<128, 128, 64>(dZ1, H, X, Dp, H, Dp, Bp, splits, nullptr, 0, &g1, &n1));
+            if (!ok) return hipErrorInvalidValue;
+            g2.batch = g3.batch = g1.batch = B;
+            const EpiSquare e2{w.part2, H, G};
+            const EpiOutput e3{w.part3, G, Ap};
+            const EpiFirst e1{w.part1, H, D, Dx};
+            constexpr size_t lds = gemm_tn_lds_bytes<128, 128>();
+            const dim3 grid(n2 + n3 + n1), block(kTnThreads);
+            if (narrow1)
+                hipLaunchKernelGGL(grad_products_kernel<true>, grid, block, lds, st, g2, e2, n2, g3, e3, n3, g1, e1);
+            else
+                hipLaunchKernelGGL(grad_products_kernel<false>, grid, block, lds, st, g2, e2, n2, g3, e3, n3, g1, e1);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            ++n;
+        }
     }
     // all three layers' update, mean loss, step counter
     {
         SquareOptArgs q;
-        q.o = o; q.R = H; q.N = G; q.splits = splits2; q.part = w.part2;
-        q.w_off = t->oW2; q.b_off = t->ob2; q.wb = w.W2; q.wbT = w.W2T; q.wbT_target = w.W2T_t;
+        q.o = o; q.R = H; q.N = G; q.splits = plan.splits2; q.part = w.part2;
+        q.w_off = t->oW2; q.wb = w.W2; q.wbT = w.W2T; q.wbT_target = w.W2T_t;
         SmallOptArgs a;
-        a.o = o; a.splits = splits; a.H = H; a.G = G; a.D = D; a.Dp = Dp; a.Dx = Dx; a.Ap = Ap; a.B = B;
+        a.o = o; a.splits3 = plan.splits3; a.splits1 = plan.splits1; a.H = H; a.G = G; a.D = D; a.Dp = Dp; a.Dx = Dx; a.Ap = Ap; a.B = B;
         a.part3 = w.part3; a.part1 = w.part1;
+        // (the second layer's bias: row H of each split's partials, or rows of its own)
+        a.part_b2 = plan.merged ? w.part2b : w.part2 + (size_t)H * G;
+        a.splits_b2 = plan.merged ? plan.splits3 * (Ap / 32) : plan.splits2;
+        a.b2_stride = plan.merged ? G : (size_t)(H + 1) * G;
+        a.ob2 = t->ob2;
         a.oW1 = t->oW1; a.ob1 = t->ob1; a.oW3 = t->oW3; a.ob3 = t->ob3;
         a.W1T = w.W1T; a.W3T = w.W3T; a.W1T_target = w.W1T_t; a.W3T_target = w.W3T_t;
         a.ctr = t->ctr; a.lossi = t->lossi;
         a.out_grad_only = t->dueling ? 1u : 0u;
-        const unsigned int elems = (G + 1) * Ap + H * (D + 1);
+        const unsigned int elems = (G + 1) * Ap + H * (D + 1) + G;
         const unsigned int own = (G / 64) * (H / kSqRows) + (elems + 255) / 256;
         if (t->rec_next) {
             // (recording a run of steps: this launch also gathers the next step's batch; the rest of

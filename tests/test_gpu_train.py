@@ -1219,6 +1219,28 @@ def test_mixed_precision_products_with_few_tiles(B, H, H2, batch, target_sync):
         assert pr.step(synth.take(rows, k, k + 1), compare=True) == 0
 
 
+@pytest.mark.parametrize("D,H,H2,A,batch,target_sync,dueling", [
+    (27, 576, 192, 30, 1030, 0, False),   # widths and a batch that end inside tiles of 128 x 128
+    (33, 1024, 64, 40, 600, 3, True),     # one slice of contraction; two blocks of states and of actions
+    (96, 512, 320, 3, 1100, 0, False),    # three blocks of states, the bias behind the last
+    (27, 64, 64, 5, 8300, 0, False),      # 256 x 128 tiles, more rows of them than rows of workgroups
+    (31, 1024, 64, 33, 9000, 0, True),
+])
+def test_mixed_precision_backward_in_two_launches(B, D, H, H2, A, batch, target_sync, dueling):
+    """Large steps form the output layer's gradient with the TD errors, and the first layer's in the launch
+    of the two large backward products; tolerances of the other mixed-precision cases."""
+    oracle.set_threads(16)
+    try:
+        rows = synth.experiences(batch + 60, D, A, 0.05, seed=79, state_dtype="bf16")
+        pr = Pair(B, capacity=batch + 30, D=D, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=5, dtype="bf16",
+                  appends=1, target_sync=target_sync, dueling=dueling, lr=1e-3)
+        pr.append_only(synth.take(rows, 0, batch + 30))
+        for k in range(batch + 30, batch + 34):
+            assert pr.step(synth.take(rows, k, k + 1), compare=True) == 0
+    finally:
+        oracle.set_threads(1)
+
+
 @pytest.mark.parametrize("dtype,H,H2,batch,n", [
     ("bf16", 8192, 64, 131_200, 100),    # H1, which the second layer reads, is 4.3 GB
     ("bf16", 64, 8192, 262_200, 100),    # so is dZ2, which the first layer's error is formed from
