@@ -348,7 +348,7 @@ bool ws_layout(const train_config* c, WsLayout* L) {
     L->part3 = take(mixed ? plan.splits3 * (G + 1) * L->Ap * 4 : 0);
     L->part1 = take(mixed ? plan.splits1 * H * Dx * 4 : 0);
     L->part2 = take(mixed ? plan.splits2 * (H + 1) * G * 4 : 0);
-    L->part2b = take(mixed && plan.merged ? plan.splits3 * (L->Ap / 32) * G * 4 : 0);
+    L->part2b = take(mixed && plan.merged ? plan.splits_b2 * G * 4 : 0);
     L->total = o;
     return true;
 }

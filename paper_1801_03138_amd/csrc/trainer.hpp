@@ -130,10 +130,11 @@ inline void set_adam_step(RowArgs& a, unsigned long long t_after, float beta1, f
 
 
 // Mixed-precision step: how its backward half is launched, and its partial products: in the two launches of large steps, and
-// there in large tiles; splits of the gradients of the output, first and second layer; rows per split of the last.
+// there in large tiles; splits of the gradients of the output, first and second layer; rows per split of the last; splits of
+// the second layer's bias.
 struct WidePlan {
     bool merged, large;
-    unsigned int splits3, splits1, splits2, k2;
+    unsigned int splits3, splits1, splits2, k2, splits_b2;
 };
 
 // Buffers of the mixed-precision step on MFMA (bf16 bit patterns; H, G: widths of the two hidden
@@ -145,7 +146,7 @@ struct WideBuffers {
     float* part3;                            // K-split partials [splits][G+1][Ap] of [dW3 ; db3]
     float* part1;                            // K-split partials [splits][H][Dx] of [dW1^T | db1]
     float* part2;                            // K-split partials [splits][H+1][G] of [dW2 ; db2]
-    float* part2b;                           // large steps: partials [splits x blocks of 32 actions][G] of db2
+    float* part2b;                           // large steps: partials [splits][G] of db2
 };
 
 // train_steps runs several steps per graph launch (a launch costs about 5 us of GPU idle time:

@@ -10,10 +10,9 @@
 // outputs: they are split along the batch over several workgroups per tile, and the optimizer kernel adds
 // the fp32 partial products up.
 //
-// The backward half of a step has two forms (WidePlan).  Large steps form the gradients of the output
-// layer and of the second bias beside the TD errors, and that of the first layer beside its error, in two
-// launches (td_grad_kernel, grad_back_kernel); small ones have a launch for each of the TD errors, the first layer's error
-// and all gradients.
+// What follows the second layer has two forms (WidePlan).  Large steps have two launches: output layer, TD
+// errors and the second layer's error (head_kernel), then the first layer's error and all gradients
+// (grad_back_kernel); small ones a launch for each of output layer, TD errors, first layer's error and gradients.
 //
 // Paper: Integration with Reinforcement Learning Algorithm (train step with no host inputs),
 // Deep Q-Network Model (update equation).
@@ -951,64 +950,56 @@ __global__ __launch_bounds__(256) void td_dz_kernel(TdArgs p) {
 }
 
 // ----------------------------------------------------------------------------------------
-// The backward half of large steps (grad_back_kernel's shapes), in two launches.
+// The backward half of large steps, in two launches.
 //
-// td_grad_kernel: targets, TD errors, loss terms, dZ2, and what can be formed from dZ2 and H2 while they
-// are in registers: db2 (column sums of dZ2) and [dW3 ; db3].  A workgroup owns 128 columns and every
-// gridDim.x-th chunk of 128 batch rows, sixteen lanes to a row.  The lanes of a row work out
-//   y_i = r_i + gamma (1 - term_i) max_a Q(s'_i, a), delta_i = y_i - Q(s_i, a_i), the loss term and
-//   g_i = dL/dQ(s_i, a_i) among themselves while their share of H2 is on its way; then
-//   dZ2[i][k] = g_i W3[k][a_i] 1[H2[i][k] > 0] goes out, 16 bytes a lane.
-// The chunk's H2 and its dL/dQ (32 actions of it: gridDim.z) go to LDS, the latter in three bf16 parts whose
-// sum is the fp32 number, and dW3 = H2^T dL/dQ is contracted from there.  dL/dQ never goes to memory and
-// H2 is read once (a product of its own read it again, 8 MB at batch 4096 and 1024 units).  A row's dZ2 is the
-// business of the workgroups of its action's block, which hold that block's columns of W3 in LDS: no load
-// waits for an action.
+// head_kernel: the output layer, Q = H2 W3 + b3, targets, TD errors, loss terms, dL/dQ, dZ2 and db2.  A workgroup has
+// whole rows, 16 of S and the same experiences' 16 of S' (and every gridDim.x-th such group), and its eight
+// wavefronts split the hidden units, 32 at a time: a lane's share of H2 is the operand of the output layer's 16x16x32
+// MFMA and afterwards the mask of dZ2.  H2 is read once, and every load of a group is requested before the first use:
+// the launch is bound by memory (16.8 MB of H2 in, 8.4 MB of dZ2 out at batch 4096 and 1024 units).
+//   y_i = r_i + gamma (1 - term_i) max_a Q(s'_i, a), delta_i = y_i - Q(s_i, a_i), g_i = dL/dQ(s_i, a_i),
+//   dZ2[i][k] = g_i W3[k][a_i] 1[H2[i][k] > 0]
+// dL/dQ is stored in three bf16 parts whose sum is the fp32 number, so that the output layer's weight gradient loses
+// nothing to the split.
+// As two launches, output layer and the rest, 7.5 + 9.5 us there (with the output layer's gradient in the second).
 // ----------------------------------------------------------------------------------------
-constexpr unsigned int kTgRows = 128, kTgCols = 128, kTgThreads = 512, kTgMaxSplits = 32;
+constexpr unsigned int kHeadThreads = 512, kHeadRows = 16, kHeadMaxGroups = 512;
 
-struct TdGradArgs {
+struct HeadStepArgs {
     unsigned int B, G, A, Ap;
-    // kz = 0: Q is complete, [2B x Ap].  Otherwise it comes as kz partial products, part_stride elements apart and
-    // without the bias (b3 for the rows of s, b3_hi for those of s'); this kernel adds them up and writes Q.
-    unsigned int kz;
-    size_t part_stride;
-    const float* parts;
-    const float *b3, *b3_hi;
-    float* Q;
     const int* act;
     const float* rew;
     const unsigned char* term;
     float gamma;
     unsigned int loss_kind;
     float beta1, beta2;
+    const float *b3, *b3_hi;             // of the rows of S and of S'
+    const bf16_bits *W3T, *W3T_hi;       // [Ap x G], likewise
+    const bf16_bits* H2;                 // [2B x G]
+    float* Q;                            // [2B x Ap]
     float *y, *delta, *lossi;
-    const bf16_bits* W3T;        // [Ap x G]
-    const bf16_bits* H2;         // [2B x G]
-    bf16_bits* dZ2;              // [B x G]
-    float* part3;                // [splits][G + 1][Ap], row G: db3
-    float* part2b;               // [splits x blocks of 32 actions][G]: db2
+    bf16_bits* dQ;                       // [B x 3 Ap]
+    bf16_bits* dZ2;                      // [B x G]
+    float* part2b;                       // [workgroups][G]: db2
     TrainCounters* ctr;
 };
 
-// v of the lane N places round the row of 16 lanes
-template <int N>
-__device__ __forceinline__ float row16_ror(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xf, 0xf, false));
+// v of another lane of the row of 16
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
 }
 
-template <bool PARTS>
-__global__ __launch_bounds__(kTgThreads) void td_grad_kernel(TdGradArgs p) {
-    constexpr unsigned int PASSES = kTgRows / 32u, DQ = kTgRows * 256u;   // dL/dQ's place behind H2's
-    __shared__ __attribute__((aligned(16))) unsigned char lds[kTgRows * (256u + 192u)];
-    __shared__ __attribute__((aligned(16))) unsigned char w3s[32u * 256u];   // W3's columns of this workgroup
-    __shared__ float colsum[8][kTgCols];
-    const unsigned int tid = threadIdx.x, lane = tid & 63u, part = tid & 15u, row16 = tid >> 4;
-    const unsigned int wave = __builtin_amdgcn_readfirstlane(tid >> 6), t = wave & 3u, h = wave >> 2;
-    const unsigned int c0 = blockIdx.y * kTgCols, k0 = c0 + part * 8u, kc = k0 < p.G ? k0 : 0u;
-    const unsigned int a0 = blockIdx.z * 32u;                // this workgroup's block of actions
-    const bool stripe0 = blockIdx.z == 0 && blockIdx.y == 0;
-    if (stripe0 && blockIdx.x == 0 && tid == 0) {
+// SW: 32-unit steps a wavefront holds in registers; layers wider than 256 SW units go in several passes, which read H2
+// once more.  TGT: the rows of S' have weights of their own.
+template <int SW, bool TGT>
+__global__ __launch_bounds__(kHeadThreads) void head_kernel(HeadStepArgs p) {
+    constexpr unsigned int LD = 36, NB = TGT ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) float part[8][2][kHeadRows][LD];   // [wavefront][S, S'][row][action]
+    __shared__ float best_s[kHeadRows], qa_s[kHeadRows], g_s[kHeadRows];
+    const unsigned int tid = threadIdx.x, lane = tid & 63u, r16 = lane & 15u, q16 = lane >> 4;
+    const unsigned int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (blockIdx.x == 0 && tid == 0) {
         // (running products beta^t in double precision: no power function on the device)
         const double pw1 = p.ctr->pw1 * (double)p.beta1, pw2 = p.ctr->pw2 * (double)p.beta2;
         p.ctr->adam_t = p.ctr->adam_t + 1;
@@ -1017,208 +1008,163 @@ __global__ __launch_bounds__(kTgThreads) void td_grad_kernel(TdGradArgs p) {
         p.ctr->c1 = (float)(1.0 - pw1);
         p.ctr->c2 = (float)(1.0 - pw2);
     }
-    const TnLane l(lane);
-    f32x16 acc[3], sum[3];
-#pragma unroll
-    for (int s = 0; s < 3; ++s)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[s][v] = sum[s][v] = 0.f;
-    float cs[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) cs[e] = 0.f;
-    const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
-    const bool with_sums = blockIdx.y == 0 && t == 0;
-    // a row's Q-values: four neighbouring actions a lane, and every second partial product
-    const unsigned int quad = part & 7u, zsel = part >> 3, nz = PARTS ? p.kz : 1u;
-    const float* const q_in = PARTS ? p.parts : p.Q;
-    const u32x4 w3 = *reinterpret_cast<const u32x4*>(p.W3T + (size_t)(a0 + row16) * p.G + kc);
-
-    const unsigned int chunks = (p.B + kTgRows - 1u) / kTgRows;
-    for (unsigned int c = blockIdx.x; c < chunks; c += gridDim.x) {
-        // (all loads of a chunk are requested before the first use)
-        unsigned int row[PASSES], ai[PASSES];
-        u32x4 hv[PASSES];
-        float best[PASSES], qa[PASSES], rew[PASSES];
-        bool term[PASSES];
-#pragma unroll
-        for (unsigned int q = 0; q < PASSES; ++q) {
-            row[q] = c * kTgRows + q * 32u + row16;
-            const unsigned int i = min(row[q], p.B - 1u);
-            ai[q] = min((unsigned int)p.act[i], p.A - 1u);   // an out-of-range action must not turn into a wild address
-            rew[q] = p.rew[i];
-            term[q] = p.term[i] != 0;
-            hv[q] = *reinterpret_cast<const u32x4*>(p.H2 + (size_t)i * p.G + kc);
-            best[q] = -INFINITY;
-            qa[q] = 0.f;
-        }
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    const unsigned int groups = (p.B + kHeadRows - 1u) / kHeadRows, passes = (p.G + 256u * SW - 1u) / (256u * SW);
+    for (unsigned int grp = blockIdx.x; grp < groups; grp += gridDim.x) {
+        // this lane's experience (the operands' row), and the same again for the rows beyond the batch
+        const unsigned int row = grp * kHeadRows + r16, i = min(row, p.B - 1u);
+        const unsigned int ai = min((unsigned int)p.act[i], p.A - 1u);   // an out-of-range action must not turn into a wild address
+        const float rew = p.rew[i];
+        const bool term = p.term[i] != 0;
+        const bf16_bits* const h_s = p.H2 + (size_t)i * p.G + 8u * q16;
+        const bf16_bits* const h_n = h_s + (size_t)p.B * p.G;
+        auto at = [&](unsigned int pass, int s) { return pass * 256u * SW + (wave + 8u * s) * 32u; };   // a step's first unit
+        u32x4 hs[SW];
+        float best = -INFINITY;
         for (unsigned int ab = 0; ab < p.Ap; ab += 32u) {
-            f32x4 qs[PASSES], qn[PASSES];
+            f32x4 c[2][2];
 #pragma unroll
-            for (unsigned int q = 0; q < PASSES; ++q) qs[q] = qn[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-            constexpr unsigned int ZU = PARTS ? 2u : 1u;     // partial products requested at a time, per lane
-            for (unsigned int z0 = 0; z0 < nz; z0 += 2u * ZU) {
-                f32x4 xs[ZU][PASSES], xn[ZU][PASSES];
+            for (int x = 0; x < 2; ++x)
 #pragma unroll
-                for (unsigned int u = 0; u < ZU; ++u) {
-                    const unsigned int z = z0 + 2u * u + zsel;
-                    const float* at = q_in + (size_t)(z < nz ? z : 0u) * p.part_stride + ab + 4u * quad;
+                for (int j = 0; j < 2; ++j) c[x][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (unsigned int pass = 0; pass < passes; ++pass) {
+                u32x4 hn[SW], w[NB][2][SW];
 #pragma unroll
-                    for (unsigned int q = 0; q < PASSES; ++q) {
-                        const size_t i = min(row[q], p.B - 1u);
-                        xs[u][q] = *reinterpret_cast<const f32x4*>(at + i * p.Ap);
-                        xn[u][q] = *reinterpret_cast<const f32x4*>(at + (p.B + i) * p.Ap);
+                for (int s = 0; s < SW; ++s) {
+                    const unsigned int k = at(pass, s), kc = k < p.G ? k : 0u;   // (G is a multiple of 32)
+                    hs[s] = *reinterpret_cast<const u32x4*>(h_s + kc);
+                    hn[s] = *reinterpret_cast<const u32x4*>(h_n + kc);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const size_t wa = (size_t)(ab + 16u * j + r16) * p.G + kc + 8u * q16;
+                        w[0][j][s] = *reinterpret_cast<const u32x4*>(p.W3T + wa);
+                        if constexpr (TGT) w[NB - 1][j][s] = *reinterpret_cast<const u32x4*>(p.W3T_hi + wa);
                     }
                 }
 #pragma unroll
-                for (unsigned int u = 0; u < ZU; ++u)
+                for (int s = 0; s < SW; ++s) {
+                    const bool in = at(pass, s) < p.G;
 #pragma unroll
-                    for (unsigned int q = 0; q < PASSES; ++q) {
-                        if (PARTS && z0 + 2u * u + zsel >= nz) continue;
-                        qs[q] += xs[u][q];
-                        qn[q] += xn[u][q];
-                    }
-            }
-            f32x4 bs = {0.f, 0.f, 0.f, 0.f}, bn = bs;
-            if constexpr (PARTS) {
-                bs = *reinterpret_cast<const f32x4*>(p.b3 + ab + 4u * quad);
-                bn = *reinterpret_cast<const f32x4*>(p.b3_hi + ab + 4u * quad);
-            }
-#pragma unroll
-            for (unsigned int q = 0; q < PASSES; ++q) {
-                if constexpr (PARTS) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        qs[q][e] = (qs[q][e] + row16_ror<8>(qs[q][e])) + bs[e];
-                        qn[q][e] = (qn[q][e] + row16_ror<8>(qn[q][e])) + bn[e];
-                    }
-                    if (stripe0 && row[q] < p.B) {
-                        const size_t i = zsel ? (size_t)p.B + row[q] : row[q];
-                        *reinterpret_cast<f32x4*>(p.Q + i * p.Ap + ab + 4u * quad) = zsel ? qn[q] : qs[q];
+                    for (int j = 0; j < 2; ++j) {
+                        c[0][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(in ? hs[s] : zero), as_bf16x8(in ? w[0][j][s] : zero), c[0][j], 0, 0, 0);
+                        c[1][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(in ? hn[s] : zero), as_bf16x8(in ? w[NB - 1][j][s] : zero), c[1][j], 0, 0, 0);
                     }
                 }
-                const unsigned int mine = ai[q] - (ab + 4u * quad);
-#pragma unroll
-                for (unsigned int e = 0; e < 4; ++e) {
-                    if (ab + 4u * quad + e < p.A) best[q] = fmaxf(best[q], qn[q][e]);
-                    if (mine == e) qa[q] = qs[q][e];
-                }
             }
-        }
-        if (c != blockIdx.x) {
-            __syncthreads();                                 // (the last chunk's operands have been read)
-        } else {
-            *reinterpret_cast<u32x4*>(w3s + row16 * 256u + part * 16u) = w3;
+            if (ab || grp != blockIdx.x) __syncthreads();    // (what is there has been read)
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) part[wave][x][4u * q16 + v][16u * j + r16] = c[x][j][v];
             __syncthreads();
-        }
+            // sixteen threads a row, two actions each: first the rows of S, then those of S'
+            const unsigned int x = tid >> 8, r = (tid >> 4) & 15u, a = ab + 2u * (tid & 15u);
+            typedef float f32x2 __attribute__((ext_vector_type(2)));
+            f32x2 qv = {0.f, 0.f};
 #pragma unroll
-        for (unsigned int q = 0; q < PASSES; ++q) {
-            const unsigned int i = min(row[q], p.B - 1u), r = q * 32u + row16;
-            const bool in = row[q] < p.B, owner = ai[q] >> 5 == blockIdx.z;
-            // (lanes 8 apart hold the same)
-            best[q] = fmaxf(best[q], row16_ror<4>(best[q]));
-            best[q] = fmaxf(best[q], row16_ror<2>(best[q]));
-            best[q] = fmaxf(best[q], row16_ror<1>(best[q]));
-            qa[q] += row16_ror<4>(qa[q]);
-            qa[q] += row16_ror<2>(qa[q]);
-            qa[q] += row16_ror<1>(qa[q]);
-            const u32x4 wv = *reinterpret_cast<const u32x4*>(w3s + (ai[q] & 31u) * 256u + part * 16u);
-            const float y = rew[q] + (term[q] ? 0.f : p.gamma * best[q]);
-            const float d = y - qa[q];
-            float li, slope;
-            if (p.loss_kind == RP_MSE || fabsf(d) <= 1.f) {
-                li = 0.5f * d * d;
-                slope = d;
-            } else {
-                li = fabsf(d) - 0.5f;
-                slope = d > 0.f ? 1.f : -1.f;
+            for (int w = 0; w < 8; ++w) qv += *reinterpret_cast<const f32x2*>(&part[w][x][r][2u * (tid & 15u)]);
+            qv += *reinterpret_cast<const f32x2*>((x ? p.b3_hi : p.b3) + a);
+            const unsigned int m = grp * kHeadRows + r;
+            if (m < p.B) *reinterpret_cast<f32x2*>(p.Q + ((x ? (size_t)p.B : 0u) + m) * p.Ap + a) = qv;
+            if (a < p.A) best = fmaxf(best, qv[0]);
+            if (a + 1u < p.A) best = fmaxf(best, qv[1]);
+            if (x == 0) {
+                const unsigned int am = min((unsigned int)p.act[min(m, p.B - 1u)], p.A - 1u);
+                if ((a ^ am) < 2u) qa_s[r] = am == a ? qv[0] : qv[1];
+            } else if (ab + 32u >= p.Ap) {
+                best = fmaxf(best, dpp<0x128>(best));        // (rotations within the sixteen)
+                best = fmaxf(best, dpp<0x124>(best));
+                best = fmaxf(best, dpp<0x122>(best));
+                best = fmaxf(best, dpp<0x121>(best));
+                if ((tid & 15u) == 0) best_s[r] = best;
             }
-            const float g = -slope / (float)p.B;
-            if (stripe0 && part == 0 && in) {
+        }
+        __syncthreads();
+        const float y = rew + (term ? 0.f : p.gamma * best_s[r16]);
+        const float d = y - qa_s[r16];
+        float li, slope;
+        if (p.loss_kind == RP_MSE || fabsf(d) <= 1.f) {
+            li = 0.5f * d * d;
+            slope = d;
+        } else {
+            li = fabsf(d) - 0.5f;
+            slope = d > 0.f ? 1.f : -1.f;
+        }
+        const float g = -slope / (float)p.B;
+        if (tid < 16u) {
+            g_s[r16] = g;
+            if (row < p.B) {
                 p.y[i] = y;
                 p.delta[i] = d;
                 p.lossi[i] = li;
             }
-            // dL/dQ's row: two actions a lane and part
-            {
-                const bf16_bits hi = bf16_bits_rne(g);
-                const float rest = g - bits_to_float(hi);
-                const bf16_bits mid = bf16_bits_rne(rest);
-                const bf16_bits lo = bf16_bits_rne(rest - bits_to_float(mid));
-                const unsigned int a = a0 + 2u * part, shift = a == ai[q] ? 0u : 16u;
-                const bool mine = in && (a ^ ai[q]) < 2u;    // (a is even)
-                unsigned int* dq = reinterpret_cast<unsigned int*>(lds + DQ + r * 192u) + part;
-                dq[0] = mine ? (unsigned int)hi << shift : 0u;
-                dq[16] = mine ? (unsigned int)mid << shift : 0u;
-                dq[32] = mine ? (unsigned int)lo << shift : 0u;
-            }
-            // (rows beyond the batch: whatever lies there must not meet a factor of zero)
-            const u32x4 zero = {0u, 0u, 0u, 0u};
-            *reinterpret_cast<u32x4*>(lds + r * 256u + 16u * (part ^ (4u * (r & 3u)))) = in && k0 < p.G ? hv[q] : zero;
-            u32x4 out;
+        }
+        for (unsigned int pass = 0; pass < passes; ++pass) {
+            u32x4 wv[SW];
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const float h_lo = __uint_as_float(hv[q][x] << 16), h_hi = __uint_as_float(hv[q][x] & 0xFFFF0000u);
-                const float w_lo = __uint_as_float(wv[x] << 16), w_hi = __uint_as_float(wv[x] & 0xFFFF0000u);
-                out[x] = bf16_pair(h_lo > 0.f ? g * w_lo : 0.f, h_hi > 0.f ? g * w_hi : 0.f);
-                cs[2 * x] += in && owner ? __uint_as_float(out[x] << 16) : 0.f;
-                cs[2 * x + 1] += in && owner ? __uint_as_float(out[x] & 0xFFFF0000u) : 0.f;
+            for (int s = 0; s < SW; ++s) {
+                const unsigned int k = at(pass, s), kc = k < p.G ? k : 0u;
+                wv[s] = *reinterpret_cast<const u32x4*>(p.W3T + (size_t)ai * p.G + kc + 8u * q16);
+                if (passes > 1u) hs[s] = *reinterpret_cast<const u32x4*>(h_s + kc);
             }
-            if (in && owner && k0 < p.G) *reinterpret_cast<u32x4*>(p.dZ2 + (size_t)i * p.G + k0) = out;
+#pragma unroll
+            for (int s = 0; s < SW; ++s) {
+                const unsigned int k = at(pass, s);
+                u32x4 out;
+                float cs[8];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const float h_lo = __uint_as_float(hs[s][x] << 16), h_hi = __uint_as_float(hs[s][x] & 0xFFFF0000u);
+                    const float w_lo = __uint_as_float(wv[s][x] << 16), w_hi = __uint_as_float(wv[s][x] & 0xFFFF0000u);
+                    out[x] = bf16_pair(h_lo > 0.f ? g * w_lo : 0.f, h_hi > 0.f ? g * w_hi : 0.f);
+                    cs[2 * x] = row < p.B ? __uint_as_float(out[x] << 16) : 0.f;
+                    cs[2 * x + 1] = row < p.B ? __uint_as_float(out[x] & 0xFFFF0000u) : 0.f;
+                }
+                if (row < p.B && k < p.G) *reinterpret_cast<u32x4*>(p.dZ2 + (size_t)i * p.G + k + 8u * q16) = out;
+                // db2: the sixteen rows' sum of each column
+                float* const sums = p.part2b + (size_t)blockIdx.x * p.G + k + 8u * q16;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    cs[e] += dpp<0x128>(cs[e]);
+                    cs[e] += dpp<0x124>(cs[e]);
+                    cs[e] += dpp<0x122>(cs[e]);
+                    cs[e] += dpp<0x121>(cs[e]);
+                }
+                if (r16 == 0 && k < p.G) {
+                    // (a later group adds to what the first one stored: the same thread did)
+                    f32x4 lo = {cs[0], cs[1], cs[2], cs[3]}, up = {cs[4], cs[5], cs[6], cs[7]};
+                    f32x4* const to = reinterpret_cast<f32x4*>(sums);
+                    if (grp != blockIdx.x) {
+                        lo += to[0];
+                        up += to[1];
+                    }
+                    to[0] = lo;
+                    to[1] = up;
+                }
+            }
         }
         __syncthreads();
-        // wavefront (t, h): tile t of 32 columns, half h of the rows
-#pragma unroll
-        for (unsigned int s = 0; s < kTgRows / 32u; ++s) {
-            const unsigned int r = h * (kTgRows / 2u) + 16u * s + l.row;
-            const u32x4 a = tn_fragment(lds, r * 256u + tn_tile_at<true>(t, l.rr) + l.col, 256u);
-            u32x4 b[3];
-#pragma unroll
-            for (int x = 0; x < 3; ++x) b[x] = tn_fragment(lds, DQ + r * 192u + 64u * x + l.col, 192u);
-#pragma unroll
-            for (int x = 0; x < 3; ++x)
-                acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b[x]), acc[x], 0, 0, 0);
-            if (with_sums) {
-#pragma unroll
-                for (int x = 0; x < 3; ++x)
-                    sum[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ones), as_bf16x8(b[x]), sum[x], 0, 0, 0);
-            }
+        if (tid < 256u) {
+            // dL/dQ: sixteen lanes a row, two actions a lane, so that a row's 32-wide parts leave as 64-byte runs
+            const unsigned int r = tid >> 4, m = grp * kHeadRows + r, am = min((unsigned int)p.act[min(m, p.B - 1u)], p.A - 1u);
+            const float gr = g_s[r];
+            const bf16_bits hi = bf16_bits_rne(gr);
+            const float rest = gr - bits_to_float(hi);
+            const bf16_bits mid = bf16_bits_rne(rest);
+            const bf16_bits lo = bf16_bits_rne(rest - bits_to_float(mid));
+            bf16_bits* dq = p.dQ + (size_t)m * 3u * p.Ap;
+            if (m < p.B)
+                for (unsigned int a = 2u * (tid & 15u); a < p.Ap; a += 32u) {
+                    const unsigned int shift = a == am ? 0u : 16u;
+                    const bool mine = (a ^ am) < 2u;         // (a is even)
+                    *reinterpret_cast<unsigned int*>(dq + dq_col(a, 0)) = mine ? (unsigned int)hi << shift : 0u;
+                    *reinterpret_cast<unsigned int*>(dq + dq_col(a, 1)) = mine ? (unsigned int)mid << shift : 0u;
+                    *reinterpret_cast<unsigned int*>(dq + dq_col(a, 2)) = mine ? (unsigned int)lo << shift : 0u;
+                }
         }
     }
-
-    // the two halves of the rows are added through LDS, as are the eight wavefronts' column sums
-    __syncthreads();
-    float* const give = reinterpret_cast<float*>(lds) + t * (17u * 64u) + lane;
-    const float sums = (sum[2][0] + sum[1][0]) + sum[0][0];   // (the same in every row)
-    if (h) {
-#pragma unroll
-        for (unsigned int v = 0; v < 16; ++v) give[v * 64u] = (acc[2][v] + acc[1][v]) + acc[0][v];
-        give[16u * 64u] = sums;
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        cs[e] += __shfl_xor(cs[e], 16, 64);
-        cs[e] += __shfl_xor(cs[e], 32, 64);
-    }
-    if (lane < 16u) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) colsum[wave][part * 8u + e] = cs[e];
-    }
-    __syncthreads();
-    const size_t split = blockIdx.x;
-    if (tid < kTgCols && c0 + tid < p.G) {
-        float x = 0.f;
-#pragma unroll
-        for (unsigned int w = 0; w < 8; ++w) x += colsum[w][tid];
-        p.part2b[(split * gridDim.z + blockIdx.z) * p.G + c0 + tid] = x;
-    }
-    if (h) return;
-    float* const at = p.part3 + split * (p.G + 1u) * p.Ap + a0 + (lane & 31u);
-    if (c0 + t * 32u < p.G) {                                 // (G is a whole number of 32)
-#pragma unroll
-        for (unsigned int v = 0; v < 16; ++v)
-            at[(size_t)(c0 + t * 32u + acc_row(v, lane)) * p.Ap] = ((acc[2][v] + acc[1][v]) + acc[0][v]) + give[v * 64u];
-    }
-    if (with_sums && lane < 32u) at[(size_t)p.G * p.Ap] = sums + give[16u * 64u];
 }
 
 // grad_back_kernel: the step's two large backward products in one launch, side by side because neither
@@ -1227,7 +1173,8 @@ __global__ __launch_bounds__(kTgThreads) void td_grad_kernel(TdGradArgs p) {
 //    [dW1^T | db1] = dZ1^T [X | 1] alone, so the tile stays in LDS as bf16, is contracted there with
 //    its rows of X and never goes to memory: part1[split][j][d] (column D: db1), a split per row of tiles, or
 //    per kGbMaxSplits-th one where there are more.
-//  - the rest: dW2 = H1^T dZ2, K-split partials part2[split][j][k].
+//  - the next n_dw: dW2 = H1^T dZ2, K-split partials part2[split][j][k].
+//  - the rest: [dW3 ; db3], partials part3[split][k][a] (row G: db3).
 // As launches of their own (dZ1 stored, then all gradients) 16.3 + 21.8 us at batch 4096 and 1024 units.
 constexpr unsigned int kGbMaxSplits = 32;
 typedef MmTile<256, 128, 2, 2, 2, 3> GbLarge;
@@ -1236,11 +1183,13 @@ typedef MmTile<128, 128, 2, 2, 2, 4> GbSmall;
 struct GradBackArgs {
     GemmArgs dz;                 // A = dZ2, Bt = W2; tiles_m: rows of workgroups
     GemmArgs dw;                 // A = H1, Bt = dZ2
-    unsigned int n_dz;           // workgroups of the first kind, a multiple of 8
+    unsigned int n_dz, n_dw;     // workgroups of the first two kinds, multiples of 8
     const bf16_bits* X;          // [B x Dp]
     const bf16_bits* H1;
     unsigned int D, Dp, Dx;
-    float *part1, *part2;
+    const bf16_bits *H2, *dQ;    // dQ: [B x 3 Ap]
+    unsigned int Ap, splits3;
+    float *part1, *part2, *part3;
 };
 
 // Byte of element (r, col) of the dZ1 tile in LDS: rows of 256 bytes whose 64-byte groups are rotated by XOR
@@ -1370,12 +1319,98 @@ __device__ __forceinline__ void dz1_block(const GradBackArgs& p, unsigned int bl
     }
 }
 
+// [dW3 ; db3] = H2^T dL/dQ for 128 units and 32 actions, over every so many'th chunk of 256 batch rows: a chunk of both
+// operands goes to LDS in one go (the sum of its 96 columns of dL/dQ, the three parts of the actions, is taken there).
+constexpr unsigned int kW3Rows = 256, kW3MaxSplits = 32;
+
+__device__ __forceinline__ void dw3_block(const GradBackArgs& p, unsigned int block, unsigned char* smem) {
+    constexpr unsigned int DQ = kW3Rows * 256u, GA = kW3Rows * 16u / 512u, GB = kW3Rows * 12u / 512u;
+    const unsigned int tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned int B = p.dz.M, G = p.dz.K, tiles = (G + 127u) / 128u, blocks_a = p.Ap / 32u;
+    const unsigned int split = block / (tiles * blocks_a), m0 = block % tiles * 128u, a0 = block / tiles % blocks_a * 32u;
+    const unsigned int t = wave & 3u, h = wave >> 2;
+    const TnLane l(lane);
+    f32x16 acc[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[s][v] = 0.f;
+    float dq_sum = 0.f;                       // db3: action tid % 32, rows 16 (tid / 32) .. of each chunk
+    for (unsigned int r0 = split * kW3Rows; r0 < B; r0 += p.splits3 * kW3Rows) {
+        if (r0 != split * kW3Rows) __syncthreads();
+        const unsigned int rows = min(kW3Rows, B - r0);
+        const gchar ha = (gchar)reinterpret_cast<const char*>(p.H2 + (size_t)r0 * G);
+        const gchar qa = (gchar)reinterpret_cast<const char*>(p.dQ + (size_t)r0 * 3u * p.Ap + a0 * 3u);
+#pragma unroll
+        for (unsigned int u = 0; u < GA; ++u) {
+            const unsigned int e = (wave * GA + u) * 64u + lane, r = e >> 4, col = m0 + 8u * ((e & 15u) ^ (4u * (r & 3u)));
+            request_lds(ha, (min(r, rows - 1u) * G + (col < G ? col : 0u)) * 2u, smem + (wave * GA + u) * 1024u);
+        }
+#pragma unroll
+        for (unsigned int u = 0; u < GB; ++u) {
+            const unsigned int e = (wave * GB + u) * 64u + lane, r = e / 12u;
+            request_lds(qa, (min(r, rows - 1u) * 3u * p.Ap + (e - r * 12u) * 8u) * 2u, smem + DQ + (wave * GB + u) * 1024u);
+        }
+        wait_loads<0>();
+        __syncthreads();
+        if (rows < kW3Rows) {                 // (whatever lies beyond the batch must not meet a factor of zero)
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            for (unsigned int e = rows * 16u + tid; e < kW3Rows * 16u; e += 512u) reinterpret_cast<u32x4*>(smem)[e] = zero;
+            for (unsigned int e = rows * 12u + tid; e < kW3Rows * 12u; e += 512u) reinterpret_cast<u32x4*>(smem + DQ)[e] = zero;
+            __syncthreads();
+        }
+        // wavefront (t, h): tile t of 32 units, half h of the rows
+#pragma unroll
+        for (unsigned int s = 0; s < kW3Rows / 32u; ++s) {
+            const unsigned int r = h * (kW3Rows / 2u) + 16u * s + l.row;
+            const u32x4 a = tn_fragment(smem, r * 256u + tn_tile_at<true>(t, l.rr) + l.col, 256u);
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                const u32x4 b = tn_fragment(smem, DQ + r * 192u + 64u * x + l.col, 192u);
+                acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), acc[x], 0, 0, 0);
+            }
+        }
+        if (m0 == 0) {
+#pragma unroll
+            for (unsigned int r = 0; r < 16; ++r) {
+                const bf16_bits* dq = reinterpret_cast<const bf16_bits*>(smem + DQ + ((tid >> 5) * 16u + r) * 192u) + (tid & 31u);
+                dq_sum += (bits_to_float(dq[64]) + bits_to_float(dq[32])) + bits_to_float(dq[0]);   // (exact: the fp32 number)
+            }
+        }
+    }
+    __syncthreads();
+    float* const give = reinterpret_cast<float*>(smem) + t * 1024u + lane;
+    float* const sums = reinterpret_cast<float*>(smem) + 4096u;
+    if (h) {
+#pragma unroll
+        for (unsigned int v = 0; v < 16; ++v) give[v * 64u] = (acc[2][v] + acc[1][v]) + acc[0][v];
+    }
+    sums[tid] = dq_sum;
+    __syncthreads();
+    float* const out = p.part3 + (size_t)split * (G + 1u) * p.Ap + a0;
+    if (m0 == 0 && tid < 32u) {
+        float x = 0.f;
+#pragma unroll
+        for (unsigned int w = 0; w < 16; ++w) x += sums[w * 32u + tid];
+        out[(size_t)G * p.Ap + tid] = x;
+    }
+    if (h || m0 + t * 32u >= G) return;       // (G is a whole number of 32)
+#pragma unroll
+    for (unsigned int v = 0; v < 16; ++v)
+        out[(size_t)(m0 + t * 32u + acc_row(v, lane)) * p.Ap + (lane & 31u)] = ((acc[2][v] + acc[1][v]) + acc[0][v]) + give[v * 64u];
+}
+
 template <class S>
 __global__ __launch_bounds__(S::kThreads) void grad_back_kernel(GradBackArgs p) {
     extern __shared__ uint4 gemm_smem[];
     unsigned char* smem = reinterpret_cast<unsigned char*>(gemm_smem);
     if (blockIdx.x < p.n_dz) {
         dz1_block<S>(p, blockIdx.x, smem);
+        return;
+    }
+    static_assert(kW3Rows * 448u <= S::kLds, "a chunk of both operands");
+    if (blockIdx.x >= p.n_dz + p.n_dw) {
+        dw3_block(p, blockIdx.x - p.n_dz - p.n_dw, smem);
         return;
     }
     unsigned int m0, n0, split;
@@ -1424,7 +1459,25 @@ __device__ __forceinline__ float sum_splits(const float* src, size_t stride, uns
     return g;
 }
 
+// The second layer's bias, 16 columns a workgroup: sixteen threads a column share the partials, of which there may be hundreds.
+__device__ __forceinline__ void bias_opt_block(const SmallOptArgs& p, unsigned int block) {
+    __shared__ float share[16][17];
+    const unsigned int c = threadIdx.x & 15u, z0 = threadIdx.x >> 4, k = block * 16u + c;
+    share[z0][c] = sum_splits(p.part_b2 + z0 * p.b2_stride + k, 16u * p.b2_stride, z0 < p.splits_b2 ? (p.splits_b2 - z0 + 15u) / 16u : 0u);
+    __syncthreads();
+    if (z0) return;
+    float g = 0.f;
+#pragma unroll
+    for (unsigned int z = 0; z < 16; ++z) g += share[z][c];
+    opt_update(p.o, p.ob2 + k, g, opt_step(p.o));
+}
+
 __device__ __forceinline__ void small_opt_block(const SmallOptArgs& p, unsigned int block) {
+    if (block < p.G / 16u) {
+        bias_opt_block(p, block);
+        return;
+    }
+    block -= p.G / 16u;
     const unsigned int n3 = (p.G + 1u) * p.Ap, n1 = p.H * (p.D + 1u);
     const unsigned int e = block * 256u + threadIdx.x;
     const OptStep st = opt_step(p.o);
@@ -1454,9 +1507,6 @@ __device__ __forceinline__ void small_opt_block(const SmallOptArgs& p, unsigned 
         } else {
             opt_update(p.o, p.ob1 + j, g, st);
         }
-    } else if (e < n3 + n1 + p.G) {
-        const unsigned int k = e - n3 - n1;
-        opt_update(p.o, p.ob2 + k, sum_splits(p.part_b2 + k, p.b2_stride, p.splits_b2), st);
     }
     if (block == 0) {
         __shared__ float wsum[4];
@@ -1630,6 +1680,13 @@ hipError_t second_layer(hipStream_t st, const bf16_bits* H1, unsigned int rows, 
                                            1, hi, m_split);
 }
 
+// (the narrowest variant that holds a row)
+const void* head_func(unsigned int G, bool target) {
+    if (G <= 256u) return target ? reinterpret_cast<const void*>(head_kernel<1, true>) : reinterpret_cast<const void*>(head_kernel<1, false>);
+    if (G <= 512u) return target ? reinterpret_cast<const void*>(head_kernel<2, true>) : reinterpret_cast<const void*>(head_kernel<2, false>);
+    return target ? reinterpret_cast<const void*>(head_kernel<4, true>) : reinterpret_cast<const void*>(head_kernel<4, false>);
+}
+
 template <class S>
 hipError_t configure_grad_back() {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(grad_back_kernel<S>),
@@ -1640,12 +1697,17 @@ hipError_t configure_grad_back() {
 WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G) {
     WidePlan p;
     const unsigned int Bp = (B + 127u) / 128u * 128u;
-    p.merged = !few_tiles(B, H);
+    // Two launches (above) wherever the first layer's error has many tiles, and on large batches: us per step in the small
+    // form, the large one (27 inputs, 30 actions): 64-64 at batch 4000 35.1, 29.3, 1000 27.0, 25.3; 256-256 at 1000 32.6,
+    // 29.6; 128-1024 at 4096, head and target network, 62.2, 52.9, 2048 48.5, 46.2, but 1024 with target network 43.1,
+    // 44.2: a long contraction in few tiles.  Below some 576 either may be the faster: 256-256 at 500 29.2,
+    // 27.2, 64-512-512-64 39.4, 41.0, 1024-1024 at 64 43.2, 45.3.
+    p.merged = !few_tiles(B, H) || B >= 1536u || (B >= 576u && G <= 512u);
     p.large = false;
     p.k2 = Bp;
     if (!p.merged) {
         p.splits3 = p.splits1 = batch_splits(Bp);
-        p.splits2 = square_splits_for(Bp, H, G);
+        p.splits2 = p.splits_b2 = square_splits_for(Bp, H, G);
         return p;
     }
     // The tiles' height and the splits of dW2's contraction: those whose launch ends first.  A compute unit holds one
@@ -1681,7 +1743,8 @@ WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G) {
     }
     const unsigned int bm = p.large ? 256u : 128u;
     p.splits1 = std::min((B + bm - 1u) / bm, kGbMaxSplits);
-    p.splits3 = std::min((B + kTgRows - 1u) / kTgRows, kTgMaxSplits);
+    p.splits3 = std::min((B + kW3Rows - 1u) / kW3Rows, kW3MaxSplits);
+    p.splits_b2 = std::min((B + kHeadRows - 1u) / kHeadRows, kHeadMaxGroups);
     return p;
 }
 
@@ -1749,7 +1812,8 @@ static bool rows_in_one_launch(const trainer* t) { return !t->wt || t->B % 128 =
 // (gather, three forward products, TD errors, the first layer's error, the gradients, the update; what
 // train_create adds itself: the dueling head's update, a draw in a launch of its own)
 unsigned int wide_step_kernels(const trainer* t) {
-    return (rows_in_one_launch(t) ? 8u : 11u) - (t->plan.merged ? 1u : 0u);
+    const unsigned int halves = rows_in_one_launch(t) ? 1u : 2u;   // launches of each layer's forward product
+    return t->plan.merged ? 4u + 2u * halves : 5u + 3u * halves;
 }
 
 template <class S>
@@ -1757,16 +1821,17 @@ static hipError_t launch_grad_back(trainer* t, hipStream_t st, const WidePlan& p
                                    const bf16_bits* dZ2) {
     const unsigned int B = t->B, H = t->H, G = t->Hb, D = t->cfg.state_dim;
     GradBackArgs a;
-    unsigned int n_dw = 0;
     // (rows of workgroups: at most plan.splits1, each with every so many'th tile)
     bool ok = gemm_args<S::BM, S::BN, 64>(dZ2, G, t->wd.W2, G, std::min(B, plan.splits1 * S::BM), H, G, 1, nullptr, 0, &a.dz, &a.n_dz);
-    ok = ok && gemm_args<S::BM, S::BN, 64>(H1, H, dZ2, G, H, G, plan.splits2 * plan.k2, plan.splits2, nullptr, 0, &a.dw, &n_dw);
+    ok = ok && gemm_args<S::BM, S::BN, 64>(H1, H, dZ2, G, H, G, plan.splits2 * plan.k2, plan.splits2, nullptr, 0, &a.dw, &a.n_dw);
     if (!ok) return hipErrorInvalidValue;
     a.dz.M = B;
     a.dw.batch = B;
     a.X = X; a.H1 = H1; a.D = D; a.Dp = t->Dp; a.Dx = (D + 1 + 31) / 32 * 32;
-    a.part1 = t->wd.part1; a.part2 = t->wd.part2;
-    hipLaunchKernelGGL(grad_back_kernel<S>, dim3(a.n_dz + n_dw), dim3(S::kThreads), S::kLds, st, a);
+    a.H2 = static_cast<const bf16_bits*>(t->H2); a.dQ = t->wd.dQ; a.Ap = t->Ap; a.splits3 = plan.splits3;
+    a.part1 = t->wd.part1; a.part2 = t->wd.part2; a.part3 = t->wd.part3;
+    const unsigned int n3 = plan.splits3 * ((G + 127) / 128) * (t->Ap / 32);
+    hipLaunchKernelGGL(grad_back_kernel<S>, dim3(a.n_dz + a.n_dw + n3), dim3(S::kThreads), S::kLds, st, a);
     return hipGetLastError();
 }
 
@@ -1822,7 +1887,8 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
         if (e != hipSuccess) return e;
         ++n;
     }
-    {
+    const WidePlan& plan = t->plan;
+    if (!plan.merged) {
         SkinnyArgs a;
         a.A = H2; a.lda = G; a.Bt = w.W3T; a.ldb = G; a.M = rows; a.N = Ap; a.K = G;
         a.Bt_hi = tgt ? w.W3T_t : w.W3T; a.m_split = tgt ? B : ~0u;
@@ -1840,20 +1906,20 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
         }
     }
     if (e != hipSuccess) return e;
-    if (!one_launch) ++n;
-    const WidePlan& plan = t->plan;
+    if (!plan.merged && !one_launch) ++n;
     const unsigned int Dx = (D + 1 + 31) / 32 * 32;
     if (plan.merged) {
-        TdGradArgs a;
+        HeadStepArgs a;
         a.B = B; a.G = G; a.A = A; a.Ap = Ap;
-        a.kz = 0; a.part_stride = 0; a.parts = nullptr; a.b3 = a.b3_hi = nullptr;
-        a.Q = t->Q; a.act = t->act; a.rew = t->rew; a.term = t->term;
+        a.act = t->act; a.rew = t->rew; a.term = t->term;
         a.gamma = t->cfg.gamma; a.loss_kind = t->cfg.loss; a.beta1 = t->cfg.beta1; a.beta2 = t->cfg.beta2;
-        a.y = t->y; a.delta = t->delta; a.lossi = t->lossi;
-        a.W3T = w.W3T; a.H2 = H2; a.dZ2 = dZ2; a.part3 = w.part3; a.part2b = w.part2b;
+        a.b3 = t->w + t->ob3; a.b3_hi = tgt ? b3t : a.b3;
+        a.W3T = w.W3T; a.W3T_hi = tgt ? w.W3T_t : w.W3T;
+        a.H2 = H2; a.Q = t->Q; a.y = t->y; a.delta = t->delta; a.lossi = t->lossi;
+        a.dQ = w.dQ; a.dZ2 = dZ2; a.part2b = w.part2b;
         a.ctr = t->ctr;
-        hipLaunchKernelGGL(td_grad_kernel<false>, dim3(plan.splits3, (G + kTgCols - 1) / kTgCols, Ap / 32), dim3(kTgThreads), 0, st, a);
-        e = hipGetLastError();
+        void* kargs[] = {&a};
+        e = hipLaunchKernel(head_func(G, tgt), dim3(plan.splits_b2), dim3(kHeadThreads), kargs, 0, st);
         if (e != hipSuccess) return e;
         ++n;
         e = plan.large ? launch_grad_back<GbLarge>(t, st, plan, X, H1, dZ2) : launch_grad_back<GbSmall>(t, st, plan, X, H1, dZ2);
@@ -1920,15 +1986,15 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
         a.part3 = w.part3; a.part1 = w.part1;
         // (the second layer's bias: row H of each split's partials, or rows of its own)
         a.part_b2 = plan.merged ? w.part2b : w.part2 + (size_t)H * G;
-        a.splits_b2 = plan.merged ? plan.splits3 * (Ap / 32) : plan.splits2;
+        a.splits_b2 = plan.splits_b2;
         a.b2_stride = plan.merged ? G : (size_t)(H + 1) * G;
         a.ob2 = t->ob2;
         a.oW1 = t->oW1; a.ob1 = t->ob1; a.oW3 = t->oW3; a.ob3 = t->ob3;
         a.W1T = w.W1T; a.W3T = w.W3T; a.W1T_target = w.W1T_t; a.W3T_target = w.W3T_t;
         a.ctr = t->ctr; a.lossi = t->lossi;
         a.out_grad_only = t->dueling ? 1u : 0u;
-        const unsigned int elems = (G + 1) * Ap + H * (D + 1) + G;
-        const unsigned int own = (G / 64) * (H / kSqRows) + (elems + 255) / 256;
+        const unsigned int elems = (G + 1) * Ap + H * (D + 1);
+        const unsigned int own = (G / 64) * (H / kSqRows) + G / 16 + (elems + 255) / 256;
         if (t->rec_next) {
             // (recording a run of steps: this launch also gathers the next step's batch; the rest of
             // its arguments is kept for the launches that replace the next step's part)

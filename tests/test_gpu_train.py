@@ -1225,10 +1225,12 @@ def test_mixed_precision_products_with_few_tiles(B, H, H2, batch, target_sync):
     (96, 512, 320, 3, 1100, 0, False),    # three blocks of states, the bias behind the last
     (27, 64, 64, 5, 8300, 0, False),      # 256 x 128 tiles, more rows of them than rows of workgroups
     (31, 1024, 64, 33, 9000, 0, True),
+    (9, 64, 512, 6, 577, 3, True),        # few tiles, a batch above the rule's line; a row of two steps a wavefront
+    (27, 64, 1088, 30, 1537, 0, False),   # rows wider than the output layer's kernel holds at a time
 ])
 def test_mixed_precision_backward_in_two_launches(B, D, H, H2, A, batch, target_sync, dueling):
-    """Large steps form the output layer's gradient with the TD errors, and the first layer's in the launch
-    of the two large backward products; tolerances of the other mixed-precision cases."""
+    """Large steps: output layer, TD errors and the second layer's error in one launch, all gradients and the first
+    layer's error in another; tolerances of the other mixed-precision cases."""
     oracle.set_threads(16)
     try:
         rows = synth.experiences(batch + 60, D, A, 0.05, seed=79, state_dtype="bf16")
