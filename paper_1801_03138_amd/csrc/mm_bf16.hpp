@@ -71,6 +71,14 @@ __device__ __forceinline__ void request_lds(gchar row, unsigned int lane_off, un
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(row + lane_off), RP_LDS_PTR(dst), 16, 0, 0);
 }
 
+// 8 bytes to LDS.  Written out, because the compiler lets an LDS write of its own wait for every request in flight
+// (it could be to the same place); slice_barrier waits for it.
+__device__ __forceinline__ void write_lds8(unsigned char* at, unsigned int lo, unsigned int hi) {
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    const unsigned int addr = (unsigned int)(size_t)RP_LDS_PTR(at);
+    asm volatile("ds_write_b64 %0, %1" ::"v"(addr), "v"((u32x2{lo, hi})) : "memory");
+}
+
 // A product's operands and how its tiles are numbered.
 struct GemmArgs {
     const bf16_bits* A;
@@ -120,12 +128,23 @@ struct MmTile {
 };
 
 // The pipelined loop over nk slices, shared by both operand layouts.  fetch_one(u, buf, slice): request u
-// (0 .. L - 1) of a slice into buffer buf; read(buf, s, set): operands of step s; mfma(i, j, set); arrived(slice,
+// (0 .. L - 1) of a slice into buffer buf; read(slice, buf, s, set): operands of step s; mfma(i, j, set); arrived(slice,
 // buf): after one of the first slice and the last NS - 1 has arrived for everybody and before anybody reads it; before_tail(): once, when
 // the last slice has arrived (loads of the epilogue's operands go there: no wait counts loads after it).
-template <class S, int L, class Fetch, class Read, class Mfma, class Arrived, class Tail>
+// make: for an operand that the workgroup works out itself, into LDS, a slice ahead: start(slice, buf) after the barrier
+// that brought slice - 1 (to buf); multiply(slice); finish(slice, part, parts) for all parts, between the MFMAs of a step;
+// after that and a barrier the slice is read, and done(slice) is called, and flush() a step later.  Loads and stores of its
+// own only make the waits for the requests stricter: those complete in order.
+struct MakeNothing {
+    __device__ __forceinline__ void start(unsigned int, unsigned int) {}
+    __device__ __forceinline__ void multiply(unsigned int) {}
+    __device__ __forceinline__ void finish(unsigned int, int, int) {}
+    __device__ __forceinline__ void done(unsigned int) {}
+    __device__ __forceinline__ void flush() {}
+};
+template <class S, int L, class Fetch, class Read, class Mfma, class Arrived, class Tail, class Make>
 __device__ __forceinline__ void mm_pipeline(unsigned int nk, Fetch&& fetch_one, Read&& read, Mfma&& mfma,
-                                            Arrived&& arrived, Tail&& before_tail) {
+                                            Arrived&& arrived, Tail&& before_tail, Make&& make) {
     constexpr int NS = S::NS, SP = S::SP, NM = SP * S::TM * S::TN;
 #pragma unroll
     for (unsigned int s0 = 0; s0 + 1 < (unsigned int)NS; ++s0)
@@ -135,11 +154,15 @@ __device__ __forceinline__ void mm_pipeline(unsigned int nk, Fetch&& fetch_one, 
         }
     if (nk < 2) before_tail();
     if (nk == 0) return;
+    make.multiply(0u);
+    make.finish(0u, 0, 1);
     wait_slices<L, NS - 2>(nk > 1 ? min(nk - 1u, (unsigned int)NS - 2u) : 0u);
     slice_barrier();
     arrived(0u, 0u);
-    read(0u, 0, 0);
-    auto step = [&](int s, auto fetch_flag, unsigned int fbuf, unsigned int fslice) {
+    read(0u, 0u, 0, 0);
+    make.done(0u);
+    if (nk > 1) make.start(1u, 0u);
+    auto step = [&](int s, auto fetch_flag, unsigned int fbuf, unsigned int fslice, bool making, unsigned int made) {
         constexpr bool FETCH = decltype(fetch_flag)::value;
 #pragma unroll
         for (int i = 0; i < S::TM; ++i)
@@ -150,8 +173,9 @@ __device__ __forceinline__ void mm_pipeline(unsigned int nk, Fetch&& fetch_one, 
                     const int m = (s * S::TM + i) * S::TN + j;   // this MFMA's number within the slice
 #pragma unroll
                     for (int u = m * L / NM; u < (m + 1) * L / NM; ++u) fetch_one(u, fbuf, fslice);
-                    __builtin_amdgcn_sched_barrier(0);
                 }
+                if (s + 2 == SP && making) make.finish(made, i * S::TN + j, S::TM * S::TN);
+                if (FETCH) __builtin_amdgcn_sched_barrier(0);
             }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -165,17 +189,23 @@ __device__ __forceinline__ void mm_pipeline(unsigned int nk, Fetch&& fetch_one, 
 #pragma unroll
         for (int s = 0; s < SP; ++s) {
             if (s + 1 < SP) {
-                read(cur, s + 1, (s + 1) & 1);
+                read(kt, cur, s + 1, (s + 1) & 1);
+                if (s == 0) {
+                    make.flush();
+                    make.multiply(kt + 1u);
+                }
             } else {
                 // the next slice is here (its requests are a whole slice old); after the barrier nobody reads
                 // this slice's buffer any more (its last operands are in registers), and the
                 // next iteration's requests go there
                 wait_loads<(NS - 3) * L + SHARE>();
                 slice_barrier();
-                read(nxt, 0, 0);
+                read(kt + 1u, nxt, 0, 0);
+                make.done(kt + 1u);
+                make.start(kt + 2u, nxt);
             }
             __builtin_amdgcn_sched_barrier(0);
-            step(s, std::true_type{}, fb, kt + NS - 1u);
+            step(s, std::true_type{}, fb, kt + NS - 1u, true, kt + 1u);
         }
         cur = nxt;
         nxt = nxt + 1 == NS ? 0 : nxt + 1;
@@ -185,16 +215,22 @@ __device__ __forceinline__ void mm_pipeline(unsigned int nk, Fetch&& fetch_one, 
 #pragma unroll
         for (int s = 0; s < SP; ++s) {
             if (s + 1 < SP) {
-                read(cur, s + 1, (s + 1) & 1);
+                read(kt, cur, s + 1, (s + 1) & 1);
+                if (s == 0) {
+                    make.flush();
+                    if (kt + 1 < nk) make.multiply(kt + 1u);
+                }
             } else if (kt + 1 < nk) {
                 wait_slices<L, NS - 2>(nk - 2u - kt);
                 slice_barrier();
                 arrived(kt + 1u, nxt);
-                read(nxt, 0, 0);
+                read(kt + 1u, nxt, 0, 0);
+                make.done(kt + 1u);
+                if (kt + 2 < nk) make.start(kt + 2u, nxt);
                 if (kt + 2 == nk) before_tail();
             }
             __builtin_amdgcn_sched_barrier(0);
-            step(s, std::false_type{}, 0u, 0u);
+            step(s, std::false_type{}, 0u, 0u, kt + 1 < nk, kt + 1u);
         }
         cur = nxt;
         nxt = nxt + 1 == NS ? 0 : nxt + 1;
@@ -302,7 +338,7 @@ __device__ __forceinline__ void mm_nt(const GemmArgs& p, unsigned int m0, unsign
     const unsigned int b_row = S::BM * 128u + (wn * S::TN * 32u + (lane & 31u)) * 128u;
     const unsigned int sw = swz(lane & 31u);
     u32x4 a[2][S::TM], b[2][S::TN];
-    auto read = [&](unsigned int buf, int s, int set) {
+    auto read = [&](unsigned int, unsigned int buf, int s, int set) {
         const unsigned char* base = smem + buf * S::kStage + ((2u * (group * S::SP + s) + half) ^ sw) * 16u;
 #pragma unroll
         for (int j = 0; j < S::TN; ++j) b[set][j] = *reinterpret_cast<const u32x4*>(base + b_row + j * 4096);
@@ -313,7 +349,7 @@ __device__ __forceinline__ void mm_nt(const GemmArgs& p, unsigned int m0, unsign
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(b[set][j]), as_bf16x8(a[set][i]), acc[i][j], 0, 0, 0);
     };
     mm_clear<S>(acc);
-    mm_pipeline<S, L>(p.K / 64u, fetch_one, read, mfma, [](unsigned int, unsigned int) {}, before_tail);
+    mm_pipeline<S, L>(p.K / 64u, fetch_one, read, mfma, [](unsigned int, unsigned int) {}, before_tail, MakeNothing{});
 }
 
 // The transposing LDS read (ds_read_b64_tr_b16) hands a lane four consecutive rows of its column: within 16
@@ -390,7 +426,7 @@ __device__ __forceinline__ void mm_tn(const GemmArgs& p, unsigned int m0, unsign
 #pragma unroll
     for (int j = 0; j < S::TN; ++j) b_at[j] = A_BYTES + lrow * ROWB + tn_tile_at<true>(wn * S::TN + j, l.rr) + l.col;
     u32x4 a[2][S::TM], b[2][S::TN];
-    auto read = [&](unsigned int buf, int s, int set) {
+    auto read = [&](unsigned int, unsigned int buf, int s, int set) {
 #pragma unroll
         for (int j = 0; j < S::TN; ++j) b[set][j] = tn_fragment(smem, buf * S::kStage + b_at[j] + 16u * s * ROWB, ROWB);
 #pragma unroll
@@ -409,7 +445,7 @@ __device__ __forceinline__ void mm_tn(const GemmArgs& p, unsigned int m0, unsign
         slice_barrier();
     };
     mm_clear<S>(acc);
-    mm_pipeline<S, L>(nk, fetch_one, read, mfma, arrived, []() {});
+    mm_pipeline<S, L>(nk, fetch_one, read, mfma, arrived, []() {}, MakeNothing{});
 }
 
 }  // namespace rp

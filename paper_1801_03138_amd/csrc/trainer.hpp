@@ -135,6 +135,7 @@ inline void set_adam_step(RowArgs& a, unsigned long long t_after, float beta1, f
 struct WidePlan {
     bool merged, large;
     unsigned int splits3, splits1, splits2, k2, splits_b2;
+    unsigned int fw_cols;   // the first two layers share a launch, in tiles this many units wide (0: they do not)
 };
 
 // Buffers of the mixed-precision step on MFMA (bf16 bit patterns; H, G: widths of the two hidden
@@ -306,7 +307,7 @@ hipError_t enqueue_mid_step(trainer* t, hipStream_t st, unsigned int* count);
 unsigned int mid_step_kernels(const trainer* t);   // launches per step, the append + gather kernel included
 // Mixed-precision step on MFMA (bf16 replay states and matrix operands).
 bool wide_step_supported(const train_config& cfg, const replay* rp_);
-WidePlan wide_plan(unsigned int B, unsigned int H, unsigned int G);
+WidePlan wide_plan(unsigned int B, unsigned int H, unsigned int G, unsigned int Dp);
 hipError_t wide_configure();                                    // once, at creation
 // bf16 operand copies from padded fp32 parameters (host): of the trained network, or of the target
 hipError_t wide_set_weights(trainer* t, const float* padded, bool target);

@@ -843,6 +843,217 @@ __global__ __launch_bounds__(64 * NW) void skinny_nt_kernel(SkinnyArgs p, Epi ep
 }
 
 // ----------------------------------------------------------------------------------------
+// The first two layers of large steps in one launch: H2 = relu(relu(X W1 + b1) W2 + b2) for a tile of 128 rows x BN
+// units.  The second layer's operand H1 is never read: the workgroup works its rows' H1 out, a slice of 64 units ahead of
+// the product (each wavefront 32 rows x 32 units, from X in its registers and W1's rows, with the bias as the
+// accumulator's start), and leaves it in LDS.  The rows' H1 is needed again by the backward half: of the rows of S each
+// of the row's tiles stores every so many'th slice.
+// The workgroups of a row of tiles repeat the first layer (an eighth of the second's MFMAs at 256 units and 32 states);
+// as a launch of its own it was bound by its start and by writing and reading H1 (17 MB each way at batch 4096 and
+// 1024 units).  6.8 + 20.8 us -> 27.0 there, but us per step 81.4 -> 79.6 (the S' half of H1 never goes to memory); at
+// batch 1024 54.5 -> 52.7, 512-512 at 1100 40.8 -> 37.7, 192-192 at 4096 35.7 -> 33.5, 768-768 at 3000 unchanged.
+// Without the first layer the launch takes 18.8 us there; its MFMAs add 2.7, ReLU, rounding and LDS writes 3.5 (as
+// much when spread between the second layer's MFMAs), the stores of H1 1.9.
+// ----------------------------------------------------------------------------------------
+typedef MmTile<128, 256, 2, 4, 1, 3> FwLarge;
+typedef MmTile<128, 128, 2, 2, 2, 4> FwSmall;
+
+struct ForwardArgs {
+    GemmArgs g;                          // Bt = W2T; K: the first layer's units
+    const bf16_bits* X;                  // [. x Dp]
+    unsigned int Dp;
+    const bf16_bits *W1T, *W1T_hi;       // [K x Dp] (_hi: of the rows from g.m_split on)
+    const float *b1, *b1_hi, *b2, *b2_hi;
+    bf16_bits* H1;                       // rows below store_rows
+    unsigned int store_rows;
+    bf16_bits* H2;
+};
+
+// Dynamic LDS: the slices of W2T and W1T, two of H1, the first bias; then the epilogue's tile.  ND: 32-wide blocks of states.
+constexpr unsigned int kFwMaxH = 2048;
+template <class S, int ND>
+constexpr size_t forward_lds() {
+    return std::max<size_t>(S::NS * (S::BN * 128u + ND * 4096u) + 2u * S::BM * 128u + kFwMaxH * 4u,
+                            std::max<size_t>(S::KG == 2 ? S::BM * S::BN * 4u : 0u, S::BM * (S::BN * 2u + 16u)));
+}
+
+// The slices of H1.  W1T's come with W2T's requests, one ahead, and the bias before them (their first from memory; a load in
+// the loop would make the compiler wait for the requests in flight); the bias is one more step of the product: its three
+// bf16 parts, which add up to the fp32 number, times ones.
+template <int ND>
+struct MakeH1 {
+    const ForwardArgs& p;
+    const float* b1;                     // of this lane's unit in a slice (in LDS)
+    unsigned char *at, *lds, *w1;        // where this lane's first four units go; H1's slices; this lane's row of a slice of W1T
+    unsigned int stage;                  // bytes between W1T's slices
+    unsigned int m0, own, stride, half, g0, r, sw;   // own: the first slice this workgroup stores, then every stride-th
+    u32x4 x[2 * ND], w[2 * ND];
+    float b;
+    f32x16 h;
+    u32x4 v[2];
+    bf16_bits* to;
+    bool keep;
+    __device__ __forceinline__ void start(unsigned int slice, unsigned int buf) {
+        b = b1[slice * 64u];
+#pragma unroll
+        for (unsigned int s = 0; s < 2 * ND; ++s)
+            w[s] = *reinterpret_cast<const u32x4*>(w1 + buf * stage + 16u * ((2u * s + half) ^ sw));
+    }
+    __device__ __forceinline__ void multiply(unsigned int) {
+        const unsigned int hi = bf16_bits_rne(b);
+        const float rest = b - bits_to_float((bf16_bits)hi);
+        const unsigned int mid = bf16_bits_rne(rest), lo = bf16_bits_rne(rest - bits_to_float((bf16_bits)mid));
+        const u32x4 parts = {half ? 0u : hi | mid << 16, half ? 0u : lo, 0u, 0u}, ones = {0x3F803F80u, 0x3F80u, 0u, 0u};
+#pragma unroll
+        for (int v = 0; v < 16; ++v) h[v] = 0.f;
+        h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(parts), as_bf16x8(ones), h, 0, 0, 0);
+#pragma unroll
+        for (int s = 0; s < 2 * ND; ++s)
+            h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(w[s]), as_bf16x8(x[s]), h, 0, 0, 0);
+    }
+    __device__ __forceinline__ void finish(unsigned int slice, int part, int parts) {
+        unsigned char* const to = at + (slice & 1u) * 16384u;
+#pragma unroll
+        for (int g = part * 4 / parts; g < (part + 1) * 4 / parts; ++g) {
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = h[4 * g + e] > 0.f ? h[4 * g + e] : 0.f;
+            write_lds8(to + 16u * ((g0 + g) ^ ((r >> 1) & 7u)), bf16_pair(y[0], y[1]), bf16_pair(y[2], y[3]));
+        }
+    }
+    // (the slice is taken from LDS, 16 bytes a thread, and stored a step later: no wait for the reads)
+    __device__ __forceinline__ void done(unsigned int slice) {
+        keep = slice % stride == own && m0 < p.store_rows;
+        if (!keep) return;
+        const unsigned int row = threadIdx.x >> 3, c = threadIdx.x & 7u;
+#pragma unroll
+        for (unsigned int u = 0; u < 2; ++u)
+            v[u] = *reinterpret_cast<const u32x4*>(lds + (slice & 1u) * 16384u + (row + 64u * u) * 128u + 16u * (c ^ ((row >> 1) & 7u)));
+        to = p.H1 + (size_t)(m0 + row) * p.g.K + slice * 64u + c * 8u;
+    }
+    __device__ __forceinline__ void flush() {
+        if (!keep) return;
+        const unsigned int row = m0 + (threadIdx.x >> 3);
+        if (row < p.store_rows) *reinterpret_cast<u32x4*>(to) = v[0];
+        if (row + 64u < p.store_rows) *reinterpret_cast<u32x4*>(to + (size_t)64u * p.g.K) = v[1];
+        keep = false;
+    }
+};
+
+template <class S, int ND>
+__global__ __launch_bounds__(S::kThreads) void forward_kernel(ForwardArgs p) {
+    static_assert(S::BM == 128 && S::kThreads == 512, "a wavefront has 32 x 32 of a slice of H1");
+    constexpr unsigned int BN = S::BN, LD = BN * 2u + 16u;
+    constexpr unsigned int STAGE = BN * 128u + ND * 4096u, H1S = S::NS * STAGE;   // a slice of W2T and of W1T; H1's slices
+    constexpr int GB = BN / 8 / S::NW, L = GB + 1;
+    extern __shared__ uint4 gemm_smem[];
+    unsigned char* smem = reinterpret_cast<unsigned char*>(gemm_smem);
+    unsigned int m0, n0, split;
+    if (!tile_of<S::BM, S::BN>(p.g, blockIdx.x, &m0, &n0, &split)) return;
+    const unsigned int tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned int half = lane >> 5, N = p.g.N, nk = p.g.K / 64u;
+    const bool hi = m0 >= p.g.m_split;
+    const unsigned int group = wave / (S::WGM * S::WGN), wi = wave % (S::WGM * S::WGN), wn = wi % S::WGN, wm = wi / S::WGN;
+    auto swz = [](unsigned int r) { return (r >> 1) & 7u; };
+    unsigned int b_off[GB];
+#pragma unroll
+    for (int u = 0; u < GB; ++u) {
+        const unsigned int r = (wave * GB + u) * 8u + (lane >> 3);
+        b_off[u] = (min(r, N - 1u - n0) * p.g.ldb + ((lane & 7u) ^ swz(r)) * 8u) * 2u;
+    }
+    const gchar b_base = (gchar)reinterpret_cast<const char*>((hi ? p.g.Bt_hi : p.g.Bt) + (size_t)n0 * p.g.ldb);
+    // W1T: 64 units of a slice, ND * 4 requests of 1 KB (ND = 1: two wavefronts make each, so that all count the same in
+    // flight).  Rows of 64 ND bytes; their 16-byte pieces are rotated so that 16 rows' reads fall on all banks.
+    constexpr unsigned int CP = 4u * ND, RR = 64u / CP;
+    auto swz1 = [](unsigned int row) { return ND == 1 ? (row >> 2) & 3u : (row >> 1) & 7u; };
+    const unsigned int w1_req = wave % (4u * ND), w1_row = w1_req * RR + lane / CP;
+    const unsigned int w1_off = (w1_row * p.Dp + ((lane % CP) ^ swz1(w1_row)) * 8u) * 2u;
+    const bf16_bits* const w1t = hi ? p.W1T_hi : p.W1T;
+    auto fetch_one = [&](int u, unsigned int buf, unsigned int slice) {
+        if (u < GB)
+            request_lds(b_base + (size_t)slice * 128u, b_off[u < GB ? u : 0], smem + buf * STAGE + (wave * GB + u) * 1024u);
+        else
+            request_lds((gchar)reinterpret_cast<const char*>(w1t) + (size_t)min(slice + 1u, nk - 1u) * (64u * 64u * ND), w1_off,
+                        smem + buf * STAGE + BN * 128u + w1_req * 1024u);
+    };
+
+    // the first layer: rows 32 (wave mod 4) .., units 32 (wave / 4) .. of a slice
+    const unsigned int rb = wave & 3u, ub = wave >> 2, r = rb * 32u + (lane & 31u), unit = ub * 32u + (lane & 31u);
+    const float* const b1 = hi ? p.b1_hi : p.b1;
+    unsigned char* const b1s = smem + H1S + 2u * S::BM * 128u;
+    for (unsigned int q = wave; q * 256u < p.g.K; q += S::NW)
+        request_lds((gchar)reinterpret_cast<const char*>(b1), min(q * 256u + lane * 4u, p.g.K - 4u) * 4u, b1s + q * 1024u);
+    MakeH1<ND> make{p, reinterpret_cast<const float*>(b1s) + unit, smem + H1S + r * 128u + 8u * half, smem + H1S,
+                    smem + BN * 128u + unit * (64u * ND), STAGE, m0, n0 / BN, p.g.tiles_n, half, ub * 4u, r, swz1(unit), {}, {}, 0.f, {}, {}, nullptr, false};
+    {
+        const bf16_bits* x = p.X + (size_t)min(m0 + r, p.g.M - 1u) * p.Dp + 8u * half;
+        const bf16_bits* w = w1t + (size_t)unit * p.Dp + 8u * half;
+#pragma unroll
+        for (int s = 0; s < 2 * ND; ++s) {
+            make.x[s] = *reinterpret_cast<const u32x4*>(x + 16 * s);
+            make.w[s] = *reinterpret_cast<const u32x4*>(w + 16 * s);
+        }
+        make.b = b1[unit];
+    }
+
+    const unsigned int a_row = H1S + (wm * S::TM * 32u + (lane & 31u)) * 128u, b_row = (wn * S::TN * 32u + (lane & 31u)) * 128u;
+    const unsigned int sw = swz(lane & 31u);
+    u32x4 a[2][S::TM], b[2][S::TN];
+    auto read = [&](unsigned int slice, unsigned int buf, int s, int set) {
+        const unsigned int ko = ((2u * (group * S::SP + s) + half) ^ sw) * 16u;
+#pragma unroll
+        for (int j = 0; j < S::TN; ++j) b[set][j] = *reinterpret_cast<const u32x4*>(smem + buf * STAGE + b_row + ko + j * 4096);
+#pragma unroll
+        for (int i = 0; i < S::TM; ++i) a[set][i] = *reinterpret_cast<const u32x4*>(smem + (slice & 1u) * 16384u + a_row + ko + i * 4096);
+    };
+    f32x16 acc[S::TM][S::TN];
+    auto mfma = [&](int i, int j, int set) {
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(b[set][j]), as_bf16x8(a[set][i]), acc[i][j], 0, 0, 0);
+    };
+    f32x4 bv[S::TN][4];
+    unsigned int em, en;
+    mm_wave_at<S>(wave, &em, &en);
+    mm_clear<S>(acc);
+    mm_pipeline<S, L>(nk, fetch_one, read, mfma, [](unsigned int, unsigned int) {}, [&]() {
+        const float* b2 = hi ? p.b2_hi : p.b2;
+#pragma unroll
+        for (int j = 0; j < S::TN; ++j)
+#pragma unroll
+            for (unsigned int g = 0; g < 4; ++g) {
+                const unsigned int n = n0 + en + j * 32u + 8u * g + 4u * half;
+                bv[j][g] = *reinterpret_cast<const f32x4*>(b2 + (n < N ? n : 0u));
+            }
+    }, make);
+    make.flush();
+    mm_swap_groups<S>(acc, smem, wave, lane);
+#pragma unroll
+    for (int i = 0; i < S::TK; ++i)
+#pragma unroll
+        for (int j = 0; j < S::TN; ++j)
+#pragma unroll
+            for (unsigned int g = 0; g < 4; ++g) {
+                float x[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    x[e] = acc[i][j][4 * g + e] + bv[j][g][e];
+                    x[e] = x[e] > 0.f ? x[e] : 0.f;
+                }
+                uint2 pk;
+                pk.x = bf16_pair(x[0], x[1]);
+                pk.y = bf16_pair(x[2], x[3]);
+                *reinterpret_cast<uint2*>(smem + (em + i * 32u + (lane & 31u)) * LD + (en + j * 32u + 8u * g + 4u * half) * 2u) = pk;
+            }
+    // (a wavefront stores what it parked: its LDS operations complete in order)
+    constexpr unsigned int CR = S::TN * 4u, RP = 64u / CR;
+#pragma unroll
+    for (unsigned int q = 0; q < S::TK * 32u / RP; ++q) {
+        const unsigned int row = em + q * RP + lane / CR, c = en + lane % CR * 8u;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(smem + row * LD + c * 2u);
+        if (m0 + row < p.g.M && n0 + c < N) *reinterpret_cast<u32x4*>(p.H2 + (size_t)(m0 + row) * N + n0 + c) = v;
+    }
+}
+
+// ----------------------------------------------------------------------------------------
 // TD target, loss and the gradient at the second hidden layer's pre-activation.
 // A workgroup owns 16 batch rows x 256 hidden units, sixteen lanes to a row.  The lanes of a row
 // work out y_i = r_i + gamma (1 - term_i) max_a Q(s'_i, a), delta_i = y_i - Q(s_i, a_i), the loss
@@ -1688,13 +1899,22 @@ const void* head_func(unsigned int G, bool target) {
 }
 
 template <class S>
+hipError_t configure_forward() {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(forward_kernel<S, 1>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)forward_lds<S, 1>());
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(forward_kernel<S, 2>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)forward_lds<S, 2>());
+}
+
+template <class S>
 hipError_t configure_grad_back() {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(grad_back_kernel<S>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::kLds);
 }
 
 // How the backward half of a step is launched.
-WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G) {
+WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G, unsigned int Dp) {
     WidePlan p;
     const unsigned int Bp = (B + 127u) / 128u * 128u;
     // Two launches (above) wherever the first layer's error has many tiles, and on large batches: us per step in the small
@@ -1705,10 +1925,18 @@ WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G) {
     p.merged = !few_tiles(B, H) || B >= 1536u || (B >= 576u && G <= 512u);
     p.large = false;
     p.k2 = Bp;
+    p.fw_cols = 0;
     if (!p.merged) {
         p.splits3 = p.splits1 = batch_splits(Bp);
         p.splits2 = p.splits_b2 = square_splits_for(Bp, H, G);
         return p;
+    }
+    // The first two layers in one launch (up to 64 states; beyond, the first layer repeated in every tile is too much),
+    // in tiles of 128 x 256 or 128 x 128: those that take less time in rounds of workgroups, 0.75 and 0.4 us a slice.
+    if (Dp <= 64u && H <= kFwMaxH) {
+        const unsigned int rows = (2u * B + 127u) / 128u;
+        const double large = (rows * ((G + 255u) / 256u) + 255u) / 256u * 0.75, small = (rows * ((G + 127u) / 128u) + 255u) / 256u * 0.4;
+        p.fw_cols = large <= small ? 256u : 128u;
     }
     // The tiles' height and the splits of dW2's contraction: those whose launch ends first.  A compute unit holds one
     // workgroup; one takes about 5 us (dZ1's, with the first layer's gradient) or 3 us and, per slice of 64 of its
@@ -1758,7 +1986,7 @@ bf16_bits host_bf16(float f) {
 
 }  // namespace
 
-WidePlan wide_plan(unsigned int B, unsigned int H, unsigned int G) { return plan_for(B, H, G); }
+WidePlan wide_plan(unsigned int B, unsigned int H, unsigned int G, unsigned int Dp) { return plan_for(B, H, G, Dp); }
 
 // Two hidden layers of one width, or of two.  This step is the faster one at every size measured (27
 // inputs, 30 actions, one new experience a step, us per step layer by layer -> this: 64-256 at batch 8
@@ -1776,6 +2004,8 @@ hipError_t wide_configure() {
     if (ec == hipSuccess) ec = configure_gemm<128, 128, 64, 2, 2, EpiForward>();
     if (ec == hipSuccess) ec = configure_grad_products<true>();
     if (ec == hipSuccess) ec = configure_grad_products<false>();
+    if (ec == hipSuccess) ec = configure_forward<FwLarge>();
+    if (ec == hipSuccess) ec = configure_forward<FwSmall>();
     if (ec == hipSuccess) ec = configure_grad_back<GbLarge>();
     if (ec == hipSuccess) ec = configure_grad_back<GbSmall>();
     return ec;
@@ -1813,7 +2043,33 @@ static bool rows_in_one_launch(const trainer* t) { return !t->wt || t->B % 128 =
 // train_create adds itself: the dueling head's update, a draw in a launch of its own)
 unsigned int wide_step_kernels(const trainer* t) {
     const unsigned int halves = rows_in_one_launch(t) ? 1u : 2u;   // launches of each layer's forward product
-    return t->plan.merged ? 4u + 2u * halves : 5u + 3u * halves;
+    return t->plan.merged ? 4u + (t->plan.fw_cols ? 1u : 2u) * halves : 5u + 3u * halves;
+}
+
+// The first two layers' products for `rows` rows from row `at` on; with m_split, rows from there on take the target
+// network's weights, with target all of them.
+template <class S>
+static hipError_t launch_forward(trainer* t, hipStream_t st, const bf16_bits* X, unsigned int at, unsigned int rows,
+                                 unsigned int m_split, bool target) {
+    const unsigned int H = t->H, G = t->Hb, Dp = t->Dp;
+    const WideBuffers& w = t->wd;
+    const float* wt = t->wt ? t->wt : t->w;
+    ForwardArgs a;
+    unsigned int blocks;
+    // (A is not read: the workgroups make it)
+    if (!gemm_args<S::BM, S::BN, 64>(nullptr, H, target ? w.W2T_t : w.W2T, H, rows, G, H, 1,
+                                     m_split != ~0u ? w.W2T_t : nullptr, m_split, &a.g, &blocks))
+        return hipErrorInvalidValue;
+    a.X = X + (size_t)at * Dp; a.Dp = Dp;
+    a.W1T = target ? w.W1T_t : w.W1T; a.W1T_hi = t->wt ? w.W1T_t : w.W1T;
+    a.b1 = (target ? wt : t->w) + t->ob1; a.b1_hi = wt + t->ob1;
+    a.b2 = (target ? wt : t->w) + t->ob2; a.b2_hi = wt + t->ob2;
+    a.H1 = static_cast<bf16_bits*>(t->H1); a.store_rows = at ? 0u : t->B;
+    a.H2 = static_cast<bf16_bits*>(t->H2) + (size_t)at * G;
+    constexpr size_t lds1 = forward_lds<S, 1>(), lds2 = forward_lds<S, 2>();
+    if (Dp == 32u) hipLaunchKernelGGL((forward_kernel<S, 1>), dim3(blocks), dim3(S::kThreads), lds1, st, a);
+    else hipLaunchKernelGGL((forward_kernel<S, 2>), dim3(blocks), dim3(S::kThreads), lds2, st, a);
+    return hipGetLastError();
 }
 
 template <class S>
@@ -1866,28 +2122,43 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
         if (e != hipSuccess) return e;
         n += launched;
     }
-    // forward on the 2B rows
-    e = launch_gemm<128, 128, 32, 2, 2>(st, X, Dp, w.W1T, Dp, rows, H, Dp,
-                                           EpiForward{t->w + t->ob1, b1t, tgt ? B : ~0u, H1, H, rows, H},
-                                           1, tgt && one_launch ? w.W1T_t : nullptr, B);
-    if (e != hipSuccess) return e;
-    ++n;
-    if (!one_launch) {
-        e = launch_gemm<128, 128, 32, 2, 2>(st, X + (size_t)B * Dp, Dp, w.W1T_t, Dp, B, H, Dp,
-                                               EpiForward{b1t, b1t, ~0u, H1 + (size_t)B * H, H, B, H});
-        if (e != hipSuccess) return e;
-        ++n;
-    }
-    const float* b2 = t->w + t->ob2;
-    e = second_layer(st, H1, rows, H, G, w.W2T, b2, H2, tgt && one_launch ? w.W2T_t : nullptr, b2t, B);
-    if (e != hipSuccess) return e;
-    ++n;
-    if (!one_launch) {
-        e = second_layer(st, H1 + (size_t)B * H, B, H, G, w.W2T_t, b2t, H2 + (size_t)B * G, nullptr, nullptr, 0);
-        if (e != hipSuccess) return e;
-        ++n;
-    }
     const WidePlan& plan = t->plan;
+    if (plan.fw_cols) {
+        auto forward = [&](unsigned int at, unsigned int n_rows, unsigned int split, bool target) {
+            return plan.fw_cols == 256u ? launch_forward<FwLarge>(t, st, X, at, n_rows, split, target)
+                                        : launch_forward<FwSmall>(t, st, X, at, n_rows, split, target);
+        };
+        e = forward(0, rows, tgt && one_launch ? B : ~0u, false);
+        if (e != hipSuccess) return e;
+        ++n;
+        if (!one_launch) {
+            e = forward(B, B, ~0u, true);
+            if (e != hipSuccess) return e;
+            ++n;
+        }
+    } else {
+        // forward on the 2B rows
+        e = launch_gemm<128, 128, 32, 2, 2>(st, X, Dp, w.W1T, Dp, rows, H, Dp,
+                                               EpiForward{t->w + t->ob1, b1t, tgt ? B : ~0u, H1, H, rows, H},
+                                               1, tgt && one_launch ? w.W1T_t : nullptr, B);
+        if (e != hipSuccess) return e;
+        ++n;
+        if (!one_launch) {
+            e = launch_gemm<128, 128, 32, 2, 2>(st, X + (size_t)B * Dp, Dp, w.W1T_t, Dp, B, H, Dp,
+                                                   EpiForward{b1t, b1t, ~0u, H1 + (size_t)B * H, H, B, H});
+            if (e != hipSuccess) return e;
+            ++n;
+        }
+        const float* b2 = t->w + t->ob2;
+        e = second_layer(st, H1, rows, H, G, w.W2T, b2, H2, tgt && one_launch ? w.W2T_t : nullptr, b2t, B);
+        if (e != hipSuccess) return e;
+        ++n;
+        if (!one_launch) {
+            e = second_layer(st, H1 + (size_t)B * H, B, H, G, w.W2T_t, b2t, H2 + (size_t)B * G, nullptr, nullptr, 0);
+            if (e != hipSuccess) return e;
+            ++n;
+        }
+    }
     if (!plan.merged) {
         SkinnyArgs a;
         a.A = H2; a.lda = G; a.Bt = w.W3T; a.ldb = G; a.M = rows; a.N = Ap; a.K = G;

@@ -1227,6 +1227,9 @@ def test_mixed_precision_products_with_few_tiles(B, H, H2, batch, target_sync):
     (31, 1024, 64, 33, 9000, 0, True),
     (9, 64, 512, 6, 577, 3, True),        # few tiles, a batch above the rule's line; a row of two steps a wavefront
     (27, 64, 1088, 30, 1537, 0, False),   # rows wider than the output layer's kernel holds at a time
+    (27, 128, 512, 30, 640, 3, False),    # both networks' rows in one launch of the first two layers; two slices of H1
+    (64, 192, 256, 30, 1600, 0, False),   # three slices, the fewest that are requested inside the loop; 64 states
+    (20, 2112, 64, 30, 600, 0, False),    # first layer too wide for that launch
 ])
 def test_mixed_precision_backward_in_two_launches(B, D, H, H2, A, batch, target_sync, dueling):
     """Large steps: output layer, TD errors and the second layer's error in one launch, all gradients and the first
