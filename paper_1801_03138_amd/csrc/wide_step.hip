@@ -751,10 +751,13 @@ hipError_t launch_gemm(hipStream_t st, const bf16_bits* A, unsigned int lda, con
 // ----------------------------------------------------------------------------------------
 // Product with few output tiles: the output layer, Q = H2 W3 + b3 (a few 32-wide column tiles, many
 // rows), and others on small batches (few_tiles):
-// one 32x32 output tile per workgroup; the wavefronts split K, each loading its MFMA operands
-// straight from global memory (eight 16-deep steps requested before the first multiply), and
-// add their accumulators through LDS.  K is a multiple of 16.  Rows beyond M / N read row 0
-// instead: they only reach accumulator elements that are not stored.
+// one tile of 16 MT x 32 outputs per workgroup; the eight wavefronts split K, each loading its MFMA operands
+// straight from global memory (four 32-deep steps requested before the first multiply), and
+// add their accumulators through LDS.  K and N are multiples of 32.  Rows beyond M repeat the last one and are not
+// stored.  What such a launch costs beyond its start is its loads: a wavefront's of 16 rows touches 16 runs of 64 bytes,
+// where one of 32 rows (32x32x16 MFMA, tiles of 32 x 32) touched 32 of 32 bytes.  32 x 32 tiles of that kind -> this:
+// output layer 1024 x 32 x 1024 6.6 -> 5.0 us, first layer's error 512 x 128 x 1024 7.0 -> 5.1; us per step, 27-128-1024-30
+// at batch 512 42.9 -> 38.7, 1024-1024 at 64 43.3 -> 38.0, at 512 57.0 -> 53.9, 64-64 at 80 24.9 -> 23.6.
 // ----------------------------------------------------------------------------------------
 struct SkinnyArgs {
     const bf16_bits* A;
@@ -803,43 +806,69 @@ struct SkinnyMask {
     }
 };
 
-template <int NW, class Epi>
-__global__ __launch_bounds__(64 * NW) void skinny_nt_kernel(SkinnyArgs p, Epi epi) {
-    __shared__ float red[NW * 16 * 64];
-    const unsigned int tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const unsigned int m0 = blockIdx.x * 32u, n0 = blockIdx.y * 32u;
-    const unsigned int am = m0 + (lane & 31u), bn = n0 + (lane & 31u);
-    const bf16_bits* ap = p.A + (size_t)(am < p.M ? am : 0u) * p.lda + 8u * (lane >> 5);
+template <int MT, class Epi>
+__global__ __launch_bounds__(512) void skinny_nt_kernel(SkinnyArgs p, Epi epi) {
+    constexpr unsigned int NW = 8, LD = 36;
+    __shared__ float red[NW][16 * MT][LD];
+    const unsigned int tid = threadIdx.x, lane = tid & 63u, r16 = lane & 15u, q16 = lane >> 4;
+    const unsigned int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned int m0 = blockIdx.x * (16u * MT), n0 = blockIdx.y * 32u;
+    const bf16_bits* ap[MT];
+#pragma unroll
+    for (unsigned int i = 0; i < MT; ++i) ap[i] = p.A + (size_t)min(m0 + 16u * i + r16, p.M - 1u) * p.lda + 8u * q16;
     const bool hi = m0 >= p.m_split;
-    const bf16_bits* bp = (hi ? p.Bt_hi : p.Bt) + (size_t)(bn < p.N ? bn : 0u) * p.ldb + 8u * (lane >> 5);
+    const bf16_bits* bp = (hi ? p.Bt_hi : p.Bt) + (size_t)(n0 + r16) * p.ldb + 8u * q16;
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
-    f32x16 acc;
+    f32x4 acc[MT][2];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (unsigned int kc = wave * 128u; kc < p.K; kc += NW * 128u) {
-        u32x4 a[8], b[8];
+        u32x4 a[MT][4], b[2][4];
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const unsigned int k = kc + s * 16u;
+        for (int s = 0; s < 4; ++s) {
+            const unsigned int k = kc + s * 32u;
             const bool in = k < p.K;
-            a[s] = in ? *reinterpret_cast<const u32x4*>(ap + k) : zero4;
-            b[s] = in ? *reinterpret_cast<const u32x4*>(bp + k) : zero4;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[i][s] = in ? *reinterpret_cast<const u32x4*>(ap[i] + k) : zero4;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                b[j][s] = in ? *reinterpret_cast<const u32x4*>(bp + (size_t)(16u * j) * p.ldb + k) : zero4;
         }
 #pragma unroll
-        for (int s = 0; s < 8; ++s)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a[s]), as_bf16x8(b[s]), acc, 0, 0, 0);
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a[i][s]), as_bf16x8(b[j][s]), acc[i][j], 0, 0, 0);
     }
 #pragma unroll
-    for (int v = 0; v < 16; ++v) red[(wave * 16u + v) * 64u + lane] = acc[v];
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[wave][16u * i + 4u * q16 + v][16u * j + r16] = acc[i][j][v];
     __syncthreads();
-    for (unsigned int e = tid; e < 1024u; e += 64u * NW) {
-        const unsigned int v = e >> 6, l = e & 63u;
+#pragma unroll
+    for (unsigned int i = 0; i < MT; ++i) {
+        const unsigned int r = 16u * i + (tid >> 5), c = tid & 31u;
         float s = 0.f;
 #pragma unroll
-        for (unsigned int w = 0; w < (unsigned int)NW; ++w) s += red[(w * 16u + v) * 64u + l];
-        const unsigned int m = m0 + acc_row(v, l), n = n0 + (l & 31u);
-        if (m < p.M && n < p.N) epi.store(m, n, s);
+        for (unsigned int w = 0; w < NW; ++w) s += red[w][r][c];
+        if (m0 + r < p.M) epi.store(m0 + r, n0 + c, s);
     }
+}
+
+// 16 rows a tile while that leaves no more tiles than two a compute unit, 32 beyond (16 rows fetch the B operand twice
+// as often: 64-512-512-64 at batch 500 41.3 us per step, 39.2 with 32; 1024-1024 at 256 49.7, 46.5).
+template <class Epi>
+hipError_t launch_skinny(hipStream_t st, const SkinnyArgs& a, const Epi& epi) {
+    const dim3 g16((a.M + 15) / 16, a.N / 32), g32((a.M + 31) / 32, a.N / 32);
+    if ((size_t)g16.x * g16.y <= 512u) hipLaunchKernelGGL((skinny_nt_kernel<1, Epi>), g16, dim3(512), 0, st, a, epi);
+    else hipLaunchKernelGGL((skinny_nt_kernel<2, Epi>), g32, dim3(512), 0, st, a, epi);
+    return hipGetLastError();
 }
 
 // ----------------------------------------------------------------------------------------
@@ -1883,9 +1912,7 @@ hipError_t second_layer(hipStream_t st, const bf16_bits* H1, unsigned int rows, 
     if (!hi) m_split = ~0u;
     if (few_tiles(rows, G)) {
         const SkinnyArgs a{H1, H, W2T, H, rows, G, H, hi ? hi : W2T, m_split};
-        hipLaunchKernelGGL((skinny_nt_kernel<8, SkinnyRelu>), dim3((rows + 31) / 32, G / 32), dim3(512), 0, st, a,
-                           SkinnyRelu{b2, b2_hi, m_split, H2, G});
-        return hipGetLastError();
+        return launch_skinny(st, a, SkinnyRelu{b2, b2_hi, m_split, H2, G});
     }
     return launch_gemm<128, 128, 64, 2, 2>(st, H1, H, W2T, H, rows, G, H, EpiForward{b2, b2_hi, m_split, H2, G, rows, G},
                                            1, hi, m_split);
@@ -1917,11 +1944,12 @@ hipError_t configure_grad_back() {
 WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G, unsigned int Dp) {
     WidePlan p;
     const unsigned int Bp = (B + 127u) / 128u * 128u;
-    // Two launches (above) wherever the first layer's error has many tiles, and on large batches: us per step in the small
-    // form, the large one (27 inputs, 30 actions): 64-64 at batch 4000 35.1, 29.3, 1000 27.0, 25.3; 256-256 at 1000 32.6,
-    // 29.6; 128-1024 at 4096, head and target network, 62.2, 52.9, 2048 48.5, 46.2, but 1024 with target network 43.1,
-    // 44.2: a long contraction in few tiles.  Below some 576 either may be the faster: 256-256 at 500 29.2,
-    // 27.2, 64-512-512-64 39.4, 41.0, 1024-1024 at 64 43.2, 45.3.
+    // The large form wherever the first layer's error has many tiles, and on large batches: us per step in the small form,
+    // the large one (27 inputs, 30 actions): 64-64 at batch 4000 34.5, 27.3, 1000 26.1, 24.1; 256-256 at 600 30.7, 27.8;
+    // 128-1024 at 4096, head and target network, 61.4, 51.2, 1536 45.1, 41.4; 96-320-320-10 at 800 38.3, 38.6.  The line
+    // for wide second layers: 128-1024 at 1024 with target network 43.1, 44.2 (a long contraction in few tiles; 39 since the
+    // small form's products took tiles of 16 rows).  Below some 576 either may be the faster: 256-256 at 500 29.2, 27.2,
+    // 64-512-512-64 39.4, 41.0, 1024-1024 at 64 43.2, 45.3.
     p.merged = !few_tiles(B, H) || B >= 1536u || (B >= 576u && G <= 512u);
     p.large = false;
     p.k2 = Bp;
@@ -2164,16 +2192,12 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
         a.A = H2; a.lda = G; a.Bt = w.W3T; a.ldb = G; a.M = rows; a.N = Ap; a.K = G;
         a.Bt_hi = tgt ? w.W3T_t : w.W3T; a.m_split = tgt ? B : ~0u;
         const float* b3 = t->w + t->ob3;
-        hipLaunchKernelGGL((skinny_nt_kernel<8, SkinnyBias>), dim3((rows + 31) / 32, Ap / 32), dim3(512), 0, st, a,
-                           SkinnyBias{b3, tgt ? b3t : b3, a.m_split, t->Q, Ap});
-        e = hipGetLastError();
+        e = launch_skinny(st, a, SkinnyBias{b3, tgt ? b3t : b3, a.m_split, t->Q, Ap});
         if (e != hipSuccess) return e;
         ++n;
         if (!one_launch) {
             a.A = H2 + (size_t)B * G; a.M = B; a.Bt = a.Bt_hi = w.W3T_t; a.m_split = ~0u;
-            hipLaunchKernelGGL((skinny_nt_kernel<8, SkinnyBias>), dim3((B + 31) / 32, Ap / 32), dim3(512), 0, st, a,
-                               SkinnyBias{b3t, b3t, ~0u, t->Q + (size_t)B * Ap, Ap});
-            e = hipGetLastError();
+            e = launch_skinny(st, a, SkinnyBias{b3t, b3t, ~0u, t->Q + (size_t)B * Ap, Ap});
         }
     }
     if (e != hipSuccess) return e;
@@ -2214,9 +2238,7 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
         }
         // dZ1 = (dZ2 W2^T) masked by the first ReLU; uses W2 before its update
         const SkinnyArgs za{dZ2, G, w.W2, G, B, H, G, w.W2, ~0u};
-        hipLaunchKernelGGL((skinny_nt_kernel<8, SkinnyMask>), dim3((B + 31) / 32, H / 32), dim3(512), 0, st, za,
-                           SkinnyMask{H1, dZ1, H});
-        e = hipGetLastError();
+        e = launch_skinny(st, za, SkinnyMask{H1, dZ1, H});
         if (e != hipSuccess) return e;
         ++n;
         // the three weight-gradient products, K-split partials each, in one launch:
