@@ -44,8 +44,8 @@ GATHER_KERNEL = "sample_gather_pair_kernel<4, 2, 0>"
 LARGE_256_HBM_BYTES = (7154.9 * 2.000 + 56461.1 * 1.000) * 1024
 # and for append_pair_bulk_kernel<unsigned int> at 65,536 rows (profiles/append_bulk_kernel_hbm_traffic_pmc.txt)
 APPEND_65536_HBM_BYTES = (7314.5 * 2.000 + 16384.0 * 1.000) * 1024
-# and summed over the seven kernels of one wide step of a recorded run (profiles/wide_step_kernels_hbm_traffic_pmc.txt)
-WIDE_STEP_HBM_BYTES = (85891.6 * 2.000 + 94051.8 * 1.000) * 1024
+# and summed over the four kernels of one wide step of a recorded run (profiles/wide_step_kernels_hbm_traffic_pmc.txt)
+WIDE_STEP_HBM_BYTES = (70863.4 * 2.000 + 78676.4 * 1.000) * 1024
 
 
 def log(*a):
@@ -583,7 +583,7 @@ def main():
         out["wide_step"] = w
         log("[bench]   %.1f steps/s, %.1f TFLOP/s" % (w["steps_per_s"], w["TFLOPs"]))
         rooflines.append({"kernel": "whole wide step (%d kernels step by step, one fewer in the recorded runs "
-                                    "timed here; the dense products are gemm_nt_kernel)" % w["kernels_per_step"],
+                                    "timed here; the dense products are forward_kernel and grad_back_kernel)" % w["kernels_per_step"],
                           "workload": "wide fused step: batch 4096, 27-1024-1024-30, bf16 operands, fp32 "
                                       "accumulation, Adam, 64 appends per step", "bound": "mfma",
                           "achieved": w["TFLOPs"], "peak": BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
