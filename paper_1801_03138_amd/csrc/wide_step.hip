@@ -20,7 +20,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <functional>
-#include <queue>
 #include <type_traits>
 #include <vector>
 
@@ -1980,14 +1979,13 @@ WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G, unsigned int D
         for (unsigned int s = 1; s <= 16u && (s == 1 || B / s >= 256u); s *= 2u) {
             const unsigned int k = ((B + s - 1u) / s + 63u) / 64u * 64u, splits = (B + k - 1u) / k;
             const double t_dz = rounds * (5. + G / 64u * slice), t_dw = 3. + k / 64u * slice;
-            std::priority_queue<double, std::vector<double>, std::greater<double>> free_at(std::greater<double>(), std::vector<double>(256, 0.));
-            double end = 0.;
+            double free_at[256] = {}, end = 0.;              // (a heap, the earliest at the front)
             const unsigned int n_dz = rows * ((H + 127u) / 128u), n = n_dz + tiles(H, G) * splits;
             for (unsigned int i = 0; i < n; ++i) {
-                const double t = free_at.top() + (i < n_dz ? t_dz : t_dw);
-                free_at.pop();
-                free_at.push(t);
-                end = std::max(end, t);
+                std::pop_heap(free_at, free_at + 256, std::greater<double>());
+                free_at[255] += i < n_dz ? t_dz : t_dw;
+                end = std::max(end, free_at[255]);
+                std::push_heap(free_at, free_at + 256, std::greater<double>());
             }
             end += 8e-6 * splits * H * G / 4.5;
             if (best != 0. && end >= best) continue;
