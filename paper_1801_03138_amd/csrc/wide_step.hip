@@ -394,7 +394,7 @@ __device__ __forceinline__ void gemm_nt_block(const GemmArgs& p, const Epi& epi,
 // of a slice's steps, and add their accumulators through LDS at the end.  The square layer's tiles
 // have a compute unit to themselves, and with one wavefront per SIMD the transposing reads (twice
 // the instructions of the 16-byte ones), the MFMAs and the requests hardly overlapped: 23.9 us per
-// launch at batch 4096 and 1024 units with one group, 21.8 with two.  Deeper pipelines (four slices of
+// launch at batch 4096 and 1024 units (which take grad_back_kernel now) with one group, 21.8 with two.  Deeper pipelines (four slices of
 // 64 or 32 rows: 23.8, 24.4) and two workgroups per compute unit (128 registers, spills: 23.2) were slower.
 //
 // Transposed copies of H1, H2 and both errors (24 MB written and 16 MB read a step by the kernel
@@ -1896,9 +1896,9 @@ unsigned int square_splits_for(unsigned int Bp, unsigned int H, unsigned int G) 
 }
 
 // A product with M x N outputs that has few tiles of 128 x 64: those leave most of the chip idle, each
-// a serial chain over the whole contraction, and the product in 32 x 32 tiles, K split over eight
+// a serial chain over the whole contraction, and the product in tiles of 32 columns, K split over eight
 // wavefronts, is the faster one although it fetches its operands more often.  us per step, tiled
-// -> this (27 inputs, 30 actions), for the first layer's error: 8 tiles (batch 512, 128-1024) 48.2 ->
+// -> this, in tiles of 32 rows (27 inputs, 30 actions), for the first layer's error: 8 tiles (batch 512, 128-1024) 48.2 ->
 // 41.7, 64 tiles (batch 512, 1024-1024) 61.3 -> 59.2, 128 tiles (batch 1024) 68.1 -> 73.3; for the second
 // layer: 64 tiles (batch 256, 1024-1024) 54.8 -> 51.3, 16 (batch 40, 1024-1024) 51.7 -> 44.9, K = 64
 // (batch 100, 64-64) 27.1 -> 25.9, 128 tiles (batch 512, 1024-1024) 59.4 -> 63.1.
