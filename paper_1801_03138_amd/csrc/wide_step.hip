@@ -873,9 +873,12 @@ hipError_t launch_skinny(hipStream_t st, const SkinnyArgs& a, const Epi& epi) {
 // ----------------------------------------------------------------------------------------
 // The first two layers of large steps in one launch: H2 = relu(relu(X W1 + b1) W2 + b2) for a tile of 128 rows x BN
 // units.  The second layer's operand H1 is never read: the workgroup works its rows' H1 out, a slice of 64 units ahead of
-// the product (each wavefront 32 rows x 32 units, from X in its registers and W1's rows, with the bias as the
-// accumulator's start), and leaves it in LDS.  The rows' H1 is needed again by the backward half: of the rows of S each
-// of the row's tiles stores every so many'th slice.
+// the product (each wavefront 32 rows x 32 units, from X in its registers and W1's rows), and leaves it in LDS.  The rows'
+// H1 is needed again by the backward half: of the rows of S each of the row's tiles stores every so many'th slice.
+// The bias is added in fp32 after the product, as in the launch of its own that smaller steps have, and H1 has the same
+// bits.  With the bias as a step of the product, in three bf16 parts, the step was no faster (1024-1024 at batch 4096 76.9
+// us, 76.3 like this), an infinite bias became NaN and so zero, and the gradients were twice as far from those worked out
+// in 64 bits with the same bf16 roundings (dW1 there 5.6e-4, like this 2.9e-4).
 // The workgroups of a row of tiles repeat the first layer (an eighth of the second's MFMAs at 256 units and 32 states);
 // as a launch of its own it was bound by its start and by writing and reading H1 (17 MB each way at batch 4096 and
 // 1024 units).  6.8 + 20.8 us -> 27.0 there, but us per step 81.4 -> 79.6 (the S' half of H1 never goes to memory); at
@@ -906,35 +909,30 @@ constexpr size_t forward_lds() {
 }
 
 // The slices of H1.  W1T's come with W2T's requests, one ahead, and the bias before them (their first from memory; a load in
-// the loop would make the compiler wait for the requests in flight); the bias is one more step of the product: its three
-// bf16 parts, which add up to the fp32 number, times ones.
+// the loop would make the compiler wait for the requests in flight).
 template <int ND>
 struct MakeH1 {
     const ForwardArgs& p;
-    const float* b1;                     // of this lane's unit in a slice (in LDS)
+    const float* b1;                     // of this lane's first unit in a slice (in LDS)
     unsigned char *at, *lds, *w1;        // where this lane's first four units go; H1's slices; this lane's row of a slice of W1T
     unsigned int stage;                  // bytes between W1T's slices
     unsigned int m0, own, stride, half, g0, r, sw;   // own: the first slice this workgroup stores, then every stride-th
     u32x4 x[2 * ND], w[2 * ND];
-    float b;
+    f32x4 b[4];
     f32x16 h;
     u32x4 v[2];
     bf16_bits* to;
     bool keep;
     __device__ __forceinline__ void start(unsigned int slice, unsigned int buf) {
-        b = b1[slice * 64u];
+#pragma unroll
+        for (unsigned int g = 0; g < 4; ++g) b[g] = *reinterpret_cast<const f32x4*>(b1 + slice * 64u + 8u * g);
 #pragma unroll
         for (unsigned int s = 0; s < 2 * ND; ++s)
             w[s] = *reinterpret_cast<const u32x4*>(w1 + buf * stage + 16u * ((2u * s + half) ^ sw));
     }
     __device__ __forceinline__ void multiply(unsigned int) {
-        const unsigned int hi = bf16_bits_rne(b);
-        const float rest = b - bits_to_float((bf16_bits)hi);
-        const unsigned int mid = bf16_bits_rne(rest), lo = bf16_bits_rne(rest - bits_to_float((bf16_bits)mid));
-        const u32x4 parts = {half ? 0u : hi | mid << 16, half ? 0u : lo, 0u, 0u}, ones = {0x3F803F80u, 0x3F80u, 0u, 0u};
 #pragma unroll
         for (int v = 0; v < 16; ++v) h[v] = 0.f;
-        h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(parts), as_bf16x8(ones), h, 0, 0, 0);
 #pragma unroll
         for (int s = 0; s < 2 * ND; ++s)
             h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(w[s]), as_bf16x8(x[s]), h, 0, 0, 0);
@@ -945,7 +943,10 @@ struct MakeH1 {
         for (int g = part * 4 / parts; g < (part + 1) * 4 / parts; ++g) {
             float y[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] = h[4 * g + e] > 0.f ? h[4 * g + e] : 0.f;
+            for (int e = 0; e < 4; ++e) {
+                y[e] = h[4 * g + e] + b[g][e];
+                y[e] = y[e] > 0.f ? y[e] : 0.f;
+            }
             write_lds8(to + 16u * ((g0 + g) ^ ((r >> 1) & 7u)), bf16_pair(y[0], y[1]), bf16_pair(y[2], y[3]));
         }
     }
@@ -1011,8 +1012,9 @@ __global__ __launch_bounds__(S::kThreads) void forward_kernel(ForwardArgs p) {
     unsigned char* const b1s = smem + H1S + 2u * S::BM * 128u;
     for (unsigned int q = wave; q * 256u < p.g.K; q += S::NW)
         request_lds((gchar)reinterpret_cast<const char*>(b1), min(q * 256u + lane * 4u, p.g.K - 4u) * 4u, b1s + q * 1024u);
-    MakeH1<ND> make{p, reinterpret_cast<const float*>(b1s) + unit, smem + H1S + r * 128u + 8u * half, smem + H1S,
-                    smem + BN * 128u + unit * (64u * ND), STAGE, m0, n0 / BN, p.g.tiles_n, half, ub * 4u, r, swz1(unit), {}, {}, 0.f, {}, {}, nullptr, false};
+    const unsigned int unit0 = ub * 32u + 4u * half;         // units unit0 + 8 g .. + 3 are this lane's
+    MakeH1<ND> make{p, reinterpret_cast<const float*>(b1s) + unit0, smem + H1S + r * 128u + 8u * half, smem + H1S,
+                    smem + BN * 128u + unit * (64u * ND), STAGE, m0, n0 / BN, p.g.tiles_n, half, ub * 4u, r, swz1(unit), {}, {}, {}, {}, {}, nullptr, false};
     {
         const bf16_bits* x = p.X + (size_t)min(m0 + r, p.g.M - 1u) * p.Dp + 8u * half;
         const bf16_bits* w = w1t + (size_t)unit * p.Dp + 8u * half;
@@ -1021,7 +1023,8 @@ __global__ __launch_bounds__(S::kThreads) void forward_kernel(ForwardArgs p) {
             make.x[s] = *reinterpret_cast<const u32x4*>(x + 16 * s);
             make.w[s] = *reinterpret_cast<const u32x4*>(w + 16 * s);
         }
-        make.b = b1[unit];
+#pragma unroll
+        for (unsigned int g = 0; g < 4; ++g) make.b[g] = *reinterpret_cast<const f32x4*>(b1 + unit0 + 8u * g);
     }
 
     const unsigned int a_row = H1S + (wm * S::TM * 32u + (lane & 31u)) * 128u, b_row = (wn * S::TN * 32u + (lane & 31u)) * 128u;

@@ -1246,6 +1246,48 @@ def test_mixed_precision_backward_in_two_launches(B, D, H, H2, A, batch, target_
         oracle.set_threads(1)
 
 
+@pytest.mark.parametrize("bias", [None, np.inf, 3.4e38, -np.inf])
+@pytest.mark.parametrize("D,H2,batch", [
+    (27, 128, 640),       # tiles of 128 x 128
+    (64, 128, 577),       # ... two blocks of states, a batch that ends inside a tile
+    (27, 2048, 1600),     # tiles of 128 x 256
+])
+def test_first_layer_of_large_steps_is_that_of_small_ones(B, D, H2, batch, bias):
+    """Large steps form the first layer inside the launch of the second, small ones in a launch of its own; both round
+    the same fp32 sum to bf16.  Here W2 passes the first layer's units on and W3 picks one for each action, so that
+    the Q-values are those units, and equal bit for bit.  With `bias` one unit has a bias that is not finite, or is
+    finite and rounds to infinity in bf16: what the network makes of it (NaNs among it) is the same too."""
+    H, A, part = 128, 32, 64
+    rng = np.random.default_rng(80)
+    p0 = synth.init_params(D, H, A, 80, hidden2=H2)
+    o = D * H
+    if bias is not None:
+        p0[o + 5] = bias
+    W2, W3 = np.zeros((H, H2), np.float32), np.zeros((H2, A), np.float32)
+    W2[np.arange(H), np.arange(H)] = 1
+    W3[rng.permutation(H)[:A], np.arange(A)] = 1
+    p0[o + H:] = np.concatenate([W2.ravel(), np.zeros(H2), W3.ravel(), np.zeros(A)])
+    rows = synth.experiences(batch, D, A, 0.05, seed=80, state_dtype="bf16")
+    d = {k: torch.from_numpy(v.view(np.int16) if v.dtype == np.uint16 else v).cuda() for k, v in rows.items()}
+    q, kernels = [], []
+    for n in (batch, part):
+        ring = B.Replay(64, D, B.RP_BF16, seed=1)
+        tr = B.Trainer(ring, H, A, n, param_dtype=B.RP_BF16, opt=B.RP_SGD, lr=1e-3, appends_per_step=0, init_params=p0,
+                       hidden2=H2 if H2 != H else 0)
+        kernels.append(tr.kernels_per_step())
+        got = {"Q": np.empty((batch, A), np.float32), "Qn": np.empty((batch, A), np.float32)}
+        for lo in list(range(0, batch - n, n)) + [batch - n]:
+            tr.set_state(p0, None, None, 0, 0)
+            assert tr.step_batch(*(d[k][lo:lo + n].contiguous() for k in ("s", "s_next", "a", "r", "term"))) == 0
+            for k in got:
+                got[k][lo:lo + n] = tr.last()[k]
+        q.append(got)
+    assert kernels == [5, 8]
+    for k in ("Q", "Qn"):
+        assert np.array_equal(q[0][k], q[1][k], equal_nan=True), k
+        assert (bias == np.inf or bias == 3.4e38) != np.isfinite(q[0][k]).all(), k
+
+
 @pytest.mark.parametrize("dtype,H,H2,batch,n", [
     ("bf16", 8192, 64, 131_200, 100),    # H1, which the second layer reads, is 4.3 GB
     ("bf16", 64, 8192, 262_200, 100),    # so is dZ2, which the first layer's error is formed from
