@@ -1511,8 +1511,11 @@ __device__ __forceinline__ void dz1_block(const GradBackArgs& p, unsigned int bl
         const unsigned int t = wave & 3u, h = wave >> 2;
         for (unsigned int d0 = 0; d0 < p.Dp; d0 += 32u) {
 #pragma unroll
-            for (unsigned int u = 0; u < XN; ++u)
-                *reinterpret_cast<u32x4*>(smem + XT + (tid + u * S::kThreads) * 16u) = xv[u];
+            for (unsigned int u = 0; u < XN; ++u) {
+                // (zeros for rows beyond the batch: their dZ1 is zero, and a factor that is not finite would make that NaN)
+                const unsigned int e = tid + u * S::kThreads;
+                *reinterpret_cast<u32x4*>(smem + XT + e * 16u) = m0 + (e >> 2) < p.dz.M ? xv[u] : u32x4{0u, 0u, 0u, 0u};
+            }
             if (d0 + 32u < p.Dp) load_x(d0 + 32u);
             __syncthreads();
             f32x16 c, sum;

@@ -1246,6 +1246,30 @@ def test_mixed_precision_backward_in_two_launches(B, D, H, H2, A, batch, target_
         oracle.set_threads(1)
 
 
+@pytest.mark.parametrize("H,batch,kernels", [
+    (128, 1100, 5),      # tiles of 128 x 128, the batch ends inside one
+    (64, 8300, 5),       # of 256 x 128
+    (64, 70, 8),         # a launch for each layer
+])
+def test_infinite_state_in_the_last_row_of_the_batch(B, H, batch, kernels):
+    """The contraction over the batch goes in whole tiles of rows; what stands in for the rows beyond the batch
+    contributes nothing, whatever the last row holds.  All weights are positive here and the last experience's
+    state has an infinite entry d: its TD error is minus infinity, its Huber slope one and its dZ1 positive and
+    finite, so that row d of dW1 is infinite, not NaN, and the other rows and the bias are finite."""
+    D, A, d = 27, 6, 3
+    p0 = np.abs(synth.init_params(D, H, A, 81))
+    rows = synth.experiences(batch, D, A, 0.05, seed=81, state_dtype="bf16")
+    rows["s"][-1, d] = 0x7F80
+    dev = {k: torch.from_numpy(v.view(np.int16) if v.dtype == np.uint16 else v).cuda() for k, v in rows.items()}
+    ring = B.Replay(64, D, B.RP_BF16, seed=1)
+    tr = B.Trainer(ring, H, A, batch, param_dtype=B.RP_BF16, opt=B.RP_SGD, lr=1e-3, appends_per_step=0, init_params=p0)
+    assert tr.kernels_per_step() == kernels
+    assert tr.step_batch(*(dev[k] for k in ("s", "s_next", "a", "r", "term"))) == 0
+    dW1, db1 = tr.grads()[:D * H].reshape(D, H), tr.grads()[D * H:D * H + H]
+    assert np.isposinf(dW1[d]).all()
+    assert np.isfinite(np.delete(dW1, d, axis=0)).all() and np.isfinite(db1).all()
+
+
 @pytest.mark.parametrize("bias", [None, np.inf, 3.4e38, -np.inf])
 @pytest.mark.parametrize("D,H2,batch", [
     (27, 128, 640),       # tiles of 128 x 128
