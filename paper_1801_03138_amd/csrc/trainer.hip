@@ -344,7 +344,7 @@ bool ws_layout(const train_config* c, WsLayout* L) {
     L->dQ3 = take(mixed ? B * 3 * L->Ap * 2 : 0);
     // K-split partial products of the gradients
     WidePlan& plan = L->plan;
-    plan = mixed ? wide_plan((unsigned int)B, (unsigned int)H, (unsigned int)G, L->Dp) : WidePlan{};
+    plan = mixed ? wide_plan((unsigned int)B, (unsigned int)H, (unsigned int)G, L->Dp, L->Ap) : WidePlan{};
     L->part3 = take(mixed ? plan.splits3 * (G + 1) * L->Ap * 4 : 0);
     L->part1 = take(mixed ? plan.splits1 * H * Dx * 4 : 0);
     L->part2 = take(mixed ? plan.splits2 * (H + 1) * G * 4 : 0);

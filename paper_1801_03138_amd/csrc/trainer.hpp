@@ -307,7 +307,7 @@ hipError_t enqueue_mid_step(trainer* t, hipStream_t st, unsigned int* count);
 unsigned int mid_step_kernels(const trainer* t);   // launches per step, the append + gather kernel included
 // Mixed-precision step on MFMA (bf16 replay states and matrix operands).
 bool wide_step_supported(const train_config& cfg, const replay* rp_);
-WidePlan wide_plan(unsigned int B, unsigned int H, unsigned int G, unsigned int Dp);
+WidePlan wide_plan(unsigned int B, unsigned int H, unsigned int G, unsigned int Dp, unsigned int Ap);
 hipError_t wide_configure();                                    // once, at creation
 // bf16 operand copies from padded fp32 parameters (host): of the trained network, or of the target
 hipError_t wide_set_weights(trainer* t, const float* padded, bool target);

@@ -1945,8 +1945,8 @@ hipError_t configure_grad_back() {
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::kLds);
 }
 
-// How the backward half of a step is launched.
-WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G, unsigned int Dp) {
+// How a step is launched.
+WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G, unsigned int Dp, unsigned int Ap) {
     WidePlan p;
     const unsigned int Bp = (B + 127u) / 128u * 128u;
     // The large form wherever the first layer's error has many tiles, and on large batches: us per step in the small form,
@@ -1965,35 +1965,46 @@ WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G, unsigned int D
         return p;
     }
     // The first two layers in one launch (up to 64 states; beyond, the first layer repeated in every tile is too much),
-    // in tiles of 128 x 256 or 128 x 128: those that take less time in rounds of workgroups, 0.75 and 0.4 us a slice.
+    // in tiles of 128 x 256 or 128 x 128: those that take less time in rounds of workgroups, 0.75 and 0.5 us a slice.
+    // Over 370 shapes (64 to 2048 units, batches of 450 to 8192) the choice was nowhere more than 0.3 % of the step behind
+    // the other; with 0.4 us for the narrow ones up to 9.2 %.
     if (Dp <= 64u && H <= kFwMaxH) {
         const unsigned int rows = (2u * B + 127u) / 128u;
-        const double large = (rows * ((G + 255u) / 256u) + 255u) / 256u * 0.75, small = (rows * ((G + 127u) / 128u) + 255u) / 256u * 0.4;
+        const double large = (rows * ((G + 255u) / 256u) + 255u) / 256u * 0.75, small = (rows * ((G + 127u) / 128u) + 255u) / 256u * 0.5;
         p.fw_cols = large <= small ? 256u : 128u;
     }
-    // The tiles' height and the splits of dW2's contraction: those whose launch ends first.  A compute unit holds one
-    // workgroup; one takes about 5 us (dZ1's, with the first layer's gradient) or 3 us and, per slice of 64 of its
-    // contraction, 0.75 us in 256 x 128 tiles and 0.4 us in 128 x 128; a split's partials are written and read at 4.5 TB/s.
-    // us per step in large, small tiles (27 inputs, 30 actions): 1024-1024 at batch 4096 83.7, 123.4, 3000 77.5, 91.4,
-    // 2048 71.7, 63.2; 768-768 at 3000 63.9, 67.1; 512-512 at 4096 60.7, 52.0; 192-1024 at 3000 79.0, 73.0.
+    // The tiles' height and the splits of dW2's contraction: those whose launch ends first.  Workgroups are dealt to the
+    // XCDs in turn, 32 compute units each, and a compute unit holds one: the first XCD's share is followed.  A workgroup of
+    // dZ1's or dW2's takes so many us and so many more per slice of 64 of its contraction, one of dZ1's also for every 32
+    // states beyond the first, one of dW3's per chunk; a split's partials are written and read at 9 TB/s (a launch apart:
+    // in part from the caches).  The figures are those that tell the measured steps in all tiles and splits of 620 shapes
+    // apart best (64 to 2048 units, batches of 450 to 8192, 27 to 96 states): the choice is 0.13 % behind the fastest on
+    // average, 6 % at worst and more than 3 % in 4.  us per step, the best in tiles of 256 x 128, of 128 x 128 (27 states, 30
+    // actions): 1024-1024 at batch 3000 69.3, 74.3; 896-896 at 2700 62.9, 66.1, at 2304 58.6, 55.5; 512-512 at 8192 62.2, 72.0.
+    struct Cost { double dz, dz_slice, dz_states, dw, dw_slice; };
+    static const Cost kCost[2] = {{9.5, 0.24, 1.2, 3.6, 0.65}, {11.5, 0.49, 1.3, 2.3, 0.91}};
+    const unsigned int chunks = (B + kW3Rows - 1u) / kW3Rows;
+    p.splits3 = std::min(chunks, kW3MaxSplits);
+    const unsigned int n_w3 = p.splits3 * ((G + 127u) / 128u) * (Ap / 32u);
+    const double t_w3 = 3.8 * ((chunks + p.splits3 - 1u) / p.splits3);
     double best = 0.;
     for (int large = 0; large < 2; ++large) {
+        const Cost& c = kCost[large];
         const unsigned int bm = large ? 256u : 128u;
-        const double slice = large ? 0.75 : 0.4;
         auto tiles = [bm](unsigned int m, unsigned int n) { return ((m + bm - 1u) / bm) * ((n + 127u) / 128u); };
         const unsigned int rows = std::min((B + bm - 1u) / bm, kGbMaxSplits), rounds = ((B + bm - 1u) / bm + rows - 1u) / rows;
         for (unsigned int s = 1; s <= 16u && (s == 1 || B / s >= 256u); s *= 2u) {
             const unsigned int k = ((B + s - 1u) / s + 63u) / 64u * 64u, splits = (B + k - 1u) / k;
-            const double t_dz = rounds * (5. + G / 64u * slice), t_dw = 3. + k / 64u * slice;
-            double free_at[256] = {}, end = 0.;              // (a heap, the earliest at the front)
-            const unsigned int n_dz = rows * ((H + 127u) / 128u), n = n_dz + tiles(H, G) * splits;
-            for (unsigned int i = 0; i < n; ++i) {
-                std::pop_heap(free_at, free_at + 256, std::greater<double>());
-                free_at[255] += i < n_dz ? t_dz : t_dw;
-                end = std::max(end, free_at[255]);
-                std::push_heap(free_at, free_at + 256, std::greater<double>());
+            const double t_dz = rounds * (c.dz + G / 64u * c.dz_slice + (Dp / 32u - 1u) * c.dz_states), t_dw = c.dw + k / 64u * c.dw_slice;
+            double free_at[32] = {}, end = 0.;               // (a heap, the earliest at the front)
+            const unsigned int n_dz = (rows * ((H + 127u) / 128u) + 7u) / 8u, n_dw = (tiles(H, G) * splits + 7u) / 8u;
+            for (unsigned int i = 0; i < n_dz + n_dw + (n_w3 + 7u) / 8u; ++i) {
+                std::pop_heap(free_at, free_at + 32, std::greater<double>());
+                free_at[31] += i < n_dz ? t_dz : i < n_dz + n_dw ? t_dw : t_w3;
+                end = std::max(end, free_at[31]);
+                std::push_heap(free_at, free_at + 32, std::greater<double>());
             }
-            end += 8e-6 * splits * H * G / 4.5;
+            end += 0.9e-6 * splits * H * G;
             if (best != 0. && end >= best) continue;
             best = end;
             p.large = large != 0;
@@ -2003,7 +2014,6 @@ WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G, unsigned int D
     }
     const unsigned int bm = p.large ? 256u : 128u;
     p.splits1 = std::min((B + bm - 1u) / bm, kGbMaxSplits);
-    p.splits3 = std::min((B + kW3Rows - 1u) / kW3Rows, kW3MaxSplits);
     p.splits_b2 = std::min((B + kHeadRows - 1u) / kHeadRows, kHeadMaxGroups);
     return p;
 }
@@ -2018,7 +2028,9 @@ bf16_bits host_bf16(float f) {
 
 }  // namespace
 
-WidePlan wide_plan(unsigned int B, unsigned int H, unsigned int G, unsigned int Dp) { return plan_for(B, H, G, Dp); }
+WidePlan wide_plan(unsigned int B, unsigned int H, unsigned int G, unsigned int Dp, unsigned int Ap) {
+    return plan_for(B, H, G, Dp, Ap);
+}
 
 // Two hidden layers of one width, or of two.  This step is the faster one at every size measured (27
 // inputs, 30 actions, one new experience a step, us per step layer by layer -> this: 64-256 at batch 8
