@@ -114,6 +114,25 @@ __device__ __forceinline__ unsigned int relu_mask(unsigned int v, unsigned int k
     return (lo_on ? v & 0xFFFFu : 0u) | (hi_on ? v & 0xFFFF0000u : 0u);
 }
 
+// out[m][n] = bf16(acc) where mask[m][n] > 0, else 0  (the ReLU derivative; both [M x ld])
+struct EpiMask {
+    const bf16_bits* mask;
+    bf16_bits* out;
+    unsigned int ld;
+    unsigned int M, N;
+    __device__ __forceinline__ float pre(unsigned int, unsigned int, float x) const { return x; }
+    // eight consecutive columns n..n+7 of row m (N is a multiple of 8)
+    __device__ __forceinline__ void store(unsigned int m, unsigned int n, const u32x4& v) const {
+        if (m >= M || n >= N) return;
+        const size_t at = (size_t)m * ld + n;
+        const u32x4 k = *reinterpret_cast<const u32x4*>(mask + at);
+        u32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = relu_mask(v[e], k[e]);
+        *reinterpret_cast<u32x4*>(out + at) = o;
+    }
+};
+
 // Partial gradients of one K split, added up by the optimizer kernel.  M: rows of the weight
 // matrix (of its transpose in EpiFirst); sums() gets the 32 column (row) sums of an error tile.
 // part[split][m][n] = acc, row M the bias
@@ -1949,19 +1968,27 @@ hipError_t configure_grad_back() {
 WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G, unsigned int Dp, unsigned int Ap) {
     WidePlan p;
     const unsigned int Bp = (B + 127u) / 128u * 128u;
-    // The large form wherever the first layer's error has many tiles, and on large batches: us per step in the small form,
-    // the large one (27 inputs, 30 actions): 64-64 at batch 4000 34.5, 27.3, 1000 26.1, 24.1; 256-256 at 600 30.7, 27.8;
-    // 128-1024 at 4096, head and target network, 61.4, 51.2, 1536 45.1, 41.4; 96-320-320-10 at 800 38.3, 38.6.  The line
-    // for wide second layers: 128-1024 at 1024 with target network 43.1, 44.2 (a long contraction in few tiles; 39 since the
-    // small form's products took tiles of 16 rows).  Below some 576 either may be the faster: 256-256 at 500 29.2, 27.2,
-    // 64-512-512-64 39.4, 41.0, 1024-1024 at 64 43.2, 45.3.
-    p.merged = !few_tiles(B, H) || B >= 1536u || (B >= 576u && G <= 512u);
+    // The large form wherever the first layer's error has many tiles, and on large batches (below some 576 either may be
+    // the faster, 1024-1024 at batch 64 37.7 us per step in the small form, 49.9 in the large one; before wide second layers
+    // as well, 128-1024 at 512 35.0, 36.0, at 1280 42.6, 40.0), unless it is behind by this estimate of how much longer (us)
+    // its step takes: it walks the states (grad_back_kernel) and the actions (head_kernel) 32 at a time within a workgroup,
+    // where the small form has tiles for them; that form's dW2 walks its share of the batch in fewer workgroups, and it
+    // takes H1 and dZ1 through memory.  Fitted to 3,900 shapes measured in both (64 to 2048 units, 27 to 1024 states, 30 to
+    // 1024 actions, batches of 64 to 8192): the form taken is 0.5 % behind the other on average (3.9 % without the
+    // estimate); of the shapes that go to the large form 25 were slower than a step in eight launches whose products had
+    // fewer tricks (579 without), by 9 % at most.  us per step, small form, large one (30 actions and 27 states if not given):
+    // 256-256 at batch 1024 31.3, 28.7; with 256 states 38.7, 47.3; 1024 states 59.0, 107; 128 actions 33.3, 34.5; 1024
+    // actions 66.5, 91.2; 1024-1024 at 4096 86.5, 76.0; 1024 states 163, 187; 256 actions 132, 120; 1024 actions 284, 288.
+    const unsigned int splits2 = square_splits_for(Bp, H, G);
+    const double behind = 0.8 + 0.7 * (Dp / 32u - 1u) + 1.2e-3 * G * (Ap / 32u - 1u) - 3.2e-3 * Bp / splits2 -
+                          (few_tiles(2u * B, G) ? 0. : 1.) - 1.8e-9 * std::min(B, 4096u) * H * G;
+    p.merged = (!few_tiles(B, H) || B >= 1536u || (B >= 576u && G <= 512u)) && behind < 0.;
     p.large = false;
     p.k2 = Bp;
     p.fw_cols = 0;
     if (!p.merged) {
         p.splits3 = p.splits1 = batch_splits(Bp);
-        p.splits2 = p.splits_b2 = square_splits_for(Bp, H, G);
+        p.splits2 = p.splits_b2 = splits2;
         return p;
     }
     // The first two layers in one launch (up to 64 states; beyond, the first layer repeated in every tile is too much),
@@ -2046,6 +2073,7 @@ bool wide_step_supported(const train_config& cfg, const replay* rp_) {
 hipError_t wide_configure() {
     hipError_t ec = configure_gemm<128, 128, 32, 2, 2, EpiForward>();
     if (ec == hipSuccess) ec = configure_gemm<128, 128, 64, 2, 2, EpiForward>();
+    if (ec == hipSuccess) ec = configure_gemm<128, 64, 64, 2, 2, EpiMask>();
     if (ec == hipSuccess) ec = configure_grad_products<true>();
     if (ec == hipSuccess) ec = configure_grad_products<false>();
     if (ec == hipSuccess) ec = configure_forward<FwLarge>();
@@ -2253,8 +2281,12 @@ hipError_t enqueue_wide_step(trainer* t, hipStream_t st, unsigned int* count, bo
             ++n;
         }
         // dZ1 = (dZ2 W2^T) masked by the first ReLU; uses W2 before its update
-        const SkinnyArgs za{dZ2, G, w.W2, G, B, H, G, w.W2, ~0u};
-        e = launch_skinny(st, za, SkinnyMask{H1, dZ1, H});
+        if (few_tiles(B, H)) {
+            const SkinnyArgs za{dZ2, G, w.W2, G, B, H, G, w.W2, ~0u};
+            e = launch_skinny(st, za, SkinnyMask{H1, dZ1, H});
+        } else {
+            e = launch_gemm<128, 64, 64, 2, 2>(st, dZ2, G, w.W2, G, B, H, G, EpiMask{H1, dZ1, H, B, H});
+        }
         if (e != hipSuccess) return e;
         ++n;
         // the three weight-gradient products, K-split partials each, in one launch:

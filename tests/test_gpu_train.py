@@ -1246,6 +1246,30 @@ def test_mixed_precision_backward_in_two_launches(B, D, H, H2, A, batch, target_
         oracle.set_threads(1)
 
 
+@pytest.mark.parametrize("D,H,H2,A,batch,target_sync,dueling,kernels", [
+    (27, 512, 0, 30, 1100, 3, False, 6),      # the large form, in two blocks of rows
+    (27, 512, 0, 256, 1100, 3, False, 11),    # ... eight blocks of actions: the small one, the first layer's error tiled
+    (256, 512, 0, 30, 1100, 0, True, 9),      # ... eight blocks of states
+    (96, 512, 0, 64, 1100, 0, False, 6),      # some of either: the large one, the first layer in a launch of its own
+    (200, 64, 128, 100, 1540, 0, False, 8),   # a large batch, few tiles
+    (300, 64, 0, 130, 8300, 0, False, 6),     # many more slices of batch than of states and actions
+])
+def test_mixed_precision_steps_with_many_states_or_actions(B, D, H, H2, A, batch, target_sync, dueling, kernels):
+    """Both sides of the rule that takes networks with many states or actions from the large steps' launches, which
+    walk them 32 at a time, to those of small steps; tolerances of the other mixed-precision cases."""
+    oracle.set_threads(16)
+    try:
+        rows = synth.experiences(batch + 40, D, A, 0.05, seed=82, state_dtype="bf16")
+        pr = Pair(B, capacity=batch + 30, D=D, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=5, dtype="bf16",
+                  appends=1, target_sync=target_sync, dueling=dueling, lr=1e-3)
+        assert pr.trainer.kernels_per_step() == kernels
+        pr.append_only(synth.take(rows, 0, batch + 30))
+        for k in range(batch + 30, batch + 34):
+            assert pr.step(synth.take(rows, k, k + 1), compare=True) == 0
+    finally:
+        oracle.set_threads(1)
+
+
 @pytest.mark.parametrize("H,batch,kernels", [
     (128, 1100, 5),      # tiles of 128 x 128, the batch ends inside one
     (64, 8300, 5),       # of 256 x 128
@@ -1273,7 +1297,7 @@ def test_infinite_state_in_the_last_row_of_the_batch(B, H, batch, kernels):
 @pytest.mark.parametrize("bias", [None, np.inf, 3.4e38, -np.inf])
 @pytest.mark.parametrize("D,H2,batch", [
     (27, 128, 640),       # tiles of 128 x 128
-    (64, 128, 577),       # ... two blocks of states, a batch that ends inside a tile
+    (64, 128, 1100),      # ... two blocks of states, a batch that ends inside a tile
     (27, 2048, 1600),     # tiles of 128 x 256
 ])
 def test_first_layer_of_large_steps_is_that_of_small_ones(B, D, H2, batch, bias):
