@@ -1972,16 +1972,21 @@ WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G, unsigned int D
     // the faster, 1024-1024 at batch 64 37.7 us per step in the small form, 49.9 in the large one; before wide second layers
     // as well, 128-1024 at 512 35.0, 36.0, at 1280 42.6, 40.0), unless it is behind by this estimate of how much longer (us)
     // its step takes: it walks the states (grad_back_kernel) and the actions (head_kernel) 32 at a time within a workgroup,
-    // where the small form has tiles for them; that form's dW2 walks its share of the batch in fewer workgroups, and it
-    // takes H1 and dZ1 through memory.  Fitted to 3,900 shapes measured in both (64 to 2048 units, 27 to 1024 states, 30 to
-    // 1024 actions, batches of 64 to 8192): the form taken is 0.5 % behind the other on average (3.9 % without the
-    // estimate); of the shapes that go to the large form 25 were slower than a step in eight launches whose products had
-    // fewer tricks (579 without), by 9 % at most.  us per step, small form, large one (30 actions and 27 states if not given):
-    // 256-256 at batch 1024 31.3, 28.7; with 256 states 38.7, 47.3; 1024 states 59.0, 107; 128 actions 33.3, 34.5; 1024
-    // actions 66.5, 91.2; 1024-1024 at 4096 86.5, 76.0; 1024 states 163, 187; 256 actions 132, 120; 1024 actions 284, 288.
+    // where the small form has tiles for them, and the first layer (forward_kernel) in few workgroups where the second has
+    // few tiles; the small form's dW2 walks longer shares of the batch, and it takes H1 and dZ1 through memory.  Fitted to
+    // 4,900 shapes measured in both (64 to 2048 units, 4 to 1024 states, 2 to 1024 actions, batches of 64 to 8192): the form
+    // taken is 0.6 % behind the other on average (3.3 % without the estimate).  Of 3,858 shapes 46 are slower than the step
+    // was before it had a large form, by 13 % at most (without the estimate 713, the worst twice as long), and none with up
+    // to 96 states, 65 actions, 1024 units and batch 4096; of 1,400 drawn there none.  us per step, small form, large one (30
+    // actions and 27 states if not given): 256-256 at batch 1024 31.3, 28.7; with 256 states 38.7, 47.3; 1024 states 59.0, 107;
+    // 128 actions 33.3, 34.5; 1024 actions 66.5, 91.2; 1024-1024 at 4096 86.5, 76.0; 1024 states 163, 187; 256 actions 132,
+    // 120; 1024 actions 284, 288; 1024-128 at 640, 64 states and actions 39.6, 44.8.
     const unsigned int splits2 = square_splits_for(Bp, H, G);
-    const double behind = 0.8 + 0.7 * (Dp / 32u - 1u) + 1.2e-3 * G * (Ap / 32u - 1u) - 3.2e-3 * Bp / splits2 -
-                          (few_tiles(2u * B, G) ? 0. : 1.) - 1.8e-9 * std::min(B, 4096u) * H * G;
+    const bool fused = Dp <= 64u && H <= kFwMaxH;             // the first two layers in one launch
+    const double states = Dp / 32u - 1u, actions = Ap / 32u - 1u, n = std::min(B, 4096u);
+    const double behind = -0.81 + 0.53 * states + (0.17 + (1.27e-3 - 0.42e-6 * n) * G) * actions - 1.92e-3 * Bp / splits2 -
+                          1.5e-9 * n * H * G +
+                          (few_tiles(2u * B, G) ? 0.4 + (fused ? (0.58e-3 + 0.45e-3 * states) * H : 0.) : 0.);
     p.merged = (!few_tiles(B, H) || B >= 1536u || (B >= 576u && G <= 512u)) && behind < 0.;
     p.large = false;
     p.k2 = Bp;
@@ -1995,7 +2000,7 @@ WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G, unsigned int D
     // in tiles of 128 x 256 or 128 x 128: those that take less time in rounds of workgroups, 0.75 and 0.5 us a slice.
     // Over 370 shapes (64 to 2048 units, batches of 450 to 8192) the choice was nowhere more than 0.3 % of the step behind
     // the other; with 0.4 us for the narrow ones up to 9.2 %.
-    if (Dp <= 64u && H <= kFwMaxH) {
+    if (fused) {
         const unsigned int rows = (2u * B + 127u) / 128u;
         const double large = (rows * ((G + 255u) / 256u) + 255u) / 256u * 0.75, small = (rows * ((G + 127u) / 128u) + 255u) / 256u * 0.5;
         p.fw_cols = large <= small ? 256u : 128u;
@@ -2003,17 +2008,17 @@ WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G, unsigned int D
     // The tiles' height and the splits of dW2's contraction: those whose launch ends first.  Workgroups are dealt to the
     // XCDs in turn, 32 compute units each, and a compute unit holds one: the first XCD's share is followed.  A workgroup of
     // dZ1's or dW2's takes so many us and so many more per slice of 64 of its contraction, one of dZ1's also for every 32
-    // states beyond the first, one of dW3's per chunk; a split's partials are written and read at 9 TB/s (a launch apart:
+    // states beyond the first, one of dW3's per chunk; a split's partials are written and read at 10 TB/s (a launch apart:
     // in part from the caches).  The figures are those that tell the measured steps in all tiles and splits of 620 shapes
-    // apart best (64 to 2048 units, batches of 450 to 8192, 27 to 96 states): the choice is 0.13 % behind the fastest on
-    // average, 6 % at worst and more than 3 % in 4.  us per step, the best in tiles of 256 x 128, of 128 x 128 (27 states, 30
+    // apart best (64 to 2048 units, batches of 450 to 8192, 27 to 96 states): the choice is 0.15 % behind the fastest on
+    // average, 4 % at worst and more than 3 % in 6.  us per step, the best in tiles of 256 x 128, of 128 x 128 (27 states, 30
     // actions): 1024-1024 at batch 3000 69.3, 74.3; 896-896 at 2700 62.9, 66.1, at 2304 58.6, 55.5; 512-512 at 8192 62.2, 72.0.
     struct Cost { double dz, dz_slice, dz_states, dw, dw_slice; };
-    static const Cost kCost[2] = {{9.5, 0.24, 1.2, 3.6, 0.65}, {11.5, 0.49, 1.3, 2.3, 0.91}};
+    static const Cost kCost[2] = {{7.1, 0.32, 1.3, 2., 0.65}, {10.1, 0.49, 1.3, 1., 0.9}};
     const unsigned int chunks = (B + kW3Rows - 1u) / kW3Rows;
     p.splits3 = std::min(chunks, kW3MaxSplits);
     const unsigned int n_w3 = p.splits3 * ((G + 127u) / 128u) * (Ap / 32u);
-    const double t_w3 = 3.8 * ((chunks + p.splits3 - 1u) / p.splits3);
+    const double t_w3 = 3.9 * ((chunks + p.splits3 - 1u) / p.splits3);
     double best = 0.;
     for (int large = 0; large < 2; ++large) {
         const Cost& c = kCost[large];
@@ -2031,7 +2036,7 @@ WidePlan plan_for(unsigned int B, unsigned int H, unsigned int G, unsigned int D
                 end = std::max(end, free_at[31]);
                 std::push_heap(free_at, free_at + 32, std::greater<double>());
             }
-            end += 0.9e-6 * splits * H * G;
+            end += 0.8e-6 * splits * H * G;
             if (best != 0. && end >= best) continue;
             best = end;
             p.large = large != 0;

@@ -1297,7 +1297,7 @@ def test_infinite_state_in_the_last_row_of_the_batch(B, H, batch, kernels):
 @pytest.mark.parametrize("bias", [None, np.inf, 3.4e38, -np.inf])
 @pytest.mark.parametrize("D,H2,batch", [
     (27, 128, 640),       # tiles of 128 x 128
-    (64, 128, 1100),      # ... two blocks of states, a batch that ends inside a tile
+    (64, 128, 577),       # ... two blocks of states, a batch that ends inside a tile
     (27, 2048, 1600),     # tiles of 128 x 256
 ])
 def test_first_layer_of_large_steps_is_that_of_small_ones(B, D, H2, batch, bias):
