@@ -412,13 +412,12 @@ __device__ __forceinline__ void gemm_nt_block(const GemmArgs& p, const Epi& epi,
 // A workgroup is eight wavefronts, two groups of four: both groups cover the whole tile, each for half
 // of a slice's steps, and add their accumulators through LDS at the end.  The square layer's tiles
 // have a compute unit to themselves, and with one wavefront per SIMD the transposing reads (twice
-// the instructions of the 16-byte ones), the MFMAs and the requests hardly overlapped: 23.9 us per
-// launch at batch 4096 and 1024 units (which take grad_back_kernel now) with one group, 21.8 with two.  Deeper pipelines (four slices of
-// 64 or 32 rows: 23.8, 24.4) and two workgroups per compute unit (128 registers, spills: 23.2) were slower.
+// the instructions of the 16-byte ones), the MFMAs and the requests hardly overlap.  (These choices were
+// measured at batch 4096 and 1024 units, which take grad_back_kernel now: 23.9 us per launch with one group, 21.8 with
+// two; deeper pipelines, four slices of 64 or 32 rows, 23.8, 24.4; two workgroups per compute unit 23.2.)
 //
-// Transposed copies of H1, H2 and both errors (24 MB written and 16 MB read a step by the kernel
-// before) with a row of ones for the biases (one more tile row of 128) made this launch 18.9 us but
-// the kernel before 12.8 us, now 6.4: 97.7 -> 92.9 us per step; at batch 512, 512 units 49.1 -> 45.1.
+// Transposed copies of H1, H2 and both errors, with a row of ones for the biases, cost the launches that would
+// write them more than they save here: batch 512, 512 units 49.1 us per step, 45.1 without.
 //
 // The bias gradients are sums over one operand's columns: the workgroups of the first tile row
 // (SUM_ROWS: of the first tile column) multiply the fragments of B (of A) that they hold anyway
@@ -689,8 +688,8 @@ __global__ __launch_bounds__(kTnThreads) void grad_products_kernel(GemmArgs p2, 
     }
 }
 
-// The dynamic LDS size of each kernel (up to 80 KB, the gradients' launch) is announced per kernel before the first
-// launch (done at trainer creation, outside any stream capture).
+// The dynamic LDS size of each kernel is announced per kernel before the first launch (at trainer creation, outside any
+// stream capture): up to 80 KB here (the gradients' launch), 144 KB in grad_back_kernel, 160 KB in forward_kernel.
 template <int BM, int BN, int BK, int WGM, int WGN, class Epi, int NSTAGE = 2>
 hipError_t configure_gemm() {
     auto kernel = gemm_nt_kernel<BM, BN, BK, WGM, WGN, NSTAGE, Epi>;
@@ -898,7 +897,7 @@ hipError_t launch_skinny(hipStream_t st, const SkinnyArgs& a, const Epi& epi) {
 // bits.  With the bias as a step of the product, in three bf16 parts, the step was no faster (1024-1024 at batch 4096 76.9
 // us, 76.3 like this), an infinite bias became NaN and so zero, and the gradients were twice as far from those worked out
 // in 64 bits with the same bf16 roundings (dW1 there 5.6e-4, like this 2.9e-4).
-// The workgroups of a row of tiles repeat the first layer (an eighth of the second's MFMAs at 256 units and 32 states);
+// The workgroups of a row of tiles repeat the first layer (an eighth of the second's MFMAs in tiles 256 wide, 32 states);
 // as a launch of its own it was bound by its start and by writing and reading H1 (17 MB each way at batch 4096 and
 // 1024 units).  6.8 + 20.8 us -> 27.0 there, but us per step 81.4 -> 79.6 (the S' half of H1 never goes to memory); at
 // batch 1024 54.5 -> 52.7, 512-512 at 1100 40.8 -> 37.7, 192-192 at 4096 35.7 -> 33.5, 768-768 at 3000 unchanged.
@@ -926,6 +925,7 @@ constexpr size_t forward_lds() {
     return std::max<size_t>(S::NS * (S::BN * 128u + ND * 4096u) + 2u * S::BM * 128u + kFwMaxH * 4u,
                             std::max<size_t>(S::KG == 2 ? S::BM * S::BN * 4u : 0u, S::BM * (S::BN * 2u + 16u)));
 }
+static_assert(forward_lds<FwLarge, 2>() <= 160u * 1024u, "a compute unit's LDS: nothing left with 64 states");
 
 // The slices of H1.  W1T's come with W2T's requests, one ahead, and the bias before them (their first from memory; a load in
 // the loop would make the compiler wait for the requests in flight).
@@ -1921,12 +1921,12 @@ unsigned int square_splits_for(unsigned int Bp, unsigned int H, unsigned int G) 
 }
 
 // A product with M x N outputs that has few tiles of 128 x 64: those leave most of the chip idle, each
-// a serial chain over the whole contraction, and the product in tiles of 32 columns, K split over eight
-// wavefronts, is the faster one although it fetches its operands more often.  us per step, tiled
-// -> this, in tiles of 32 rows (27 inputs, 30 actions), for the first layer's error: 8 tiles (batch 512, 128-1024) 48.2 ->
-// 41.7, 64 tiles (batch 512, 1024-1024) 61.3 -> 59.2, 128 tiles (batch 1024) 68.1 -> 73.3; for the second
-// layer: 64 tiles (batch 256, 1024-1024) 54.8 -> 51.3, 16 (batch 40, 1024-1024) 51.7 -> 44.9, K = 64
-// (batch 100, 64-64) 27.1 -> 25.9, 128 tiles (batch 512, 1024-1024) 59.4 -> 63.1.
+// a serial chain over the whole contraction, and the product in tiles of 16 or 32 rows x 32 columns, K split over eight
+// wavefronts, is the faster one although it fetches its operands more often.  us per step in the small form, tiled -> this
+// (27 inputs, 30 actions), for the first layer's error: 8 tiles (batch 512, 128-1024) 42.4 -> 34.9, 64 (batch 512, 1024-1024)
+// 56.5 -> 53.9, 80 (batch 640) 56.2 -> 57.2, 128 (batch 1024) 62.8 -> 67.1; for the second layer, tiled in 128 x 128: 16
+// (batch 64, 1024-1024) 46.1 -> 37.8, 64 (batch 256) 50.7 -> 46.4, 128 (batch 512) 53.9 -> 56.3; K = 64 (batch 100, 64-64) 25.1
+// -> 23.4.  Of 130 shapes none of either product is more than 2 % faster on the other side of the line.
 bool few_tiles(unsigned int M, unsigned int N) { return (size_t)((M + 127u) / 128u) * ((N + 63u) / 64u) <= 64u; }
 
 // H2 = relu(H1 W2 + b2) for `rows` rows; with hi, rows from m_split on take those weights and biases.
