@@ -1119,14 +1119,16 @@ def test_two_hidden_widths_mixed_precision_on_mfma(B, D, H, H2, A, batch, target
         assert pr.step(synth.take(rows, k, k + 3), compare=(k % 2 == 0) or k >= batch + 140) == 0
 
 
-def test_output_gradient_keeps_fp32_in_mixed_precision(B):
+@pytest.mark.parametrize("H,H2,batch,kernels", [(64, 128, 64, 8), (128, 512, 1024, 5)])
+def test_output_gradient_keeps_fp32_in_mixed_precision(B, H, H2, batch, kernels):
     """The output layer's gradient in mixed precision contracts bf16 activations with dL/dQ in fp32: three
     bf16 parts that add up to it exactly.  Weights and states are small whole numbers here, so that the
-    activations are exact in bf16, and every experience of the batch has an action of its own, so
-    that an entry of dW3 (and of db3) is one product: the sum of three exact ones, two roundings at
-    most.  Two parts, without the last one, miss that bound by far in either array."""
-    D, H, H2, A = 27, 64, 128, 64
-    batch, rng = A, np.random.default_rng(73)
+    activations are exact in bf16, and as many experiences as there are actions have one of their own each
+    (the others have TD errors and activations of zero), so that an entry of dW3 (and of db3) is one
+    product: the sum of three exact ones, two roundings at most.  Two parts, without the last one, miss
+    that bound by far in either array."""
+    D, A = 27, 64
+    rng = np.random.default_rng(73)
     W1 = rng.integers(-1, 2, (D, H)).astype(np.float32)
     W2 = np.zeros((H, H2), np.float32)
     for k in range(H2):
@@ -1138,20 +1140,28 @@ def test_output_gradient_keeps_fp32_in_mixed_precision(B):
     h2 = np.maximum(h1 @ W2, 0).astype(np.float64)
     assert h1.max() <= 256 and h2.max() <= 256          # whole numbers that bf16 holds
     rows = synth.experiences(batch, D, A, 0.05, seed=73, state_dtype="bf16")
-    rows["s"], rows["a"] = synth.f32_to_bf16_bits(s), rng.permutation(A).astype(np.int32)
+    rows["s"], rows["a"] = synth.f32_to_bf16_bits(s), rng.permutation(batch).astype(np.int32) % A
+    own = np.sort(rng.choice(batch, A, replace=False))  # (spread over the batch: its chunks, halves and lanes)
+    if batch > A:
+        own[-1] = batch - 1
+        rows["a"][own] = rng.permutation(A)
+        rest = np.setdiff1d(np.arange(batch), own)
+        rows["s"][rest], rows["r"][rest], rows["term"][rest], h2[rest] = 0, 0, 1, 0
     ring = B.Replay(64, D, B.RP_BF16, seed=5)
     tr = B.Trainer(ring, H, A, batch, param_dtype=B.RP_BF16, loss=B.RP_MSE, opt=B.RP_SGD, appends_per_step=0, lr=1e-3,
                    init_params=p0, hidden2=H2)
     d = {k: torch.from_numpy(v.view(np.int16) if v.dtype == np.uint16 else v).cuda() for k, v in rows.items()}
+    assert tr.kernels_per_step() == kernels
     assert tr.step_batch(d["s"], d["s_next"], d["a"], d["r"], d["term"]) == 0
     g = -tr.last()["delta"] / np.float32(batch)         # dL/dQ(s_i, a_i); the batch is a power of two: exact
+    assert (np.delete(g, own) == 0).all() and (g[own] != 0).all()
     hi = synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(g))
     two_parts = hi + synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(g - hi))
 
     def gradients(x):
         dW3, db3 = np.zeros((H2, A)), np.zeros(A)
-        dW3[:, rows["a"]] = h2.T * x.astype(np.float64)
-        db3[rows["a"]] = x
+        dW3[:, rows["a"][own]] = h2[own].T * x[own].astype(np.float64)
+        db3[rows["a"][own]] = x[own]
         return dW3.ravel(), db3
 
     got = tr.grads()[-(H2 * A + A):]
@@ -1168,7 +1178,9 @@ def test_output_gradient_keeps_fp32_in_mixed_precision(B):
     (33, 64, 128, 32, 129),       # states beyond one tile; a row beyond the padding of 128
     (27, 128, 192, 30, 257),
     (64, 320, 320, 64, 191),      # widths that end inside a tile of 128
-    (27, 128, 128, 30, 1000),     # several splits, the last one ends inside a slice
+    (27, 128, 128, 30, 1000),     # (in the large steps' launches) several chunks, the last one ragged
+    (27, 128, 1024, 30, 1000),    # several splits, the last one ends inside a slice
+    (33, 128, 768, 30, 1100),     # ... two blocks of states
 ])
 def test_mixed_precision_gradients_over_ragged_batches(B, D, H, H2, A, batch):
     """The weight gradients contract over the batch in slices of 64 rows of the batch-major activations
@@ -1176,12 +1188,13 @@ def test_mixed_precision_gradients_over_ragged_batches(B, D, H, H2, A, batch):
     rows = synth.experiences(batch + 60, D, A, 0.05, seed=74, state_dtype="bf16")
     pr = Pair(B, capacity=batch + 30, D=D, H=H, H2=H2 if H2 != H else 0, A=A, batch=batch, burn_in=1, seed=5,
               dtype="bf16", appends=1, opt="sgd", lr=1e-3)
+    assert pr.trainer.kernels_per_step() == (5 if batch >= 576 and H2 <= 512 else 8)
     pr.append_only(synth.take(rows, 0, batch + 30))
     for k in range(batch + 30, batch + 36):
         assert pr.step(synth.take(rows, k, k + 1), compare=True) == 0
 
 
-@pytest.mark.parametrize("batch", [1, 65, 130])
+@pytest.mark.parametrize("batch", [1, 65, 130, 1100])   # (the last one in the large steps' launches)
 def test_mixed_precision_gradients_ignore_the_next_states_of_terminals(B, batch):
     """The rows of S' lie behind those of S in the activations: where every experience is terminal, what
     they hold, infinities included, changes no bit of the gradients."""
@@ -1194,6 +1207,7 @@ def test_mixed_precision_gradients_ignore_the_next_states_of_terminals(B, batch)
         ring = B.Replay(batch + 1, D, B.RP_BF16, burn_in=1, seed=3)
         tr = B.Trainer(ring, H, A, batch, param_dtype=B.RP_BF16, opt=B.RP_SGD, appends_per_step=1, lr=1e-3,
                        init_params=synth.init_params(D, H, A, 3))
+        assert tr.kernels_per_step() == (5 if batch == 1100 else 8)
         args = [rows[k] for k in ("s", "s_next", "a", "r", "term")]
         ring.append(*(x[:batch] for x in args))
         assert tr.step(*(x[batch:] for x in args)) == 0
@@ -1201,19 +1215,24 @@ def test_mixed_precision_gradients_ignore_the_next_states_of_terminals(B, batch)
     assert np.isfinite(grads[0]).all() and np.array_equal(grads[0], grads[1])
 
 
-@pytest.mark.parametrize("H,H2,batch,target_sync", [
-    (512, 0, 512, 3),        # second layer 64 tiles of 128 x 64, the most that go in 32 x 32 tiles
-    (512, 0, 576, 0),        # 72 of them; the first layer's error 40
-    (512, 0, 1040, 0),       # the first layer's error 72
-    (64, 192, 37, 3),        # both networks in launches of their own, rows that end inside a tile
+@pytest.mark.parametrize("H,H2,batch,target_sync,kernels", [
+    (512, 0, 512, 3, 8),     # second layer 64 tiles of 128 x 64, the most that go in tiles of 32 columns
+    (512, 0, 576, 0, 5),     # (in the large steps' launches, as is the next)
+    (512, 0, 1040, 0, 5),
+    (64, 192, 37, 3, 11),    # both networks in launches of their own, rows that end inside a tile
+    (128, 576, 448, 0, 8),   # 63 tiles
+    (128, 576, 512, 3, 8),   # 72 of them, in tiles of 128 x 128; 30 x 16 rows of output layer in tiles of 16 ...
+    (64, 1088, 530, 3, 11),  # ... rows that end inside one; seventeen 64-wide slices
 ])
-def test_mixed_precision_products_with_few_tiles(B, H, H2, batch, target_sync):
-    """Both sides of the rule that sends the second layer and the first layer's error to 32 x 32 tiles
-    with a split contraction; tolerances of the other mixed-precision cases."""
+def test_mixed_precision_products_with_few_tiles(B, H, H2, batch, target_sync, kernels):
+    """Both sides of the rule that sends the second layer of small steps to tiles of 32 columns with a split
+    contraction; tolerances of the other mixed-precision cases.  (Both sides for the first layer's error:
+    test_mixed_precision_steps_with_many_states_or_actions.)"""
     D, A = 27, 30
     rows = synth.experiences(batch + 60, D, A, 0.05, seed=76, state_dtype="bf16")
     pr = Pair(B, capacity=batch + 30, D=D, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=5, dtype="bf16",
               appends=1, target_sync=target_sync, lr=1e-3)
+    assert pr.trainer.kernels_per_step() == kernels
     pr.append_only(synth.take(rows, 0, batch + 30))
     for k in range(batch + 30, batch + 34):
         assert pr.step(synth.take(rows, k, k + 1), compare=True) == 0
@@ -1221,7 +1240,8 @@ def test_mixed_precision_products_with_few_tiles(B, H, H2, batch, target_sync):
 
 @pytest.mark.parametrize("D,H,H2,A,batch,target_sync,dueling", [
     (27, 576, 192, 30, 1030, 0, False),   # widths and a batch that end inside tiles of 128 x 128
-    (33, 1024, 64, 40, 600, 3, True),     # one slice of contraction; two blocks of states and of actions
+    (33, 1024, 64, 40, 600, 3, True),     # (small form: two blocks of states and of actions are too much here)
+    (33, 512, 64, 40, 1100, 3, True),     # one slice of contraction; two blocks of states and of actions
     (96, 512, 320, 3, 1100, 0, False),    # three blocks of states, the bias behind the last
     (27, 64, 64, 5, 8300, 0, False),      # 256 x 128 tiles, more rows of them than rows of workgroups
     (31, 1024, 64, 33, 9000, 0, True),
@@ -1239,11 +1259,52 @@ def test_mixed_precision_backward_in_two_launches(B, D, H, H2, A, batch, target_
         rows = synth.experiences(batch + 60, D, A, 0.05, seed=79, state_dtype="bf16")
         pr = Pair(B, capacity=batch + 30, D=D, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=5, dtype="bf16",
                   appends=1, target_sync=target_sync, dueling=dueling, lr=1e-3)
+        # gather, first two layers (one launch each for wide states or a wide first layer; another for a target network's
+        # rows that share a tile with the others), head, gradients, update; the dueling head's update
+        forward = (1 if D <= 64 and H <= 2048 else 2) * (2 if target_sync and batch % 128 else 1)
+        assert pr.trainer.kernels_per_step() == (11 if batch == 600 and H == 1024 else 4 + forward) + dueling
         pr.append_only(synth.take(rows, 0, batch + 30))
         for k in range(batch + 30, batch + 34):
             assert pr.step(synth.take(rows, k, k + 1), compare=True) == 0
     finally:
         oracle.set_threads(1)
+
+
+@pytest.mark.parametrize("D,H,H2,A,batch,appends,target_sync,dueling,distinct,opt", [
+    (27, 256, 0, 30, 1030, 3, 0, False, False, "adam"),     # tiles of 128 x 128
+    (27, 128, 512, 30, 640, 1, 3, True, False, "adam"),     # both networks in one launch
+    (50, 256, 128, 40, 1100, 17, 3, True, True, "adam"),    # in two, no duplicates; two blocks of states and of actions
+    (96, 320, 0, 5, 1540, 1, 0, False, True, "sgd"),        # the first layer in a launch of its own
+    (27, 1024, 0, 30, 4000, 64, 0, False, False, "adam"),   # tiles of 256 x 128 and of 128 x 256
+    (27, 64, 64, 8, 8300, 0, 4, False, False, "sgd"),       # several groups and row tiles a workgroup
+])
+def test_recorded_runs_of_large_steps_equal_single_steps(B, D, H, H2, A, batch, appends, target_sync, dueling, distinct, opt):
+    """Large steps in recorded runs, where the update's launch also gathers the next step's batch, leave the bits of the
+    same steps made one by one, each with a synchronisation; and a second recorded run those of the first."""
+    n, cap = 11, batch + 300
+    rows = synth.experiences(cap + n * max(appends, 1), D, A, 0.05, seed=83, state_dtype="bf16")
+    ends = []
+    for how in ("run", "run", "steps"):
+        pr = Pair(B, capacity=cap, D=D, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=5, dtype="bf16", appends=appends,
+                  target_sync=target_sync, dueling=dueling, distinct=distinct, opt=opt, lr=1e-3)
+        tr = pr.trainer
+        assert tr.kernels_per_step() <= 6 + dueling             # (eight and more in the small form)
+        for lo in range(0, cap, 4096):
+            pr.append_only(synth.take(rows, lo, min(lo + 4096, cap)))
+        new = synth.take(rows, cap, cap + n * appends)
+        if how == "run":
+            assert tr.steps(n, *(new[k] for k in synth.FIELDS)) == n
+        else:
+            for k in range(n):
+                assert tr.step(*(new[f][k * appends:(k + 1) * appends] for f in synth.FIELDS)) == 0
+                torch.cuda.synchronize()
+        last, (m, v, t, step) = tr.last(), tr.opt_state()
+        ends.append([tr.params(), tr.grads(), tr.target(), m, v, last["Q"], last["Qn"], last["y"], last["idx"],
+                     np.array([t, step]), np.array([last["loss"]]), np.array(pr.gpu_ring.state()), *pr.gpu_ring.read_rows(0, cap)])
+    assert np.isfinite(ends[0][0]).all()
+    for other in ends[1:]:
+        for k, (a, b) in enumerate(zip(ends[0], other)):
+            assert np.array_equal(a, b), k
 
 
 @pytest.mark.parametrize("D,H,H2,A,batch,target_sync,dueling,kernels", [
@@ -1392,13 +1453,14 @@ def test_very_large_operands(B, dtype, H, H2, batch, n):
 @pytest.mark.parametrize("dtype,H,H2,batch,layered,target_sync,dueling,A", [
     ("bf16", 128, 0, 64, False, 0, False, 30), ("bf16", 128, 0, 130, False, 3, True, 30),
     ("bf16", 64, 192, 128, False, 3, True, 40), ("bf16", 64, 128, 40, True, 3, True, 30),
+    ("bf16", 256, 0, 1100, False, 3, True, 30), ("bf16", 2112, 64, 640, False, 0, False, 30),
     ("f32", 64, 0, 32, False, 3, True, 40), ("f32", 128, 1024, 64, False, 3, True, 30),
     ("f32", 320, 0, 64, False, 0, False, 30), ("f32", 64, 0, 32, True, 0, True, 30)])
 def test_launch_count_with_and_without_recorded_runs(B, dtype, H, H2, batch, layered, target_sync, dueling, A,
                                                      appends, distinct):
     """A trainer that records runs of steps counts the launches of a step as it records them; one that
     does not gives the same number."""
-    counts = [Pair(B, capacity=300, D=27, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=1, dtype=dtype, appends=appends,
+    counts = [Pair(B, capacity=max(300, batch + 30), D=27, H=H, H2=H2, A=A, batch=batch, burn_in=1, seed=1, dtype=dtype, appends=appends,
                    layered=layered, target_sync=target_sync, dueling=dueling, distinct=distinct,
                    use_graph=use_graph).trainer.kernels_per_step() for use_graph in (True, False)]
     assert counts[0] == counts[1]
