@@ -899,7 +899,7 @@ hipError_t launch_skinny(hipStream_t st, const SkinnyArgs& a, const Epi& epi) {
 // in 64 bits with the same bf16 roundings (dW1 there 5.6e-4, like this 2.9e-4).
 // The workgroups of a row of tiles repeat the first layer (an eighth of the second's MFMAs in tiles 256 wide, 32 states);
 // as a launch of its own it was bound by its start and by writing and reading H1 (17 MB each way at batch 4096 and
-// 1024 units).  6.8 + 20.8 us -> 27.0 there, but us per step 81.4 -> 79.6 (the S' half of H1 never goes to memory); at
+// 1024 units).  As long as the two launches there, some 28 us, but us per step 81.4 -> 79.6 (the S' half of H1 never goes to memory); at
 // batch 1024 54.5 -> 52.7, 512-512 at 1100 40.8 -> 37.7, 192-192 at 4096 35.7 -> 33.5, 768-768 at 3000 unchanged.
 // Without the first layer the launch takes 18.8 us there; its MFMAs add 2.7, ReLU, rounding and LDS writes 3.5 (as
 // much when spread between the second layer's MFMAs), the stores of H1 1.9.
